@@ -54,7 +54,7 @@ static int dense_fwd_typed(int64_t n, const T *X, int64_t ldx, int32_t F_in, con
     do {                                                                                      \
         CatRows<T, VA_> a{X, ldx, X, ldx, F_in, n, F_in};                                          \
         SideWeights<VB_> b{W, W, F_in, F_out, pad8(F_out)};                                   \
-        launch_by_width<T, 32, false>(name, a, b, e, n, N_out, K, kps, 1, nullptr, s);        \
+        launch_by_width<T, 32, false, VA_>(name, a, b, e, n, N_out, K, kps, 1, nullptr, s);        \
     } while (0)
     // (va: F_in is a multiple of four, so W holds at least four elements and may be read in unaligned groups)
     if (va && vb) TMA_DENSE_FWD(true, kAligned4);
@@ -102,7 +102,7 @@ static int dense_bwd_data_typed(int64_t n, const T *g, const T *h, int64_t ld, c
     do {                                                                                      \
         MaskedGrad<true, T, VA_, kRelu> a{g, h, F_out, ld, n};                                \
         CatWeightsT<VB_> b{W, W, F_in, F_out};                                                \
-        launch_by_width<T, 32, false>(name, a, b, e, n, F_in, K, kps, 1, nullptr, s);         \
+        launch_by_width<T, 32, false, VA_ && VB_>(name, a, b, e, n, F_in, K, kps, 1, nullptr, s);         \
     } while (0)
     if (va && vb) TMA_DENSE_BD(true, true);
     else if (va) TMA_DENSE_BD(true, false);
@@ -171,11 +171,11 @@ static int dense_bwd_weight_typed(int64_t n, const T *X, int64_t ldx, const T *g
     if (v) {
         CatRowsT<T, true> a{X, ldx, X, ldx, F_in, n};
         MaskedGrad<false, T, true, kRelu> b{g, h, F_out, ld, n};
-        launch_by_width<T, 32, true>(name, a, b, e, int64_t(F_in), F_out, n, w.k_per_split, w.n_splits, colsum, s);
+        launch_by_width<T, 32, true, true>(name, a, b, e, int64_t(F_in), F_out, n, w.k_per_split, w.n_splits, colsum, s);
     } else {
         CatRowsT<T, false> a{X, ldx, X, ldx, F_in, n};
         MaskedGrad<false, T, false, kRelu> b{g, h, F_out, ld, n};
-        launch_by_width<T, 32, true>(name, a, b, e, int64_t(F_in), F_out, n, w.k_per_split, w.n_splits, colsum, s);
+        launch_by_width<T, 32, true, false>(name, a, b, e, int64_t(F_in), F_out, n, w.k_per_split, w.n_splits, colsum, s);
     }
     return check_launch("dense gemm bwd weight");
 }

@@ -150,9 +150,10 @@ static void fwd_launch(const AL &a, const BL &b, const FwdEpilogue<T> &e, int64_
             launch_gemm<128, 256, 32, 2, 4, false, T>("gemm_fwd_128x256_bf16", a, b, e, n, F_out, K, kps, 1, nullptr, s);
         else
             launch_gemm<128, 128, 32, 2, 2, false, T>("gemm_fwd_128x128_bf16", a, b, e, n, F_out, K, kps, 1, nullptr, s);
-    } else
-        launch_gemm<128, 128, (sizeof(T) == 2 ? 32 : 16), 2, 2, false, T>(kname<T>("gemm_fwd_128x128", "gemm_fwd_128x128_generic", "gemm_fwd_128x128_bf16", "gemm_fwd_128x128_bf16_generic", VA),
-                                               a, b, e, n, F_out, K, kps, 1, nullptr, s);
+    } else if constexpr (sizeof(T) == 4)
+        launch_split_128<VA, false>(VA ? "gemm_fwd_128x128" : "gemm_fwd_128x128_generic", a, b, e, n, F_out, K, kps, 1, nullptr, s);
+    else
+        launch_gemm<128, 128, 32, 2, 2, false, T>("gemm_fwd_128x128_bf16_generic", a, b, e, n, F_out, K, kps, 1, nullptr, s);
 }
 
 template <typename T, bool VA, bool VB>
@@ -260,6 +261,8 @@ static void bwd_data_dispatch(int64_t n, const T *g, const T *h, int64_t ld_next
         if constexpr (kWideBwdData && sizeof(T) == 2 && VA)   // bf16 storage: half as many passes over the gradient rows
             launch_gemm<128, 256, 32, 2, 4, false, T>("gemm_bwd_data_128x256_bf16", a, b, e, n, N, K,
                                                       int64_t(round_up(size_t(K), 32)), 1, nullptr, s);
+    } else if constexpr (sizeof(T) == 4) {
+        launch_split_128<VA && VB, false>(name, a, b, e, n, N, K, K, 1, nullptr, s);
     } else if (K <= 48) {  // short reduction: 16-wide slabs waste less of the last one
         const int64_t kps = int64_t(round_up(size_t(K), 16));
         launch_gemm<128, 128, 16, 2, 2, false, T>(name, a, b, e, n, N, K, kps, 1, nullptr, s);
@@ -369,9 +372,12 @@ static void bwd_weight_dispatch(int64_t n, const T *H, int64_t ldh, const T *M, 
         else
             launch_gemm<128, 128, 32, 2, 2, true, T>("gemm_bwd_weight_128x128_bf16", a, b, e, Mtot, F_out, n, w.k_per_split,
                                                      w.n_splits, colsum, s);
-    } else
-        launch_gemm<128, 128, (sizeof(T) == 2 ? 32 : 16), 2, 2, true, T>(kname<T>("gemm_bwd_weight_128x128", "gemm_bwd_weight_128x128_generic", "gemm_bwd_weight_128x128_bf16", "gemm_bwd_weight_128x128_bf16_generic", V),
-                                              a, b, e, Mtot, F_out, n, w.k_per_split, w.n_splits, colsum, s);
+    } else if constexpr (sizeof(T) == 4)
+        launch_split_128<V, true>(V ? "gemm_bwd_weight_128x128" : "gemm_bwd_weight_128x128_generic", a, b, e, Mtot, F_out, n,
+                                  w.k_per_split, w.n_splits, colsum, s);
+    else
+        launch_gemm<128, 128, 32, 2, 2, true, T>("gemm_bwd_weight_128x128_bf16_generic", a, b, e, Mtot, F_out, n, w.k_per_split,
+                                                 w.n_splits, colsum, s);
 }
 
 template <typename T>
@@ -451,7 +457,7 @@ static int tf_fwd_typed(int64_t n, const T *H, int64_t ldh, int32_t F_in, const 
     do {                                                                                          \
         CatRows<T, VA_> a{H, ldh, H, ldh, F_in, n, F_in};                                                   \
         SideWeights<VB_> b{W_self, W_neigh, F_in, F_out, Fp};                                     \
-        launch_by_width<T, 32, false>(name, a, b, e, n, 2 * Fp, K, kps, 1, nullptr, s);              \
+        launch_by_width<T, 32, false, VA_>(name, a, b, e, n, 2 * Fp, K, kps, 1, nullptr, s);              \
     } while (0)
     // weights whose rows are not multiples of four: 16-byte loads from 4-byte-aligned addresses
     // (the form is only chosen for F_in >= 8, so the matrices hold at least four elements)
@@ -515,7 +521,7 @@ static int tf_bwd_weight_typed(int64_t n, const T *H, int64_t ldh, const T *g, c
     do {                                                                                                              \
         CatRowsT<T, VA_> a{H, ldh, H, ldh, F_in, n};                                                                       \
         SideGrad<false, T, VB_, R_> b{g, h, dYn, F_out, Fp, ld_next, ldy, n};                                         \
-        launch_by_width<T, (sizeof(T) == 2 ? 32 : 16), true>(name, a, b, e, int64_t(F_in), 2 * Fp, n, w.k_per_split, w.n_splits, colsum, s);     \
+        launch_by_width<T, 32, true, VA_ && VB_>(name, a, b, e, int64_t(F_in), 2 * Fp, n, w.k_per_split, w.n_splits, colsum, s);     \
     } while (0)
 #define TMA_TF_BW2(VA_, VB_)         \
     do {                             \
@@ -582,7 +588,8 @@ static int tf_bwd_data_typed(int64_t n, const T *g, const T *h, int64_t ld_next,
     do {                                                                                               \
         SideGrad<true, T, VA_, R_> a{g, h, dYn, F_out, Fp, ld_next, ldy, n};                           \
         SideWeightsT<VB_> b{W_self, W_neigh, F_in, F_out, Fp};                                         \
-        launch_gemm<128, 128, (sizeof(T) == 2 ? 32 : 16), 2, 2, false, T>(name, a, b, e, n, F_in, K, kps, 1, nullptr, s);         \
+        if constexpr (sizeof(T) == 4) launch_split_128<VA_, false>(name, a, b, e, n, F_in, K, kps, 1, nullptr, s); \
+        else launch_gemm<128, 128, 32, 2, 2, false, T>(name, a, b, e, n, F_in, K, kps, 1, nullptr, s); \
     } while (0)
 #define TMA_TF_BD2(VA_, VB_)                 \
     do {                                     \

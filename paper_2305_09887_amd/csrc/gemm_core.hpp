@@ -1,21 +1,20 @@
 // The tile-product kernel template of libtma with its operand views, epilogues and launcher; included by the
 // translation units that instantiate it (the GraphSAGE transforms, the dense / GCN transforms).
 //
-// One kernel template serves every product: operands are described by small "view" structs that present
-// concatenations ([H | M], [W_self ; W_neigh]), the ReLU mask and transposes as plain A[m][k], B[k][n], and by
-// an epilogue struct.  Arithmetic: fp32 storage multiplies with v_mfma_f32_32x32x2_f32 (fp32 in, fp32
-// accumulate), bf16 storage with v_mfma_f32_32x32x16_bf16 (see TileMath).
+// Operands are described by small "view" structs that present concatenations ([H | M], [W_self ; W_neigh]), the ReLU
+// mask and transposes as plain A[m][k], B[k][n], and results by an epilogue struct; two kernel templates take them,
+// by the storage type: gemm_split_kernel (gemm_split.hpp) for fp32, gemm_bf16_kernel below for bf16
+// (v_mfma_f32_32x32x16_bf16, fp32 accumulation).
 //
-// Tiling.  128 x BN block tile, 4 wavefronts, each owning a (BM/WM) x (BN/WN) patch of 32x32 MFMA tiles; k is
-// consumed in slabs of BK through two LDS buffers (one barrier per slab) while the next slab's global loads are
-// in flight in registers.  Every operand keeps in LDS the orientation it has in HBM, so all global->LDS
-// traffic is 16-byte loads and 16-byte LDS writes:
-//   k-contiguous operand : LDS [mn][BK+4]; a lane fetches the k-values of its row with one 16-byte read (4 fp32
-//                          values for 4 MFMAs, 8 bf16 values for one);
+// Tiling of gemm_bf16_kernel.  BM x BN block tile, each wavefront owning a (BM/WM) x (BN/WN) patch of 32x32 MFMA
+// tiles; k is consumed in slabs of BK through two LDS buffers (one barrier per slab) while the next slab's global
+// loads are in flight in registers.  Every operand keeps in LDS the orientation it has in HBM, so all global->LDS
+// traffic is 8-byte loads and 8-byte LDS writes:
+//   k-contiguous operand : LDS [mn][BK+4]; a lane fetches eight k-values of its row with two 8-byte reads;
 //   mn-contiguous operand: LDS [BK][MN+4]; a lane reads one element per k-value.
-// Within a group of k-values (8 for fp32, 16 for bf16) the lanes of the upper half take the upper half of the
-// group, from both operands (any bijection of k is allowed as long as A and B agree).  Blocks are persistent and
-// numbered so that the tiles sharing operand rows land on the same die (XCD) and hit its L2.
+// Within a group of 16 k-values the lanes of the upper half take the upper half of the group, from both operands (any
+// bijection of k is allowed as long as A and B agree).  Blocks are persistent and numbered so that the tiles sharing
+// operand rows land on the same die (XCD) and hit its L2.
 #pragma once
 #include "kernels.hpp"
 
@@ -25,18 +24,16 @@ namespace tma {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-// Which products keep two slabs in flight in registers (and then run two blocks per compute unit, 256 registers):
-// the ones bound by streaming their operands -- bf16 storage, and the weight gradient whose k runs over the nodes.
-// Measured at n = 125,237 / 2,000,000 rows: bf16 forward 97 -> 79 us / 1.34 -> 1.06 ms, bf16 narrow input gradient
-// 66 -> 48 us, fp32 weight gradient 188 -> 180 us / 2.76 -> 2.53 ms; the fp32 forward and input-gradient products,
-// whose matrix work per slab is four times longer, lose 5 % with it and keep one slab and three blocks; so does the
-// bf16 input-gradient product of the aggregate-first form (169 -> 190 us), which already runs two blocks per unit.
-template <typename CT, bool kColSum, bool kRowAux = false>
+// Which bf16 products keep two slabs in flight in registers (and then run two blocks per compute unit, 256 registers):
+// the ones bound by streaming their operands.  Measured at n = 125,237 / 2,000,000 rows: forward 97 -> 79 us / 1.34 ->
+// 1.06 ms, narrow input gradient 66 -> 48 us; the input-gradient product of the aggregate-first form loses with it
+// (169 -> 190 us), which already runs two blocks per unit.
+template <bool kColSum, bool kRowAux>
 struct DeepPrefetch {
-    static constexpr bool value = (sizeof(CT) == 2 && !kRowAux) || kColSum;
+    static constexpr bool value = !kRowAux || kColSum;
 };
 
-constexpr int kPad = 4;   // LDS row padding in words: keeps 16-byte alignment, spreads banks
+constexpr int kPad = 4;   // LDS row padding in elements: keeps 8-byte alignment, spreads banks
 constexpr int kXcds = 8;  // MI355X: 8 accelerator dies, workgroups are dealt round-robin to them
 
 __device__ __forceinline__ float4 zero4() { return make_float4(0.0f, 0.0f, 0.0f, 0.0f); }
@@ -61,9 +58,9 @@ struct PacksBf16<View, std::void_t<decltype(View::kPacksBf16)>> : std::integral_
 
 // ---------------------------------------------------------------------------
 // Storage types.  T = float (fp32 storage) or uint16_t (bf16 storage).  The
-// views hand every operand over as fp32 quads (bf16 widened exactly); TileMath
-// decides what sits in LDS and which MFMA multiplies it.  Results are rounded
-// to bf16 (nearest even) on store.
+// views hand every operand over as fp32 quads (bf16 widened exactly); what sits
+// in LDS is the kernel's business.  Results are rounded to bf16 (nearest even)
+// on store.
 // ---------------------------------------------------------------------------
 template <typename T>
 struct Pack4;
@@ -113,12 +110,14 @@ struct RawV {
         const float4 f = Pack4<T>::widen(v);
         return make_float4(ok ? f.x : 0.0f, ok ? f.y : 0.0f, ok ? f.z : 0.0f, ok ? f.w : 0.0f);
     }
+    __device__ __forceinline__ float4 any() const { return Pack4<T>::widen(v); }
 };
 template <typename T>
 struct RawV<T, false> {  // element-wise path: already fp32, already zero outside
     float4 v;
     bool ok;
     __device__ __forceinline__ float4 get() const { return v; }
+    __device__ __forceinline__ float4 any() const { return v; }
 };
 
 // Weight matrices whose rows are not multiples of four (F_out = 47): four consecutive elements starting at
@@ -165,6 +164,7 @@ struct CatRows {  // A[m][k] = k < F ? H[m][k] : M[m][k-F]  for k < Kv, zero bey
     int64_t rows;
     int Kv;  // extent of k: 2F for the concatenation, F when only the first part is used (Mx is then never read)
     static __device__ __forceinline__ float4 resolve(const Raw &r) { return r.get(); }
+    static __device__ __forceinline__ float4 in_range(const Raw &r) { return r.any(); }
     static constexpr bool kPacksBf16 = V && sizeof(T) == 2;
     static __device__ __forceinline__ uint2 packed(const Raw &r)
     {
@@ -194,16 +194,16 @@ struct CatRows {  // A[m][k] = k < F ? H[m][k] : M[m][k-F]  for k < Kv, zero bey
         return r;
     }
     __device__ __forceinline__ bool k_plain() const { return V; }
-    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t k64) const
+    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const
     {
         if constexpr (V) {
-            const int k = int(k64);
+            const int k = int(kt) + dk;
             Raw r;
             r.ok = l.ok;
             r.v = Pack4<T>::load((k < F ? l.p0 : l.p1) + k);
             return r;
         } else {
-            return load(l, k64);
+            return load(l, kt + dk);
         }
     }
 };
@@ -225,6 +225,7 @@ struct CatRowsT {  // A[m][k] = (m < F ? H[k][m] : M[k][m-F])          (contiguo
     int F;
     int64_t rows;
     static __device__ __forceinline__ float4 resolve(const Raw &r) { return r.get(); }
+    static __device__ __forceinline__ float4 in_range(const Raw &r) { return r.any(); }
     __device__ __forceinline__ Lane prepare(int64_t m64) const
     {
         const int m = int(m64);
@@ -249,15 +250,15 @@ struct CatRowsT {  // A[m][k] = (m < F ? H[k][m] : M[k][m-F])          (contiguo
         return r;
     }
     __device__ __forceinline__ bool k_plain() const { return V; }
-    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t node) const
+    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const
     {
         if constexpr (V) {
             Raw r;
             r.ok = l.ok;
-            r.v = Pack4<T>::load(l.p + node * l.ld);
+            r.v = Pack4<T>::load(l.p + (kt + dk) * l.ld);
             return r;
         } else {
-            return load(l, node);
+            return load(l, kt + dk);
         }
     }
 };
@@ -274,6 +275,7 @@ struct CatWeights {  // B[k][n] = k < F ? W_self[k][n] : W_neigh[k-F][n]  (conti
     int F;
     int N;
     static __device__ __forceinline__ float4 resolve(const Raw &r) { return r.get(); }
+    static __device__ __forceinline__ float4 in_range(const Raw &r) { return r.any(); }
     __device__ __forceinline__ Lane prepare(int64_t n) const { return Lane{int(n)}; }
     __device__ __forceinline__ Raw load(const Lane &l, int64_t k64) const
     {
@@ -295,17 +297,16 @@ struct CatWeights {  // B[k][n] = k < F ? W_self[k][n] : W_neigh[k-F][n]  (conti
         return r;
     }
     __device__ __forceinline__ bool k_plain() const { return V; }
-    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t k64) const
+    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const
     {
         if constexpr (V) {
-            const int k = int(k64);
             Raw r;
             r.ok = l.n < N;
-            const float *row = k < F ? Ws + int64_t(k) * N : Wn + int64_t(k - F) * N;
-            r.v = *reinterpret_cast<const float4 *>(row + (l.n < N ? l.n : 0));
+            const int64_t e = kt * N + (dk * N + (l.n < N ? l.n : 0));   // (rows of a slab: below 2^31 elements)
+            r.v = *reinterpret_cast<const float4 *>((kt + dk < F ? Ws : Wn - int64_t(F) * N) + e);
             return r;
         } else {
-            return load(l, k64);
+            return load(l, kt + dk);
         }
     }
 };
@@ -323,6 +324,7 @@ struct CatWeightsT {  // B[k][n] = n < F ? W_self[n][k] : W_neigh[n-F][k]  (cont
     int F;
     int Fo;
     static __device__ __forceinline__ float4 resolve(const Raw &r) { return r.get(); }
+    static __device__ __forceinline__ float4 in_range(const Raw &r) { return r.any(); }
     __device__ __forceinline__ Lane prepare(int64_t n64) const
     {
         const int n = int(n64);
@@ -347,15 +349,15 @@ struct CatWeightsT {  // B[k][n] = n < F ? W_self[n][k] : W_neigh[n-F][k]  (cont
         return r;
     }
     __device__ __forceinline__ bool k_plain() const { return V; }
-    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t k64) const
+    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const
     {
         if constexpr (V) {
             Raw r;
             r.ok = l.ok;
-            r.v = *reinterpret_cast<const float4 *>(l.row + k64);
+            r.v = *reinterpret_cast<const float4 *>(l.row + kt + dk);
             return r;
         } else {
-            return load(l, k64);
+            return load(l, kt + dk);
         }
     }
 };
@@ -438,23 +440,23 @@ struct MaskedGrad {
         return r;
     }
     __device__ __forceinline__ bool k_plain() const { return V; }
-    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t k) const
+    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const
     {
         if constexpr (V) {
             Raw r;
             int64_t e;
             if (kAsA) {   // k = output feature, whole groups of four inside [0, Fo)
                 r.nv = l.ok ? 4 : 0;
-                e = l.off + k;
+                e = l.off + kt + dk;
             } else {      // k = node
                 r.nv = l.ok ? Fo - int(l.off) : 0;
-                e = k * ld + l.off;
+                e = kt * ld + (dk * ld + l.off);
             }
             r.g = Pack4<T>::load(dHn + e);
             if constexpr (kRelu) r.h = Pack4<T>::load(Hn + e);
             return r;
         } else {
-            return load(l, k);
+            return load(l, kt + dk);
         }
     }
 };
@@ -514,15 +516,15 @@ struct SideWeights {  // B[k][n] = n < Fp ? W_self[k][n] : W_neigh[k][n-Fp]   (c
         }
     }
     __device__ __forceinline__ bool k_plain() const { return V; }
-    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t k64) const
+    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const
     {
         if constexpr (V) {
             Raw r;
             r.ok = l.nv > 0;
-            r.v = *reinterpret_cast<const float4 *>(l.col + k64 * Fo);
+            r.v = *reinterpret_cast<const float4 *>(l.col + kt * Fo + dk * Fo);
             return r;
         } else {
-            return load(l, k64);
+            return load(l, kt + dk);
         }
     }
 };
@@ -575,16 +577,16 @@ struct SideWeightsT {  // B[k][n] = k < Fp ? W_self[n][k] : W_neigh[n][k-Fp]   (
     }
     // without padding columns inside the halves every group of four along k is whole
     __device__ __forceinline__ bool k_plain() const { return V && Fo == Fp; }
-    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t k64) const
+    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const
     {
         if constexpr (V) {
-            const int k = int(k64);
+            const int k = int(kt) + dk;
             Raw r;
             r.ok = l.ok;
             r.v = *reinterpret_cast<const float4 *>((k >= Fp ? l.rn : l.rs) + k);
             return r;
         } else {
-            return load(l, k64);
+            return load(l, kt + dk);
         }
     }
 };
@@ -689,12 +691,13 @@ struct SideGrad {
         return r;
     }
     __device__ __forceinline__ bool k_plain() const { return V && (!kAsA || Fo == Fp); }
-    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t k) const
+    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const
     {
         if constexpr (V) {
             Raw r;
             int64_t eg, ey;
             if (kAsA) {   // k = position in [dZ | dYn], no padding inside the halves
+                const int64_t k = kt + dk;
                 r.second = k >= Fp;
                 const int c = int(k - (r.second ? Fp : 0));
                 r.nv = l.ok ? 4 : 0;
@@ -704,15 +707,15 @@ struct SideGrad {
                 r.second = l.second;
                 const int c = int(l.a);
                 r.nv = l.ok ? (r.second ? Fp : Fo) - c : 0;
-                eg = k * ld + c;
-                ey = k * ldy + c;
+                eg = kt * ld + (dk * ld + c);
+                ey = kt * ldy + (dk * ldy + c);
             }
             r.g = Pack4<T>::load(r.second ? dYn + ey : dHn + eg);
             if constexpr (kRelu) r.h = Pack4<T>::load(Hn + eg);
             else r.h = r.g;
             return r;
         } else {
-            return load(l, k);
+            return load(l, kt + dk);
         }
     }
 };
@@ -846,13 +849,9 @@ struct SplitEpilogue {  // partial products, one slab per split
 };
 
 // ---------------------------------------------------------------------------
-// Arithmetic of the tile product.  CT = float: operands sit in LDS as fp32 and a
-// group of 8 k-values is four v_mfma_f32_32x32x2_f32.  CT = uint16_t: operands sit
-// in LDS as bf16 (activations stored in bf16 pass through unchanged, fp32 weights
-// are rounded to nearest even on their way in) and a group of 16 k-values is ONE
-// v_mfma_f32_32x32x16_bf16, whose operand layout -- lane l holds row l%32 and the
-// eight k-values 8*(l/32) .. +7 -- is the fp32 fragment's with twice the k-values, so
-// tile layouts, loaders and epilogues are shared.  Accumulation is fp32 in both.
+// bf16 fragments.  A group of 16 k-values is ONE v_mfma_f32_32x32x16_bf16 (the instruction this chip adds; the
+// 32x32x8 one runs at half its rate): lane l holds row l%32 and the eight k-values 8*(l/32) .. +7.  Activations
+// stored in bf16 pass through LDS unchanged, fp32 weights are rounded to nearest even on their way in.
 // ---------------------------------------------------------------------------
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -867,63 +866,28 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-template <typename CT>
-struct TileMath;
-
-template <>
-struct TileMath<float> {
-    static constexpr int kGroupK = 8;   // k-values per fragment: four MFMAs of two
-    typedef float4 Frag;
-    static __device__ __forceinline__ void put(float *dst, const float4 &v) { *reinterpret_cast<float4 *>(dst) = v; }
-    static __device__ __forceinline__ Frag along(const float *p) { return *reinterpret_cast<const float4 *>(p); }
-    static __device__ __forceinline__ Frag strided(const float *p, int ld)
-    {
-        return make_float4(p[0], p[ld], p[2 * ld], p[3 * ld]);
-    }
-    static __device__ __forceinline__ float value(const float *p) { return *p; }
-    static __device__ __forceinline__ void mma(const Frag &a, const Frag &b, floatx16 &acc)
-    {
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
-    }
-};
-
-template <>
-struct TileMath<uint16_t> {
-    // one v_mfma_f32_32x32x16_bf16 per group of 16 k-values: lane l holds row l%32 and the eight k-values
-    // 8*(l/32) .. +7 (the instruction this chip adds; the 32x32x8 one runs at half its rate)
-    static constexpr int kGroupK = 16;
-    typedef bf16x8 Frag;
-    static __device__ __forceinline__ void put(uint16_t *dst, const float4 &v)
-    {
-        *reinterpret_cast<uint2 *>(dst) = make_uint2(pack_bf16(v.x, v.y), pack_bf16(v.z, v.w));
-    }
-    static __device__ __forceinline__ void put_bits(uint16_t *dst, const uint2 &w) { *reinterpret_cast<uint2 *>(dst) = w; }
-    static __device__ __forceinline__ Frag along(const uint16_t *p)   // (tile rows are 8-byte aligned, not 16)
-    {
-        const uint2 lo = *reinterpret_cast<const uint2 *>(p), hi = *reinterpret_cast<const uint2 *>(p + 4);
-        return __builtin_bit_cast(Frag, make_uint4(lo.x, lo.y, hi.x, hi.y));
-    }
-    static __device__ __forceinline__ Frag strided(const uint16_t *p, int ld)
-    {
-        uint4 w;
-        w.x = uint32_t(p[0]) | (uint32_t(p[ld]) << 16);
-        w.y = uint32_t(p[2 * ld]) | (uint32_t(p[3 * ld]) << 16);
-        w.z = uint32_t(p[4 * ld]) | (uint32_t(p[5 * ld]) << 16);
-        w.w = uint32_t(p[6 * ld]) | (uint32_t(p[7 * ld]) << 16);
-        return __builtin_bit_cast(Frag, w);
-    }
-    static __device__ __forceinline__ float value(const uint16_t *p) { return bf16_to_f32(*p); }
-    static __device__ __forceinline__ void mma(const Frag &a, const Frag &b, floatx16 &acc)
-    {
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
-    }
-};
+constexpr int kGroupK = 16;
+__device__ __forceinline__ void put_bf16(uint16_t *dst, const float4 &v)
+{
+    *reinterpret_cast<uint2 *>(dst) = make_uint2(pack_bf16(v.x, v.y), pack_bf16(v.z, v.w));
+}
+__device__ __forceinline__ bf16x8 fragment_along(const uint16_t *p)   // (tile rows are 8-byte aligned, not 16)
+{
+    const uint2 lo = *reinterpret_cast<const uint2 *>(p), hi = *reinterpret_cast<const uint2 *>(p + 4);
+    return __builtin_bit_cast(bf16x8, make_uint4(lo.x, lo.y, hi.x, hi.y));
+}
+__device__ __forceinline__ bf16x8 fragment_strided(const uint16_t *p, int ld)
+{
+    uint4 w;
+    w.x = uint32_t(p[0]) | (uint32_t(p[ld]) << 16);
+    w.y = uint32_t(p[2 * ld]) | (uint32_t(p[3 * ld]) << 16);
+    w.z = uint32_t(p[4 * ld]) | (uint32_t(p[5 * ld]) << 16);
+    w.w = uint32_t(p[6 * ld]) | (uint32_t(p[7 * ld]) << 16);
+    return __builtin_bit_cast(bf16x8, w);
+}
 
 // ---------------------------------------------------------------------------
-// C[M,N] = A[M,K] B[K,N], k split into ranges of k_per_split, fp32 MFMA.
+// C[M,N] = A[M,K] B[K,N], k split into ranges of k_per_split, bf16 MFMA.
 // Work item = (split, m-tile, n-tile), numbered split-major then m then n.
 // Persistent blocks: the grid is 8 x (blocks per die); the block with id b sits
 // on die b % 8 and walks the work items  die*per_die + b/8, + blocks_per_die, ...
@@ -937,23 +901,22 @@ struct TileMath<uint16_t> {
 // inside the result is written out without per-element bounds tests, which also
 // gives the compiler a fixed number of stores to count its waits against.
 // ---------------------------------------------------------------------------
-template <typename CT, int BM, int BN, int BK, int WM, int WN, bool kColSum, class AL, class BL, class Epi>
-__global__ __launch_bounds__(WM *WN * 64, (BK * sizeof(CT) <= 64 && !Epi::kRowAux && !DeepPrefetch<CT, kColSum, Epi::kRowAux>::value ? 3 : 2)) void gemm_f32_kernel(AL a, BL b, Epi epi, int64_t M, int N, int64_t K,
+template <int BM, int BN, int BK, int WM, int WN, bool kColSum, class AL, class BL, class Epi>
+__global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_kernel(AL a, BL b, Epi epi, int64_t M, int N, int64_t K,
                                                                  int64_t k_per_split, int n_tiles,
                                                                  int64_t tiles_per_split, int64_t total_work,
                                                                  float *__restrict__ colsum_partial)
 {
     constexpr int NT = WM * WN * 64;
-    constexpr bool kPrefetch2 = DeepPrefetch<CT, kColSum, Epi::kRowAux>::value && (BM / WM / 32) * (BN / WN / 32) <= 4;   // (8 accumulator tiles leave no registers for it)
+    constexpr bool kPrefetch2 = DeepPrefetch<kColSum, Epi::kRowAux>::value && (BM / WM / 32) * (BN / WN / 32) <= 4;   // (8 accumulator tiles leave no registers for it)
     constexpr int kDepth = 2;   // slabs in flight in registers (3 and 4 measured: no faster for any product, the wide forward one slower)
     constexpr int TM = BM / WM / 32;
     constexpr int TN = BN / WN / 32;
-    constexpr int A_Q = BM * BK / 4, B_Q = BN * BK / 4;   // 16-byte pieces of a slab
+    constexpr int A_Q = BM * BK / 4, B_Q = BN * BK / 4;   // pieces (four values) of a slab
     constexpr int A_V = (A_Q + NT - 1) / NT;              // load slots per thread; when the pieces do not divide
     constexpr int B_V = (B_Q + NT - 1) / NT;              // evenly the last slots repeat the last piece (same value)
-    using Math = TileMath<CT>;
-    typedef typename Math::Frag Frag;
-    constexpr int GK = Math::kGroupK;   // k-values per fragment: 8 = 4 fp32 MFMAs, 16 = one bf16 MFMA
+    typedef bf16x8 Frag;
+    constexpr int GK = kGroupK;
     constexpr int KG = BK / GK;
     constexpr int A_LD = AL::kContigK ? BK + kPad : BM + kPad;
     constexpr int B_LD = BL::kContigK ? BK + kPad : BN + kPad;
@@ -961,11 +924,11 @@ __global__ __launch_bounds__(WM *WN * 64, (BK * sizeof(CT) <= 64 && !Epi::kRowAu
     constexpr int B_WORDS = BL::kContigK ? BN * B_LD : BK * B_LD;
     static_assert(BM % (WM * 32) == 0 && BN % (WN * 32) == 0 && BK % GK == 0, "tile shape");
     static_assert(!kColSum || !BL::kContigK, "column sums are taken from a [k][n] tile");
-    static_assert(A_WORDS * sizeof(CT) >= BN * sizeof(float) && B_WORDS * sizeof(CT) >= BM * sizeof(float),
+    static_assert(A_WORDS * sizeof(uint16_t) >= BN * sizeof(float) && B_WORDS * sizeof(uint16_t) >= BM * sizeof(float),
                   "epilogue staging fits");
 
-    __shared__ __attribute__((aligned(16))) CT As[2][A_WORDS];
-    __shared__ __attribute__((aligned(16))) CT Bs[2][B_WORDS];
+    __shared__ __attribute__((aligned(16))) uint16_t As[2][A_WORDS];
+    __shared__ __attribute__((aligned(16))) uint16_t Bs[2][B_WORDS];
     float *const a_aux = reinterpret_cast<float *>(&As[0][0]);   // per-column / per-row epilogue inputs
     float *const b_aux = reinterpret_cast<float *>(&Bs[0][0]);
 
@@ -1038,20 +1001,20 @@ __global__ __launch_bounds__(WM *WN * 64, (BK * sizeof(CT) <= 64 && !Epi::kRowAu
     };
     auto fetch_plain = [&](int64_t kt, typename AL::Raw(&ar)[A_V], typename BL::Raw(&br)[B_V]) {
 #pragma unroll
-        for (int i = 0; i < A_V; ++i) ar[i] = a.load_plain(alane[i], kt + a_k[i]);
+        for (int i = 0; i < A_V; ++i) ar[i] = a.load_plain(alane[i], kt, a_k[i]);
 #pragma unroll
-        for (int i = 0; i < B_V; ++i) br[i] = b.load_plain(blane[i], kt + b_k[i]);
+        for (int i = 0; i < B_V; ++i) br[i] = b.load_plain(blane[i], kt, b_k[i]);
     };
     auto stage = [&](int buf, const typename AL::Raw(&ar)[A_V], const typename BL::Raw(&br)[B_V]) {
 #pragma unroll
         for (int i = 0; i < A_V; ++i) {
-            if constexpr (sizeof(CT) == 2 && PacksBf16<AL>::value) Math::put_bits(&As[buf][a_lds[i]], AL::packed(ar[i]));
-            else Math::put(&As[buf][a_lds[i]], AL::resolve(ar[i]));
+            if constexpr (PacksBf16<AL>::value) *reinterpret_cast<uint2 *>(&As[buf][a_lds[i]]) = AL::packed(ar[i]);
+            else put_bf16(&As[buf][a_lds[i]], AL::resolve(ar[i]));
         }
 #pragma unroll
         for (int i = 0; i < B_V; ++i) {
-            if constexpr (sizeof(CT) == 2 && PacksBf16<BL>::value) Math::put_bits(&Bs[buf][b_lds[i]], BL::packed(br[i]));
-            else Math::put(&Bs[buf][b_lds[i]], BL::resolve(br[i]));
+            if constexpr (PacksBf16<BL>::value) *reinterpret_cast<uint2 *>(&Bs[buf][b_lds[i]]) = BL::packed(br[i]);
+            else put_bf16(&Bs[buf][b_lds[i]], BL::resolve(br[i]));
         }
     };
     // This lane's k-values of group g (the upper half of the wavefront holds the upper half of the group) of its
@@ -1059,14 +1022,14 @@ __global__ __launch_bounds__(WM *WN * 64, (BK * sizeof(CT) <= 64 && !Epi::kRowAu
     auto frag_a = [&](int buf, int g, int i) -> Frag {
         const int mn = wm0 + i * 32 + l31;
         const int k = g * GK + (GK / 2) * hi;
-        if (AL::kContigK) return Math::along(&As[buf][mn * A_LD + k]);
-        return Math::strided(&As[buf][k * A_LD + mn], A_LD);
+        if (AL::kContigK) return fragment_along(&As[buf][mn * A_LD + k]);
+        return fragment_strided(&As[buf][k * A_LD + mn], A_LD);
     };
     auto frag_b = [&](int buf, int g, int j) -> Frag {
         const int mn = wn0 + j * 32 + l31;
         const int k = g * GK + (GK / 2) * hi;
-        if (BL::kContigK) return Math::along(&Bs[buf][mn * B_LD + k]);
-        return Math::strided(&Bs[buf][k * B_LD + mn], B_LD);
+        if (BL::kContigK) return fragment_along(&Bs[buf][mn * B_LD + k]);
+        return fragment_strided(&Bs[buf][k * B_LD + mn], B_LD);
     };
 
     int64_t work = die * per_die + blockIdx.x / kXcds;
@@ -1105,27 +1068,15 @@ __global__ __launch_bounds__(WM *WN * 64, (BK * sizeof(CT) <= 64 && !Epi::kRowAu
 #pragma unroll
                     for (int j = 0; j < TN; ++j) fb[nxt][j] = frag_b(buf, g + 1, j);
                 }
-                if constexpr (sizeof(CT) == 4) {   // fp32: the four k-pairs in turn, round-robin over the output tiles
 #pragma unroll
-                    for (int q = 0; q < 4; ++q)
+                for (int i = 0; i < TM; ++i)
 #pragma unroll
-                        for (int i = 0; i < TM; ++i)
-#pragma unroll
-                            for (int j = 0; j < TN; ++j) {
-                                const float av = q == 0 ? fa[cur][i].x : q == 1 ? fa[cur][i].y : q == 2 ? fa[cur][i].z : fa[cur][i].w;
-                                const float bv = q == 0 ? fb[cur][j].x : q == 1 ? fb[cur][j].y : q == 2 ? fb[cur][j].z : fb[cur][j].w;
-                                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[i][j], 0, 0, 0);
-                            }
-                } else {
-#pragma unroll
-                    for (int i = 0; i < TM; ++i)
-#pragma unroll
-                        for (int j = 0; j < TN; ++j) Math::mma(fa[cur][i], fb[cur][j], acc[i][j]);
-                }
+                    for (int j = 0; j < TN; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[cur][i], fb[cur][j], acc[i][j], 0, 0, 0);
             }
             if (kColSum && t.m0 == 0 && tid < BN) {
 #pragma unroll
-                for (int k = 0; k < BK; ++k) colsum += Math::value(&Bs[buf][k * B_LD + tid]);
+                for (int k = 0; k < BK; ++k) colsum += bf16_to_f32(Bs[buf][k * B_LD + tid]);
             }
         };
         auto main_loop = [&](auto plain_tag) {
@@ -1249,9 +1200,14 @@ __global__ __launch_bounds__(WM *WN * 64, (BK * sizeof(CT) <= 64 && !Epi::kRowAu
     }
 }
 
+}  // namespace tma
+#include "gemm_split.hpp"
+namespace tma {
+
 template <typename T>
 static bool vec4_ok(const T *p, int64_t ld) { return aligned(p, 4 * sizeof(T)) && ld % 4 == 0; }
 
+// BK: k-values per slab of the bf16 kernel (the fp32 one has its own).
 template <int BM, int BN, int BK, int WM, int WN, bool kColSum, typename CT = float, class AL, class BL, class Epi>
 static void launch_gemm(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K,
                         int64_t k_per_split, int n_splits, float *colsum_partial, hipStream_t s)
@@ -1261,19 +1217,21 @@ static void launch_gemm(const char *name, const AL &a, const BL &b, const Epi &e
     const int64_t tiles = ceil_div(M, BM) * n_tiles;
     const int64_t total = tiles * n_splits;
     // resident blocks per compute unit follow from the kernel's LDS footprint (160 KB per unit) and its
-    // register budget (launch bounds); 256 units in 8 dies
-    constexpr int kLdsBytes = 2 * int(sizeof(CT)) * ((AL::kContigK ? BM * (BK + kPad) : BK * (BM + kPad)) + (BL::kContigK ? BN * (BK + kPad) : BK * (BN + kPad)));
-    // the launch bound's second number is waves per SIMD: 3 or 2, i.e. that many blocks of four wavefronts per compute
-    // unit, half as many (at least one) of eight
-    constexpr int kWavesPerSimd = (BK * sizeof(CT) <= 64 && !Epi::kRowAux && kLdsBytes <= 53 * 1024 && !DeepPrefetch<CT, kColSum, Epi::kRowAux>::value) ? 3 : 2;
-    constexpr int kByWaves = kWavesPerSimd * 4 / (WM * WN) > 0 ? kWavesPerSimd * 4 / (WM * WN) : 1;
+    // register budget (launch bounds: two waves per SIMD); 256 units in 8 dies
+    constexpr int kLdsBytes = 2 * 2 * ((AL::kContigK ? BM * (BK + kPad) : BK * (BM + kPad)) + (BL::kContigK ? BN * (BK + kPad) : BK * (BN + kPad)));
+    constexpr int kByWaves = 2 * 4 / (WM * WN) > 0 ? 2 * 4 / (WM * WN) : 1;
     constexpr int kByLds = 160 * 1024 / kLdsBytes > 0 ? 160 * 1024 / kLdsBytes : 1;
-    constexpr int kPerCu = kByWaves < kByLds ? kByWaves : kByLds;
+    constexpr int kPerCu = sizeof(CT) == 4 ? kSplitPerCu * 4 / (WM * WN) : kByWaves < kByLds ? kByWaves : kByLds;
     int64_t blocks_per_die = ceil_div(total, kXcds);
     if (blocks_per_die > 32 * kPerCu) blocks_per_die = 32 * kPerCu;
+    const dim3 grid(unsigned(blocks_per_die * kXcds)), block(WM * WN * 64);
     TMA_TIMED(name, s);
-    hipLaunchKernelGGL((gemm_f32_kernel<CT, BM, BN, BK, WM, WN, kColSum, AL, BL, Epi>), dim3(unsigned(blocks_per_die * kXcds)),
-                       dim3(WM * WN * 64), 0, s, a, b, e, M, N, K, k_per_split, n_tiles, tiles, total, colsum_partial);
+    if constexpr (sizeof(CT) == 4)
+        hipLaunchKernelGGL((gemm_split_kernel<BM, BN, WM, WN, kColSum, AL, BL, Epi>), grid, block, 0, s, a, b, e, M, N, K,
+                           k_per_split, n_tiles, tiles, total, colsum_partial);
+    else
+        hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, BK, WM, WN, kColSum, AL, BL, Epi>), grid, block, 0, s, a, b, e, M, N, K,
+                           k_per_split, n_tiles, tiles, total, colsum_partial);
 }
 
 // Kernel names for the timing hook: <what>_<tile>[_bf16][_generic]; "generic" = a streaming operand is
@@ -1298,12 +1256,34 @@ static inline bool few_tiles(int64_t M, int64_t N, int n_splits = 1)
     return ceil_div(M, int64_t(128)) * ceil_div(N, int64_t(128)) * n_splits < kFewTiles;
 }
 
-template <typename CT, int BK, bool kColSum, class AL, class BL, class Epi>
+// fp32 products with more than 96 columns.  The 256-wide tile of eight wavefronts reads the operand it is wide across
+// once instead of twice and converts a quarter fewer values per product; it is taken where it pads no more than two
+// tiles of 128 would, across the columns for a product whose rows are nodes and across the rows for a weight gradient.
+// Measured, 128 x 128 -> 256-wide, n = 125,237 / 1,000,000: forward 2 x 128 -> 256 133 -> 116 us / 961 -> 838 us, its
+// input gradient 166 -> 142 / 1,210 -> 1,031 us, its weight gradient 125 -> 117 / 901 -> 840 us.  Operands on the
+// element-wise path are bound by their loads and keep the one tile.
+template <bool kWide, bool kColSum, class AL, class BL, class Epi>
+static void launch_split_128(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K,
+                             int64_t kps, int n_splits, float *colsum, hipStream_t s)
+{
+    if constexpr (kWide && kColSum) {
+        if (ceil_div(M, int64_t(128)) % 2 == 0)
+            return launch_gemm<256, 128, 32, 4, 2, true, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    } else if constexpr (kWide) {
+        if (ceil_div(N, 128) % 2 == 0)
+            return launch_gemm<128, 256, 32, 2, 4, false, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    }
+    launch_gemm<128, 128, 32, 2, 2, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+}
+
+// kWide: the operands are on the vector path
+template <typename CT, int BK, bool kColSum, bool kWide, class AL, class BL, class Epi>
 static void launch_by_width(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K,
                             int64_t kps, int n_splits, float *colsum, hipStream_t s)
 {
     if (N <= 64 || few_tiles(M, N, n_splits)) launch_gemm<128, 64, BK, 4, 1, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
     else if (N <= 96) launch_gemm<128, 96, BK, 4, 1, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    else if constexpr (sizeof(CT) == 4) launch_split_128<kWide, kColSum>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
     else launch_gemm<128, 128, BK, 2, 2, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
 }
 
