@@ -46,7 +46,7 @@ static int dense_fwd_typed(int64_t n, const T *X, int64_t ldx, int32_t F_in, con
     DenseEpilogue<T, kRowScale> e{Y, ldy, bias, row_scale, relu};
     const int64_t K = F_in, kps = int64_t(round_up(size_t(K), 32));
     // a group of four along k must not reach into row padding, nor a group of four columns past F_out
-    const bool va = vec4_ok(X, ldx) && F_in % 4 == 0;
+    const bool va = groups_ok(X, ldx, F_in);
     const bool vb = F_out % 4 == 0 && aligned(W, 16);
     const char *name = kname<T>("gemm_dense_fwd", "gemm_dense_fwd_generic", "gemm_dense_fwd_bf16",
                                 "gemm_dense_fwd_bf16_generic", va);
@@ -59,7 +59,13 @@ static int dense_fwd_typed(int64_t n, const T *X, int64_t ldx, int32_t F_in, con
     // (va: F_in is a multiple of four, so W holds at least four elements and may be read in unaligned groups)
     if (va && vb) TMA_DENSE_FWD(true, kAligned4);
     else if (va) TMA_DENSE_FWD(true, kUnaligned4);
-    else TMA_DENSE_FWD(false, kElementwise);
+    else if constexpr (sizeof(T) == 4) {
+        if (rows_u_ok(n, ldx, F_in) && weights_u_ok(F_in, F_out)) {
+            CatRowsU a{X, ldx, X, ldx, F_in, pad4(F_in), n, 1};
+            SideWeights<kUnaligned4> b{W, W, F_in, F_out, pad8(F_out)};
+            launch_by_width<T, 32, false, true>(name, a, b, e, n, N_out, K, kps, 1, nullptr, s);
+        } else TMA_DENSE_FWD(false, kElementwise);
+    } else TMA_DENSE_FWD(false, kElementwise);
 #undef TMA_DENSE_FWD
     return check_launch("dense gemm fwd");
 }
@@ -94,19 +100,22 @@ static int dense_bwd_data_typed(int64_t n, const T *g, const T *h, int64_t ld, c
 {
     DenseEpilogue<T, kRowScale> e{dX, ldx, nullptr, row_scale, false};
     const int64_t K = F_out, kps = int64_t(round_up(size_t(K), 32));
-    const bool va = vec4_ok(g, ld) && (!kRelu || vec4_ok(h, ld));
-    const bool vb = vec4_ok(W, F_out);
+    const bool va = padded_groups_ok(g, ld, F_out) && (!kRelu || padded_groups_ok(h, ld, F_out));
+    const bool vb = groups_ok(W, F_out, F_out);
     const char *name = kname<T>("gemm_dense_bwd_data", "gemm_dense_bwd_data_generic", "gemm_dense_bwd_data_bf16",
                                 "gemm_dense_bwd_data_bf16_generic", va);
-#define TMA_DENSE_BD(VA_, VB_)                                                                \
+#define TMA_DENSE_BD(VA_, BView_)                                                             \
     do {                                                                                      \
         MaskedGrad<true, T, VA_, kRelu> a{g, h, F_out, ld, n};                                \
-        CatWeightsT<VB_> b{W, W, F_in, F_out};                                                \
-        launch_by_width<T, 32, false, VA_ && VB_>(name, a, b, e, n, F_in, K, kps, 1, nullptr, s);         \
+        BView_ b{W, W, F_in, F_out};                                                          \
+        launch_by_width<T, 32, false, VA_>(name, a, b, e, n, F_in, K, kps, 1, nullptr, s);         \
     } while (0)
-    if (va && vb) TMA_DENSE_BD(true, true);
-    else if (va) TMA_DENSE_BD(true, false);
-    else TMA_DENSE_BD(false, false);
+    if (va && vb) TMA_DENSE_BD(true, CatWeightsT<true>);
+    else if constexpr (sizeof(T) == 4) {
+        if (va && weights_u_ok(F_in, F_out)) TMA_DENSE_BD(true, CatWeightsTU);
+        else TMA_DENSE_BD(false, CatWeightsT<false>);
+    } else if (va) TMA_DENSE_BD(true, CatWeightsT<false>);
+    else TMA_DENSE_BD(false, CatWeightsT<false>);
 #undef TMA_DENSE_BD
     return check_launch("dense gemm bwd data");
 }
@@ -165,18 +174,26 @@ static int dense_bwd_weight_typed(int64_t n, const T *X, int64_t ldx, const T *g
                                   int32_t F_out, const WeightSplit &w, float *partial, float *colsum, hipStream_t s)
 {
     SplitEpilogue e{partial, int64_t(F_in), F_out};
-    const bool v = vec4_ok(X, ldx) && F_in % 4 == 0 && vec4_ok(g, ld) && (!kRelu || vec4_ok(h, ld));
+    const bool vg = padded_groups_ok(g, ld, F_out) && (!kRelu || padded_groups_ok(h, ld, F_out));
+    const bool v = groups_ok(X, ldx, F_in) && vg;
     const char *name = kname<T>("gemm_dense_bwd_weight", "gemm_dense_bwd_weight_generic", "gemm_dense_bwd_weight_bf16",
                                 "gemm_dense_bwd_weight_bf16_generic", v);
     if (v) {
         CatRowsT<T, true> a{X, ldx, X, ldx, F_in, n};
         MaskedGrad<false, T, true, kRelu> b{g, h, F_out, ld, n};
         launch_by_width<T, 32, true, true>(name, a, b, e, int64_t(F_in), F_out, n, w.k_per_split, w.n_splits, colsum, s);
-    } else {
-        CatRowsT<T, false> a{X, ldx, X, ldx, F_in, n};
-        MaskedGrad<false, T, false, kRelu> b{g, h, F_out, ld, n};
-        launch_by_width<T, 32, true, false>(name, a, b, e, int64_t(F_in), F_out, n, w.k_per_split, w.n_splits, colsum, s);
+        return check_launch("dense gemm bwd weight");
     }
+    if constexpr (sizeof(T) == 4)
+        if (vg && rows_u_ok(n, ldx, F_in)) {
+            CatRowsTU a{X, ldx, X, ldx, F_in, pad4(F_in), n};
+            MaskedGrad<false, T, true, kRelu> b{g, h, F_out, ld, n};
+            launch_by_width<T, 32, true, true>(name, a, b, e, int64_t(F_in), F_out, n, w.k_per_split, w.n_splits, colsum, s);
+            return check_launch("dense gemm bwd weight");
+        }
+    CatRowsT<T, false> a{X, ldx, X, ldx, F_in, n};
+    MaskedGrad<false, T, false, kRelu> b{g, h, F_out, ld, n};
+    launch_by_width<T, 32, true, false>(name, a, b, e, int64_t(F_in), F_out, n, w.k_per_split, w.n_splits, colsum, s);
     return check_launch("dense gemm bwd weight");
 }
 

@@ -33,6 +33,12 @@ struct DeepPrefetch {
     static constexpr bool value = !kRowAux || kColSum;
 };
 
+// An operand that is contiguous along k and takes it from two arrays of different pitch
+template <class View, class = void>
+struct TwoSourcesAlongK : std::false_type {};
+template <class View>
+struct TwoSourcesAlongK<View, std::void_t<decltype(View::kTwoSources)>> : std::integral_constant<bool, View::kContigK> {};
+
 constexpr int kPad = 4;   // LDS row padding in elements: keeps 8-byte alignment, spreads banks
 constexpr int kXcds = 8;  // MI355X: 8 accelerator dies, workgroups are dealt round-robin to them
 
@@ -67,7 +73,12 @@ struct Pack4;
 template <>
 struct Pack4<float> {
     typedef float4 Packed;  // 16 bytes
-    static __device__ __forceinline__ Packed load(const float *p) { return *reinterpret_cast<const float4 *>(p); }
+    static __device__ __forceinline__ Packed load(const float *p)   // (the instruction needs 4-byte alignment only)
+    {
+        Packed v;
+        __builtin_memcpy(&v, p, 16);
+        return v;
+    }
     static __device__ __forceinline__ float4 widen(const Packed &v) { return v; }
 };
 template <>
@@ -98,8 +109,11 @@ __device__ __forceinline__ void narrow1(uint16_t *p, float v) { *p = f32_to_bf16
 // matrix work.  V = the vector path is legal (bases aligned to four elements,
 // leading dimensions and inner extents multiples of 4); its loads are
 // branch-free: an out-of-range position is clamped to a valid address and the
-// value is discarded by resolve() through the `ok` flag.  Without V the view
-// loads element by element, guarded (the side-weight views have a third way: see RawU).
+// value is discarded by resolve() through the `ok` flag.  fp32 loads need only
+// the extents; alignment and leading dimension are free.  Without V the view
+// loads element by element, guarded; fp32 operands whose extents are no
+// multiples of four have views of their own (see RawU), and take that way only
+// when an array is too small for those.
 // ---------------------------------------------------------------------------
 template <typename T, bool V>
 struct RawV {
@@ -120,8 +134,8 @@ struct RawV<T, false> {  // element-wise path: already fp32, already zero outsid
     __device__ __forceinline__ float4 any() const { return v; }
 };
 
-// Weight matrices whose rows are not multiples of four (F_out = 47): four consecutive elements starting at
-// element e of a dense fp32 array of `count` >= 4 elements, fetched with one 16-byte load from a base that is
+// fp32 arrays whose rows are not multiples of four (F_out = 47): four consecutive elements starting at
+// element e of an array of `count` >= 4 elements, fetched with one 16-byte load from a base that is
 // only 4-byte aligned (the load instruction needs no more), unconditionally.  A group that would run past the
 // end of the array is fetched `shift` elements earlier and moved back in registers; `valid` leading elements are
 // kept, the rest read as zero.
@@ -144,6 +158,16 @@ __device__ __forceinline__ RawU load_unaligned4(const float *base, int e, int co
     RawU r;
     __builtin_memcpy(&r.v, base + (e - shift), 16);
     r.meta = (valid < 4 ? valid : 4) | (shift << 4);
+    return r;
+}
+// the same from p, of whose row `room` elements are left in the array (past the end of a row that is not the last one
+// the group runs into the next row)
+__device__ __forceinline__ RawU load_unaligned4_at(const float *p, int room, int valid)
+{
+    const int shift = room < 4 ? 4 - room : 0;
+    RawU r;
+    __builtin_memcpy(&r.v, p - shift, 16);
+    r.meta = (valid < 0 ? 0 : valid < 4 ? valid : 4) | (shift << 4);
     return r;
 }
 enum : int { kElementwise = 0, kAligned4 = 1, kUnaligned4 = 2 };   // how a weight view fetches its groups of four
@@ -193,7 +217,6 @@ struct CatRows {  // A[m][k] = k < F ? H[m][k] : M[m][k-F]  for k < Kv, zero bey
         }
         return r;
     }
-    __device__ __forceinline__ bool k_plain() const { return V; }
     __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const
     {
         if constexpr (V) {
@@ -249,7 +272,6 @@ struct CatRowsT {  // A[m][k] = (m < F ? H[k][m] : M[k][m-F])          (contiguo
         }
         return r;
     }
-    __device__ __forceinline__ bool k_plain() const { return V; }
     __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const
     {
         if constexpr (V) {
@@ -285,7 +307,7 @@ struct CatWeights {  // B[k][n] = k < F ? W_self[k][n] : W_neigh[k-F][n]  (conti
         const int kc = k < 2 * F ? k : 0;
         const float *row = kc < F ? Ws + int64_t(kc) * N : Wn + int64_t(kc - F) * N;
         if constexpr (V) {
-            r.v = *reinterpret_cast<const float4 *>(row + (n < N ? n : 0));
+            r.v = Pack4<float>::load(row + (n < N ? n : 0));
         } else if (r.ok) {
             r.v.x = row[n];
             r.v.y = n + 1 < N ? row[n + 1] : 0.0f;
@@ -296,14 +318,13 @@ struct CatWeights {  // B[k][n] = k < F ? W_self[k][n] : W_neigh[k-F][n]  (conti
         }
         return r;
     }
-    __device__ __forceinline__ bool k_plain() const { return V; }
     __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const
     {
         if constexpr (V) {
             Raw r;
             r.ok = l.n < N;
             const int64_t e = kt * N + (dk * N + (l.n < N ? l.n : 0));   // (rows of a slab: below 2^31 elements)
-            r.v = *reinterpret_cast<const float4 *>((kt + dk < F ? Ws : Wn - int64_t(F) * N) + e);
+            r.v = Pack4<float>::load((kt + dk < F ? Ws : Wn - int64_t(F) * N) + e);
             return r;
         } else {
             return load(l, kt + dk);
@@ -337,7 +358,7 @@ struct CatWeightsT {  // B[k][n] = n < F ? W_self[n][k] : W_neigh[n-F][k]  (cont
         Raw r;
         r.ok = l.ok && k < Fo;
         if constexpr (V) {
-            r.v = *reinterpret_cast<const float4 *>(l.row + (k < Fo ? k : 0));
+            r.v = Pack4<float>::load(l.row + (k < Fo ? k : 0));
         } else if (r.ok) {
             r.v.x = l.row[k];
             r.v.y = k + 1 < Fo ? l.row[k + 1] : 0.0f;
@@ -348,13 +369,12 @@ struct CatWeightsT {  // B[k][n] = n < F ? W_self[n][k] : W_neigh[n-F][k]  (cont
         }
         return r;
     }
-    __device__ __forceinline__ bool k_plain() const { return V; }
     __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const
     {
         if constexpr (V) {
             Raw r;
             r.ok = l.ok;
-            r.v = *reinterpret_cast<const float4 *>(l.row + kt + dk);
+            r.v = Pack4<float>::load(l.row + kt + dk);
             return r;
         } else {
             return load(l, kt + dk);
@@ -439,7 +459,6 @@ struct MaskedGrad {
         }
         return r;
     }
-    __device__ __forceinline__ bool k_plain() const { return V; }
     __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const
     {
         if constexpr (V) {
@@ -515,7 +534,6 @@ struct SideWeights {  // B[k][n] = n < Fp ? W_self[k][n] : W_neigh[k][n-Fp]   (c
             return r;
         }
     }
-    __device__ __forceinline__ bool k_plain() const { return V; }
     __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const
     {
         if constexpr (V) {
@@ -575,15 +593,14 @@ struct SideWeightsT {  // B[k][n] = k < Fp ? W_self[n][k] : W_neigh[n][k-Fp]   (
             return r;
         }
     }
-    // without padding columns inside the halves every group of four along k is whole
-    __device__ __forceinline__ bool k_plain() const { return V && Fo == Fp; }
     __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const
     {
         if constexpr (V) {
             const int k = int(kt) + dk;
+            const bool second = k >= Fp;
             Raw r;
-            r.ok = l.ok;
-            r.v = *reinterpret_cast<const float4 *>((k >= Fp ? l.rn : l.rs) + k);
+            r.ok = l.ok && k - (second ? Fp : 0) < Fo;      // (Fo < Fp: padding inside the halves)
+            r.v = *reinterpret_cast<const float4 *>((second ? l.rn : l.rs) + (r.ok ? k : second ? Fp : 0));
             return r;
         } else {
             return load(l, kt + dk);
@@ -597,6 +614,7 @@ struct SideWeightsT {  // B[k][n] = k < Fp ? W_self[n][k] : W_neigh[n][k-Fp]   (
 template <bool kAsA, typename T, bool V, bool kRelu>
 struct SideGrad {
     static constexpr bool kContigK = kAsA;
+    static constexpr bool kTwoSources = true;
     typedef typename std::conditional<V, typename Pack4<T>::Packed, float4>::type Quad;
     struct Raw {
         Quad g, h;
@@ -690,18 +708,17 @@ struct SideGrad {
         }
         return r;
     }
-    __device__ __forceinline__ bool k_plain() const { return V && (!kAsA || Fo == Fp); }
     __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const
     {
         if constexpr (V) {
             Raw r;
             int64_t eg, ey;
-            if (kAsA) {   // k = position in [dZ | dYn], no padding inside the halves
+            if (kAsA) {   // k = position in [dZ | dYn]
                 const int64_t k = kt + dk;
                 r.second = k >= Fp;
                 const int c = int(k - (r.second ? Fp : 0));
-                r.nv = l.ok ? 4 : 0;
-                eg = l.a + c;
+                r.nv = !l.ok ? 0 : r.second ? 4 : Fo - c;       // (Fo < Fp: padding at the end of dZ's half)
+                eg = l.a + (c < Fo ? c : 0);
                 ey = l.b + c;
             } else {      // k = node
                 r.second = l.second;
@@ -718,6 +735,126 @@ struct SideGrad {
             return load(l, kt + dk);
         }
     }
+};
+
+// ---------------------------------------------------------------------------
+// fp32 operands whose inner extent F is not a multiple of four.  The halves of a concatenation are padded to Fq = F
+// rounded up to four, so that no group of four straddles them; the padding reads as zero in both operands.  Groups are
+// fetched whole from 4-byte-aligned addresses: past the end of a row lies the next one, and in the last row the group is
+// fetched `shift` elements earlier (RawU).  See rows_u_ok for the arrays this takes.
+// ---------------------------------------------------------------------------
+struct CatRowsU {  // A[m][k] = k < Fq ? H[m][k] : M[m][k-Fq]   (contiguous along k)
+    static constexpr bool kContigK = true;
+    typedef RawU Raw;
+    struct Lane {
+        const float *p0, *p1;   // rows
+        bool ok, last;
+    };
+    const float *H;
+    int64_t ldh;
+    const float *Mx;
+    int64_t ldm;
+    int F, Fq;
+    int64_t rows;
+    int halves;   // 1: H alone
+    static __device__ __forceinline__ float4 resolve(const Raw &r) { return r.get(); }
+    __device__ __forceinline__ Lane prepare(int64_t m) const
+    {
+        const int64_t mm = m < rows ? m : 0;
+        return Lane{H + mm * ldh, Mx + mm * ldm, m < rows, mm == rows - 1};
+    }
+    __device__ __forceinline__ Raw load(const Lane &l, int64_t k64) const
+    {
+        const int k = int(k64);
+        const bool second = k >= Fq && halves == 2;
+        int c = k - (second ? Fq : 0);
+        const int valid = l.ok ? F - c : 0;
+        if (valid <= 0) c = 0;
+        return load_unaligned4_at((second ? l.p1 : l.p0) + c, l.last ? F - c : 4, valid);
+    }
+    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const { return load(l, kt + dk); }
+};
+
+struct CatRowsTU {  // A[m][k] = (m < Fq ? H[k][m] : M[k][m-Fq])   (contiguous along m); k = node
+    static constexpr bool kContigK = false;
+    typedef RawU Raw;
+    struct Lane {
+        const float *p;   // column pointer: element of node k is p[k * ld]
+        int64_t ld;
+        int left;         // elements of the row from this column on (<= 0: padding)
+    };
+    const float *H;
+    int64_t ldh;
+    const float *Mx;
+    int64_t ldm;
+    int F, Fq;
+    int64_t rows;
+    static __device__ __forceinline__ float4 resolve(const Raw &r) { return r.get(); }
+    __device__ __forceinline__ Lane prepare(int64_t m64) const
+    {
+        const int m = int(m64);
+        const bool second = m >= Fq && m < 2 * Fq;
+        const int c = m - (second ? Fq : 0);
+        return Lane{(second ? Mx : H) + (c < F ? c : 0), second ? ldm : ldh, F - c};
+    }
+    __device__ __forceinline__ Raw load(const Lane &l, int64_t node) const
+    {
+        const bool ok = node < rows && l.left > 0;
+        const int64_t at = node < rows ? node : 0;
+        // (a padding lane fetches from column 0)
+        return load_unaligned4_at(l.p + at * l.ld, at == rows - 1 ? (l.left > 0 ? l.left : F) : 4, ok ? l.left : 0);
+    }
+    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const { return load(l, kt + dk); }
+};
+
+struct CatWeightsU {  // B[k][n] = k < Fq ? W_self[k][n] : W_neigh[k-Fq][n]   (contiguous along n); rows past F are zero
+    static constexpr bool kContigK = false;
+    typedef RawU Raw;
+    struct Lane {
+        int n;
+    };
+    const float *Ws;
+    const float *Wn;
+    int F, Fq;
+    int N;
+    static __device__ __forceinline__ float4 resolve(const Raw &r) { return r.get(); }
+    __device__ __forceinline__ Lane prepare(int64_t n) const { return Lane{int(n)}; }
+    __device__ __forceinline__ Raw load(const Lane &l, int64_t k64) const
+    {
+        const int k = int(k64);
+        const bool second = k >= Fq;
+        const int c = k - (second ? Fq : 0);
+        const bool ok = c < F && l.n < N;
+        return load_unaligned4(second ? Wn : Ws, (c < F ? c : 0) * N + (l.n < N ? l.n : 0), F * N, ok ? N - l.n : 0);
+    }
+    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const { return load(l, kt + dk); }
+};
+
+struct CatWeightsTU {  // B[k][n] = n < F ? W_self[n][k] : W_neigh[n-F][k]  (contiguous along k); k = output feature
+    static constexpr bool kContigK = true;
+    typedef RawU Raw;
+    struct Lane {
+        const float *W;
+        int row;      // first element of the row
+        bool ok;
+    };
+    const float *Ws;
+    const float *Wn;
+    int F;
+    int Fo;
+    static __device__ __forceinline__ float4 resolve(const Raw &r) { return r.get(); }
+    __device__ __forceinline__ Lane prepare(int64_t n64) const
+    {
+        const int n = int(n64);
+        if (n < F) return Lane{Ws, n * Fo, true};
+        return Lane{Wn, (n < 2 * F ? n - F : 0) * Fo, n < 2 * F};
+    }
+    __device__ __forceinline__ Raw load(const Lane &l, int64_t k64) const
+    {
+        const int k = int(k64);
+        return load_unaligned4(l.W, l.row + (k < Fo ? k : 0), F * Fo, l.ok ? (k < Fo ? Fo - k : 0) : 0);
+    }
+    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const { return load(l, kt + dk); }
 };
 
 // ---------------------------------------------------------------------------
@@ -848,6 +985,22 @@ struct SplitEpilogue {  // partial products, one slab per split
     }
 };
 
+struct SplitEpiloguePad {  // the same from [H | M] with halves padded to Fq columns, which are left out
+    static constexpr bool kColAux = false, kRowAux = false;
+    float *partial;
+    int F, Fq;
+    int N;
+    __device__ __forceinline__ float col_aux(int) const { return 0.0f; }
+    __device__ __forceinline__ float row_aux(int64_t) const { return 0.0f; }
+    __device__ __forceinline__ float value(float v, float, float, int) const { return v; }
+    __device__ __forceinline__ void store(int64_t row, int col, float v, int split) const
+    {
+        const bool second = row >= Fq;
+        const int64_t c = row - (second ? Fq : 0);
+        if (c < F) partial[(int64_t(split) * 2 * F + c + (second ? F : 0)) * N + col] = v;
+    }
+};
+
 // ---------------------------------------------------------------------------
 // bf16 fragments.  A group of 16 k-values is ONE v_mfma_f32_32x32x16_bf16 (the instruction this chip adds; the
 // 32x32x8 one runs at half its rate): lane l holds row l%32 and the eight k-values 8*(l/32) .. +7.  Activations
@@ -895,9 +1048,9 @@ __device__ __forceinline__ bf16x8 fragment_strided(const uint16_t *p, int ld)
 // of one row block, the output tiles of one node range) and share them in its L2.
 // The first slab of a block's next tile is fetched before the results of the
 // current one are written out, so that its latency passes behind the stores.
-// A tile whose k range consists of whole slabs inside both operands runs a main
-// loop with unguarded loads (addresses affine in k: one addition per load and
-// slab instead of clamps and 64-bit multiplications); a tile that lies wholly
+// Whole slabs are fetched with unguarded loads (addresses affine in k: one
+// addition per load and slab instead of clamps and 64-bit multiplications) where
+// the operands' views have them; a tile that lies wholly
 // inside the result is written out without per-element bounds tests, which also
 // gives the compiler a fixed number of stores to count its waits against.
 // ---------------------------------------------------------------------------
@@ -908,8 +1061,9 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_kernel(AL a, BL b, E
                                                                  float *__restrict__ colsum_partial)
 {
     constexpr int NT = WM * WN * 64;
-    constexpr bool kPrefetch2 = DeepPrefetch<kColSum, Epi::kRowAux>::value && (BM / WM / 32) * (BN / WN / 32) <= 4;   // (8 accumulator tiles leave no registers for it)
-    constexpr int kDepth = 2;   // slabs in flight in registers (3 and 4 measured: no faster for any product, the wide forward one slower)
+    constexpr int kDepth = DeepPrefetch<kColSum, Epi::kRowAux>::value ? 2 : 1;   // slabs in flight in registers
+    // 8 accumulator tiles, or the two sources of [dZ | dYn], leave registers for one, and not across the barrier
+    constexpr bool kLean = (BM / WM / 32) * (BN / WN / 32) > 4 || TwoSourcesAlongK<AL>::value;
     constexpr int TM = BM / WM / 32;
     constexpr int TN = BN / WN / 32;
     constexpr int A_Q = BM * BK / 4, B_Q = BN * BK / 4;   // pieces (four values) of a slab
@@ -1034,7 +1188,6 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_kernel(AL a, BL b, E
 
     int64_t work = die * per_die + blockIdx.x / kXcds;
     if (work >= die_end) return;
-    const bool views_plain = a.k_plain() && b.k_plain();
     Tile t = tile_of(work);
     prepare(t);
     fetch(t.k_begin, afirst, bfirst);
@@ -1079,53 +1232,73 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_kernel(AL a, BL b, E
                 for (int k = 0; k < BK; ++k) colsum += bf16_to_f32(Bs[buf][k * B_LD + tid]);
             }
         };
-        auto main_loop = [&](auto plain_tag) {
-            constexpr bool kPlain = decltype(plain_tag)::value;
-            if constexpr (kPlain && kPrefetch2) {
-                // Two slabs in flight in registers beside the two in LDS: a slab's loads are issued two iterations
-                // before it is staged.  One iteration's matrix work is far shorter than a memory round trip under
-                // load, so with a single slab in flight every iteration ends up waiting for one.
-                // (kDepth register sets: slab s >= 1 waits in set (s - 1) % kDepth)
-                typename AL::Raw areg[kDepth][A_V];
-                typename BL::Raw breg[kDepth][B_V];
-                const int64_t n_slabs = (t.k_end - t.k_begin) / BK;
-                static_for<kDepth>([&](auto d_tag) {
-                    constexpr int D = decltype(d_tag)::value;
-                    if (n_slabs > D + 1) fetch_plain(t.k_begin + (D + 1) * BK, areg[D], breg[D]);
-                });
-                int buf = 0;
-                for (int64_t sl0 = 0; sl0 < n_slabs; sl0 += kDepth) {
-                    static_for<kDepth>([&](auto r_tag) {
-                        constexpr int R = decltype(r_tag)::value;
-                        const int64_t sl = sl0 + R;
-                        if (sl < n_slabs) {      // the same for every thread
-                            multiply(buf);
-                            if (sl + 1 < n_slabs) stage(buf ^ 1, areg[R], breg[R]);
-                            if (sl + 1 + kDepth < n_slabs) fetch_plain(t.k_begin + (sl + 1 + kDepth) * BK, areg[R], breg[R]);
-                            __syncthreads();
-                            buf ^= 1;
-                        }
-                    });
+        int buf = 0;     // holds the slab that comes next
+        auto one_loop = [&](auto plain_tag) {      // few registers: nothing but the next slab's loads, one multiply in the code
+            typename AL::Raw areg[A_V];
+            typename BL::Raw breg[B_V];
+            for (int64_t kt = t.k_begin; kt < t.k_end; kt += BK) {
+                const bool more = kt + BK < t.k_end;
+                if (more) {  // in flight while this slab is multiplied
+                    if constexpr (decltype(plain_tag)::value) fetch_plain(kt + BK, areg, breg);
+                    else fetch(kt + BK, areg, breg);
                 }
-            } else {
-                typename AL::Raw areg[A_V];
-                typename BL::Raw breg[B_V];
-                int buf = 0;
-                for (int64_t kt = t.k_begin; kt < t.k_end; kt += BK) {
-                    const bool more = kt + BK < t.k_end;
-                    if (more) {  // in flight while this slab is multiplied
-                        if constexpr (kPlain) fetch_plain(kt + BK, areg, breg);
-                        else fetch(kt + BK, areg, breg);
-                    }
-                    multiply(buf);
-                    if (more) stage(buf ^ 1, areg, breg);  // the other buffer was last read before the previous barrier
-                    __syncthreads();
-                    buf ^= 1;
-                }
+                multiply(buf);
+                if (more) stage(buf ^ 1, areg, breg);  // the other buffer was last read before the previous barrier
+                __syncthreads();
+                buf ^= 1;
             }
         };
-        if (views_plain && (t.k_end - t.k_begin) % BK == 0) main_loop(std::true_type{});
-        else main_loop(std::false_type{});
+        if constexpr (kLean) {
+            // (two sources: the guarded loads need no more registers than the others and fewer in all: 41 us against 50)
+            if constexpr (TwoSourcesAlongK<AL>::value) one_loop(std::false_type{});
+            else if ((t.k_end - t.k_begin) % BK == 0) one_loop(std::true_type{});
+            else one_loop(std::false_type{});
+        } else {
+        // Whole slabs, in a body without branches, so that the waits ahead of a slab's staging count the younger slabs'
+        // loads exactly and leave them in flight (a conditional fetch had made every wait drain them: forward 2 x 256 ->
+        // 256 at 2,000,000 rows 1,228 -> 1,114 us, its input gradient 1,950 -> 1,801 us).
+        const int64_t n_whole = (t.k_end - t.k_begin) / BK;
+        const bool tail = t.k_begin + n_whole * BK < t.k_end;
+        auto slab = [&](int64_t s) { return t.k_begin + s * BK; };
+        if (n_whole > 1) {
+            // Slab s >= 1 waits in register set (s - 1) % kDepth; its loads are issued kDepth iterations before it is
+            // staged.  The last steps, with nothing or less to fetch, come after the loop.
+            typename AL::Raw areg[kDepth][A_V];
+            typename BL::Raw breg[kDepth][B_V];
+            static_for<kDepth>([&](auto d_tag) {
+                constexpr int D = decltype(d_tag)::value;
+                if (D + 1 < n_whole) fetch_plain(slab(D + 1), areg[D], breg[D]);
+            });
+            int64_t s = 0;
+            for (; s + 2 + kDepth < n_whole; s += 2)
+                static_for<2>([&](auto r_tag) {
+                    constexpr int R = decltype(r_tag)::value;
+                    multiply(R);
+                    stage(1 - R, areg[R % kDepth], breg[R % kDepth]);   // (last read before the previous barrier)
+                    fetch_plain(slab(s + R + 1 + kDepth), areg[R % kDepth], breg[R % kDepth]);
+                    __syncthreads();
+                });
+            static_for<kDepth + 1>([&](auto r_tag) {
+                constexpr int R = decltype(r_tag)::value;
+                if (s + R + 1 < n_whole) {
+                    multiply(R % 2);
+                    stage(1 - R % 2, areg[R % kDepth], breg[R % kDepth]);
+                    if (s + R + 1 + kDepth < n_whole) fetch_plain(slab(s + R + 1 + kDepth), areg[R % kDepth], breg[R % kDepth]);
+                    __syncthreads();
+                }
+            });
+            buf = int((n_whole - 1) % 2);
+        }
+        if (n_whole > 0 && tail) {      // the last slab reaches past the end of k
+            fetch(t.k_begin + n_whole * BK, afirst, bfirst);
+            multiply(buf);
+            buf ^= 1;
+            stage(buf, afirst, bfirst);
+            __syncthreads();
+        }
+        multiply(buf);
+        __syncthreads();
+        }
 
         // Per-column / per-row epilogue inputs (bias, 1/deg) go through LDS: they are loaded from
         // global memory once, here, before any store is in flight.  Fetched into registers directly they
@@ -1206,6 +1379,20 @@ namespace tma {
 
 template <typename T>
 static bool vec4_ok(const T *p, int64_t ld) { return aligned(p, 4 * sizeof(T)) && ld % 4 == 0; }
+// groups of four inside rows of F elements may be fetched whole: fp32 needs no alignment for it
+template <typename T>
+static bool groups_ok(const T *p, int64_t ld, int F)
+{
+    return F % 4 == 0 && (sizeof(T) == 4 || vec4_ok(p, ld));
+}
+// the same for a gradient or activation whose rows may have padding after F elements (then read, and discarded)
+template <typename T>
+static bool padded_groups_ok(const T *p, int64_t ld, int F) { return vec4_ok(p, ld) || groups_ok(p, ld, F); }
+// what the views of RawU need: four elements at least, a group that starts in one row ends in the next at the latest
+// (one row has none), and element numbers of weights in 32 bits
+static inline bool rows_u_ok(int64_t n, int64_t ld, int F) { return (n - 1) * ld + F >= 4 && (n == 1 || ld >= 3); }
+static inline bool weights_u_ok(int64_t F_in, int64_t F_out) { return F_in * F_out >= 4 && F_in * F_out <= INT32_MAX; }
+static inline int pad4(int F) { return (F + 3) / 4 * 4; }
 
 // BK: k-values per slab of the bf16 kernel (the fp32 one has its own).
 template <int BM, int BN, int BK, int WM, int WN, bool kColSum, typename CT = float, class AL, class BL, class Epi>
@@ -1260,30 +1447,49 @@ static inline bool few_tiles(int64_t M, int64_t N, int n_splits = 1)
 // once instead of twice and converts a quarter fewer values per product; it is taken where it pads no more than two
 // tiles of 128 would, across the columns for a product whose rows are nodes and across the rows for a weight gradient.
 // Measured, 128 x 128 -> 256-wide, n = 125,237 / 1,000,000: forward 2 x 128 -> 256 133 -> 116 us / 961 -> 838 us, its
-// input gradient 166 -> 142 / 1,210 -> 1,031 us, its weight gradient 125 -> 117 / 901 -> 840 us.  Operands on the
-// element-wise path are bound by their loads and keep the one tile.
-template <bool kWide, bool kColSum, class AL, class BL, class Epi>
+// input gradient 166 -> 142 / 1,210 -> 1,031 us, its weight gradient 125 -> 117 / 901 -> 840 us.
+template <bool kColSum, class AL, class BL, class Epi>
 static void launch_split_128(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K,
                              int64_t kps, int n_splits, float *colsum, hipStream_t s)
 {
-    if constexpr (kWide && kColSum) {
+    if constexpr (kColSum) {
         if (ceil_div(M, int64_t(128)) % 2 == 0)
             return launch_gemm<256, 128, 32, 4, 2, true, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
-    } else if constexpr (kWide) {
+    } else {
         if (ceil_div(N, 128) % 2 == 0)
             return launch_gemm<128, 256, 32, 2, 4, false, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
     }
     launch_gemm<128, 128, 32, 2, 2, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
 }
 
-// kWide: the operands are on the vector path
+// Every fp32 product.  kWide: the operands are fetched in groups of four.  With up to one 64 x 64 tile per compute unit that is
+// the tile, above that 64 x 128 up to some 1.5 tiles of 128 x 128 per unit.  Measured, us, 128 x 64 -> 64 x 64 at 5,000
+// rows: forward 2 x 64 -> 64 8.7 -> 7.1, its weight gradient 9.8 -> 8.4; 64 x 128 -> 64 x 64 at 12,000 rows, 128 wide:
+// 12.4 -> 14.0; 128 x 64 -> 64 x 128 at 24,000 rows: forward 2 x 128 -> 128 20.1 -> 17.7, 2 x 256 -> 256 51.5 -> 44.7.
+template <bool kColSum, bool kWide, class AL, class BL, class Epi>
+static void launch_split(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K, int64_t kps,
+                         int n_splits, float *colsum, hipStream_t s)
+{
+    if constexpr (!kWide)    // rare, and bound by its loads: one tile is enough
+        return launch_gemm<128, 64, 32, 4, 1, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    else {
+    if (ceil_div(M, int64_t(64)) * ceil_div(N, 64) * n_splits <= 256)
+        return launch_gemm<64, 64, 32, 2, 2, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    if (N <= 64) return launch_gemm<128, 64, 32, 4, 1, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    if (few_tiles(M, N, n_splits))
+        return launch_gemm<64, 128, 32, 2, 2, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    if (N <= 96) return launch_gemm<128, 96, 32, 4, 1, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    launch_split_128<kColSum>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    }
+}
+
 template <typename CT, int BK, bool kColSum, bool kWide, class AL, class BL, class Epi>
 static void launch_by_width(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K,
                             int64_t kps, int n_splits, float *colsum, hipStream_t s)
 {
-    if (N <= 64 || few_tiles(M, N, n_splits)) launch_gemm<128, 64, BK, 4, 1, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    if constexpr (sizeof(CT) == 4) launch_split<kColSum, kWide>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    else if (N <= 64 || few_tiles(M, N, n_splits)) launch_gemm<128, 64, BK, 4, 1, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
     else if (N <= 96) launch_gemm<128, 96, BK, 4, 1, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
-    else if constexpr (sizeof(CT) == 4) launch_split_128<kWide, kColSum>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
     else launch_gemm<128, 128, BK, 2, 2, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
 }
 

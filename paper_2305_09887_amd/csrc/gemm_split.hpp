@@ -166,7 +166,12 @@ __global__ __launch_bounds__(WM *WN * 64, kSplitPerCu) void gemm_split_kernel(AL
                                                                     float *__restrict__ colsum_partial)
 {
     constexpr int NT = WM * WN * 64;
-    constexpr int kDepth = kColSum ? 2 : 1;
+    // Slabs in flight in registers: two for four wavefronts (5 to 8 %: 434 -> 412 us forward 256 -> 2 x 48 at 1,000,000 rows,
+    // 394 -> 361 us its weight gradient) and for the weight gradient, which streams both operands; one for the other
+    // products of eight (no gain).  The unaligned views take registers of their own and go without a set that lives
+    // across the barrier (48 -> 45 us and 47 -> 41 us, widths 90 -> 150 at 40,004 rows; the others lose 5 to 20 % so).
+    constexpr int kDepth = kColSum || WM * WN == 4 ? 2 : 1;
+    constexpr bool kLean = WM * WN == 8 && (std::is_same<typename AL::Raw, RawU>::value || std::is_same<typename BL::Raw, RawU>::value);
     constexpr int TM = BM / WM / 32;
     constexpr int TN = BN / WN / 32;
     typedef SlabSlots<AL, BM, NT> ASlots;
@@ -289,39 +294,47 @@ __global__ __launch_bounds__(WM *WN * 64, kSplitPerCu) void gemm_split_kernel(AL
         __syncthreads();  // the previous tile's epilogue has finished reading LDS
         stage(0, afirst, bfirst, std::false_type{});
         __syncthreads();
-        // Whole slabs: a body without branches, in which conversions and loads can pass behind the matrix work (loads past
-        // the last slab fetch that one again).  Slab s >= 1 waits in register set (s - 1) % kDepth; its loads are issued
-        // kDepth iterations before it is staged.
+        // Whole slabs: a body without branches, in which conversions and loads can pass behind the matrix work and every
+        // wait counts exactly.
         const int n_whole = int((t.k_end - t.k_begin) / kSlabK);
         const bool tail = t.k_begin + int64_t(n_whole) * kSlabK < t.k_end;
+        auto slab = [&](int s) { return t.k_begin + int64_t(s) * kSlabK; };
         int buf = 0;     // holds the slab that comes next
-        if (n_whole > 1) {
+        if constexpr (kLean) {
+            for (int s = 0; s + 1 < n_whole; ++s) {
+                typename ASlots::Raws areg;
+                typename BSlots::Raws breg;
+                fetch_whole(slab(s + 1), areg, breg);
+                multiply(buf);
+                buf ^= 1;
+                stage(buf, areg, breg, std::true_type{});
+                __syncthreads();
+            }
+        } else if (n_whole > 1) {
+            // Slab s >= 1 waits in register set (s - 1) % kDepth; its loads are issued kDepth iterations before it is staged.
+            // Past the end the last slab is fetched again: steps without a fetch after the loop cost more (forward
+            // 2 x 128 -> 256 at 125,237 rows 110 -> 116 us, its weight gradient 110 -> 119 us).
             typename ASlots::Raws areg[kDepth];
             typename BSlots::Raws breg[kDepth];
-            auto slab = [&](int s) { return t.k_begin + int64_t(s < n_whole ? s : n_whole - 1) * kSlabK; };
+            auto at = [&](int s) { return slab(s < n_whole ? s : n_whole - 1); };
             static_for<kDepth>([&](auto d_tag) {
                 constexpr int D = decltype(d_tag)::value;
-                fetch_whole(slab(D + 1), areg[D], breg[D]);
+                fetch_whole(at(D + 1), areg[D], breg[D]);
             });
             auto step = [&](int s, auto buf_tag, auto set_tag) {
                 constexpr int kBuf = decltype(buf_tag)::value, kSet = decltype(set_tag)::value;
                 multiply(kBuf);
-                stage(1 - kBuf, areg[kSet], breg[kSet], std::true_type{});
-                fetch_whole(slab(s + 1 + kDepth), areg[kSet], breg[kSet]);
+                stage(1 - kBuf, areg[kSet], breg[kSet], std::true_type{});   // (last read before the previous barrier)
+                fetch_whole(at(s + 1 + kDepth), areg[kSet], breg[kSet]);
                 __syncthreads();
             };
-            constexpr int kTurn = kDepth % 2 ? 2 * kDepth : kDepth;   // buffers and register sets come round together
             int s = 0;
-            for (; s + kTurn < n_whole; s += kTurn)
-                static_for<kTurn>([&](auto r_tag) {
+            for (; s + 2 < n_whole; s += 2)
+                static_for<2>([&](auto r_tag) {
                     constexpr int R = decltype(r_tag)::value;
-                    step(s + R, std::integral_constant<int, R % 2>{}, std::integral_constant<int, R % kDepth>{});
+                    step(s + R, std::integral_constant<int, R>{}, std::integral_constant<int, R % kDepth>{});
                 });
-            static_for<kTurn - 1>([&](auto r_tag) {
-                constexpr int R = decltype(r_tag)::value;
-                if (s + R + 1 < n_whole)
-                    step(s + R, std::integral_constant<int, R % 2>{}, std::integral_constant<int, R % kDepth>{});
-            });
+            if (s + 1 < n_whole) step(s, std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{});
             buf = (n_whole - 1) % 2;
         }
         if (n_whole > 0 && tail) {      // the last slab reaches past the end of k

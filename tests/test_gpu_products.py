@@ -34,7 +34,7 @@ def data(n, fi, fo, seed):
     return f(n, fi), f(fi, fo) * np.float32(0.1), f(fo) * np.float32(0.1), f(n, fo) * np.float32(1e-6)
 
 
-SHAPES = [(1, 4, 5), (15, 16, 47), (129, 20, 64), (128, 33, 96), (257, 47, 100), (1000, 64, 130), (4100, 130, 48),
+SHAPES = [(1, 1, 2), (1, 3, 1), (2, 1, 4), (3, 5, 6), (1, 7, 3), (40, 2, 66), (1, 4, 5), (15, 16, 47), (129, 20, 64), (128, 33, 96), (257, 47, 100), (1000, 64, 130), (4100, 130, 48),
           (20000, 128, 128), (70001, 100, 256), (50000, 90, 41)]
 
 
@@ -50,6 +50,55 @@ def test_dense_products(B, n, fi, fo):
     within(dW, X.T, g, "weight gradient")
     within(db.reshape(1, -1), np.ones((1, n)), g, "bias gradient")
     within(dX, g, W.T, "input gradient")
+
+
+@pytest.mark.parametrize("pitch,offset", [(0, 0), (1, 0), (3, 1), (2, 2)])
+@pytest.mark.parametrize("n,fi,fo", [(130, 90, 150), (1000, 33, 41), (257, 64, 7), (77, 5, 300)])
+def test_rows_at_any_address(B, n, fi, fo, pitch, offset):
+    """The same products with rows that are neither aligned nor a multiple of four apart, in arrays that end with them."""
+    X, W, _, g = data(n, fi, fo, n + pitch)
+
+    def placed(t):
+        flat = torch.full(((t.shape[0] - 1) * (t.shape[1] + pitch) + t.shape[1] + offset,), float("nan"), device="cuda")
+        view = flat.as_strided(t.shape, (t.shape[1] + pitch, 1), offset)
+        view.copy_(torch.as_tensor(t))
+        return view
+
+    x, d, w = placed(X), placed(g), torch.as_tensor(W).cuda()
+    Y = B.tma_dense_fwd(x, w, None, B.TMA_ACT_NONE)
+    X, W, g = X.astype(np.float64), W.astype(np.float64), g.astype(np.float64)
+    within(Y, X, W, "forward")
+    dW, db, dX = B.tma_dense_bwd(x, None, d, w, B.TMA_ACT_NONE)[:3]
+    within(dW, X.T, g, "weight gradient")
+    within(db.reshape(1, -1), np.ones((1, n)), g, "bias gradient")
+    within(dX, g, W.T, "input gradient")
+
+
+@pytest.mark.parametrize("n,fi,fo,pitch", [(700, 90, 150, 0), (701, 33, 41, 3), (300, 150, 41, 0), (50, 6, 130, 1), (2, 3, 5, 0)])
+def test_sage_layer_at_any_width(B, n, fi, fo, pitch):
+    """[H | M] with halves that are no multiples of four, in both orders of the layer's two steps."""
+    r = np.random.default_rng(n)
+    X, Ws, b, g = data(n, fi, fo, n)
+    Wn = data(n, fi, fo, n + 1)[1]
+    A = np.triu(r.random((n, n)) < 4.0 / n, 1)
+    A = A | A.T
+    deg = A.sum(1)
+    rowptr, colidx = np.concatenate([[0], np.cumsum(deg)]).astype(np.int32), np.nonzero(A)[1].astype(np.int32)
+    inv = np.where(deg > 0, 1.0 / np.maximum(deg, 1), 0.0)
+    x = torch.zeros((n, fi + pitch), device="cuda")[:, :fi]
+    x.copy_(torch.as_tensor(X))
+    c = lambda t: torch.as_tensor(t).cuda()
+    graph = c(rowptr), c(colidx) if colidx.size else torch.zeros(1, dtype=torch.int32, device="cuda"), c(inv.astype(np.float32))
+    M, out = B.tma_sage_layer_fwd(*graph, x, c(Ws), c(Wn), c(b), B.TMA_ACT_NONE)
+    X, Ws, Wn, b, g64 = (t.astype(np.float64) for t in (X, Ws, Wn, b, g))
+    mean = inv[:, None] * (A @ X)
+    tol = 2e-6      # sums of a few fp32 roundings per term, far below the terms' own sizes
+    close = lambda got, want: np.linalg.norm(got.double().cpu().numpy() - want) <= tol * np.linalg.norm(want) + 1e-30
+    assert close(out, X @ Ws + mean @ Wn + b)
+    dWs, dWn, db, dH = B.tma_sage_layer_bwd(*graph, x, M, out, c(g), c(Ws.astype(np.float32)), c(Wn.astype(np.float32)),
+                                            B.TMA_ACT_NONE)[:4]
+    assert close(dWs, X.T @ g64) and close(dWn, mean.T @ g64) and close(db, g64.sum(0))
+    assert close(dH, g64 @ Ws.T + A.T @ (inv[:, None] * (g64 @ Wn.T)))
 
 
 @pytest.mark.parametrize("n,fi,fo", [(300, 64, 47), (1000, 33, 130)])
