@@ -165,10 +165,23 @@ extern "C" int tma_sage_layer_bwd(int64_t n, const int32_t *rowptr_T, const int3
         const int Fp = pad_cols(F_out, dtype);
         void *dZs = base;
         void *dYn = base + w.dm_bytes / 2;
-        if (int rc = launch_scale_mask_rows(n, F_out, Fp, dHnext, Hnext, ld_next, inv_deg, act == TMA_ACT_RELU, dtype,
-                                            dZs, Fp, s))
-            return rc;
-        if (int rc = launch_spmm(n, rowptr_T, colidx_T, nullptr, dZs, Fp, Fp, dtype, dYn, Fp, false, s)) return rc;
+        // Without an activation dZ is dHnext itself: its rows are gathered with their inv_deg as weights, where they
+        // have room for the padded width (whatever their padding holds), and the scaled copy of them is not made.
+        // fp32, 47 wide: 23 + 13 -> 26 us at 125,237 rows of 2.5 entries, 68 + 11 -> 71 us at 100,000 rows of 20.  bf16
+        // has twice the values to weight per 16 bytes: 1,615 + 1,064 -> 2,300 us at 12.5 M rows of 1.6 entries, but
+        // 111 + 17 -> 138 us at 150,000 rows of 23, whose copy stays in cache.
+        const int64_t per16 = 16 / int64_t(elem_size(dtype));
+        const bool weigh = dtype == TMA_F32 || n >= (int64_t(1) << 20);
+        if (weigh && act == TMA_ACT_NONE && ld_next >= Fp && ld_next % per16 == 0 && aligned(dHnext, 16)) {
+            if (int rc = launch_spmm_combine(n, rowptr_T, colidx_T, nullptr, dHnext, ld_next, Fp, dtype, dYn, Fp, false, nullptr, 0,
+                                             nullptr, F_out, false, false, inv_deg, s))
+                return rc;
+        } else {
+            if (int rc = launch_scale_mask_rows(n, F_out, Fp, dHnext, Hnext, ld_next, inv_deg, act == TMA_ACT_RELU, dtype,
+                                                dZs, Fp, s))
+                return rc;
+            if (int rc = launch_spmm(n, rowptr_T, colidx_T, nullptr, dZs, Fp, Fp, dtype, dYn, Fp, false, s)) return rc;
+        }
         if (int rc = launch_sage_tf_gemm_bwd_weight(n, H, ldh, dHnext, Hnext, ld_next, dYn, Fp, F_in, F_out, act, dtype,
                                                     dW_self, dW_neigh, dbias, wws, w.weight_bytes, s))
             return rc;
