@@ -7,6 +7,8 @@ namespace tma {
 
 // Split reduction for the transform-first form: partial is [splits][F][2*Fp]; column c of the left half
 // goes to dW_self[:, c], of the right half to dW_neigh[:, c]; the column sums of the left half are dbias.
+// Columns in groups of four, which never straddle the halves (Fp is a multiple of four); one column per lane asked for a
+// quarter of the bytes at a time (256 splits of 256 x 96: 12.0 -> 8.3 us).
 __global__ __launch_bounds__(256) void reduce_splits_halves_kernel(const float *__restrict__ partial,
                                                                    const float *__restrict__ colsum_partial,
                                                                    int n_splits, int F, int Fo, int Fp,
@@ -14,36 +16,43 @@ __global__ __launch_bounds__(256) void reduce_splits_halves_kernel(const float *
                                                                    float *__restrict__ dW_neigh,
                                                                    float *__restrict__ dbias)
 {
-    __shared__ float part[kRedSlices][kRedCols];
+    __shared__ float4 part[kRedSlices][kRedCols];
     const int N = 2 * Fp;
     const int64_t total = int64_t(F) * N;
     const int64_t total_all = total + N;
     const int col = threadIdx.x % kRedCols, q = threadIdx.x / kRedCols;
-    const int64_t e = int64_t(blockIdx.x) * kRedCols + col;
+    const int64_t e = (int64_t(blockIdx.x) * kRedCols + col) * 4;
     const int per = (n_splits + kRedSlices - 1) / kRedSlices;
     const int s_begin = q * per, s_end = (s_begin + per < n_splits) ? s_begin + per : n_splits;
-    float s = 0.0f;
-    if (e < total) {
+    float4 s = zero4();
+    if (e < total_all) {
+        const float *from = e < total ? partial + e : colsum_partial + (e - total);
+        const int64_t step = e < total ? total : N;
 #pragma unroll 8
-        for (int sp = s_begin; sp < s_end; ++sp) s += partial[int64_t(sp) * total + e];
-    } else if (e < total_all) {
-        for (int sp = s_begin; sp < s_end; ++sp) s += colsum_partial[int64_t(sp) * N + (e - total)];
+        for (int sp = s_begin; sp < s_end; ++sp) {
+            const float4 v = *reinterpret_cast<const float4 *>(from + int64_t(sp) * step);
+            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+        }
     }
     part[q][col] = s;
     __syncthreads();
     if (q == 0 && e < total_all) {
-        float r = 0.0f;
+        float r[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int w = 0; w < kRedSlices; ++w) r += part[w][col];
-        if (e < total) {
-            const int64_t m = e / N;
-            const int c = int(e - m * N);
-            const bool second = c >= Fp;
-            const int cc = c - (second ? Fp : 0);
-            if (cc < Fo) (second ? dW_neigh : dW_self)[m * Fo + cc] = r;
-        } else {
-            const int c = int(e - total);
-            if (c < Fo) dbias[c] = r;
+        for (int w = 0; w < kRedSlices; ++w) {
+            const float4 v = part[w][col];
+            r[0] += v.x; r[1] += v.y; r[2] += v.z; r[3] += v.w;
+        }
+        const bool weight = e < total;
+        const int64_t m = weight ? e / N : 0;
+        const int c = int(weight ? e - m * N : e - total);
+        const bool second = c >= Fp;
+        const int cc = c - (second ? Fp : 0);
+        float *out = weight ? (second ? dW_neigh : dW_self) + m * Fo : (second ? nullptr : dbias);
+        if (out) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (cc + i < Fo) out[cc + i] = r[i];
         }
     }
 }
@@ -191,7 +200,7 @@ int launch_sage_tf_gemm_bwd_weight(int64_t n, const void *H, int64_t ldh, const 
     if (rc) return rc;
     const int64_t total_all = int64_t(F_in) * 2 * Fp + 2 * Fp;
     TMA_TIMED("reduce_splits_halves", stream);
-    hipLaunchKernelGGL(reduce_splits_halves_kernel, dim3(unsigned(ceil_div(total_all, kRedCols))), dim3(256), 0, stream,
+    hipLaunchKernelGGL(reduce_splits_halves_kernel, dim3(unsigned(ceil_div(total_all, 4 * kRedCols))), dim3(256), 0, stream,
                        partial, colsum, n > 0 ? w.n_splits : 0, F_in, F_out, Fp, dW_self, dW_neigh, dbias);
     return check_launch("sage gemm tf bwd weight reduce");
 }

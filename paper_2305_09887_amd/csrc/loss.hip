@@ -123,11 +123,12 @@ __global__ __launch_bounds__(256) void sigmoid_l2_kernel(int64_t n, int C, const
     if (threadIdx.x == 0) block_loss[blockIdx.x] = s;
 }
 
-// Single block: fixed-order sum of the per-block terms, times `scale`.
+// Single block: fixed-order sum of the per-block terms, times `scale`; eight loads of a thread in flight, added in order.
 __global__ __launch_bounds__(256) void finish_loss_kernel(int64_t nb, const float *__restrict__ block_loss,
                                                           float scale, float *__restrict__ loss_out)
 {
     float s = 0.0f;
+#pragma unroll 8
     for (int64_t i = threadIdx.x; i < nb; i += 256) s += block_loss[i];
     s = block_sum_256(s);
     if (threadIdx.x == 0) *loss_out = s * scale;
