@@ -1254,50 +1254,50 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_kernel(AL a, BL b, E
             else if ((t.k_end - t.k_begin) % BK == 0) one_loop(std::true_type{});
             else one_loop(std::false_type{});
         } else {
-        // Whole slabs, in a body without branches, so that the waits ahead of a slab's staging count the younger slabs'
-        // loads exactly and leave them in flight (a conditional fetch had made every wait drain them: forward 2 x 256 ->
-        // 256 at 2,000,000 rows 1,228 -> 1,114 us, its input gradient 1,950 -> 1,801 us).
-        const int64_t n_whole = (t.k_end - t.k_begin) / BK;
-        const bool tail = t.k_begin + n_whole * BK < t.k_end;
-        auto slab = [&](int64_t s) { return t.k_begin + s * BK; };
-        if (n_whole > 1) {
-            // Slab s >= 1 waits in register set (s - 1) % kDepth; its loads are issued kDepth iterations before it is
-            // staged.  The last steps, with nothing or less to fetch, come after the loop.
-            typename AL::Raw areg[kDepth][A_V];
-            typename BL::Raw breg[kDepth][B_V];
-            static_for<kDepth>([&](auto d_tag) {
-                constexpr int D = decltype(d_tag)::value;
-                if (D + 1 < n_whole) fetch_plain(slab(D + 1), areg[D], breg[D]);
-            });
-            int64_t s = 0;
-            for (; s + 2 + kDepth < n_whole; s += 2)
-                static_for<2>([&](auto r_tag) {
-                    constexpr int R = decltype(r_tag)::value;
-                    multiply(R);
-                    stage(1 - R, areg[R % kDepth], breg[R % kDepth]);   // (last read before the previous barrier)
-                    fetch_plain(slab(s + R + 1 + kDepth), areg[R % kDepth], breg[R % kDepth]);
-                    __syncthreads();
+            // Whole slabs, in a body without branches, so that the waits ahead of a slab's staging count the younger slabs'
+            // loads exactly and leave them in flight (a conditional fetch had made every wait drain them: forward 2 x 256 ->
+            // 256 at 2,000,000 rows 1,228 -> 1,114 us, its input gradient 1,950 -> 1,801 us).
+            const int64_t n_whole = (t.k_end - t.k_begin) / BK;
+            const bool tail = t.k_begin + n_whole * BK < t.k_end;
+            auto slab = [&](int64_t s) { return t.k_begin + s * BK; };
+            if (n_whole > 1) {
+                // Slab s >= 1 waits in register set (s - 1) % kDepth; its loads are issued kDepth iterations before it is
+                // staged.  The last steps, with nothing or less to fetch, come after the loop.
+                typename AL::Raw areg[kDepth][A_V];
+                typename BL::Raw breg[kDepth][B_V];
+                static_for<kDepth>([&](auto d_tag) {
+                    constexpr int D = decltype(d_tag)::value;
+                    if (D + 1 < n_whole) fetch_plain(slab(D + 1), areg[D], breg[D]);
                 });
-            static_for<kDepth + 1>([&](auto r_tag) {
-                constexpr int R = decltype(r_tag)::value;
-                if (s + R + 1 < n_whole) {
-                    multiply(R % 2);
-                    stage(1 - R % 2, areg[R % kDepth], breg[R % kDepth]);
-                    if (s + R + 1 + kDepth < n_whole) fetch_plain(slab(s + R + 1 + kDepth), areg[R % kDepth], breg[R % kDepth]);
-                    __syncthreads();
-                }
-            });
-            buf = int((n_whole - 1) % 2);
-        }
-        if (n_whole > 0 && tail) {      // the last slab reaches past the end of k
-            fetch(t.k_begin + n_whole * BK, afirst, bfirst);
+                int64_t s = 0;
+                for (; s + 2 + kDepth < n_whole; s += 2)
+                    static_for<2>([&](auto r_tag) {
+                        constexpr int R = decltype(r_tag)::value;
+                        multiply(R);
+                        stage(1 - R, areg[R % kDepth], breg[R % kDepth]);   // (last read before the previous barrier)
+                        fetch_plain(slab(s + R + 1 + kDepth), areg[R % kDepth], breg[R % kDepth]);
+                        __syncthreads();
+                    });
+                static_for<kDepth + 1>([&](auto r_tag) {
+                    constexpr int R = decltype(r_tag)::value;
+                    if (s + R + 1 < n_whole) {
+                        multiply(R % 2);
+                        stage(1 - R % 2, areg[R % kDepth], breg[R % kDepth]);
+                        if (s + R + 1 + kDepth < n_whole) fetch_plain(slab(s + R + 1 + kDepth), areg[R % kDepth], breg[R % kDepth]);
+                        __syncthreads();
+                    }
+                });
+                buf = int((n_whole - 1) % 2);
+            }
+            if (n_whole > 0 && tail) {      // the last slab reaches past the end of k
+                fetch(t.k_begin + n_whole * BK, afirst, bfirst);
+                multiply(buf);
+                buf ^= 1;
+                stage(buf, afirst, bfirst);
+                __syncthreads();
+            }
             multiply(buf);
-            buf ^= 1;
-            stage(buf, afirst, bfirst);
             __syncthreads();
-        }
-        multiply(buf);
-        __syncthreads();
         }
 
         // Per-column / per-row epilogue inputs (bias, 1/deg) go through LDS: they are loaded from
@@ -1470,16 +1470,16 @@ template <bool kColSum, bool kWide, class AL, class BL, class Epi>
 static void launch_split(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K, int64_t kps,
                          int n_splits, float *colsum, hipStream_t s)
 {
-    if constexpr (!kWide)    // rare, and bound by its loads: one tile is enough
-        return launch_gemm<128, 64, 32, 4, 1, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
-    else {
-    if (ceil_div(M, int64_t(64)) * ceil_div(N, 64) * n_splits <= 256)
-        return launch_gemm<64, 64, 32, 2, 2, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
-    if (N <= 64) return launch_gemm<128, 64, 32, 4, 1, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
-    if (few_tiles(M, N, n_splits))
-        return launch_gemm<64, 128, 32, 2, 2, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
-    if (N <= 96) return launch_gemm<128, 96, 32, 4, 1, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
-    launch_split_128<kColSum>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    if constexpr (!kWide) {   // rare, and bound by its loads: one tile is enough
+        launch_gemm<128, 64, 32, 4, 1, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    } else {
+        if (ceil_div(M, int64_t(64)) * ceil_div(N, 64) * n_splits <= 256)
+            launch_gemm<64, 64, 32, 2, 2, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+        else if (N <= 64) launch_gemm<128, 64, 32, 4, 1, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+        else if (few_tiles(M, N, n_splits))
+            launch_gemm<64, 128, 32, 2, 2, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+        else if (N <= 96) launch_gemm<128, 96, 32, 4, 1, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+        else launch_split_128<kColSum>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
     }
 }
 
@@ -1492,7 +1492,6 @@ static void launch_by_width(const char *name, const AL &a, const BL &b, const Ep
     else if (N <= 96) launch_gemm<128, 96, BK, 4, 1, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
     else launch_gemm<128, 128, BK, 2, 2, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
 }
-
 
 struct WeightSplit {
     int n_splits;
