@@ -54,16 +54,17 @@ static int dense_fwd_typed(int64_t n, const T *X, int64_t ldx, int32_t F_in, con
     do {                                                                                      \
         CatRows<T, VA_> a{X, ldx, X, ldx, F_in, n, F_in};                                          \
         SideWeights<VB_> b{W, W, F_in, F_out, pad8(F_out)};                                   \
-        launch_by_width<T, 32, false, VA_>(name, a, b, e, n, N_out, K, kps, 1, nullptr, s);        \
+        if constexpr (sizeof(T) == 4) launch_fwd_f32<32>(name, a, b, e, n, N_out, K, s);      \
+        else launch_by_width<T, 32, false, VA_>(name, a, b, e, n, N_out, K, kps, 1, nullptr, s); \
     } while (0)
     // (va: F_in is a multiple of four, so W holds at least four elements and may be read in unaligned groups)
     if (va && vb) TMA_DENSE_FWD(true, kAligned4);
     else if (va) TMA_DENSE_FWD(true, kUnaligned4);
     else if constexpr (sizeof(T) == 4) {
         if (rows_u_ok(n, ldx, F_in) && weights_u_ok(F_in, F_out)) {
-            CatRowsU a{X, ldx, X, ldx, F_in, pad4(F_in), n, 1};
+            CatRowsU a{X, ldx, F_in, n};
             SideWeights<kUnaligned4> b{W, W, F_in, F_out, pad8(F_out)};
-            launch_by_width<T, 32, false, true>(name, a, b, e, n, N_out, K, kps, 1, nullptr, s);
+            launch_fwd_f32<32>(name, a, b, e, n, N_out, K, s);
         } else TMA_DENSE_FWD(false, kElementwise);
     } else TMA_DENSE_FWD(false, kElementwise);
 #undef TMA_DENSE_FWD

@@ -6,9 +6,9 @@
 // with dZ = dH' (.) act'(Z) formed while loading (chain rule as in the proof of
 // the paper's Thm. 1).  The transform-first form of the layer is in gemm_tf.hip.
 //
-// The products run in the tile kernels of gemm_core.hpp (fp32 storage: fp32-accurate products from bf16 parts, so
-// the 1e-4 parity bound holds; bf16 storage: bf16 MFMA with fp32 accumulation); these files hold the operand /
-// epilogue combinations of the GraphSAGE layer.
+// The products run in the tile kernels of gemm_core.hpp (fp32 storage: forward on the fp32 matrix instruction, backward
+// as fp32-accurate products from bf16 parts; bf16 storage: bf16 MFMA with fp32 accumulation); these files hold the
+// operand / epilogue combinations of the GraphSAGE layer.
 #include "gemm_core.hpp"
 
 namespace tma {
@@ -19,9 +19,9 @@ static void fwd_launch(const AL &a, const BL &b, const FwdEpilogue<T> &e, int64_
                        hipStream_t s)
 {
     if constexpr (sizeof(T) == 4)
-        launch_split<false, VA>(F_out <= 64 || few_tiles(n, F_out) ? (VA ? "gemm_fwd_128x64" : "gemm_fwd_128x64_generic")
-                                                                   : (VA ? "gemm_fwd_128x128" : "gemm_fwd_128x128_generic"),
-                                a, b, e, n, F_out, K, kps, 1, nullptr, s);   // (the name of its size class)
+        launch_fwd_f32<16>(F_out <= 64 || few_tiles(n, F_out) ? (VA ? "gemm_fwd_128x64" : "gemm_fwd_128x64_generic")
+                                                              : (VA ? "gemm_fwd_128x128" : "gemm_fwd_128x128_generic"),
+                           a, b, e, n, F_out, K, s);   // (the name of its size class)
     else if (F_out <= 64 || few_tiles(n, F_out))
         launch_gemm<128, 64, 32, 4, 1, false, T>(VA ? "gemm_fwd_128x64_bf16" : "gemm_fwd_128x64_bf16_generic", a, b, e, n, F_out, K,
                                                  kps, 1, nullptr, s);
@@ -46,23 +46,21 @@ static void fwd_dispatch(int64_t n, const T *H, int64_t ldh, const T *M, int64_t
     fwd_launch<T, VA>(a, b, e, n, F_out, K, kps, s);
 }
 
-// fp32: groups of four throughout, also where a row or the weights' rows are no multiples of four.  Element by element
-// (the one other way) a step of the widths 90-150-41 on 40,004 rows took 333 us, this way 289 us.
+// fp32: groups of four at any 4-byte-aligned address.  Rows of [H | M] whose halves are no multiples of four are read
+// element by element: a group that straddles the halves could not be fetched whole, and halves padded to groups would
+// sum in another order (gemm_f32.hpp).
 static void fwd_dispatch_f32(int64_t n, const float *H, int64_t ldh, const float *M, int64_t ldm, int F_in,
                              const float *W_self, const float *W_neigh, const FwdEpilogue<float> &e, int F_out, hipStream_t s)
 {
-    const int Fq = pad4(F_in);
-    const int64_t K = 2 * int64_t(Fq);
-    if (F_in % 4 == 0 && F_out % 4 == 0) return fwd_dispatch<float, true, true>(n, H, ldh, M, ldm, F_in, W_self, W_neigh, e, F_out, s);
-    if (!weights_u_ok(F_in, F_out) || !rows_u_ok(n, ldh, F_in) || !rows_u_ok(n, ldm, F_in))
-        return fwd_dispatch<float, false, false>(n, H, ldh, M, ldm, F_in, W_self, W_neigh, e, F_out, s);
-    CatWeightsU b{W_self, W_neigh, F_in, Fq, F_out};
-    if (F_in % 4 == 0) {
-        CatRows<float, true> a{H, ldh, M, ldm, F_in, n, 2 * F_in};
-        return fwd_launch<float, true>(a, b, e, n, F_out, K, K, s);
-    }
-    CatRowsU a{H, ldh, M, ldm, F_in, Fq, n, 2};
-    fwd_launch<float, true>(a, b, e, n, F_out, K, K, s);
+    const int64_t K = 2 * int64_t(F_in);
+    const auto with_rows = [&](const auto &a, auto grouped_tag) {
+        constexpr bool VA = decltype(grouped_tag)::value;
+        if (F_out % 4 == 0) fwd_launch<float, VA>(a, CatWeights<true>{W_self, W_neigh, F_in, F_out}, e, n, F_out, K, K, s);
+        else if (weights_u_ok(F_in, F_out)) fwd_launch<float, VA>(a, CatWeightsU{W_self, W_neigh, F_in, F_out}, e, n, F_out, K, K, s);
+        else fwd_launch<float, VA>(a, CatWeights<false>{W_self, W_neigh, F_in, F_out}, e, n, F_out, K, K, s);
+    };
+    if (F_in % 4 == 0) with_rows(CatRows<float, true>{H, ldh, M, ldm, F_in, n, 2 * F_in}, std::true_type{});
+    else with_rows(CatRows<float, false>{H, ldh, M, ldm, F_in, n, 2 * F_in}, std::false_type{});
 }
 
 // bf16 storage with the weights prepared as Wt[o][k] (bf16): both operands are rows of packed bf16, contiguous

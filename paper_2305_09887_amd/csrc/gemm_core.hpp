@@ -2,9 +2,9 @@
 // translation units that instantiate it (the GraphSAGE transforms, the dense / GCN transforms).
 //
 // Operands are described by small "view" structs that present concatenations ([H | M], [W_self ; W_neigh]), the ReLU
-// mask and transposes as plain A[m][k], B[k][n], and results by an epilogue struct; two kernel templates take them,
-// by the storage type: gemm_split_kernel (gemm_split.hpp) for fp32, gemm_bf16_kernel below for bf16
-// (v_mfma_f32_32x32x16_bf16, fp32 accumulation).
+// mask and transposes as plain A[m][k], B[k][n], and results by an epilogue struct; three kernel templates take them:
+// gemm_f32_kernel (gemm_f32.hpp) for the forward products of fp32 storage, gemm_split_kernel (gemm_split.hpp) for its
+// backward products, gemm_bf16_kernel below for bf16 (v_mfma_f32_32x32x16_bf16, fp32 accumulation).
 //
 // Tiling of gemm_bf16_kernel.  BM x BN block tile, each wavefront owning a (BM/WM) x (BN/WN) patch of 32x32 MFMA
 // tiles; k is consumed in slabs of BK through two LDS buffers (one barrier per slab) while the next slab's global
@@ -188,7 +188,6 @@ struct CatRows {  // A[m][k] = k < F ? H[m][k] : M[m][k-F]  for k < Kv, zero bey
     int64_t rows;
     int Kv;  // extent of k: 2F for the concatenation, F when only the first part is used (Mx is then never read)
     static __device__ __forceinline__ float4 resolve(const Raw &r) { return r.get(); }
-    static __device__ __forceinline__ float4 in_range(const Raw &r) { return r.any(); }
     static constexpr bool kPacksBf16 = V && sizeof(T) == 2;
     static __device__ __forceinline__ uint2 packed(const Raw &r)
     {
@@ -297,7 +296,6 @@ struct CatWeights {  // B[k][n] = k < F ? W_self[k][n] : W_neigh[k-F][n]  (conti
     int F;
     int N;
     static __device__ __forceinline__ float4 resolve(const Raw &r) { return r.get(); }
-    static __device__ __forceinline__ float4 in_range(const Raw &r) { return r.any(); }
     __device__ __forceinline__ Lane prepare(int64_t n) const { return Lane{int(n)}; }
     __device__ __forceinline__ Raw load(const Lane &l, int64_t k64) const
     {
@@ -738,39 +736,33 @@ struct SideGrad {
 };
 
 // ---------------------------------------------------------------------------
-// fp32 operands whose inner extent F is not a multiple of four.  The halves of a concatenation are padded to Fq = F
-// rounded up to four, so that no group of four straddles them; the padding reads as zero in both operands.  Groups are
-// fetched whole from 4-byte-aligned addresses: past the end of a row lies the next one, and in the last row the group is
+// fp32 operands whose inner extent F is not a multiple of four.  Groups along the concatenation of a backward product are
+// padded to Fq = F rounded up to four, so that no group of four straddles the halves (a forward product's order of sums
+// leaves no room for that: see gemm_f32.hpp); the padding reads as zero in both operands.  Groups are fetched whole from 4-byte-aligned addresses: past the end of a row lies the next one, and in the last row the group is
 // fetched `shift` elements earlier (RawU).  See rows_u_ok for the arrays this takes.
 // ---------------------------------------------------------------------------
-struct CatRowsU {  // A[m][k] = k < Fq ? H[m][k] : M[m][k-Fq]   (contiguous along k)
+struct CatRowsU {  // A[m][k] = H[m][k]   (contiguous along k)
     static constexpr bool kContigK = true;
     typedef RawU Raw;
     struct Lane {
-        const float *p0, *p1;   // rows
+        const float *p;   // row
         bool ok, last;
     };
     const float *H;
     int64_t ldh;
-    const float *Mx;
-    int64_t ldm;
-    int F, Fq;
+    int F;
     int64_t rows;
-    int halves;   // 1: H alone
     static __device__ __forceinline__ float4 resolve(const Raw &r) { return r.get(); }
     __device__ __forceinline__ Lane prepare(int64_t m) const
     {
         const int64_t mm = m < rows ? m : 0;
-        return Lane{H + mm * ldh, Mx + mm * ldm, m < rows, mm == rows - 1};
+        return Lane{H + mm * ldh, m < rows, mm == rows - 1};
     }
     __device__ __forceinline__ Raw load(const Lane &l, int64_t k64) const
     {
         const int k = int(k64);
-        const bool second = k >= Fq && halves == 2;
-        int c = k - (second ? Fq : 0);
-        const int valid = l.ok ? F - c : 0;
-        if (valid <= 0) c = 0;
-        return load_unaligned4_at((second ? l.p1 : l.p0) + c, l.last ? F - c : 4, valid);
+        const int c = k < F ? k : 0;
+        return load_unaligned4_at(l.p + c, l.last ? F - c : 4, l.ok && k < F ? F - k : 0);
     }
     __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const { return load(l, kt + dk); }
 };
@@ -807,7 +799,7 @@ struct CatRowsTU {  // A[m][k] = (m < Fq ? H[k][m] : M[k][m-Fq])   (contiguous a
     __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const { return load(l, kt + dk); }
 };
 
-struct CatWeightsU {  // B[k][n] = k < Fq ? W_self[k][n] : W_neigh[k-Fq][n]   (contiguous along n); rows past F are zero
+struct CatWeightsU {  // B[k][n] = k < F ? W_self[k][n] : W_neigh[k-F][n]   (contiguous along n)
     static constexpr bool kContigK = false;
     typedef RawU Raw;
     struct Lane {
@@ -815,15 +807,15 @@ struct CatWeightsU {  // B[k][n] = k < Fq ? W_self[k][n] : W_neigh[k-Fq][n]   (c
     };
     const float *Ws;
     const float *Wn;
-    int F, Fq;
+    int F;
     int N;
     static __device__ __forceinline__ float4 resolve(const Raw &r) { return r.get(); }
     __device__ __forceinline__ Lane prepare(int64_t n) const { return Lane{int(n)}; }
     __device__ __forceinline__ Raw load(const Lane &l, int64_t k64) const
     {
         const int k = int(k64);
-        const bool second = k >= Fq;
-        const int c = k - (second ? Fq : 0);
+        const bool second = k >= F;
+        const int c = k - (second ? F : 0);
         const bool ok = c < F && l.n < N;
         return load_unaligned4(second ? Wn : Ws, (c < F ? c : 0) * N + (l.n < N ? l.n : 0), F * N, ok ? N - l.n : 0);
     }
@@ -1374,6 +1366,7 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_kernel(AL a, BL b, E
 }
 
 }  // namespace tma
+#include "gemm_f32.hpp"
 #include "gemm_split.hpp"
 namespace tma {
 
@@ -1394,7 +1387,7 @@ static inline bool rows_u_ok(int64_t n, int64_t ld, int F) { return (n - 1) * ld
 static inline bool weights_u_ok(int64_t F_in, int64_t F_out) { return F_in * F_out >= 4 && F_in * F_out <= INT32_MAX; }
 static inline int pad4(int F) { return (F + 3) / 4 * 4; }
 
-// BK: k-values per slab of the bf16 kernel (the fp32 one has its own).
+// BK: k-values per slab of the bf16 kernel (gemm_split_kernel, CT = float, has its own).
 template <int BM, int BN, int BK, int WM, int WN, bool kColSum, typename CT = float, class AL, class BL, class Epi>
 static void launch_gemm(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K,
                         int64_t k_per_split, int n_splits, float *colsum_partial, hipStream_t s)
@@ -1443,11 +1436,37 @@ static inline bool few_tiles(int64_t M, int64_t N, int n_splits = 1)
     return ceil_div(M, int64_t(128)) * ceil_div(N, int64_t(128)) * n_splits < kFewTiles;
 }
 
+// A forward product of fp32 storage (gemm_f32.hpp).  BK of the 128 x 128 tile: 16 leaves room for a third block per
+// compute unit, 32 halves the barriers.
+template <int BM, int BN, int BK, int WM, int WN, class AL, class BL, class Epi>
+static void launch_f32(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K, hipStream_t s)
+{
+    if (M <= 0 || N <= 0 || K <= 0) return;   // an empty product: callers zero-fill what they need
+    const int n_tiles = int(ceil_div(N, BN));
+    const int64_t total = ceil_div(M, BM) * n_tiles;
+    constexpr int kLdsBytes = 2 * 4 * ((AL::kContigK ? BM * (BK + kPad) : BK * (BM + kPad)) + (BL::kContigK ? BN * (BK + kPad) : BK * (BN + kPad)));
+    constexpr int kPerCu = (BK <= 16 && !Epi::kRowAux && kLdsBytes <= 53 * 1024 ? 3 : 2) * 4 / (WM * WN);
+    static_assert(kPerCu * kLdsBytes <= 160 * 1024, "blocks per compute unit");
+    int64_t blocks_per_die = ceil_div(total, kXcds);
+    if (blocks_per_die > 32 * kPerCu) blocks_per_die = 32 * kPerCu;
+    TMA_TIMED(name, s);
+    hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, BK, WM, WN, AL, BL, Epi>), dim3(unsigned(blocks_per_die * kXcds)), dim3(WM * WN * 64),
+                       0, s, a, b, e, M, N, K, n_tiles, total);
+}
+
+template <int BK, class AL, class BL, class Epi>
+static void launch_fwd_f32(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K, hipStream_t s)
+{
+    if (N <= 64 || few_tiles(M, N)) launch_f32<128, 64, 32, 4, 1>(name, a, b, e, M, N, K, s);
+    else if (BK == 32 && N <= 96) launch_f32<128, 96, 32, 4, 1>(name, a, b, e, M, N, K, s);
+    else launch_f32<128, 128, BK, 2, 2>(name, a, b, e, M, N, K, s);
+}
+
 // fp32 products with more than 96 columns.  The 256-wide tile of eight wavefronts reads the operand it is wide across
 // once instead of twice and converts a quarter fewer values per product; it is taken where it pads no more than two
 // tiles of 128 would, across the columns for a product whose rows are nodes and across the rows for a weight gradient.
-// Measured, 128 x 128 -> 256-wide, n = 125,237 / 1,000,000: forward 2 x 128 -> 256 133 -> 116 us / 961 -> 838 us, its
-// input gradient 166 -> 142 / 1,210 -> 1,031 us, its weight gradient 125 -> 117 / 901 -> 840 us.
+// Measured, 128 x 128 -> 256-wide, n = 125,237 / 1,000,000, 2 x 128 -> 256: input gradient 166 -> 142 / 1,210 -> 1,031 us,
+// weight gradient 125 -> 117 / 901 -> 840 us.
 template <bool kColSum, class AL, class BL, class Epi>
 static void launch_split_128(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K,
                              int64_t kps, int n_splits, float *colsum, hipStream_t s)
@@ -1462,10 +1481,11 @@ static void launch_split_128(const char *name, const AL &a, const BL &b, const E
     launch_gemm<128, 128, 32, 2, 2, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
 }
 
-// Every fp32 product.  kWide: the operands are fetched in groups of four.  With up to one 64 x 64 tile per compute unit that is
-// the tile, above that 64 x 128 up to some 1.5 tiles of 128 x 128 per unit.  Measured, us, 128 x 64 -> 64 x 64 at 5,000
-// rows: forward 2 x 64 -> 64 8.7 -> 7.1, its weight gradient 9.8 -> 8.4; 64 x 128 -> 64 x 64 at 12,000 rows, 128 wide:
-// 12.4 -> 14.0; 128 x 64 -> 64 x 128 at 24,000 rows: forward 2 x 128 -> 128 20.1 -> 17.7, 2 x 256 -> 256 51.5 -> 44.7.
+// Every backward product of fp32 storage.  kWide: the operands are fetched in groups of four.  With up to one 64 x 64
+// tile per compute unit that is the tile, above that 64 x 128 up to some 1.5 tiles of 128 x 128 per unit.  Measured, us,
+// weight gradient of 2 x 64 -> 64 at 5,000 rows, 128 x 64 -> 64 x 64: 9.8 -> 8.4; and with forward products, which this
+// kernel ran at that time: 64 x 128 -> 64 x 64 at 12,000 rows, 128 wide, 12.4 -> 14.0; 128 x 64 -> 64 x 128 at 24,000
+// rows 2 x 128 -> 128 20.1 -> 17.7, 2 x 256 -> 256 51.5 -> 44.7.
 template <bool kColSum, bool kWide, class AL, class BL, class Epi>
 static void launch_split(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K, int64_t kps,
                          int n_splits, float *colsum, hipStream_t s)

@@ -1,4 +1,5 @@
-// The tile product of fp32 storage: fp32 operands, fp32-accurate results, on the bf16 matrix instruction.
+// The backward tile product of fp32 storage: fp32 operands, fp32-accurate results, on the bf16 matrix instruction.
+// (Forward products keep the fp32 instruction and its order of sums: see gemm_f32.hpp.)
 //
 // The fp32 matrix instruction multiplies at a sixteenth of the bf16 one's rate and bounded every wide fp32 product.
 // Here each operand value is taken apart on its way into LDS into three bf16 values whose sum it is (x = h + m + l,
@@ -166,10 +167,10 @@ __global__ __launch_bounds__(WM *WN * 64, kSplitPerCu) void gemm_split_kernel(AL
                                                                     float *__restrict__ colsum_partial)
 {
     constexpr int NT = WM * WN * 64;
-    // Slabs in flight in registers: two for four wavefronts (5 to 8 %: 434 -> 412 us forward 256 -> 2 x 48 at 1,000,000 rows,
-    // 394 -> 361 us its weight gradient) and for the weight gradient, which streams both operands; one for the other
-    // products of eight (no gain).  The unaligned views take registers of their own and go without a set that lives
-    // across the barrier (48 -> 45 us and 47 -> 41 us, widths 90 -> 150 at 40,004 rows; the others lose 5 to 20 % so).
+    // Slabs in flight in registers: two for four wavefronts (394 -> 361 us the weight gradient of 256 -> 2 x 48 at 1,000,000
+    // rows) and for the weight gradient, which streams both operands; one for the other products of eight (no gain).  The
+    // unaligned views take registers of their own and go without a set that lives across the barrier (47 -> 41 us the weight
+    // gradient of widths 90 -> 150 at 40,004 rows; the others lose 5 to 20 % so).
     constexpr int kDepth = kColSum || WM * WN == 4 ? 2 : 1;
     constexpr bool kLean = WM * WN == 8 && (std::is_same<typename AL::Raw, RawU>::value || std::is_same<typename BL::Raw, RawU>::value);
     constexpr int TM = BM / WM / 32;
@@ -312,8 +313,8 @@ __global__ __launch_bounds__(WM *WN * 64, kSplitPerCu) void gemm_split_kernel(AL
             }
         } else if (n_whole > 1) {
             // Slab s >= 1 waits in register set (s - 1) % kDepth; its loads are issued kDepth iterations before it is staged.
-            // Past the end the last slab is fetched again: steps without a fetch after the loop cost more (forward
-            // 2 x 128 -> 256 at 125,237 rows 110 -> 116 us, its weight gradient 110 -> 119 us).
+            // Past the end the last slab is fetched again: steps without a fetch after the loop cost more (weight gradient of
+            // 2 x 128 -> 256 at 125,237 rows 110 -> 119 us).
             typename ASlots::Raws areg[kDepth];
             typename BSlots::Raws breg[kDepth];
             auto at = [&](int s) { return slab(s < n_whole ? s : n_whole - 1); };

@@ -75,7 +75,8 @@ static int tf_fwd_typed(int64_t n, const T *H, int64_t ldh, int32_t F_in, const 
     do {                                                                                          \
         CatRows<T, VA_> a{H, ldh, H, ldh, F_in, n, F_in};                                                   \
         SideWeights<VB_> b{W_self, W_neigh, F_in, F_out, Fp};                                     \
-        launch_by_width<T, 32, false, VA_>(name, a, b, e, n, 2 * Fp, K, kps, 1, nullptr, s);              \
+        if constexpr (sizeof(T) == 4) launch_fwd_f32<32>(name, a, b, e, n, 2 * Fp, K, s);         \
+        else launch_by_width<T, 32, false, VA_>(name, a, b, e, n, 2 * Fp, K, kps, 1, nullptr, s); \
     } while (0)
     // weights whose rows are not multiples of four: 16-byte loads from 4-byte-aligned addresses
     // (the form is only chosen for F_in >= 8, so the matrices hold at least four elements)
@@ -83,9 +84,9 @@ static int tf_fwd_typed(int64_t n, const T *H, int64_t ldh, int32_t F_in, const 
     else if (va) TMA_TF_FWD(true, kUnaligned4);
     else if constexpr (sizeof(T) == 4) {
         if (rows_u_ok(n, ldh, F_in)) {
-            CatRowsU a{H, ldh, H, ldh, F_in, pad4(F_in), n, 1};
+            CatRowsU a{H, ldh, F_in, n};
             SideWeights<kUnaligned4> b{W_self, W_neigh, F_in, F_out, Fp};
-            launch_by_width<T, 32, false, true>(name, a, b, e, n, 2 * Fp, K, kps, 1, nullptr, s);
+            launch_fwd_f32<32>(name, a, b, e, n, 2 * Fp, K, s);
         } else TMA_TF_FWD(false, kUnaligned4);
     } else if (vb) TMA_TF_FWD(false, kAligned4);
     else TMA_TF_FWD(false, kUnaligned4);

@@ -178,6 +178,7 @@ __device__ __forceinline__ void finish_row(int64_t v, const SpmmOut<T> &o, int s
 
 constexpr int kStreamU = 4;              // neighbours per step
 constexpr int kMinDefer = 24;            // rows up to this length are never deferred
+constexpr int kMinDeferOverlap = 256;    // the same for fp32 rows with an overlapping last piece (see launch_typed)
 constexpr int kDeferFactor = 4;          // ... nor rows up to this multiple of the mean degree
 constexpr int kMaxRowsPerBlock = 1024;   // rows of one workgroup (row bounds and deferred-row list sit in LDS)
 constexpr int kPartialBytes = 16384;     // LDS for the partial sums of deferred rows
@@ -213,10 +214,16 @@ __device__ __forceinline__ void issue_gathers(const T *__restrict__ in, int64_t 
     }
 }
 
-template <typename T, int U, bool kEdge>
+// How a weighted neighbour row enters the sum: its product with the weight rounded on its own, or inside the addition.
+// A forward sum is compared with zero further on, where a unit within a rounding of it is worth 1e-4 of a small batch's
+// gradient and more: which of the two, and the order of the additions, is part of the result (see launch_typed).
+enum class Weighting { kNone, kRounded, kFused };
+
+template <typename T, int U, Weighting kW>
 __device__ __forceinline__ void consume(const Step &s, const uint4 (&V)[U], const float (&Wt)[U],
                                         float (&acc)[Chunk<T>::kElems])
 {
+#pragma clang fp contract(off)
     constexpr int E = Chunk<T>::kElems;
 #pragma unroll
     for (int q = 0; q < U; ++q) {
@@ -225,7 +232,11 @@ __device__ __forceinline__ void consume(const Step &s, const uint4 (&V)[U], cons
         float v[E];
         Chunk<T>::widen(make_uint4(used ? V[q].x : 0u, used ? V[q].y : 0u, used ? V[q].z : 0u, used ? V[q].w : 0u), v);
 #pragma unroll
-        for (int i = 0; i < E; ++i) acc[i] = kEdge ? fmaf(used ? Wt[q] : 0.0f, v[i], acc[i]) : acc[i] + v[i];
+        for (int i = 0; i < E; ++i) {
+            if constexpr (kW == Weighting::kFused) acc[i] = fmaf(used ? Wt[q] : 0.0f, v[i], acc[i]);
+            else if constexpr (kW == Weighting::kRounded) acc[i] += (used ? Wt[q] : 0.0f) * v[i];
+            else acc[i] += v[i];
+        }
     }
 }
 
@@ -237,13 +248,14 @@ struct RowExtra {
 
 // Runs the steps that `gen` hands out through the ids -> gathers -> additions pipeline.  `extra(seg, X)`
 // issues the loads a closing step needs (or nothing); `emit(seg, acc, X)` takes a finished segment.
-template <typename T, bool kEdge, typename Gen, typename Extra, typename Emit>
+template <typename T, Weighting kW, typename Gen, typename Extra, typename Emit>
 __device__ __forceinline__ void stream_segments(const T *__restrict__ in, int64_t ld, const int32_t *__restrict__ ids,
                                                 const float *__restrict__ edge_scale, int32_t last_entry, int col,
                                                 int32_t recent, Gen &&gen, Extra &&extra, Emit &&emit)
 {
     constexpr int E = Chunk<T>::kElems;
     constexpr int U = kStreamU;
+    constexpr bool kEdge = kW != Weighting::kNone;
     int32_t I0[U], I1[U];
     uint4 V0[U], V1[U];
     float W0[U], W1[U];
@@ -265,7 +277,7 @@ __device__ __forceinline__ void stream_segments(const T *__restrict__ in, int64_
         issue_ids<U>(ids, last_entry, c, Ia);
         issue_gathers<T, U, kEdge>(in, ld, edge_scale, b, Ib, recent, col, Vb, Wb);
         extra(b.seg, Xb);
-        consume<T, U, kEdge>(a, Va, Wa, acc);
+        consume<T, U, kW>(a, Va, Wa, acc);
         if (a.last) {
             emit(a.seg, acc, Xa);
 #pragma unroll
@@ -282,8 +294,8 @@ __device__ __forceinline__ void stream_segments(const T *__restrict__ in, int64_
 }
 
 // kExtra: 0 = nothing, 1 = "+ self_v", 2 = "+ out_v" (accumulate).  kScale: multiply by inv_deg[v].
-// kEdge: weighted neighbours (and self row), see SpmmOut::edge_scale.
-template <typename T, int kExtra, bool kScale, bool kEdge = false>
+// kW: weighted neighbours (and self row), see SpmmOut::edge_scale.
+template <typename T, int kExtra, bool kScale, Weighting kW = Weighting::kNone>
 __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, const int32_t *__restrict__ rowptr,
                                                                    const int32_t *__restrict__ colidx,
                                                                    const T *__restrict__ in, int64_t ld_in,
@@ -292,6 +304,7 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, co
 {
     constexpr int E = Chunk<T>::kElems;
     constexpr int U = kStreamU;
+    constexpr bool kEdge = kW != Weighting::kNone;
     constexpr int kHubsPerPass = kPartialBytes / (kSpmmThreads * E * int(sizeof(float)));
     __shared__ int32_t bounds[kMaxRowsPerBlock + 1];   // rowptr of the workgroup's rows
     __shared__ int32_t deferred[kMaxRowsPerBlock];
@@ -393,7 +406,7 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, co
     };
     // a row that exists in the gathered matrix, for the loads of slots that carry nothing yet
     const int32_t filler_row = int32_t((base + r_first) < o.in_rows ? (base + r_first) : o.in_rows - 1);
-    stream_segments<T, kEdge>(in, ld_in, ids, o.edge_scale, last_entry, col, filler_row, next_row_step, row_extra,
+    stream_segments<T, kW>(in, ld_in, ids, o.edge_scale, last_entry, col, filler_row, next_row_step, row_extra,
                               finish);
     __syncthreads();
 
@@ -434,7 +447,7 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, co
 #pragma unroll
                 for (int i = 0; i < E; ++i) partial[(seg * NG + grp) * width + sub * E + i] = acc[i];
             };
-            stream_segments<T, kEdge>(in, ld_in, ids, o.edge_scale, last_entry, col, filler_row, next_share_step,
+            stream_segments<T, kW>(in, ld_in, ids, o.edge_scale, last_entry, col, filler_row, next_share_step,
                                       no_extra, to_lds);
         }
         __syncthreads();
@@ -585,9 +598,9 @@ static void launch_wide_rows(int64_t n, const int32_t *rowptr, const int32_t *co
                        rowptr, colidx, in, ld_in, o, n_chunks);
 }
 
-template <typename T, int kExtra, bool kScale, bool kEdge = false>
+template <typename T, int kExtra, bool kScale, Weighting kW = Weighting::kNone>
 static void launch_stream(int64_t n, const int32_t *rowptr, const int32_t *colidx, const T *in, int64_t ld_in,
-                          const SpmmOut<T> &o, int G, int last_col, hipStream_t s)
+                          const SpmmOut<T> &o, int G, int last_col, int min_defer, hipStream_t s)
 {
     // rows per group: long enough a stream for the pipeline to pay, short enough to leave the chip
     // several workgroups per compute unit
@@ -602,12 +615,12 @@ static void launch_stream(int64_t n, const int32_t *rowptr, const int32_t *colid
     if (rpg * NG > kMaxRowsPerBlock) rpg = kMaxRowsPerBlock / NG;
     char name[48];
     snprintf(name, sizeof(name), "%s_%s_g%dx1",
-             kEdge ? "spmm_weighted" : (kExtra == 1 ? "spmm_combine" : (kScale ? "spmm_mean" : "spmm_sum")),
+             kW != Weighting::kNone ? "spmm_weighted" : (kExtra == 1 ? "spmm_combine" : (kScale ? "spmm_mean" : "spmm_sum")),
              sizeof(T) == 4 ? "f32" : "bf16", G);
     TMA_TIMED(name, s);
-    hipLaunchKernelGGL((spmm_stream_kernel<T, kExtra, kScale, kEdge>),
+    hipLaunchKernelGGL((spmm_stream_kernel<T, kExtra, kScale, kW>),
                        dim3(unsigned(round_up(size_t(ceil_div(n, rpg * NG)), kDies))), dim3(kSpmmThreads), 0, s, n, rowptr,
-                       colidx, in, ld_in, o, G, int(rpg), kMinDefer, last_col);
+                       colidx, in, ld_in, o, G, int(rpg), min_defer, last_col);
 }
 
 template <typename T>
@@ -633,6 +646,11 @@ static int launch_typed(int64_t n, const int32_t *rowptr, const int32_t *colidx,
     const bool overlap = !vec_ok && F >= E && (size_t(F) * sizeof(T)) % 4 == 0 && row_bytes / 16 <= 64 && !o.accumulate &&
                          words(in, ld_in) && words(o.out, o.ld_out) && (!o.self || words(o.self, o.ld_self));
     const int last_col = overlap ? F - E : INT32_MAX;
+    // The order of the additions is kept as it was before such rows came here (element by element, in neighbour order):
+    // fp32 rows are cut into shares only where one group would take longer than the rest of the launch (means over 90
+    // features of a power-law graph, never / above 256 / above 24 entries: 110 / 68 / 32 us at 40,000 nodes, 611 / 359 /
+    // 347 us at 300,000), which no sampled block and fewer than one row in a thousand of a power-law graph reaches.
+    const int min_defer = overlap && sizeof(T) == 4 ? kMinDeferOverlap : kMinDefer;
     // the streaming kernel's weighted forms: with the self weight from the row scale it already holds, or without
     // self, scale and accumulation
     const bool edge_self = o.edge_scale && o.self && o.inv_deg == o.edge_scale;
@@ -646,11 +664,12 @@ static int launch_typed(int64_t n, const int32_t *rowptr, const int32_t *colidx,
     const int nc = int(row_bytes / 16);
     if (nc <= 64) {
         const int extra = o.self ? 1 : (o.accumulate ? 2 : 0);
-#define TMA_SPMM_STREAM(X, S) launch_stream<T, X, S>(n, rowptr, colidx, in, ld_in, o, nc, last_col, s)
+#define TMA_SPMM_STREAM(X, S) launch_stream<T, X, S>(n, rowptr, colidx, in, ld_in, o, nc, last_col, min_defer, s)
         if (edge_self) {
-            launch_stream<T, 1, true, true>(n, rowptr, colidx, in, ld_in, o, nc, last_col, s);
+            if (overlap) launch_stream<T, 1, true, Weighting::kFused>(n, rowptr, colidx, in, ld_in, o, nc, last_col, min_defer, s);
+            else launch_stream<T, 1, true, Weighting::kRounded>(n, rowptr, colidx, in, ld_in, o, nc, last_col, min_defer, s);
         } else if (edge_plain) {
-            launch_stream<T, 0, false, true>(n, rowptr, colidx, in, ld_in, o, nc, last_col, s);
+            launch_stream<T, 0, false, Weighting::kFused>(n, rowptr, colidx, in, ld_in, o, nc, last_col, min_defer, s);
         } else if (o.inv_deg) {
             if (extra == 0) TMA_SPMM_STREAM(0, true);
             else if (extra == 1) TMA_SPMM_STREAM(1, true);
