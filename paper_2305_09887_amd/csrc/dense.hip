@@ -180,7 +180,7 @@ static int dense_bwd_weight_typed(int64_t n, const T *X, int64_t ldx, const T *g
     const char *name = kname<T>("gemm_dense_bwd_weight", "gemm_dense_bwd_weight_generic", "gemm_dense_bwd_weight_bf16",
                                 "gemm_dense_bwd_weight_bf16_generic", v);
     if (v) {
-        CatRowsT<T, true> a{X, ldx, X, ldx, F_in, n};
+        CatRowsT<T, true> a{X, ldx, X, ldx, F_in, n, F_in};
         MaskedGrad<false, T, true, kRelu> b{g, h, F_out, ld, n};
         launch_by_width<T, 32, true, true>(name, a, b, e, int64_t(F_in), F_out, n, w.k_per_split, w.n_splits, colsum, s);
         return check_launch("dense gemm bwd weight");
@@ -192,7 +192,7 @@ static int dense_bwd_weight_typed(int64_t n, const T *X, int64_t ldx, const T *g
             launch_by_width<T, 32, true, true>(name, a, b, e, int64_t(F_in), F_out, n, w.k_per_split, w.n_splits, colsum, s);
             return check_launch("dense gemm bwd weight");
         }
-    CatRowsT<T, false> a{X, ldx, X, ldx, F_in, n};
+    CatRowsT<T, false> a{X, ldx, X, ldx, F_in, n, F_in};
     MaskedGrad<false, T, false, kRelu> b{g, h, F_out, ld, n};
     launch_by_width<T, 32, true, false>(name, a, b, e, int64_t(F_in), F_out, n, w.k_per_split, w.n_splits, colsum, s);
     return check_launch("dense gemm bwd weight");

@@ -231,7 +231,7 @@ struct CatRows {  // A[m][k] = k < F ? H[m][k] : M[m][k-F]  for k < Kv, zero bey
 };
 
 template <typename T, bool V>
-struct CatRowsT {  // A[m][k] = (m < F ? H[k][m] : M[k][m-F])          (contiguous along m); k = node
+struct CatRowsT {  // A[m][k] = m < F ? H[k][m] : M[k][m-F]  for m < Mv   (contiguous along m); k = node
     static constexpr bool kContigK = false;
     typedef RawV<T, V> Raw;
     struct Lane {
@@ -246,18 +246,20 @@ struct CatRowsT {  // A[m][k] = (m < F ? H[k][m] : M[k][m-F])          (contiguo
     int64_t ldm;
     int F;
     int64_t rows;
+    int Mv;  // extent of m: 2F for the concatenation, F when only the first part is used (Mx is then never read)
     static __device__ __forceinline__ float4 resolve(const Raw &r) { return r.get(); }
     static __device__ __forceinline__ float4 in_range(const Raw &r) { return r.any(); }
     __device__ __forceinline__ Lane prepare(int64_t m64) const
     {
         const int m = int(m64);
         if (m < F) return Lane{H + m, ldh, m, true};
-        return Lane{Mx + (m < 2 * F ? m - F : 0), ldm, m, m < 2 * F};
+        if (m < Mv) return Lane{Mx + (m - F), ldm, m, true};
+        return Lane{H, ldh, m, false};   // (the first column, and discarded)
     }
     __device__ __forceinline__ float at(int64_t node, int m) const
     {
         if (m < F) return widen1(H + node * ldh + m);
-        if (m < 2 * F) return widen1(Mx + node * ldm + (m - F));
+        if (m < Mv) return widen1(Mx + node * ldm + (m - F));
         return 0.0f;
     }
     __device__ __forceinline__ Raw load(const Lane &l, int64_t node) const

@@ -144,7 +144,7 @@ static int tf_bwd_weight_typed(int64_t n, const T *H, int64_t ldh, const T *g, c
                                 "gemm_tf_bwd_weight_bf16_generic", va && vb);
 #define TMA_TF_BW(VA_, VB_, R_)                                                                                       \
     do {                                                                                                              \
-        CatRowsT<T, VA_> a{H, ldh, H, ldh, F_in, n};                                                                       \
+        CatRowsT<T, VA_> a{H, ldh, H, ldh, F_in, n, F_in};                                                                       \
         SideGrad<false, T, VB_, R_> b{g, h, dYn, F_out, Fp, ld_next, ldy, n};                                         \
         launch_by_width<T, 32, true, VA_ && VB_>(name, a, b, e, int64_t(F_in), 2 * Fp, n, w.k_per_split, w.n_splits, colsum, s);     \
     } while (0)

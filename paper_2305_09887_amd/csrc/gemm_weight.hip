@@ -145,7 +145,7 @@ static void bwd_weight_dispatch(int64_t n, const T *H, int64_t ldh, const T *M, 
         bwd_weight_launch<T, true>(a, b, SplitEpiloguePad{e.partial, F_in, pad4(F_in), F_out}, 2 * int64_t(pad4(F_in)), F_in,
                                    F_out, n, w, colsum, s);
     } else {
-        CatRowsT<T, VA> a{H, ldh, M, ldm, F_in, n};
+        CatRowsT<T, VA> a{H, ldh, M, ldm, F_in, n, 2 * F_in};
         bwd_weight_launch<T, VA && VB>(a, b, e, 2 * int64_t(F_in), F_in, F_out, n, w, colsum, s);
     }
 }

@@ -101,6 +101,35 @@ def test_sage_layer_at_any_width(B, n, fi, fo, pitch):
     assert close(dH, g64 @ Ws.T + A.T @ (inv[:, None] * (g64 @ Wn.T)))
 
 
+def ring(n):
+    """Every node with the two beside it: rowptr, colidx, inv_deg on the GPU, and the mean over a row's neighbours."""
+    v = np.arange(n)
+    colidx = np.sort(np.stack([(v - 1) % n, (v + 1) % n], 1), 1).astype(np.int32).reshape(-1)
+    graph = [torch.as_tensor(t).cuda() for t in (np.arange(0, 2 * n + 1, 2, dtype=np.int32), colidx, np.full(n, 0.5, np.float32))]
+    return graph, lambda X: 0.5 * (np.roll(X, 1, 0) + np.roll(X, -1, 0))
+
+
+# widths that are 3 mod 4 in padded rows, at the row counts of the 64 x 64 and of the 128 x 64 tile; NaN behind the last row
+@pytest.mark.parametrize("n,fi,fo", [(300, 63, 20), (40000, 63, 20), (40000, 51, 7)])
+def test_transform_first_weight_gradient_at_the_end_of_the_rows(B, n, fi, fo):
+    graph, mean = ring(n)
+    X, Ws, _, g = data(n, fi, fo, n)
+    Wn = data(n, fi, fo, n + 1)[1]
+    ld = (fi + 3) // 4 * 4
+    x = torch.full((n + 1, ld), float("nan"), device="cuda")
+    x[:n] = 0.0
+    x = x[:n, :fi]
+    x.copy_(torch.as_tensor(X))
+    c = lambda t: torch.as_tensor(t).cuda()
+    M, out = B.tma_sage_layer_fwd(*graph, x, c(Ws), c(Wn), c(np.zeros(fo, np.float32)), B.TMA_ACT_NONE)
+    dWs, dWn, db = B.tma_sage_layer_bwd(*graph, x, M, out, c(g), c(Ws), c(Wn), B.TMA_ACT_NONE)[:3]
+    X, g = X.astype(np.float64), g.astype(np.float64)
+    within(dWs, X.T, g, "self weights")
+    within(db.reshape(1, -1), np.ones((1, n)), g, "bias")
+    # (the gathered gradient itself is rounded once per element: one more 2^-24 per term than within() has, and it has 64 to spare)
+    within(dWn, X.T, mean(g), "neighbour weights")
+
+
 @pytest.mark.parametrize("n,fi,fo", [(300, 64, 47), (1000, 33, 130)])
 def test_special_values(B, n, fi, fo):
     X, W, _, g = data(n, fi, fo, 9)
