@@ -671,14 +671,14 @@ struct SideGrad {
             c = int(k - (second ? Fp : 0));
             inside = l.ok && k < 2 * Fp && (second || c < Fo);
             if (!inside) c = 0;
-            eg = l.a + c;
+            eg = l.a + (c < Fo ? c : 0);       // (a half is padded to Fp, dZ's rows end at Fo)
             ey = l.b + c;
         } else {
             second = l.second;
             c = int(l.a);
             inside = l.ok && k < rows;
             const int64_t node = k < rows ? k : 0;
-            eg = node * ld + c;
+            eg = node * ld + (c < Fo ? c : 0);
             ey = node * ldy + c;
         }
         r.second = second;
@@ -724,7 +724,7 @@ struct SideGrad {
                 r.second = l.second;
                 const int c = int(l.a);
                 r.nv = l.ok ? (r.second ? Fp : Fo) - c : 0;
-                eg = kt * ld + (dk * ld + c);
+                eg = kt * ld + (dk * ld + (c < Fo ? c : 0));
                 ey = kt * ldy + (dk * ldy + c);
             }
             r.g = Pack4<T>::load(r.second ? dYn + ey : dHn + eg);

@@ -61,6 +61,8 @@ static void rows_of(const char *type, int64_t n, int F_in, int F_out, int64_t ld
     const bool h_padded = vec4_ok(static_cast<const T *>(nullptr), ldh), g_padded = vec4_ok(static_cast<const T *>(nullptr), ldg);
     const Guarded<T> H(h_padded && F_in % 4 ? n * ldh : (n - 1) * ldh + F_in, at_end);
     const Guarded<T> G(g_padded && F_out % 4 ? n * ldg : (n - 1) * ldg + F_out, at_end);
+    const int Fp = int(round_up(size_t(F_out), sizeof(T) == 4 ? 4 : 8));
+    const Guarded<T> Y(n * Fp, at_end);
 #define RUN(V_, MN_, K_)                                                                                              \
     do {                                                                                                              \
         snprintf(name, sizeof(name), "%s n=%ld F_in=%d F_out=%d ldh=%ld ldg=%ld end=%d: " #V_, type, long(n), F_in, F_out, \
@@ -71,9 +73,12 @@ static void rows_of(const char *type, int64_t n, int F_in, int F_out, int64_t ld
     if (padded_groups_ok(G.p, ldg, F_out)) {
         RUN((MaskedGrad<true, T, true, true>{G.p, G.p, F_out, ldg, n}), n, F_out);
         RUN((MaskedGrad<false, T, true, true>{G.p, G.p, F_out, ldg, n}), F_out, n);
+        RUN((SideGrad<true, T, true, true>{G.p, G.p, Y.p, F_out, Fp, ldg, Fp, n}), n, 2 * Fp);
+        RUN((SideGrad<false, T, true, true>{G.p, G.p, Y.p, F_out, Fp, ldg, Fp, n}), 2 * Fp, n);
     }
     RUN((MaskedGrad<true, T, false, true>{G.p, G.p, F_out, ldg, n}), n, F_out);
     RUN((MaskedGrad<false, T, false, true>{G.p, G.p, F_out, ldg, n}), F_out, n);
+    RUN((SideGrad<false, T, false, true>{G.p, G.p, Y.p, F_out, Fp, ldg, Fp, n}), 2 * Fp, n);
     // layer inputs: [H | M] in the aggregate-first form, H alone otherwise
     if (groups_ok(H.p, ldh, F_in)) {
         RUN((CatRows<T, true>{H.p, ldh, H.p, ldh, F_in, n, 2 * F_in}), n, 2 * F_in);
