@@ -230,6 +230,41 @@ struct CatRows {  // A[m][k] = k < F ? H[m][k] : M[m][k-F]  for k < Kv, zero bey
     }
 };
 
+// bf16 rows whose width is no multiple of four, in rows padded to one: the padding comes in with the last group and is
+// masked there, whatever it holds (against the zero rows of the other operand a NaN would still be one).
+struct PaddedRows {  // A[m][k] = H[m][k] for k < F, zero beyond    (contiguous along k)
+    static constexpr bool kContigK = true;
+    static constexpr bool kPacksBf16 = true;
+    struct Raw {
+        uint2 v, keep;
+    };
+    struct Lane {
+        const uint16_t *p;
+        bool ok;
+    };
+    const uint16_t *H;
+    int64_t ldh;
+    int F;
+    int64_t rows;
+    static __device__ __forceinline__ uint2 packed(const Raw &r) { return make_uint2(r.v.x & r.keep.x, r.v.y & r.keep.y); }
+    static __device__ __forceinline__ float4 resolve(const Raw &r) { return Pack4<uint16_t>::widen(packed(r)); }
+    __device__ __forceinline__ Lane prepare(int64_t m) const { return Lane{H + (m < rows ? m : 0) * ldh, m < rows}; }
+    __device__ __forceinline__ Raw load(const Lane &l, int64_t k64) const
+    {
+        const int k = int(k64);
+        const int valid = l.ok ? F - k : 0;
+        Raw r;
+        r.v = Pack4<uint16_t>::load(l.p + (k < F ? k : 0));
+        r.keep = make_uint2(valid > 1 ? ~0u : valid > 0 ? 0xFFFFu : 0u, valid > 3 ? ~0u : valid > 2 ? 0xFFFFu : 0u);
+        return r;
+    }
+    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const
+    {
+        const uint32_t keep = l.ok ? ~0u : 0u;
+        return Raw{Pack4<uint16_t>::load(l.p + kt + dk), make_uint2(keep, keep)};
+    }
+};
+
 template <typename T, bool V>
 struct CatRowsT {  // A[m][k] = m < F ? H[k][m] : M[k][m-F]  for m < Mv   (contiguous along m); k = node
     static constexpr bool kContigK = false;

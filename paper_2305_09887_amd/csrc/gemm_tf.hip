@@ -67,30 +67,29 @@ static int tf_fwd_typed(int64_t n, const T *H, int64_t ldh, int32_t F_in, const 
 {
     HalvesEpilogue<T> e{Ys, Yn, ldy, Fp};
     const int64_t K = F_in, kps = int64_t(round_up(size_t(K), 32));
-    const bool va = padded_groups_ok(H, ldh, F_in);
+    // The rows are the k side here: a group that reaches into their padding has to mask it (a NaN there would get through
+    // the zero weights it meets), which the plain groups do not.
+    const bool va = groups_ok(H, ldh, F_in);
+    const bool padded = sizeof(T) == 2 && !va && vec4_ok(H, ldh);
     const bool vb = F_out % 4 == 0 && aligned(W_self, 16) && aligned(W_neigh, 16);
     TMA_REQUIRE(vb || int64_t(F_in) * F_out >= 4, TMA_ERR_INVALID_ARG, "sage gemm tf fwd: weight matrix below four elements");
-    const char *name = kname<T>("gemm_tf_fwd", "gemm_tf_fwd_generic", "gemm_tf_fwd_bf16", "gemm_tf_fwd_bf16_generic", va);
-#define TMA_TF_FWD(VA_, VB_)                                                                      \
-    do {                                                                                          \
-        CatRows<T, VA_> a{H, ldh, H, ldh, F_in, n, F_in};                                                   \
-        SideWeights<VB_> b{W_self, W_neigh, F_in, F_out, Fp};                                     \
-        if constexpr (sizeof(T) == 4) launch_fwd_f32<32>(name, a, b, e, n, 2 * Fp, K, s);         \
-        else launch_by_width<T, 32, false, VA_>(name, a, b, e, n, 2 * Fp, K, kps, 1, nullptr, s); \
-    } while (0)
+    const char *name = kname<T>("gemm_tf_fwd", "gemm_tf_fwd_generic", "gemm_tf_fwd_bf16", "gemm_tf_fwd_bf16_generic", va || padded);
     // weights whose rows are not multiples of four: 16-byte loads from 4-byte-aligned addresses
     // (the form is only chosen for F_in >= 8, so the matrices hold at least four elements)
-    if (va && vb) TMA_TF_FWD(true, kAligned4);
-    else if (va) TMA_TF_FWD(true, kUnaligned4);
+    const auto with_rows = [&](const auto &a, auto grouped_tag) {
+        const auto with_weights = [&](const auto &b) {
+            if constexpr (sizeof(T) == 4) launch_fwd_f32<32>(name, a, b, e, n, 2 * Fp, K, s);
+            else launch_by_width<T, 32, false, decltype(grouped_tag)::value>(name, a, b, e, n, 2 * Fp, K, kps, 1, nullptr, s);
+        };
+        if (vb) with_weights(SideWeights<kAligned4>{W_self, W_neigh, F_in, F_out, Fp});
+        else with_weights(SideWeights<kUnaligned4>{W_self, W_neigh, F_in, F_out, Fp});
+    };
+    if (va) with_rows(CatRows<T, true>{H, ldh, H, ldh, F_in, n, F_in}, std::true_type{});
     else if constexpr (sizeof(T) == 4) {
-        if (rows_u_ok(n, ldh, F_in)) {
-            CatRowsU a{H, ldh, F_in, n};
-            SideWeights<kUnaligned4> b{W_self, W_neigh, F_in, F_out, Fp};
-            launch_fwd_f32<32>(name, a, b, e, n, 2 * Fp, K, s);
-        } else TMA_TF_FWD(false, kUnaligned4);
-    } else if (vb) TMA_TF_FWD(false, kAligned4);
-    else TMA_TF_FWD(false, kUnaligned4);
-#undef TMA_TF_FWD
+        if (rows_u_ok(n, ldh, F_in)) with_rows(CatRowsU{H, ldh, F_in, n}, std::true_type{});
+        else with_rows(CatRows<T, false>{H, ldh, H, ldh, F_in, n, F_in}, std::false_type{});
+    } else if (padded) with_rows(PaddedRows{H, ldh, F_in, n}, std::true_type{});
+    else with_rows(CatRows<T, false>{H, ldh, H, ldh, F_in, n, F_in}, std::false_type{});
     return check_launch("sage gemm tf fwd");
 }
 

@@ -130,6 +130,26 @@ def test_transform_first_weight_gradient_at_the_end_of_the_rows(B, n, fi, fo):
     within(dWn, X.T, mean(g), "neighbour weights")
 
 
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("n,fi,fo", [(700, 150, 41), (301, 99, 24), (60, 30, 7), (129, 65, 16)])
+def test_row_padding_leaves_no_trace(B, n, fi, fo, dtype):
+    """The transform-first layer on rows padded to a multiple of 16 bytes: whatever the padding holds, the same bits."""
+    graph, _ = ring(n)
+    X, Ws, b, g = data(n, fi, fo, n)
+    Wn = data(n, fi, fo, n + 1)[1]
+    c = lambda t: torch.as_tensor(t).cuda()
+    got = []
+    for fill in (0.0, float("nan")):
+        x = B._padded(n, fi, dtype, "cuda")
+        x._base.fill_(fill)
+        x.copy_(torch.as_tensor(X))
+        M, out = B.tma_sage_layer_fwd(*graph, x, c(Ws), c(Wn), c(b), B.TMA_ACT_RELU)
+        got.append([out])
+    assert not B.tma_sage_layer_aggregates_first(fi, fo, B.TMA_F32 if dtype == torch.float32 else B.TMA_BF16)
+    for clean, dirty in zip(*got):
+        assert torch.isfinite(clean.float()).all() and torch.equal(clean, dirty)
+
+
 @pytest.mark.parametrize("n,fi,fo", [(300, 64, 47), (1000, 33, 130)])
 def test_special_values(B, n, fi, fo):
     X, W, _, g = data(n, fi, fo, 9)

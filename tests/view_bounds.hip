@@ -85,7 +85,7 @@ static void rows_of(const char *type, int64_t n, int F_in, int F_out, int64_t ld
         RUN((CatRowsT<T, true>{H.p, ldh, H.p, ldh, F_in, n, 2 * F_in}), 2 * F_in, n);
     }
     if (padded_groups_ok(H.p, ldh, F_in)) {
-        RUN((CatRows<T, true>{H.p, ldh, H.p, ldh, F_in, n, F_in}), n, F_in);
+        if constexpr (sizeof(T) == 2) RUN((PaddedRows{H.p, ldh, F_in, n}), n, F_in);
         RUN((CatRowsT<T, true>{H.p, ldh, H.p, ldh, F_in, n, F_in}), F_in, n);
     }
     RUN((CatRows<T, false>{H.p, ldh, H.p, ldh, F_in, n, 2 * F_in}), n, 2 * F_in);
