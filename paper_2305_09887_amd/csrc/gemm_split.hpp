@@ -14,7 +14,7 @@
 // instruction.  (Values below 2^-110 lose their smallest parts to the bf16 range: at 2^-112 still 1.6e-7.)
 //
 // A value without such parts (Inf, NaN, magnitudes that round to Inf in bf16) makes every result it touches
-// non-finite; a tile with a non-finite result is multiplied again with the fp32 instruction, so that infinities,
+// non-finite; a tile that would store a non-finite result is multiplied again with the fp32 instruction, so that infinities,
 // NaNs and overflows come out as they do there.
 //
 // Tiling: BM x BN block tile, k in slabs of 16 (one k-group), double-buffered in LDS with one barrier per slab,
@@ -357,7 +357,22 @@ __global__ __launch_bounds__(WM *WN * 64, kSplitPerCu) void gemm_split_kernel(AL
                     acc[i][j][r] += rest[i][j][r];
                     odd = fmaf(acc[i][j][r], 0.0f, odd);
                 }
-        if (__any(odd != 0.0f) && lane == 0) odd_tile[wave] = 1;
+        bool stored_odd = false;
+        if (__builtin_expect(__any(odd != 0.0f), 0)) {
+            // Lanes outside the result do not count: they may hold sums of row padding, which nobody wrote (every tile of a
+            // weight gradient of 150 columns in rows of 152 was multiplied twice for it).
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const bool in = t.n0 + wn0 + j * 32 + l31 < N &&
+                                        t.m0 + wm0 + i * 32 + 8 * (r / 4) + 4 * hi + (r % 4) < M;
+                        stored_odd |= in && acc[i][j][r] * 0.0f != 0.0f;
+                    }
+        }
+        if (__any(stored_odd) && lane == 0) odd_tile[wave] = 1;
         else if (lane == 0) odd_tile[wave] = 0;
         __syncthreads();
         int redo = 0;

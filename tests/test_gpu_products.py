@@ -138,15 +138,22 @@ def test_row_padding_leaves_no_trace(B, n, fi, fo, dtype):
     X, Ws, b, g = data(n, fi, fo, n)
     Wn = data(n, fi, fo, n + 1)[1]
     c = lambda t: torch.as_tensor(t).cuda()
+
+    def padded(t, fill):
+        p = B._padded(*t.shape, dtype, "cuda")
+        p._base.fill_(fill)
+        return p.copy_(torch.as_tensor(t))
+
     got = []
     for fill in (0.0, float("nan")):
-        x = B._padded(n, fi, dtype, "cuda")
-        x._base.fill_(fill)
-        x.copy_(torch.as_tensor(X))
+        x = padded(X, fill)
         M, out = B.tma_sage_layer_fwd(*graph, x, c(Ws), c(Wn), c(b), B.TMA_ACT_RELU)
-        got.append([out])
+        if fill == 0.0:
+            first = out.clone()      # (the backward pass of both from the same output)
+        for act in (B.TMA_ACT_RELU, B.TMA_ACT_NONE):
+            got.append([out, *B.tma_sage_layer_bwd(*graph, x, M, padded(first, fill), padded(g, fill), c(Ws), c(Wn), act)[:4]])
     assert not B.tma_sage_layer_aggregates_first(fi, fo, B.TMA_F32 if dtype == torch.float32 else B.TMA_BF16)
-    for clean, dirty in zip(*got):
+    for clean, dirty in zip(got[0] + got[1], got[2] + got[3]):
         assert torch.isfinite(clean.float()).all() and torch.equal(clean, dirty)
 
 
