@@ -5,17 +5,22 @@
 // Here each operand value is taken apart on its way into LDS into three bf16 values whose sum it is (x = h + m + l,
 // each the rounding of what the ones before left over: 3 x 8 significant bits hold the 24), and a product becomes
 // the six products of parts that reach fp32 accuracy,
-//   a b = ah bh + (ah bm + am bh) + (am bm + ah bl + al bh) + ...,      the dropped rest below 2^-25 |a b|.
+//   a b = ah bh + (ah bm + am bh) + (am bm + ah bl + al bh) + ...,      the dropped rest below 2^-24 |a b|
+// (two terms of up to 2^-25 near 1 + 2^-8 and a smaller one).  Splitting a number into parts of fewer bits by exact
+// differences of roundings is a known method (Dekker, "A floating-point technique for extending the available precision",
+// 1971); three parts are what a 24-bit significand takes.
 // ah bh has accumulators of its own: the other five are 2^-8 and less of it, and added up beside it their roundings
 // vanish, so that a k-group of 16 rounds the large sum once where the fp32 instruction rounds it eight times.
 // Relative error of the sum against 64 bits, one 32x32 tile, fp32 instruction -> this, at K = 256 / 2,048 / 16,384:
 // N(0,1) x 0.1 N(0,1) 2.9e-7 / 8.7e-7 / 2.3e-6 -> 0.9e-7 / 2.7e-7 / 0.8e-6; non-negative operands 2.3e-7 / 6.2e-7 /
 // 1.7e-6 -> 0.9e-7 / 2.2e-7 / 0.6e-6; all six products in one accumulator would be no better than the fp32
-// instruction.  (Values below 2^-110 lose their smallest parts to the bf16 range: at 2^-112 still 1.6e-7.)
+// instruction.
 //
-// A value without such parts (Inf, NaN, magnitudes that round to Inf in bf16) makes every result it touches
-// non-finite; a tile that would store a non-finite result is multiplied again with the fp32 instruction, so that infinities,
-// NaNs and overflows come out as they do there.
+// Range.  bf16 ends where fp32 does, so the smaller parts of a value below 2^-110 would end before its 24 bits do.  Values
+// are multiplied by 2^24 before they are taken apart and the sum by 2^-48 at the end, both exact: the last bit of the
+// smallest fp32 value is then a normal bf16 number.  At the other end a value without such parts (Inf, NaN, magnitudes from
+// 2^104 on) or a sum from 2^80 on makes a result non-finite; a tile that would store one is multiplied again with the fp32
+// instruction, so that large values, infinities, NaNs and overflows come out as they do there.
 //
 // Tiling: BM x BN block tile, k in slabs of 16 (one k-group), double-buffered in LDS with one barrier per slab,
 // kDepth further slabs in flight in registers.  Both operands lie in LDS as [plane][mn][16 + 8] bf16: a row is twelve
@@ -30,6 +35,7 @@ constexpr int kSplitPerCu = 2;        // blocks per compute unit: two waves per 
 constexpr int kSlabK = 16;            // k-values per slab: one v_mfma_f32_32x32x16_bf16
 constexpr int kSplitLd = kSlabK + 8;  // row pitch of a tile plane in bf16 values
 constexpr int kFullLd = kSlabK + 4;   // row pitch in floats where a slab is staged unsplit
+constexpr float kSplitScale = 0x1p24f, kSplitUnscale = 0x1p-48f;   // of both operands; of their product (see Range)
 
 // two values -> their three parts as bf16 pairs (first value in the low half).  What a rounding left over is exact, and
 // comes from one instruction: v - h as the dot product of the pair (h0, h1) with (-1, 0) or (0, -1), plus v.
@@ -48,6 +54,8 @@ struct SplitPair {
     }
     __device__ __forceinline__ void operator()(float x, float y, uint32_t &h, uint32_t &m, uint32_t &l) const
     {
+        x *= kSplitScale;
+        y *= kSplitScale;
         h = pack_bf16(x, y);
         x = left(x, h, first);
         y = left(y, h, second);
@@ -354,7 +362,7 @@ __global__ __launch_bounds__(WM *WN * 64, kSplitPerCu) void gemm_split_kernel(AL
             for (int j = 0; j < TN; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
-                    acc[i][j][r] += rest[i][j][r];
+                    acc[i][j][r] = (acc[i][j][r] + rest[i][j][r]) * kSplitUnscale;
                     odd = fmaf(acc[i][j][r], 0.0f, odd);
                 }
         bool stored_odd = false;

@@ -1,8 +1,11 @@
-"""The fp32 products from bf16 parts: against 64 bits at the edges of tiles and slabs, and with special values.
+"""The fp32 products, forward and backward: against 64 bits at the edges of tiles and slabs, and with special values.
 
-Bound: the leading products of a group of 16 k-values round the running sum once, the other five sums are 2^-8 of it
-and less, and splits of a long k meet in at most 64 further additions; a value's three parts drop below 2^-25 of a
-product.  Each result is therefore within (K/16 + 64) 2^-24 of the sum of |a b|.
+Bound of the backward products (from bf16 parts): the leading products of a group of 16 k-values round the running sum
+once, the other five sums are 2^-8 of it and less, and splits of a long k meet in at most 64 further additions; what the
+parts of a value leave out of a product is below 2^-24 of it, one of the 64.  Each result is therefore within
+(K/16 + 64) 2^-24 of the sum of |a b|, and within K roundings at the end of the range (2^-149 each).  A forward product
+rounds once per k-value, K 2^-24 of the sum at most: less than that bound up to K = 68, and above it by roundings that would
+all have to fall the same way (its bits are pinned in test_gpu_forward_order.py).
 """
 import numpy as np
 import pytest
@@ -23,7 +26,7 @@ def B():
 def within(got, a, b, what):
     got = got.double().cpu().numpy()
     want, size = a @ b, np.abs(a) @ np.abs(b)
-    bound = (a.shape[1] / 16 + 64) * 2.0 ** -24 * size + 1e-37
+    bound = (a.shape[1] / 16 + 64) * 2.0 ** -24 * size + a.shape[1] * 2.0 ** -149
     off = np.abs(got - want) / bound
     assert np.all(off <= 1.0), f"{what}: {off.max():.2f} of the bound"
 
@@ -192,3 +195,17 @@ def test_overflow_and_small_values(B):
     X, W = X.astype(np.float64), W.astype(np.float64)
     err = np.abs(Y[usual].astype(np.float64) - X[usual] @ W)
     assert np.all(err <= 67 * 2.0 ** -24 * (np.abs(X[usual]) @ np.abs(W)))
+
+
+# Both ends of the fp32 range: operands down to the smallest normal numbers and below, products up to its end
+@pytest.mark.parametrize("xe,we,ge", [(0, 0, -126), (20, 12, -140), (-70, -60, -50), (-120, 10, 100), (-126, 0, 0), (60, -126, -20), (100, -140, 0),
+                                      (110, 100, -115), (-133, 0, 110)])
+def test_backward_products_over_the_whole_range(B, xe, we, ge):
+    X, W, _, g = data(300, 40, 72, 4)
+    X, W, g = (np.ldexp(t, e).astype(np.float32) for t, e in ((X, xe), (W * 8, we), (g * 2 ** 20, ge)))
+    X[::7], W[::5], g[:, ::3] = np.ldexp(X[::7], -3), np.ldexp(W[::5], 3), np.ldexp(g[:, ::3], -2)
+    x, w, d = (torch.as_tensor(t).cuda() for t in (X, W, g))
+    dW, db, dX = B.tma_dense_bwd(x, None, d, w, B.TMA_ACT_NONE)[:3]
+    X, W, g = (t.astype(np.float64) for t in (X, W, g))
+    within(dW, X.T, g, "weight gradient")
+    within(dX, g, W.T, "input gradient")
