@@ -29,7 +29,10 @@ static void fwd_launch(const AL &a, const BL &b, const FwdEpilogue<T> &e, int64_
         // bf16 storage: the product is bound by streaming [H | M]; a tile as wide as the output reads it once
         if (F_out > 128 && F_out <= 256)
             launch_gemm<128, 256, 32, 2, 4, false, T>("gemm_fwd_128x256_bf16", a, b, e, n, F_out, K, kps, 1, nullptr, s);
-        else
+        else if (std::is_same<BL, CatWeights<true>>::value && K % 32 != 0) {
+            if constexpr (std::is_same<BL, CatWeights<true>>::value)
+                launch_gemm<128, 128, 32, 2, 2, false, T>("gemm_fwd_128x128_bf16", a, CatWeightsRest{b}, e, n, F_out, K, kps, 1, nullptr, s);
+        } else
             launch_gemm<128, 128, 32, 2, 2, false, T>("gemm_fwd_128x128_bf16", a, b, e, n, F_out, K, kps, 1, nullptr, s);
     } else
         launch_gemm<128, 128, 32, 2, 2, false, T>("gemm_fwd_128x128_bf16_generic", a, b, e, n, F_out, K, kps, 1, nullptr, s);

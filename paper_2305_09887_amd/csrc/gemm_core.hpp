@@ -54,6 +54,22 @@ __device__ __forceinline__ void static_for(F &&f)
     }
 }
 
+struct PaddedRows;
+struct CatWeightsRest;
+// Which bf16 products run the unrolled loop of gemm_bf16_kernel, three copies of whose body have to share the registers.
+// Not views that load element by element, which spill up to 900 registers there (us at 125,237 / 1,000,000 rows, the rolled
+// loop against the unrolled one: weight gradient of 2 x 150 -> 150 with ReLU 357 / 3,090 against 964 / 8,960, of
+// 2 x 90 -> 150 142 / 1,220 against 430 / 3,380); not PaddedRows (42 / 307 against 62 / 472, 130 -> 50); not gradients along k but for the
+// 256-wide tile (input gradient of 128 -> 128 41 / 275 against 48 / 342, of 2 x 100 -> 128 with ReLU 57 / 410 against
+// 72 / 524; the 256-wide one of 2 x 128 -> 256 with ReLU 73 / 515 against 68 / 484); not the forward product of two
+// weight matrices with a rest of k (2 x 100 -> 128 36 / 271 against 45 / 315; without a rest, 2 x 64 -> 120, 34 / 226
+// against 30 / 191).
+template <int kBN, class AL, class BL>
+struct SteadyLoop {
+    static constexpr bool value = AL::kGroups && BL::kGroups && !std::is_same<AL, PaddedRows>::value &&
+                                  !std::is_same<BL, CatWeightsRest>::value && !(AL::kMasks && AL::kContigK && kBN != 256);
+};
+
 // An optional member of an operand view: kPacksBf16 + packed(raw) say that the view's Raw already holds four bf16
 // values the way a bf16 tile keeps them in LDS (bits unchanged), so a bf16 product stores them as they are instead
 // of widening and rounding them again (the same bits either way).
@@ -175,6 +191,8 @@ enum : int { kElementwise = 0, kAligned4 = 1, kUnaligned4 = 2 };   // how a weig
 template <typename T, bool V>
 struct CatRows {  // A[m][k] = k < F ? H[m][k] : M[m][k-F]  for k < Kv, zero beyond    (contiguous along k)
     static constexpr bool kContigK = true;
+    static constexpr bool kMasks = false;
+    static constexpr bool kGroups = V;
     typedef RawV<T, V> Raw;
     struct Lane {
         const T *p0, *p1;  // row pointers such that element k is p0[k] (k < F) or p1[k] (k >= F)
@@ -234,9 +252,12 @@ struct CatRows {  // A[m][k] = k < F ? H[m][k] : M[m][k-F]  for k < Kv, zero bey
 // masked there, whatever it holds (against the zero rows of the other operand a NaN would still be one).
 struct PaddedRows {  // A[m][k] = H[m][k] for k < F, zero beyond    (contiguous along k)
     static constexpr bool kContigK = true;
+    static constexpr bool kMasks = false;
+    static constexpr bool kGroups = true;
     static constexpr bool kPacksBf16 = true;
     struct Raw {
-        uint2 v, keep;
+        uint2 v;
+        int valid;   // leading elements that are inside the operand (<= 0: none)
     };
     struct Lane {
         const uint16_t *p;
@@ -246,28 +267,29 @@ struct PaddedRows {  // A[m][k] = H[m][k] for k < F, zero beyond    (contiguous 
     int64_t ldh;
     int F;
     int64_t rows;
-    static __device__ __forceinline__ uint2 packed(const Raw &r) { return make_uint2(r.v.x & r.keep.x, r.v.y & r.keep.y); }
+    static __device__ __forceinline__ uint2 packed(const Raw &r)
+    {
+        return make_uint2(r.v.x & (r.valid > 1 ? ~0u : r.valid > 0 ? 0xFFFFu : 0u),
+                          r.v.y & (r.valid > 3 ? ~0u : r.valid > 2 ? 0xFFFFu : 0u));
+    }
     static __device__ __forceinline__ float4 resolve(const Raw &r) { return Pack4<uint16_t>::widen(packed(r)); }
     __device__ __forceinline__ Lane prepare(int64_t m) const { return Lane{H + (m < rows ? m : 0) * ldh, m < rows}; }
     __device__ __forceinline__ Raw load(const Lane &l, int64_t k64) const
     {
         const int k = int(k64);
-        const int valid = l.ok ? F - k : 0;
-        Raw r;
-        r.v = Pack4<uint16_t>::load(l.p + (k < F ? k : 0));
-        r.keep = make_uint2(valid > 1 ? ~0u : valid > 0 ? 0xFFFFu : 0u, valid > 3 ? ~0u : valid > 2 ? 0xFFFFu : 0u);
-        return r;
+        return Raw{Pack4<uint16_t>::load(l.p + (k < F ? k : 0)), l.ok ? F - k : 0};
     }
     __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const
     {
-        const uint32_t keep = l.ok ? ~0u : 0u;
-        return Raw{Pack4<uint16_t>::load(l.p + kt + dk), make_uint2(keep, keep)};
+        return Raw{Pack4<uint16_t>::load(l.p + kt + dk), l.ok ? 4 : 0};
     }
 };
 
 template <typename T, bool V>
 struct CatRowsT {  // A[m][k] = m < F ? H[k][m] : M[k][m-F]  for m < Mv   (contiguous along m); k = node
     static constexpr bool kContigK = false;
+    static constexpr bool kMasks = false;
+    static constexpr bool kGroups = V;
     typedef RawV<T, V> Raw;
     struct Lane {
         const T *p;  // column pointer: element of node k is p[k * ld]
@@ -324,6 +346,7 @@ struct CatRowsT {  // A[m][k] = m < F ? H[k][m] : M[k][m-F]  for m < Mv   (conti
 template <bool V>
 struct CatWeights {  // B[k][n] = k < F ? W_self[k][n] : W_neigh[k-F][n]  (contiguous along n); fp32 master weights
     static constexpr bool kContigK = false;
+    static constexpr bool kGroups = V;
     typedef RawV<float, V> Raw;
     struct Lane {
         int n;
@@ -367,9 +390,12 @@ struct CatWeights {  // B[k][n] = k < F ? W_self[k][n] : W_neigh[k-F][n]  (conti
     }
 };
 
+struct CatWeightsRest : CatWeights<true> {};   // the same for a k that is no multiple of a slab: see SteadyLoop
+
 template <bool V>
 struct CatWeightsT {  // B[k][n] = n < F ? W_self[n][k] : W_neigh[n-F][k]  (contiguous along k); k = output feature
     static constexpr bool kContigK = true;
+    static constexpr bool kGroups = V;
     typedef RawV<float, V> Raw;
     struct Lane {
         const float *row;
@@ -424,6 +450,8 @@ struct CatWeightsT {  // B[k][n] = n < F ? W_self[n][k] : W_neigh[n-F][k]  (cont
 template <bool kAsA, typename T, bool V, bool kRelu>
 struct MaskedGrad {
     static constexpr bool kContigK = kAsA;
+    static constexpr bool kMasks = true;
+    static constexpr bool kGroups = V;
     typedef typename std::conditional<V, typename Pack4<T>::Packed, float4>::type Quad;
     struct RawRelu {
         Quad g, h;
@@ -525,6 +553,7 @@ struct MaskedGrad {
 template <int kMode>
 struct SideWeights {  // B[k][n] = n < Fp ? W_self[k][n] : W_neigh[k][n-Fp]   (contiguous along n)
     static constexpr bool kContigK = false;
+    static constexpr bool kGroups = kMode != kElementwise;
     static constexpr bool V = kMode == kAligned4;
     typedef typename std::conditional<kMode == kUnaligned4, RawU, RawV<float, V>>::type Raw;
     struct Lane {
@@ -585,6 +614,7 @@ struct SideWeights {  // B[k][n] = n < Fp ? W_self[k][n] : W_neigh[k][n-Fp]   (c
 template <int kMode>
 struct SideWeightsT {  // B[k][n] = k < Fp ? W_self[n][k] : W_neigh[n][k-Fp]   (contiguous along k); n = input feature
     static constexpr bool kContigK = true;
+    static constexpr bool kGroups = kMode != kElementwise;
     static constexpr bool V = kMode == kAligned4;
     typedef typename std::conditional<kMode == kUnaligned4, RawU, RawV<float, V>>::type Raw;
     struct Lane {
@@ -649,6 +679,8 @@ struct SideWeightsT {  // B[k][n] = k < Fp ? W_self[n][k] : W_neigh[n][k-Fp]   (
 template <bool kAsA, typename T, bool V, bool kRelu>
 struct SideGrad {
     static constexpr bool kContigK = kAsA;
+    static constexpr bool kMasks = true;
+    static constexpr bool kGroups = V;
     static constexpr bool kTwoSources = true;
     typedef typename std::conditional<V, typename Pack4<T>::Packed, float4>::type Quad;
     struct Raw {
@@ -1093,6 +1125,7 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_kernel(AL a, BL b, E
     constexpr int kDepth = DeepPrefetch<kColSum, Epi::kRowAux>::value ? 2 : 1;   // slabs in flight in registers
     // 8 accumulator tiles, or the two sources of [dZ | dYn], leave registers for one, and not across the barrier
     constexpr bool kLean = (BM / WM / 32) * (BN / WN / 32) > 4 || TwoSourcesAlongK<AL>::value;
+    constexpr bool kSteady = !kLean && SteadyLoop<BN, AL, BL>::value;
     constexpr int TM = BM / WM / 32;
     constexpr int TN = BN / WN / 32;
     constexpr int A_Q = BM * BK / 4, B_Q = BN * BK / 4;   // pieces (four values) of a slab
@@ -1277,11 +1310,36 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_kernel(AL a, BL b, E
                 buf ^= 1;
             }
         };
-        if constexpr (kLean) {
-            // (two sources: the guarded loads need no more registers than the others and fewer in all: 41 us against 50)
-            if constexpr (TwoSourcesAlongK<AL>::value) one_loop(std::false_type{});
-            else if ((t.k_end - t.k_begin) % BK == 0) one_loop(std::true_type{});
-            else one_loop(std::false_type{});
+        // two slabs in flight in registers (slab s >= 1 waits in set (s - 1) % kDepth), whole slabs only
+        auto two_loop = [&]() {
+            typename AL::Raw areg[kDepth][A_V];
+            typename BL::Raw breg[kDepth][B_V];
+            const int64_t n_slabs = (t.k_end - t.k_begin) / BK;
+            static_for<kDepth>([&](auto d_tag) {
+                constexpr int D = decltype(d_tag)::value;
+                if (n_slabs > D + 1) fetch_plain(t.k_begin + (D + 1) * BK, areg[D], breg[D]);
+            });
+            for (int64_t sl0 = 0; sl0 < n_slabs; sl0 += kDepth)
+                static_for<kDepth>([&](auto r_tag) {
+                    constexpr int R = decltype(r_tag)::value;
+                    const int64_t sl = sl0 + R;
+                    if (sl < n_slabs) {      // the same for every thread
+                        multiply(buf);
+                        if (sl + 1 < n_slabs) stage(buf ^ 1, areg[R], breg[R]);
+                        if (sl + 1 + kDepth < n_slabs) fetch_plain(t.k_begin + (sl + 1 + kDepth) * BK, areg[R], breg[R]);
+                        __syncthreads();
+                        buf ^= 1;
+                    }
+                });
+        };
+        if constexpr (!kSteady) {
+            // guarded loads: (two sources) they need no more registers than the others and fewer in all, 41 us against 50;
+            // (element by element) they are the only ones; (rows of no multiple of four) no range of theirs is whole slabs
+            if constexpr (TwoSourcesAlongK<AL>::value || !AL::kGroups || !BL::kGroups || std::is_same<AL, PaddedRows>::value)
+                one_loop(std::false_type{});
+            else if ((t.k_end - t.k_begin) % BK != 0) one_loop(std::false_type{});
+            else if constexpr (kLean || kDepth == 1) one_loop(std::true_type{});
+            else two_loop();
         } else {
             // Whole slabs, in a body without branches, so that the waits ahead of a slab's staging count the younger slabs'
             // loads exactly and leave them in flight (a conditional fetch had made every wait drain them: forward 2 x 256 ->
