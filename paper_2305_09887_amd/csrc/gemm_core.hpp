@@ -1578,9 +1578,9 @@ static void launch_split_128(const char *name, const AL &a, const BL &b, const E
 
 // Every backward product of fp32 storage.  kWide: the operands are fetched in groups of four.  With up to one 64 x 64
 // tile per compute unit that is the tile, above that 64 x 128 up to some 1.5 tiles of 128 x 128 per unit.  Measured, us,
-// weight gradient of 2 x 64 -> 64 at 5,000 rows, 128 x 64 -> 64 x 64: 9.8 -> 8.4; and with forward products, which this
-// kernel ran at that time: 64 x 128 -> 64 x 64 at 12,000 rows, 128 wide, 12.4 -> 14.0; 128 x 64 -> 64 x 128 at 24,000
-// rows 2 x 128 -> 128 20.1 -> 17.7, 2 x 256 -> 256 51.5 -> 44.7.
+// 128 x 64 and 64 x 128 -> 64 x 64 at 5,000 rows: input gradient of 64 -> 64 8.4 -> 6.8, of 128 -> 128 11.0 -> 8.4, their weight
+// gradients 13.2 -> 11.1 and 12.8 -> 11.6; 128 x 64 -> 64 x 128 at 40,000 rows: input gradient of 128 -> 256 33.5 -> 30.2, weight
+// gradient of 64 -> 128 24.4 -> 16.7 (of tiles 96 wide 23.3 -> 24.6).
 template <bool kColSum, bool kWide, class AL, class BL, class Epi>
 static void launch_split(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K, int64_t kps,
                          int n_splits, float *colsum, hipStream_t s)

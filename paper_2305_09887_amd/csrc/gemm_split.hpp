@@ -175,12 +175,15 @@ __global__ __launch_bounds__(WM *WN * 64, kSplitPerCu) void gemm_split_kernel(AL
                                                                     float *__restrict__ colsum_partial)
 {
     constexpr int NT = WM * WN * 64;
-    // Slabs in flight in registers: two for four wavefronts (394 -> 361 us the weight gradient of 256 -> 2 x 48 at 1,000,000
-    // rows) and for the weight gradient, which streams both operands; one for the other products of eight (no gain).  The
-    // unaligned views take registers of their own and go without a set that lives across the barrier (47 -> 41 us the weight
-    // gradient of widths 90 -> 150 at 40,004 rows; the others lose 5 to 20 % so).
-    constexpr int kDepth = kColSum || WM * WN == 4 ? 2 : 1;
-    constexpr bool kLean = WM * WN == 8 && (std::is_same<typename AL::Raw, RawU>::value || std::is_same<typename BL::Raw, RawU>::value);
+    // Slabs in flight in registers.  Two for a weight gradient, which streams both operands (us at 1,000,000 rows, one -> two:
+    // 128 -> 128 335 -> 305, 128 -> 256 605 -> 545), and for the other products of four wavefronts in tiles below 128 x 128; one for the rest,
+    // whose accumulators leave no registers for two (input gradient of 128 -> 128 401 with two, 383 with one, of 2 x 64 -> 100
+    // with ReLU 493 and 474).  The unaligned views take registers of their own: one slab in the 128 x 128 tile (weight gradient of
+    // 50 -> 128 at 125,237 rows 44 with two, 41 with one), and no set that lives across the barrier in the tiles of eight
+    // wavefronts (47 -> 41 us the weight gradient of widths 90 -> 150 at 40,004 rows; the other views lose 5 to 20 % so).
+    constexpr bool kUnaligned = std::is_same<typename AL::Raw, RawU>::value || std::is_same<typename BL::Raw, RawU>::value;
+    constexpr int kDepth = (BM * BN < 128 * 128 && WM * WN == 4) || (kColSum && !(kUnaligned && WM * WN == 4)) ? 2 : 1;
+    constexpr bool kLean = WM * WN == 8 && kUnaligned;
     constexpr int TM = BM / WM / 32;
     constexpr int TN = BN / WN / 32;
     typedef SlabSlots<AL, BM, NT> ASlots;
