@@ -5,12 +5,20 @@
 
 namespace tma {
 
+// Which of two forms of a step runs, decided on the device by the graph's entries (rowptr[n]), which the host does not know:
+// both are launched, with opposite sides, and the one that is not meant returns at once.
+struct EntryGate {
+    enum Side : int { kAlways = 0, kUpTo = 1, kAbove = 2 };
+    int64_t entries = 0;
+    int side = kAlways;
+};
+
 // Row gather-reduce over a CSR:  out_v = scale_v * sum_{u in row v} in_u  (+ out_v when accumulate).
 // scale_v = inv_deg[v] when inv_deg != nullptr, else 1.  fp32 accumulation in neighbour order.
 // in_rows: rows of `in` when it is not an n-row matrix (the ids of colidx index it); 0 = n rows.
 int launch_spmm(int64_t n, const int32_t *rowptr, const int32_t *colidx, const float *inv_deg, const void *in,
                 int64_t ld_in, int32_t F, int32_t dtype, void *out, int64_t ld_out, bool accumulate,
-                hipStream_t stream, int64_t in_rows = 0);
+                hipStream_t stream, int64_t in_rows = 0, EntryGate gate = {});
 
 // Same gather with the layer epilogue fused: out_v = act(scale_v * sum + [out_v] + self_v + bias), or, with
 // scale_all, out_v = act(scale_v * (sum + [out_v] + self_v) + bias) (the GCN form, self inside the normalisation).
@@ -18,12 +26,14 @@ int launch_spmm(int64_t n, const int32_t *rowptr, const int32_t *colidx, const f
 int launch_spmm_combine(int64_t n, const int32_t *rowptr, const int32_t *colidx, const float *inv_deg, const void *in,
                         int64_t ld_in, int32_t F, int32_t dtype, void *out, int64_t ld_out, bool accumulate,
                         const void *self, int64_t ld_self, const float *bias, int32_t F_valid, bool relu,
-                        bool scale_all, const float *edge_scale, hipStream_t stream, int64_t in_rows = 0);
+                        bool scale_all, const float *edge_scale, hipStream_t stream, int64_t in_rows = 0,
+                        EntryGate gate = {});
 
 // dst_v = inv_deg[v] * g_v (.) [h_v > 0]  (mask only with relu); columns F..F_pad-1 of dst are zeroed.
+// rowptr is read with a gate only.
 int launch_scale_mask_rows(int64_t n, int32_t F, int32_t F_pad, const void *g, const void *h, int64_t ld,
                            const float *inv_deg, bool relu, int32_t dtype, void *dst, int64_t ld_dst,
-                           hipStream_t stream);
+                           hipStream_t stream, const int32_t *rowptr = nullptr, EntryGate gate = {});
 
 // Z = [H | M] [W_self ; W_neigh] + b ;  Hnext = act(Z)      (M: [n, F_in] with leading dimension ldm)
 int launch_sage_gemm_fwd(int64_t n, const void *H, int64_t ldh, const void *M, int64_t ldm, int32_t F_in, const float *W_self,

@@ -165,22 +165,33 @@ extern "C" int tma_sage_layer_bwd(int64_t n, const int32_t *rowptr_T, const int3
         const int Fp = pad_cols(F_out, dtype);
         void *dZs = base;
         void *dYn = base + w.dm_bytes / 2;
-        // Without an activation dZ is dHnext itself: its rows are gathered with their inv_deg as weights, where they
-        // have room for the padded width (whatever their padding holds), and the scaled copy of them is not made.
-        // fp32, 47 wide: 23 + 13 -> 26 us at 125,237 rows of 2.5 entries, 68 + 11 -> 71 us at 100,000 rows of 20.  bf16
-        // has twice the values to weight per 16 bytes: 1,615 + 1,064 -> 2,300 us at 12.5 M rows of 1.6 entries, but
-        // 111 + 17 -> 138 us at 150,000 rows of 23, whose copy stays in cache.
+        // Without an activation dZ is dHnext itself: its rows can be gathered with their inv_deg as weights, where they
+        // have room for the padded width (whatever their padding holds), and the scaled copy of them is not made.  The
+        // copy costs by the rows' elements, the weights by the entries.  us of both kernels, copy -> weights, power-law graphs,
+        // 47 wide, mean degree 2.5 / 10 / 20 / 40:
+        //   fp32 125,000 rows 39 -> 28 / 62 -> 52 / 90 -> 86 / 156 -> 158, 400,000 rows 102 -> 69 / 174 -> 165 / 287 -> 307 / 518 -> 603
+        //   bf16 2,000,000 rows, degree 2 / 8 / 20: 387 -> 278 / 627 -> 669 / 1,152 -> 1,535
+        // So fp32 takes the weights where the table of them stays in the L2 (rows below 32 elements: 24 wide 44 -> 39 / 81 -> 86 /
+        // 124 -> 139 at 250,000 rows, but 24 -> 18 / 35 -> 30 / 50 -> 44 / 73 -> 72 at 20,000), and larger parts of either type take
+        // them up to a mean degree of an eighth of the width, which the device sees (128 wide: 1,771 -> 1,913 at 2,000,000
+        // rows of 20, 1,093 -> 794 of 8).  bf16 below 2^20 rows has less to save (150,000 rows of 23: 113 -> 114).
         const int64_t per16 = 16 / int64_t(elem_size(dtype));
-        const bool weigh = dtype == TMA_F32 || n >= (int64_t(1) << 20);
-        if (weigh && act == TMA_ACT_NONE && ld_next >= Fp && ld_next % per16 == 0 && aligned(dHnext, 16)) {
+        const bool room = act == TMA_ACT_NONE && ld_next >= Fp && ld_next % per16 == 0 && aligned(dHnext, 16);
+        const bool weigh = room && dtype == TMA_F32 && n <= (int64_t(1) << (Fp >= 32 ? 18 : 15));
+        const bool weigh_sparse = room && !weigh && Fp >= 32 && (dtype == TMA_F32 || n >= (int64_t(1) << 20));
+        const int64_t sparse = n * Fp / 8;
+        if (weigh || weigh_sparse) {
+            const EntryGate gate{sparse, weigh ? EntryGate::kAlways : EntryGate::kUpTo};
             if (int rc = launch_spmm_combine(n, rowptr_T, colidx_T, nullptr, dHnext, ld_next, Fp, dtype, dYn, Fp, false, nullptr, 0,
-                                             nullptr, F_out, false, false, inv_deg, s))
+                                             nullptr, F_out, false, false, inv_deg, s, 0, gate))
                 return rc;
-        } else {
+        }
+        if (!weigh) {
+            const EntryGate gate{sparse, weigh_sparse ? EntryGate::kAbove : EntryGate::kAlways};
             if (int rc = launch_scale_mask_rows(n, F_out, Fp, dHnext, Hnext, ld_next, inv_deg, act == TMA_ACT_RELU, dtype,
-                                                dZs, Fp, s))
+                                                dZs, Fp, s, rowptr_T, gate))
                 return rc;
-            if (int rc = launch_spmm(n, rowptr_T, colidx_T, nullptr, dZs, Fp, Fp, dtype, dYn, Fp, false, s)) return rc;
+            if (int rc = launch_spmm(n, rowptr_T, colidx_T, nullptr, dZs, Fp, Fp, dtype, dYn, Fp, false, s, 0, gate)) return rc;
         }
         if (int rc = launch_sage_tf_gemm_bwd_weight(n, H, ldh, dHnext, Hnext, ld_next, dYn, Fp, F_in, F_out, act, dtype,
                                                     dW_self, dW_neigh, dbias, wws, w.weight_bytes, s))

@@ -123,7 +123,13 @@ struct SpmmOut {
     const float *edge_scale;  // neighbour u enters the sum as edge_scale[u] * in_u, and self_v as edge_scale[v] * self_v
     int64_t in_rows;          // rows of the gathered matrix (>= 1): filler loads stay below it
     int clear_padding;        // elements from F on come out as zeros whatever the gathered rows hold there
+    EntryGate gate;
 };
+
+__device__ __forceinline__ bool shut(const EntryGate &gate, const int32_t *__restrict__ rowptr, int64_t n)
+{
+    return gate.side != EntryGate::kAlways && (rowptr[n] > gate.entries) != (gate.side == EntryGate::kAbove);
+}
 
 // last_col: see launch_typed (the first column of a row's last chunk)
 template <typename T, int G, int CPL>
@@ -306,6 +312,7 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, co
     constexpr int U = kStreamU;
     constexpr bool kEdge = kW != Weighting::kNone;
     constexpr int kHubsPerPass = kPartialBytes / (kSpmmThreads * E * int(sizeof(float)));
+    if (shut(o.gate, rowptr, n)) return;
     __shared__ int32_t bounds[kMaxRowsPerBlock + 1];   // rowptr of the workgroup's rows
     __shared__ int32_t deferred[kMaxRowsPerBlock];
     __shared__ int32_t n_deferred;
@@ -480,6 +487,7 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_rows_kernel(int64_t n, cons
     constexpr int NG = kSpmmThreads / G;
     constexpr int R = kRowsPerGroup;
     constexpr int RPB = NG * R;
+    if (shut(o.gate, rowptr, n)) return;
     __shared__ int32_t hub_rows[RPB];
     __shared__ int32_t hub_count;
     __shared__ float partial[NG][G * CPL * E];
@@ -547,6 +555,7 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_rows_generic_kernel(int64_t
                                                                          const T *__restrict__ in, int64_t ld_in,
                                                                          SpmmOut<T> o, int F)
 {
+    if (shut(o.gate, rowptr, n)) return;
     constexpr int kPer = 8;  // elements per lane per sweep: 512 features per sweep
     const int lane = threadIdx.x % kWave;
     const int64_t v = int64_t(blockIdx.x) * (kSpmmThreads / kWave) + threadIdx.x / kWave;
@@ -692,33 +701,33 @@ template <typename T>
 static int spmm_any(int64_t n, const int32_t *rowptr, const int32_t *colidx, const float *inv_deg, const void *in,
                     int64_t ld_in, int32_t F, void *out, int64_t ld_out, bool accumulate, const void *self,
                     int64_t ld_self, const float *bias, int32_t F_valid, bool relu, bool scale_all,
-                    const float *edge_scale, int64_t in_rows, hipStream_t stream)
+                    const float *edge_scale, int64_t in_rows, EntryGate gate, hipStream_t stream)
 {
     SpmmOut<T> o{static_cast<T *>(out), ld_out, inv_deg, accumulate ? 1 : 0, static_cast<const T *>(self), ld_self,
-                 bias, F_valid, relu ? 1 : 0, (scale_all && inv_deg) ? 1 : 0, edge_scale, in_rows > 0 ? in_rows : n, F_valid < F ? 1 : 0};
+                 bias, F_valid, relu ? 1 : 0, (scale_all && inv_deg) ? 1 : 0, edge_scale, in_rows > 0 ? in_rows : n, F_valid < F ? 1 : 0, gate};
     return launch_typed<T>(n, rowptr, colidx, static_cast<const T *>(in), ld_in, F, o, stream);
 }
 
 int launch_spmm(int64_t n, const int32_t *rowptr, const int32_t *colidx, const float *inv_deg, const void *in,
                 int64_t ld_in, int32_t F, int32_t dtype, void *out, int64_t ld_out, bool accumulate,
-                hipStream_t stream, int64_t in_rows)
+                hipStream_t stream, int64_t in_rows, EntryGate gate)
 {
     return launch_spmm_combine(n, rowptr, colidx, inv_deg, in, ld_in, F, dtype, out, ld_out, accumulate, nullptr, 0,
-                               nullptr, F, false, false, nullptr, stream, in_rows);
+                               nullptr, F, false, false, nullptr, stream, in_rows, gate);
 }
 
 int launch_spmm_combine(int64_t n, const int32_t *rowptr, const int32_t *colidx, const float *inv_deg, const void *in,
                         int64_t ld_in, int32_t F, int32_t dtype, void *out, int64_t ld_out, bool accumulate,
                         const void *self, int64_t ld_self, const float *bias, int32_t F_valid, bool relu,
-                        bool scale_all, const float *edge_scale, hipStream_t stream, int64_t in_rows)
+                        bool scale_all, const float *edge_scale, hipStream_t stream, int64_t in_rows, EntryGate gate)
 {
     if (n == 0 || F == 0) return TMA_OK;
     if (dtype == TMA_F32)
         return spmm_any<float>(n, rowptr, colidx, inv_deg, in, ld_in, F, out, ld_out, accumulate, self, ld_self, bias,
-                               F_valid, relu, scale_all, edge_scale, in_rows, stream);
+                               F_valid, relu, scale_all, edge_scale, in_rows, gate, stream);
     if (dtype == TMA_BF16)
         return spmm_any<uint16_t>(n, rowptr, colidx, inv_deg, in, ld_in, F, out, ld_out, accumulate, self, ld_self,
-                                  bias, F_valid, relu, scale_all, edge_scale, in_rows, stream);
+                                  bias, F_valid, relu, scale_all, edge_scale, in_rows, gate, stream);
     return fail(TMA_ERR_UNSUPPORTED_DTYPE, "spmm: dtype %d", dtype);
 }
 
@@ -727,8 +736,10 @@ template <typename T>
 __global__ __launch_bounds__(256) void scale_mask_rows_kernel(int64_t n, int F, int F_pad, const T *__restrict__ g,
                                                               const T *__restrict__ h, int64_t ld,
                                                               const float *__restrict__ inv_deg, int relu,
-                                                              T *__restrict__ dst, int64_t ld_dst)
+                                                              T *__restrict__ dst, int64_t ld_dst,
+                                                              const int32_t *__restrict__ rowptr, EntryGate gate)
 {
+    if (shut(gate, rowptr, n)) return;
     const int64_t total = n * F_pad;
     const int64_t stride = int64_t(gridDim.x) * 256;
     for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < total; i += stride) {
@@ -745,7 +756,7 @@ __global__ __launch_bounds__(256) void scale_mask_rows_kernel(int64_t n, int F, 
 
 int launch_scale_mask_rows(int64_t n, int32_t F, int32_t F_pad, const void *g, const void *h, int64_t ld,
                            const float *inv_deg, bool relu, int32_t dtype, void *dst, int64_t ld_dst,
-                           hipStream_t stream)
+                           hipStream_t stream, const int32_t *rowptr, EntryGate gate)
 {
     if (n == 0 || F_pad == 0) return TMA_OK;
     int64_t blocks = ceil_div(n * F_pad, 256);
@@ -754,11 +765,11 @@ int launch_scale_mask_rows(int64_t n, int32_t F, int32_t F_pad, const void *g, c
     if (dtype == TMA_F32)
         hipLaunchKernelGGL(scale_mask_rows_kernel<float>, dim3(unsigned(blocks)), dim3(256), 0, stream, n, F, F_pad,
                            static_cast<const float *>(g), static_cast<const float *>(h), ld, inv_deg, relu ? 1 : 0,
-                           static_cast<float *>(dst), ld_dst);
+                           static_cast<float *>(dst), ld_dst, rowptr, gate);
     else
         hipLaunchKernelGGL(scale_mask_rows_kernel<uint16_t>, dim3(unsigned(blocks)), dim3(256), 0, stream, n, F, F_pad,
                            static_cast<const uint16_t *>(g), static_cast<const uint16_t *>(h), ld, inv_deg,
-                           relu ? 1 : 0, static_cast<uint16_t *>(dst), ld_dst);
+                           relu ? 1 : 0, static_cast<uint16_t *>(dst), ld_dst, rowptr, gate);
     return check_launch("scale_mask_rows");
 }
 
