@@ -160,6 +160,7 @@ def kernel_work(name, n, nnz, dims, N=0, nnz_glob=0, K=1, n_params=0, encoder="s
         "spmm_combine": 2 * n * Cp * s + nnz * 4 + n * 8 + n * Cp * s,
         # dYn = A^T (D^-1 dZ): scaled rows once + ids + rowptr + output
         "spmm_sum": n * Cp * s + nnz * 4 + n * 4 + n * Cp * s,
+        "spmm_weighted": n * Cp * s + nnz * 4 + n * 8 + n * Cp * s,      # in place of these two, without an activation
         "scale_mask_rows": n * C * s + n * 4 + n * Cp * s,
         "softmax_ce": 2 * n * C * s + n * 4,
         "ln_prelu_fwd_f32": 2 * n * F1 * s,                   # Z read, H' written
@@ -345,7 +346,7 @@ def main():
     d_rowptr, d_colidx = torch.as_tensor(rowptr).to(dev), torch.as_tensor(colidx).to(dev)
     feat_dtype = torch.bfloat16 if args.dtype == "bf16" else torch.float32
     sb = 2 if args.dtype == "bf16" else 4          # bytes per stored feature / activation element
-    peak_mfma = PEAK_MFMA_BF16_TFLOPS if args.dtype == "bf16" else PEAK_MFMA_F32_TFLOPS
+    dtype_peak = PEAK_MFMA_BF16_TFLOPS if args.dtype == "bf16" else PEAK_MFMA_F32_TFLOPS
     d_X, d_y = torch.as_tensor(X).to(dev).to(feat_dtype), torch.as_tensor(y).to(dev)
     part = torch.empty(N, dtype=torch.int32, device=dev)
 
@@ -575,11 +576,12 @@ def main():
     bound, work = work_of(dominant)
     avg_ms = dom[1] / max(dom[0], 1)
     if bound == "mfma":
-        achieved, peak, unit = work / (avg_ms * 1e-3) / 1e12, peak_mfma, "TFLOP/s"
+        achieved, unit = work / (avg_ms * 1e-3) / 1e12, "TFLOP/s"
+        peak, peak_of = benchlib.matrix_peak(dominant, dtype_peak)
     else:
-        bound = "hbm"
+        bound, peak_of = "hbm", "HBM"
         achieved, peak, unit = work / (avg_ms * 1e-3) / 1e9, PEAK_HBM_GBS, "GB/s"
-    roofline = dict(bound=bound, kernel=dominant, achieved=round(achieved, 3), peak=peak, unit=unit,
+    roofline = dict(bound=bound, kernel=dominant, achieved=round(achieved, 3), peak=peak, peak_of=peak_of, unit=unit,
                     frac=round(achieved / peak, 4), traffic=traffic_table.get(dominant.replace("_generic", "")),
                     avg_launch_ms=round(avg_ms, 5), launches=dom[0],
                     algorithmic_work_per_launch=work)
@@ -595,8 +597,9 @@ def main():
         per_launch_s = ms * 1e-3 / launches
         traffic = traffic_table.get(k.replace("_generic", ""))
         if b == "mfma":
-            kernel_rooflines[k] = {"bound": b, "achieved": round(wk / per_launch_s / 1e12, 2), "peak": peak_mfma,
-                                   "unit": "TFLOP/s", "frac": round(wk / per_launch_s / 1e12 / peak_mfma, 4), "traffic": traffic,
+            peak, peak_of = benchlib.matrix_peak(k, dtype_peak)
+            kernel_rooflines[k] = {"bound": b, "achieved": round(wk / per_launch_s / 1e12, 2), "peak": peak, "peak_of": peak_of,
+                                   "unit": "TFLOP/s", "frac": round(wk / per_launch_s / 1e12 / peak, 4), "traffic": traffic,
                                    "traffic_GBs": round(traffic / per_launch_s / 1e9, 1) if traffic else None}
         else:
             kernel_rooflines[k] = {"bound": b, "achieved": round(wk / per_launch_s / 1e9, 1), "peak": PEAK_HBM_GBS,
@@ -616,7 +619,7 @@ def main():
                         "positives_per_s": round(args.batch / (ms_per_step * 1e-3), 1),
                         "value_definition": "entries of the sampled blocks (all layers) / step time"}
     train_ms = sum(v for k, v in per_step.items()
-                   if k.startswith(("spmm", "gemm", "reduce", "softmax", "finish", "sgd", "ln_prelu", "scale_mask", "sum_partials", "edge_batch",
+                   if k.startswith(("spmm", "gated", "gemm", "reduce", "softmax", "finish", "sgd", "ln_prelu", "scale_mask", "sum_partials", "edge_batch",
                                     "pair_product", "incidence", "exclusive_scan", "prelu", "bce", "sample_", "mfg_",
                                     "block_", "transpose_")))
     out = {

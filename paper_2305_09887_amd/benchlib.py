@@ -18,12 +18,22 @@ PEAK_HBM_GBS = 8000.0
 PEAK_MFMA_F32_TFLOPS = 157.3
 PEAK_MFMA_BF16_TFLOPS = 2500.0
 
+
+
+def matrix_peak(kernel: str, dtype_peak: float):
+    """(peak, of what) of the matrix units a product runs on: backward products of fp32 storage are six bf16 products
+    of parts per fp32 product, forward ones run on the fp32 instruction, bf16 storage on the bf16 one."""
+    if dtype_peak == PEAK_MFMA_F32_TFLOPS and "_bwd_" in kernel:
+        return round(PEAK_MFMA_BF16_TFLOPS / 6, 1), "a sixth of the bf16 matrix peak (six bf16 products per fp32 product)"
+    return dtype_peak, "fp32 matrix instruction" if dtype_peak == PEAK_MFMA_F32_TFLOPS else "bf16 matrix instruction"
+
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
 
 # kernel families, longest prefix first
 FAMILIES = ("gemm_tf_bwd_weight", "gemm_tf_bwd_data", "gemm_tf_fwd", "gemm_bwd_weight", "gemm_bwd_data", "gemm_fwd",
-            "spmm_mean", "spmm_combine", "spmm_sum", "scale_mask_rows")
+            "spmm_mean", "spmm_combine", "spmm_sum", "spmm_weighted", "scale_mask_rows")
 
 
 def family(name: str):
@@ -62,6 +72,7 @@ def sage_layer_work(n: int, nnz: int, dims, s: int, dt: int):
             out[("fwd", l, "spmm_combine")] = ("hbm", 3.0 * n * Fp * s + nnz * 4 + n * 8)    # Yn rows once, Ys, output
             out[("bwd", l, "scale_mask_rows")] = ("hbm", float(n * Fo * s + n * 4 + n * Fp * s))
             out[("bwd", l, "spmm_sum")] = ("hbm", 2.0 * n * Fp * s + nnz * 4 + n * 4)
+            out[("bwd", l, "spmm_weighted")] = ("hbm", 2.0 * n * Fp * s + nnz * 4 + n * 8)   # in place of these two
             out[("bwd", l, "gemm_tf_bwd_weight")] = ("mfma", 2.0 * n * Fi * 2 * Fo, n * Fi * s + g + n * Fp * s)
             if l > 0:
                 out[("bwd", l, "gemm_tf_bwd_data")] = ("mfma", 2.0 * n * 2 * Fo * Fi, g + n * Fp * s + n * Fi * s)
@@ -155,10 +166,10 @@ def rooflines(per_step, prof, repeats, work_of, peak_mfma, traffic):
         sec = ms * 1e-3 / launches
         tr = traffic.get(k)
         if b == "mfma":
-            a, peak, unit = wk / sec / 1e12, peak_mfma, "TFLOP/s"
+            a, (peak, peak_of), unit = wk / sec / 1e12, matrix_peak(k, peak_mfma), "TFLOP/s"
         else:
-            a, peak, unit = wk / sec / 1e9, PEAK_HBM_GBS, "GB/s"
-        out[k] = {"bound": b, "achieved": round(a, 2), "peak": peak, "unit": unit, "frac": round(a / peak, 4),
+            a, peak, peak_of, unit = wk / sec / 1e9, PEAK_HBM_GBS, "HBM", "GB/s"
+        out[k] = {"bound": b, "achieved": round(a, 2), "peak": peak, "peak_of": peak_of, "unit": unit, "frac": round(a / peak, 4),
                   "us_per_launch": round(sec * 1e6, 2), "traffic": tr,
                   "traffic_GBs": round(tr / sec / 1e9, 1) if tr else None}
         if streamed:      # a product against its other ceiling: streamed operands and results per time
@@ -171,11 +182,11 @@ def dominant_roofline(name, dom, work_of, peak_mfma, traffic):
     bound, work, *streamed = work_of(name)
     avg_ms = dom[1] / max(dom[0], 1)
     if bound == "mfma":
-        achieved, peak, unit = work / (avg_ms * 1e-3) / 1e12, peak_mfma, "TFLOP/s"
+        achieved, (peak, peak_of), unit = work / (avg_ms * 1e-3) / 1e12, matrix_peak(name, peak_mfma), "TFLOP/s"
     else:
         bound = "hbm"
-        achieved, peak, unit = work / (avg_ms * 1e-3) / 1e9, PEAK_HBM_GBS, "GB/s"
-    out = dict(bound=bound, kernel=name, achieved=round(achieved, 3), peak=peak, unit=unit,
+        achieved, peak, peak_of, unit = work / (avg_ms * 1e-3) / 1e9, PEAK_HBM_GBS, "HBM", "GB/s"
+    out = dict(bound=bound, kernel=name, achieved=round(achieved, 3), peak=peak, peak_of=peak_of, unit=unit,
                frac=round(achieved / peak, 4), traffic=traffic.get(name), avg_launch_ms=round(avg_ms, 5),
                launches=dom[0], algorithmic_work_per_launch=work)
     if streamed:

@@ -6,7 +6,8 @@
 namespace tma {
 
 // Which of two forms of a step runs, decided on the device by the graph's entries (rowptr[n]), which the host does not know:
-// both are launched, with opposite sides, and the one that is not meant returns at once.
+// both are launched, with opposite sides, and the one that is not meant returns at once.  (The timing hook calls such
+// launches gated_*: their time says nothing about the bytes of the one form or the other.)
 struct EntryGate {
     enum Side : int { kAlways = 0, kUpTo = 1, kAbove = 2 };
     int64_t entries = 0;

@@ -600,7 +600,7 @@ static void launch_wide_rows(int64_t n, const int32_t *rowptr, const int32_t *co
 {
     constexpr int RPB = (kSpmmThreads / G) * kRowsPerGroup;
     char name[48];
-    snprintf(name, sizeof(name), "%s_%s_g%dx%d", o.self ? "spmm_combine" : (o.inv_deg ? "spmm_mean" : "spmm_sum"),
+    snprintf(name, sizeof(name), "%s%s_%s_g%dx%d", o.gate.side ? "gated_" : "", o.self ? "spmm_combine" : (o.inv_deg ? "spmm_mean" : "spmm_sum"),
              sizeof(T) == 4 ? "f32" : "bf16", G, CPL);
     TMA_TIMED(name, s);
     hipLaunchKernelGGL((spmm_rows_kernel<T, G, CPL>), dim3(unsigned(ceil_div(n, RPB))), dim3(kSpmmThreads), 0, s, n,
@@ -623,7 +623,7 @@ static void launch_stream(int64_t n, const int32_t *rowptr, const int32_t *colid
     rpg = rpg < 4 ? 4 : (rpg > rpg_max ? rpg_max : rpg);
     if (rpg * NG > kMaxRowsPerBlock) rpg = kMaxRowsPerBlock / NG;
     char name[48];
-    snprintf(name, sizeof(name), "%s_%s_g%dx1",
+    snprintf(name, sizeof(name), "%s%s_%s_g%dx1", o.gate.side ? "gated_" : "",
              kW != Weighting::kNone ? "spmm_weighted" : (kExtra == 1 ? "spmm_combine" : (kScale ? "spmm_mean" : "spmm_sum")),
              sizeof(T) == 4 ? "f32" : "bf16", G);
     TMA_TIMED(name, s);
@@ -665,7 +665,7 @@ static int launch_typed(int64_t n, const int32_t *rowptr, const int32_t *colidx,
     const bool edge_self = o.edge_scale && o.self && o.inv_deg == o.edge_scale;
     const bool edge_plain = o.edge_scale && !o.self && !o.inv_deg && !o.accumulate;
     if ((!vec_ok && !overlap) || (o.edge_scale && !edge_self && !edge_plain && row_bytes / 16 <= 64)) {
-        TMA_TIMED(o.self ? "spmm_combine_generic" : (o.inv_deg ? "spmm_mean_generic" : "spmm_sum_generic"), s);
+        TMA_TIMED(o.gate.side ? "gated_spmm_generic" : o.self ? "spmm_combine_generic" : (o.inv_deg ? "spmm_mean_generic" : "spmm_sum_generic"), s);
         hipLaunchKernelGGL((spmm_rows_generic_kernel<T>), dim3(unsigned(ceil_div(n, kSpmmThreads / kWave))),
                            dim3(kSpmmThreads), 0, s, n, rowptr, colidx, in, ld_in, o, F);
         return check_launch("spmm (generic)");
@@ -761,7 +761,7 @@ int launch_scale_mask_rows(int64_t n, int32_t F, int32_t F_pad, const void *g, c
     if (n == 0 || F_pad == 0) return TMA_OK;
     int64_t blocks = ceil_div(n * F_pad, 256);
     if (blocks > 256 * 32) blocks = 256 * 32;
-    TMA_TIMED("scale_mask_rows", stream);
+    TMA_TIMED(gate.side ? "gated_scale_mask_rows" : "scale_mask_rows", stream);
     if (dtype == TMA_F32)
         hipLaunchKernelGGL(scale_mask_rows_kernel<float>, dim3(unsigned(blocks)), dim3(256), 0, stream, n, F, F_pad,
                            static_cast<const float *>(g), static_cast<const float *>(h), ld, inv_deg, relu ? 1 : 0,
