@@ -577,7 +577,7 @@ def main():
     avg_ms = dom[1] / max(dom[0], 1)
     if bound == "mfma":
         achieved, unit = work / (avg_ms * 1e-3) / 1e12, "TFLOP/s"
-        peak, peak_of = benchlib.matrix_peak(dominant, dtype_peak)
+        peak, peak_of = benchlib.matrix_peak(dominant, dtype_peak, n_loc)
     else:
         bound, peak_of = "hbm", "HBM"
         achieved, peak, unit = work / (avg_ms * 1e-3) / 1e9, PEAK_HBM_GBS, "GB/s"
@@ -597,7 +597,7 @@ def main():
         per_launch_s = ms * 1e-3 / launches
         traffic = traffic_table.get(k.replace("_generic", ""))
         if b == "mfma":
-            peak, peak_of = benchlib.matrix_peak(k, dtype_peak)
+            peak, peak_of = benchlib.matrix_peak(k, dtype_peak, n_loc)
             kernel_rooflines[k] = {"bound": b, "achieved": round(wk / per_launch_s / 1e12, 2), "peak": peak, "peak_of": peak_of,
                                    "unit": "TFLOP/s", "frac": round(wk / per_launch_s / 1e12 / peak, 4), "traffic": traffic,
                                    "traffic_GBs": round(traffic / per_launch_s / 1e9, 1) if traffic else None}

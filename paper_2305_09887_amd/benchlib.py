@@ -17,13 +17,14 @@ from . import binding as B
 PEAK_HBM_GBS = 8000.0
 PEAK_MFMA_F32_TFLOPS = 157.3
 PEAK_MFMA_BF16_TFLOPS = 2500.0
+FEW_ROWS = 1 << 16      # backward products of fewer rows keep the fp32 instruction (csrc/kernels.hpp)
 
 
 
-def matrix_peak(kernel: str, dtype_peak: float):
+def matrix_peak(kernel: str, dtype_peak: float, rows: int = FEW_ROWS):
     """(peak, of what) of the matrix units a product runs on: backward products of fp32 storage are six bf16 products
-    of parts per fp32 product, forward ones run on the fp32 instruction, bf16 storage on the bf16 one."""
-    if dtype_peak == PEAK_MFMA_F32_TFLOPS and "_bwd_" in kernel:
+    of parts per fp32 product, forward ones and those of few rows run on the fp32 instruction, bf16 storage on the bf16 one."""
+    if dtype_peak == PEAK_MFMA_F32_TFLOPS and "_bwd_" in kernel and rows >= FEW_ROWS:
         return round(PEAK_MFMA_BF16_TFLOPS / 6, 1), "a sixth of the bf16 matrix peak (six bf16 products per fp32 product)"
     return dtype_peak, "fp32 matrix instruction" if dtype_peak == PEAK_MFMA_F32_TFLOPS else "bf16 matrix instruction"
 

@@ -3,8 +3,8 @@
 //
 // Operands are described by small "view" structs that present concatenations ([H | M], [W_self ; W_neigh]), the ReLU
 // mask and transposes as plain A[m][k], B[k][n], and results by an epilogue struct; three kernel templates take them:
-// gemm_f32_kernel (gemm_f32.hpp) for the forward products of fp32 storage, gemm_split_kernel (gemm_split.hpp) for its
-// backward products, gemm_bf16_kernel below for bf16 (v_mfma_f32_32x32x16_bf16, fp32 accumulation).
+// gemm_f32_kernel (gemm_f32.hpp) for the forward products of fp32 storage and backward ones of few rows, gemm_split_kernel
+// (gemm_split.hpp) for the other backward ones, gemm_bf16_kernel below for bf16 (v_mfma_f32_32x32x16_bf16, fp32 accumulation).
 //
 // Tiling of gemm_bf16_kernel.  BM x BN block tile, each wavefront owning a (BM/WM) x (BN/WN) patch of 32x32 MFMA
 // tiles; k is consumed in slabs of BK through two LDS buffers (one barrier per slab) while the next slab's global
@@ -812,6 +812,7 @@ struct SideGrad {
 // ---------------------------------------------------------------------------
 struct CatRowsU {  // A[m][k] = H[m][k]   (contiguous along k)
     static constexpr bool kContigK = true;
+    static constexpr bool kGroups = true;
     typedef RawU Raw;
     struct Lane {
         const float *p;   // row
@@ -838,6 +839,7 @@ struct CatRowsU {  // A[m][k] = H[m][k]   (contiguous along k)
 
 struct CatRowsTU {  // A[m][k] = (m < Fq ? H[k][m] : M[k][m-Fq])   (contiguous along m); k = node
     static constexpr bool kContigK = false;
+    static constexpr bool kGroups = true;
     typedef RawU Raw;
     struct Lane {
         const float *p;   // column pointer: element of node k is p[k * ld]
@@ -870,6 +872,7 @@ struct CatRowsTU {  // A[m][k] = (m < Fq ? H[k][m] : M[k][m-Fq])   (contiguous a
 
 struct CatWeightsU {  // B[k][n] = k < F ? W_self[k][n] : W_neigh[k-F][n]   (contiguous along n)
     static constexpr bool kContigK = false;
+    static constexpr bool kGroups = true;
     typedef RawU Raw;
     struct Lane {
         int n;
@@ -893,6 +896,7 @@ struct CatWeightsU {  // B[k][n] = k < F ? W_self[k][n] : W_neigh[k-F][n]   (con
 
 struct CatWeightsTU {  // B[k][n] = n < F ? W_self[n][k] : W_neigh[n-F][k]  (contiguous along k); k = output feature
     static constexpr bool kContigK = true;
+    static constexpr bool kGroups = true;
     typedef RawU Raw;
     struct Lane {
         const float *W;
@@ -1531,30 +1535,32 @@ static inline bool few_tiles(int64_t M, int64_t N, int n_splits = 1)
     return ceil_div(M, int64_t(128)) * ceil_div(N, int64_t(128)) * n_splits < kFewTiles;
 }
 
-// A forward product of fp32 storage (gemm_f32.hpp).  BK of the 128 x 128 tile: 16 leaves room for a third block per
-// compute unit, 32 halves the barriers.
-template <int BM, int BN, int BK, int WM, int WN, class AL, class BL, class Epi>
-static void launch_f32(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K, hipStream_t s)
+// A product of fp32 storage on the fp32 instruction (gemm_f32.hpp).  BK of the 128 x 128 tile: 16 leaves room for a third
+// block per compute unit, 32 halves the barriers.
+template <int BM, int BN, int BK, int WM, int WN, bool kColSum, class AL, class BL, class Epi>
+static void launch_f32(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K, int64_t k_per_split,
+                       int n_splits, float *colsum_partial, hipStream_t s)
 {
     if (M <= 0 || N <= 0 || K <= 0) return;   // an empty product: callers zero-fill what they need
     const int n_tiles = int(ceil_div(N, BN));
-    const int64_t total = ceil_div(M, BM) * n_tiles;
+    const int64_t tiles = ceil_div(M, BM) * n_tiles;
+    const int64_t total = tiles * n_splits;
     constexpr int kLdsBytes = 2 * 4 * ((AL::kContigK ? BM * (BK + kPad) : BK * (BM + kPad)) + (BL::kContigK ? BN * (BK + kPad) : BK * (BN + kPad)));
-    constexpr int kPerCu = (BK <= 16 && !Epi::kRowAux && kLdsBytes <= 53 * 1024 ? 3 : 2) * 4 / (WM * WN);
+    constexpr int kPerCu = (BK <= 16 && !Epi::kRowAux && !kColSum && kLdsBytes <= 53 * 1024 ? 3 : 2) * 4 / (WM * WN);
     static_assert(kPerCu * kLdsBytes <= 160 * 1024, "blocks per compute unit");
     int64_t blocks_per_die = ceil_div(total, kXcds);
     if (blocks_per_die > 32 * kPerCu) blocks_per_die = 32 * kPerCu;
     TMA_TIMED(name, s);
-    hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, BK, WM, WN, AL, BL, Epi>), dim3(unsigned(blocks_per_die * kXcds)), dim3(WM * WN * 64),
-                       0, s, a, b, e, M, N, K, n_tiles, total);
+    hipLaunchKernelGGL((gemm_f32_kernel<BM, BN, BK, WM, WN, kColSum, AL, BL, Epi>), dim3(unsigned(blocks_per_die * kXcds)),
+                       dim3(WM * WN * 64), 0, s, a, b, e, M, N, K, k_per_split, n_tiles, tiles, total, colsum_partial);
 }
 
 template <int BK, class AL, class BL, class Epi>
 static void launch_fwd_f32(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K, hipStream_t s)
 {
-    if (N <= 64 || few_tiles(M, N)) launch_f32<128, 64, 32, 4, 1>(name, a, b, e, M, N, K, s);
-    else if (BK == 32 && N <= 96) launch_f32<128, 96, 32, 4, 1>(name, a, b, e, M, N, K, s);
-    else launch_f32<128, 128, BK, 2, 2>(name, a, b, e, M, N, K, s);
+    if (N <= 64 || few_tiles(M, N)) launch_f32<128, 64, 32, 4, 1, false>(name, a, b, e, M, N, K, K, 1, nullptr, s);
+    else if (BK == 32 && N <= 96) launch_f32<128, 96, 32, 4, 1, false>(name, a, b, e, M, N, K, K, 1, nullptr, s);
+    else launch_f32<128, 128, BK, 2, 2, false>(name, a, b, e, M, N, K, K, 1, nullptr, s);
 }
 
 // fp32 products with more than 96 columns.  The 256-wide tile of eight wavefronts reads the operand it is wide across
@@ -1576,23 +1582,31 @@ static void launch_split_128(const char *name, const AL &a, const BL &b, const E
     launch_gemm<128, 128, 32, 2, 2, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
 }
 
-// Every backward product of fp32 storage.  kWide: the operands are fetched in groups of four.  With up to one 64 x 64
-// tile per compute unit that is the tile, above that 64 x 128 up to some 1.5 tiles of 128 x 128 per unit.  Measured, us,
-// 128 x 64 and 64 x 128 -> 64 x 64 at 5,000 rows: input gradient of 64 -> 64 8.4 -> 6.8, of 128 -> 128 11.0 -> 8.4, their weight
-// gradients 13.2 -> 11.1 and 12.8 -> 11.6; 128 x 64 -> 64 x 128 at 40,000 rows: input gradient of 128 -> 256 33.5 -> 30.2, weight
-// gradient of 64 -> 128 24.4 -> 16.7 (of tiles 96 wide 23.3 -> 24.6).
+// A backward product of few rows (see few_rows).  us, from bf16 parts -> so, weight gradient of 128 -> 128 and input gradient of
+// 2 x 128 -> 256: 5,000 rows 14 -> 14 and 16 -> 18, 60,000 rows 34 -> 47 and 60 -> 86.  Tiles, 128 x 64 -> 64 x 64 with up to one
+// of these per compute unit, 5,000 rows: input gradient of 64 -> 64 9.4 -> 7.1, weight gradients of 64 -> 128 18.8 -> 10.9.
+template <bool kColSum, class AL, class BL, class Epi>
+static void launch_few_rows(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K, int64_t kps,
+                            int n_splits, float *colsum, hipStream_t s)
+{
+    if (ceil_div(M, int64_t(64)) * ceil_div(N, 64) * n_splits <= 256)
+        launch_f32<64, 64, 32, 2, 2, kColSum>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    else if (N <= 64 || few_tiles(M, N, n_splits))
+        launch_f32<128, 64, 32, 4, 1, kColSum>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    else if (N <= 96) launch_f32<128, 96, 32, 4, 1, kColSum>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    else launch_f32<128, 128, kColSum ? 16 : 32, 2, 2, kColSum>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+}
+
+// Every backward product of fp32 storage.  kWide: the operands are fetched in groups of four.
 template <bool kColSum, bool kWide, class AL, class BL, class Epi>
 static void launch_split(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K, int64_t kps,
                          int n_splits, float *colsum, hipStream_t s)
 {
+    if (few_rows(kColSum ? K : M)) return launch_few_rows<kColSum>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
     if constexpr (!kWide) {   // rare, and bound by its loads: one tile is enough
         launch_gemm<128, 64, 32, 4, 1, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
     } else {
-        if (ceil_div(M, int64_t(64)) * ceil_div(N, 64) * n_splits <= 256)
-            launch_gemm<64, 64, 32, 2, 2, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
-        else if (N <= 64) launch_gemm<128, 64, 32, 4, 1, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
-        else if (few_tiles(M, N, n_splits))
-            launch_gemm<64, 128, 32, 2, 2, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+        if (N <= 64) launch_gemm<128, 64, 32, 4, 1, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
         else if (N <= 96) launch_gemm<128, 96, 32, 4, 1, kColSum, float>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
         else launch_split_128<kColSum>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
     }

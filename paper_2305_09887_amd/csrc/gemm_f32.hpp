@@ -1,13 +1,14 @@
-// The forward tile product of fp32 storage: v_mfma_f32_32x32x2_f32, fp32 in, fp32 accumulate.
+// The tile product of fp32 storage on v_mfma_f32_32x32x2_f32, fp32 in, fp32 accumulate: forward products, and backward
+// products of few rows.
 //
-// Why not the product of bf16 parts (gemm_split.hpp), which the backward products take and which is faster: what a layer
+// Why not the product of bf16 parts (gemm_split.hpp), which the other backward products take and which is faster: what a layer
 // puts out is compared with zero (ReLU, PReLU, in this layer or one that follows), and an input of such a comparison that
 // lies within a rounding of zero falls on the other side when its sum is taken in another order.  In a mini-batch of some
 // thousand rows ONE such unit is worth 1e-4 to 5e-4 of the weights' gradient, a thousand times what the rounding itself
 // is.  The order is therefore part of a forward result, whatever the size and the tile:
 //     c <- fma(a[k], b[k], c)    for k = 0, 4, 1, 5, 2, 6, 3, 7 of every eight k-values, from one accumulator.
-// (An instruction takes two k-values, the first half of the wavefront's before the second's.)  Nothing that follows a
-// gradient is decided by it, so the backward products are free to sum as they like.
+// (An instruction takes two k-values, the first half of the wavefront's before the second's.)  A gradient decides nothing in
+// its own step, but the next one from its weights: see few_rows.
 //
 // Tiling: BM x BN block tile, each wavefront owning a (BM/WM) x (BN/WN) patch of 32x32 MFMA tiles, k in slabs of BK through
 // two LDS buffers (one barrier per slab) while the next slab's global loads are in flight in registers.  Every operand keeps
@@ -20,10 +21,11 @@
 
 namespace tma {
 
-template <int BM, int BN, int BK, int WM, int WN, class AL, class BL, class Epi>
-__global__ __launch_bounds__(WM *WN * 64, (BK <= 16 && !Epi::kRowAux ? 3 : 2)) void gemm_f32_kernel(AL a, BL b, Epi epi,
-                                                                                                   int64_t M, int N, int64_t K,
-                                                                                                   int n_tiles, int64_t total_work)
+// C[M,N] = A[M,K] B[K,N], k split into ranges of k_per_split; work items and their order over the dies as in gemm_bf16_kernel.
+template <int BM, int BN, int BK, int WM, int WN, bool kColSum, class AL, class BL, class Epi>
+__global__ __launch_bounds__(WM *WN * 64, (BK <= 16 && !Epi::kRowAux && !kColSum ? 3 : 2)) void gemm_f32_kernel(
+    AL a, BL b, Epi epi, int64_t M, int N, int64_t K, int64_t k_per_split, int n_tiles, int64_t tiles_per_split, int64_t total_work,
+    float *__restrict__ colsum_partial)
 {
     constexpr int NT = WM * WN * 64;
     constexpr int TM = BM / WM / 32;
@@ -38,6 +40,7 @@ __global__ __launch_bounds__(WM *WN * 64, (BK <= 16 && !Epi::kRowAux ? 3 : 2)) v
     constexpr int A_WORDS = AL::kContigK ? BM * A_LD : BK * A_LD;
     constexpr int B_WORDS = BL::kContigK ? BN * B_LD : BK * B_LD;
     static_assert(BM % (WM * 32) == 0 && BN % (WN * 32) == 0 && BK % GK == 0, "tile shape");
+    static_assert(!kColSum || !BL::kContigK, "column sums are taken from a [k][n] tile");
     static_assert(A_WORDS >= BN && B_WORDS >= BM, "epilogue staging fits");
 
     __shared__ __attribute__((aligned(16))) float As[2][A_WORDS];
@@ -70,7 +73,6 @@ __global__ __launch_bounds__(WM *WN * 64, (BK <= 16 && !Epi::kRowAux ? 3 : 2)) v
         b_lds[i] = BL::kContigK ? b_mn[i] * B_LD + b_k[i] : b_k[i] * B_LD + b_mn[i];
     }
 
-    // work items and their order over the dies as in gemm_bf16_kernel
     const int64_t blocks_per_die = gridDim.x / kXcds;
     const int64_t per_die = (total_work + kXcds - 1) / kXcds;
     const int64_t die = blockIdx.x % kXcds;
@@ -82,15 +84,23 @@ __global__ __launch_bounds__(WM *WN * 64, (BK <= 16 && !Epi::kRowAux ? 3 : 2)) v
     // first slab of the tile that comes next; the slabs inside a tile's main loop have registers of their own
     typename AL::Raw afirst[A_V];
     typename BL::Raw bfirst[B_V];
-    int64_t m0 = 0;
-    int n0 = 0;
+    struct Tile {
+        int64_t m0;
+        int n0, split;
+        int64_t k_begin, k_end;
+    };
+    Tile t{};
     auto prepare = [&](int64_t work) {
-        m0 = (work / n_tiles) * BM;
-        n0 = int(work % n_tiles) * BN;
+        t.split = int(work / tiles_per_split);
+        const int64_t tile = work % tiles_per_split;
+        t.m0 = (tile / n_tiles) * BM;
+        t.n0 = int(tile % n_tiles) * BN;
+        t.k_begin = int64_t(t.split) * k_per_split;
+        t.k_end = t.k_begin + k_per_split < K ? t.k_begin + k_per_split : K;
 #pragma unroll
-        for (int i = 0; i < A_V; ++i) alane[i] = a.prepare(m0 + a_mn[i]);
+        for (int i = 0; i < A_V; ++i) alane[i] = a.prepare(t.m0 + a_mn[i]);
 #pragma unroll
-        for (int i = 0; i < B_V; ++i) blane[i] = b.prepare(n0 + b_mn[i]);
+        for (int i = 0; i < B_V; ++i) blane[i] = b.prepare(t.n0 + b_mn[i]);
     };
     auto fetch = [&](int64_t kt, typename AL::Raw(&ar)[A_V], typename BL::Raw(&br)[B_V]) {   // any slab
 #pragma unroll
@@ -130,7 +140,7 @@ __global__ __launch_bounds__(WM *WN * 64, (BK <= 16 && !Epi::kRowAux ? 3 : 2)) v
     int64_t work = die * per_die + blockIdx.x / kXcds;
     if (work >= die_end) return;
     prepare(work);
-    fetch(0, afirst, bfirst);
+    fetch(t.k_begin, afirst, bfirst);
     while (true) {
         floatx16 acc[TM][TN];
 #pragma unroll
@@ -139,6 +149,7 @@ __global__ __launch_bounds__(WM *WN * 64, (BK <= 16 && !Epi::kRowAux ? 3 : 2)) v
             for (int j = 0; j < TN; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
+        float colsum = 0.0f;
 
         __syncthreads();  // the previous tile's epilogue has finished reading LDS
         stage(0, afirst, bfirst);
@@ -171,13 +182,17 @@ __global__ __launch_bounds__(WM *WN * 64, (BK <= 16 && !Epi::kRowAux ? 3 : 2)) v
                             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[i][j], 0, 0, 0);
                         }
             }
+            if (kColSum && t.m0 == 0 && tid < BN) {
+#pragma unroll
+                for (int k = 0; k < BK; ++k) colsum += Bs[buf][k * B_LD + tid];
+            }
         };
         auto main_loop = [&](auto whole_tag) {
             typename AL::Raw areg[A_V];
             typename BL::Raw breg[B_V];
             int buf = 0;
-            for (int64_t kt = 0; kt < K; kt += BK) {
-                const bool more = kt + BK < K;
+            for (int64_t kt = t.k_begin; kt < t.k_end; kt += BK) {
+                const bool more = kt + BK < t.k_end;
                 if (more) {  // in flight while this slab is multiplied
                     if constexpr (decltype(whole_tag)::value) fetch_whole(kt + BK, areg, breg);
                     else fetch(kt + BK, areg, breg);
@@ -188,21 +203,21 @@ __global__ __launch_bounds__(WM *WN * 64, (BK <= 16 && !Epi::kRowAux ? 3 : 2)) v
                 buf ^= 1;
             }
         };
-        if (K % BK == 0) main_loop(std::true_type{});
+        if ((t.k_end - t.k_begin) % BK == 0) main_loop(std::true_type{});
         else main_loop(std::false_type{});
 
         // Per-column / per-row epilogue inputs (bias, 1/deg) go through LDS (see gemm_bf16_kernel).
-        if (Epi::kColAux && tid < BN) a_aux[tid] = epi.col_aux(n0 + tid < N ? n0 + tid : N - 1);
-        if (Epi::kRowAux && tid < BM) b_aux[tid] = epi.row_aux(m0 + tid < M ? m0 + tid : M - 1);
+        if (Epi::kColAux && tid < BN) a_aux[tid] = epi.col_aux(t.n0 + tid < N ? t.n0 + tid : N - 1);
+        if (Epi::kRowAux && tid < BM) b_aux[tid] = epi.row_aux(t.m0 + tid < M ? t.m0 + tid : M - 1);
         if (Epi::kColAux || Epi::kRowAux) __syncthreads();
 
-        const int64_t done_m0 = m0;
-        const int done_n0 = n0;
+        const Tile done = t;
+        const float done_colsum = colsum;
         const int64_t next = work + blocks_per_die;
         const bool has_next = next < die_end;
         if (has_next) {   // its latency passes behind the write-out below
             prepare(next);
-            fetch(0, afirst, bfirst);
+            fetch(t.k_begin, afirst, bfirst);
         }
 
         // MFMA 32x32 result layout: register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4, column l%32.
@@ -219,18 +234,20 @@ __global__ __launch_bounds__(WM *WN * 64, (BK <= 16 && !Epi::kRowAux ? 3 : 2)) v
                     raux[r] = Epi::kRowAux ? b_aux[wm0 + i * 32 + 8 * (r / 4) + 4 * hi + (r % 4)] : 0.0f;
 #pragma unroll
                 for (int j = 0; j < TN; ++j) {
-                    const int col = done_n0 + wn0 + j * 32 + l31;
+                    const int col = done.n0 + wn0 + j * 32 + l31;
 #pragma unroll
                     for (int r = 0; r < 16; ++r) {
-                        const int64_t row = done_m0 + wm0 + i * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
+                        const int64_t row = done.m0 + wm0 + i * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
                         const float val = epi.value(acc[i][j][r], caux[j], raux[r], col);
-                        if (kInside || (row < M && col < N)) epi.store(row, col, val, 0);
+                        if (kInside || (row < M && col < N)) epi.store(row, col, val, done.split);
                     }
                 }
             }
         };
-        if (done_m0 + BM <= M && done_n0 + BN <= N) write_out(std::true_type{});
+        if (done.m0 + BM <= M && done.n0 + BN <= N) write_out(std::true_type{});
         else write_out(std::false_type{});
+        if (kColSum && done.m0 == 0 && tid < BN && done.n0 + tid < N)
+            colsum_partial[int64_t(done.split) * N + done.n0 + tid] = done_colsum;
         if (!has_next) break;
         work = next;
     }

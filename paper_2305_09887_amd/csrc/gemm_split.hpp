@@ -1,5 +1,5 @@
 // The backward tile product of fp32 storage: fp32 operands, fp32-accurate results, on the bf16 matrix instruction.
-// (Forward products keep the fp32 instruction and its order of sums: see gemm_f32.hpp.)
+// (Forward products, and backward ones of few rows, keep the fp32 instruction and its order of sums: see gemm_f32.hpp.)
 //
 // The fp32 matrix instruction multiplies at a sixteenth of the bf16 one's rate and bounded every wide fp32 product.
 // Here each operand value is taken apart on its way into LDS into three bf16 values whose sum it is (x = h + m + l,

@@ -5,6 +5,14 @@
 
 namespace tma {
 
+// fp32 parts of few rows (nodes), whose backward sums keep their order too.  Weights that differ in their last bits decide units
+// within a rounding of zero otherwise in the next step, and Adam, which divides a small gradient by itself, makes such a
+// difference from 1e-7 of a gradient.  One unit is worth some 0.1 to 0.25 of sqrt(2 / (rows x width)) of the gradient
+// (1.7e-4 to 4.8e-4 in batches of 1,000 to 3,000 rows, 2.9e-4 at 27,000 rows of 256): from here on it is lost in the 1e-5 to
+// 5e-5 that such units come to on either side.
+constexpr int64_t kFewRows = int64_t(1) << 16;
+inline bool few_rows(int64_t rows) { return rows < kFewRows; }
+
 // Which of two forms of a step runs, decided on the device by the graph's entries (rowptr[n]), which the host does not know:
 // both are launched, with opposite sides, and the one that is not meant returns at once.  (The timing hook calls such
 // launches gated_*: their time says nothing about the bytes of the one form or the other.)

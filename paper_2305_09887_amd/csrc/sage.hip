@@ -171,14 +171,14 @@ extern "C" int tma_sage_layer_bwd(int64_t n, const int32_t *rowptr_T, const int3
         // 47 wide, mean degree 2.5 / 10 / 20 / 40:
         //   fp32 125,000 rows 39 -> 28 / 62 -> 52 / 90 -> 86 / 156 -> 158, 400,000 rows 102 -> 69 / 174 -> 165 / 287 -> 307 / 518 -> 603
         //   bf16 2,000,000 rows, degree 2 / 8 / 20: 387 -> 278 / 627 -> 669 / 1,152 -> 1,535
-        // So fp32 takes the weights where the table of them stays in the L2 (rows below 32 elements: 24 wide 44 -> 39 / 81 -> 86 /
-        // 124 -> 139 at 250,000 rows, but 24 -> 18 / 35 -> 30 / 50 -> 44 / 73 -> 72 at 20,000), and larger parts of either type take
-        // them up to a mean degree of an eighth of the width, which the device sees (128 wide: 1,771 -> 1,913 at 2,000,000
-        // rows of 20, 1,093 -> 794 of 8).  bf16 below 2^20 rows has less to save (150,000 rows of 23: 113 -> 114).
+        // So fp32 takes the weights where the table of them stays in the L2 and rows are not narrow (24 wide 44 -> 39 / 81 -> 86 /
+        // 124 -> 139 at 250,000 rows), and larger parts of either type take them up to a mean degree of an eighth of the
+        // width, which the device sees (128 wide: 1,771 -> 1,913 at 2,000,000 rows of 20, 1,093 -> 794 of 8).  bf16 below
+        // 2^20 rows has less to save (150,000 rows of 23: 113 -> 114); fp32 parts of few rows keep their sums.
         const int64_t per16 = 16 / int64_t(elem_size(dtype));
         const bool room = act == TMA_ACT_NONE && ld_next >= Fp && ld_next % per16 == 0 && aligned(dHnext, 16);
-        const bool weigh = room && dtype == TMA_F32 && n <= (int64_t(1) << (Fp >= 32 ? 18 : 15));
-        const bool weigh_sparse = room && !weigh && Fp >= 32 && (dtype == TMA_F32 || n >= (int64_t(1) << 20));
+        const bool weigh = room && dtype == TMA_F32 && Fp >= 32 && !few_rows(n) && n <= (int64_t(1) << 18);
+        const bool weigh_sparse = room && Fp >= 32 && n > (int64_t(1) << (dtype == TMA_F32 ? 18 : 20));
         const int64_t sparse = n * Fp / 8;
         if (weigh || weigh_sparse) {
             const EntryGate gate{sparse, weigh ? EntryGate::kAlways : EntryGate::kUpTo};

@@ -6,6 +6,8 @@ falls on the other side when its sum is taken in another order, and in a batch o
   products     c <- fma(a[k], b[k], c), k = 0, 4, 1, 5, 2, 6, 3, 7 of every eight k-values, one accumulator;
   aggregation  neighbours in the order of the list; a weighted one is rounded before it is added where rows are whole
                16-byte pieces, and inside the addition where they are not.
+Backward products of fewer than 65,536 rows keep the order too: Adam turns the last bits of a small gradient into weights that
+decide otherwise in the next step.
 An fma is taken here as the sum in 64 bits rounded to 32 (exact but for a second rounding, once in 2^29).
 """
 import numpy as np
@@ -126,3 +128,18 @@ def test_gcn_weights(B, f):
         total = sum_in_order(rowptr, colidx, X, lambda t, x, u: fma(s[u, None], x, t))
     want = fma(s[:, None], X, total) * s[:, None]
     assert np.array_equal(M.cpu().numpy().reshape(-1)[:n * f].reshape(n, f), want)
+
+
+@pytest.mark.parametrize("n,fi,fo", [(1, 5, 3), (127, 64, 40), (300, 33, 41), (500, 130, 70), (4097, 24, 17), (40000, 200, 20), (65535, 16, 12)])
+def test_input_gradient_of_few_rows(B, n, fi, fo):
+    W, g = normal(2, fi, fo), normal(5, n, fo)
+    dX = B.tma_dense_bwd(torch.zeros((n, fi), device="cuda"), None, dev(g), dev(W), B.TMA_ACT_NONE, need_dbias=False)[2]
+    assert np.array_equal(dX.cpu().numpy(), product_in_order(g, np.ascontiguousarray(W.T)))
+
+
+# up to 128 rows are one range of the sum over the rows; longer ones are tested by their error in test_gpu_products.py
+@pytest.mark.parametrize("n,fi,fo", [(1, 5, 3), (96, 64, 40), (128, 33, 41), (100, 260, 130), (128, 128, 300)])
+def test_weight_gradient_of_few_rows(B, n, fi, fo):
+    X, g = normal(1, n, fi), normal(5, n, fo)
+    dW = B.tma_dense_bwd(dev(X), None, dev(g), torch.zeros((fi, fo), device="cuda"), B.TMA_ACT_NONE, need_dX=False)[0]
+    assert np.array_equal(dW.cpu().numpy(), product_in_order(np.ascontiguousarray(X.T), g))

@@ -39,9 +39,11 @@ def data(n, fi, fo, seed):
 
 SHAPES = [(1, 1, 2), (1, 3, 1), (2, 1, 4), (3, 5, 6), (1, 7, 3), (40, 2, 66), (1, 4, 5), (15, 16, 47), (129, 20, 64), (128, 33, 96), (257, 47, 100), (1000, 64, 130), (4100, 130, 48),
           (20000, 128, 128), (70001, 100, 256), (50000, 90, 41)]
+# backward products of 65,536 rows and more are the ones from bf16 parts: every tile, its edges and its rest of k
+MANY_ROWS = [(65536, 64, 64), (65537, 20, 66), (65600, 96, 100), (66000, 33, 96), (65599, 128, 41), (70000, 130, 130), (65550, 250, 24), (65543, 5, 300)]
 
 
-@pytest.mark.parametrize("n,fi,fo", SHAPES)
+@pytest.mark.parametrize("n,fi,fo", SHAPES + MANY_ROWS)
 def test_dense_products(B, n, fi, fo):
     X, W, b, g = data(n, fi, fo, n + fi)
     x, w, bias, d = (torch.as_tensor(t).cuda() for t in (X, W, b, g))
@@ -56,7 +58,7 @@ def test_dense_products(B, n, fi, fo):
 
 
 @pytest.mark.parametrize("pitch,offset", [(0, 0), (1, 0), (3, 1), (2, 2)])
-@pytest.mark.parametrize("n,fi,fo", [(130, 90, 150), (1000, 33, 41), (257, 64, 7), (77, 5, 300)])
+@pytest.mark.parametrize("n,fi,fo", [(130, 90, 150), (1000, 33, 41), (257, 64, 7), (77, 5, 300), (65601, 90, 150), (65537, 33, 41)])
 def test_rows_at_any_address(B, n, fi, fo, pitch, offset):
     """The same products with rows that are neither aligned nor a multiple of four apart, in arrays that end with them."""
     X, W, _, g = data(n, fi, fo, n + pitch)
@@ -112,8 +114,8 @@ def ring(n):
     return graph, lambda X: 0.5 * (np.roll(X, 1, 0) + np.roll(X, -1, 0))
 
 
-# widths that are 3 mod 4 in padded rows, at the row counts of the 64 x 64 and of the 128 x 64 tile; NaN behind the last row
-@pytest.mark.parametrize("n,fi,fo", [(300, 63, 20), (40000, 63, 20), (40000, 51, 7)])
+# widths that are 3 mod 4 in padded rows, at the row counts of the 64 x 64 and of the 128 x 64 tiles; NaN behind the last row
+@pytest.mark.parametrize("n,fi,fo", [(300, 63, 20), (40000, 63, 20), (40000, 51, 7), (70000, 63, 20)])
 def test_transform_first_weight_gradient_at_the_end_of_the_rows(B, n, fi, fo):
     graph, mean = ring(n)
     X, Ws, _, g = data(n, fi, fo, n)
@@ -134,7 +136,7 @@ def test_transform_first_weight_gradient_at_the_end_of_the_rows(B, n, fi, fo):
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("n,fi,fo", [(700, 150, 41), (301, 99, 24), (60, 30, 7), (129, 65, 16)])
+@pytest.mark.parametrize("n,fi,fo", [(700, 150, 41), (301, 99, 24), (60, 30, 7), (129, 65, 16), (65700, 150, 41), (65537, 99, 24)])
 def test_row_padding_leaves_no_trace(B, n, fi, fo, dtype):
     """The transform-first layer on rows padded to a multiple of 16 bytes: whatever the padding holds, the same bits."""
     graph, _ = ring(n)
@@ -160,7 +162,7 @@ def test_row_padding_leaves_no_trace(B, n, fi, fo, dtype):
         assert torch.isfinite(clean.float()).all() and torch.equal(clean, dirty)
 
 
-@pytest.mark.parametrize("n,fi,fo", [(300, 64, 47), (1000, 33, 130)])
+@pytest.mark.parametrize("n,fi,fo", [(300, 64, 47), (1000, 33, 130), (65600, 64, 47), (65600, 33, 130)])
 def test_special_values(B, n, fi, fo):
     X, W, _, g = data(n, fi, fo, 9)
     X[3, 5], X[140, 0], X[141, fi - 1], X[142, 7] = np.inf, -np.inf, np.nan, 3.3e38
@@ -200,8 +202,9 @@ def test_overflow_and_small_values(B):
 # Both ends of the fp32 range: operands down to the smallest normal numbers and below, products up to its end
 @pytest.mark.parametrize("xe,we,ge", [(0, 0, -126), (20, 12, -140), (-70, -60, -50), (-120, 10, 100), (-126, 0, 0), (60, -126, -20), (100, -140, 0),
                                       (110, 100, -115), (-133, 0, 110)])
-def test_backward_products_over_the_whole_range(B, xe, we, ge):
-    X, W, _, g = data(300, 40, 72, 4)
+@pytest.mark.parametrize("n", [300, 65600])
+def test_backward_products_over_the_whole_range(B, n, xe, we, ge):
+    X, W, _, g = data(n, 40, 72, 4)
     X, W, g = (np.ldexp(t, e).astype(np.float32) for t, e in ((X, xe), (W * 8, we), (g * 2 ** 20, ge)))
     X[::7], W[::5], g[:, ::3] = np.ldexp(X[::7], -3), np.ldexp(W[::5], 3), np.ldexp(g[:, ::3], -2)
     x, w, d = (torch.as_tensor(t).cuda() for t in (X, W, g))

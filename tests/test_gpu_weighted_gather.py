@@ -41,9 +41,9 @@ def nan_padded(B, t, dtype):
     return p.copy_(torch.as_tensor(t))
 
 
-# fp32: weights below 2^18 rows (2^15 where rows are narrow); above, and in bf16 from 2^20 on, by entries up to n Fp / 8 or not
+# fp32: weights from 2^16 to 2^18 rows of 32 elements and more; above, and in bf16 above 2^20, by entries up to n Fp / 8 or not
 @pytest.mark.parametrize("n,degree,hubs,fi,fo,dtype", [
-    (1500, 4, 3, 96, 47, "f32"), (1500, 4, 3, 88, 41, "f32"), (900, 0.5, 0, 64, 30, "f32"), (33000, 3, 1, 16, 7, "f32"), (70, 2, 1, 600, 300, "f32"),
+    (66000, 3, 2, 96, 47, "f32"), (66000, 0.5, 0, 64, 30, "f32"), (65536, 4, 1, 88, 41, "f32"), (66000, 3, 1, 48, 20, "f32"), (1500, 4, 3, 96, 47, "f32"), (1500, 4, 3, 88, 41, "f32"), (900, 0.5, 0, 64, 30, "f32"), (33000, 3, 1, 16, 7, "f32"), (70, 2, 1, 600, 300, "f32"),
     (265000, 2, 1, 72, 33, "f32"), (265000, 6, 1, 72, 33, "f32"),
     (1500, 4, 3, 96, 47, "bf16"), (1050000, 1.5, 1, 96, 41, "bf16"), (1050000, 8, 0, 96, 41, "bf16")])
 def test_backward_without_activation(B, n, degree, hubs, fi, fo, dtype):
