@@ -171,7 +171,7 @@ int tma_induced_subgraph_fill(int64_t n_nodes, const int32_t *colidx,
  * first equation of its proof), over the local neighbourhood:
  *     M_v = inv_deg[v] * sum_{u in N'(v)} H_u        (0 for an isolated node)
  * H, M_out: [n, F] of `dtype`, leading dimensions ldh / ldm.  fp32 accumulation
- * in neighbour order.  Also exported on its own because it is the HBM-bound
+ * in neighbour order (far longer rows than the mean: in shares, in a fixed order).  Also exported on its own because it is the HBM-bound
  * kernel of the path.  With 16-byte aligned pointers and pitches a row is
  * handled in 16-byte pieces; if F is no multiple of such a piece and both
  * pitches leave room for the last whole piece, the padding elements of M_out
@@ -197,10 +197,13 @@ int tma_mean_aggregate(int64_t n, const int32_t *rowptr, const int32_t *colidx,
  *   Hnext_out [n, F_out] dtype, leading dimension ld_next >= F_out; padding
  *           columns are either left alone or set to zero.  With TMA_ACT_RELU the sign pattern of
  *           H' equals that of Z, so H' is all that backward needs.
- * The 16-byte vector paths need 16-byte aligned pointers and leading
- * dimensions that are multiples of 16 bytes (pad rows for widths such as
- * 47, or 100 in bf16); anything else takes a slower element-wise path with
- * the same result.  A row width that is no multiple of 16 bytes still takes
+ * Fastest with 16-byte aligned pointers and leading dimensions that are
+ * multiples of 16 bytes (pad rows for widths such as 47, or 100 in bf16).  fp32
+ * rows of any width at any 4-byte-aligned address are read in 16-byte groups too;
+ * element by element, with the same result, go: [H | M] in the aggregate-first
+ * form where F_in is no multiple of four, gradients with an odd width in rows
+ * that are no multiples of four apart, and bf16 rows that are no multiples of
+ * four or not aligned.  A row width that is no multiple of 16 bytes takes
  * the vector path of the aggregation when ldh and ldm leave room for the last
  * whole 16-byte piece (100 bf16 elements with ld >= 104): the padding elements
  * of M_out up to that piece are then overwritten (with sums of H's padding).
