@@ -56,18 +56,24 @@ __device__ __forceinline__ void static_for(F &&f)
 
 struct PaddedRows;
 struct CatWeightsRest;
+struct RawU;
+template <class View>
+struct UnalignedGroups : std::is_same<typename View::Raw, RawU> {};
 // Which bf16 products run the unrolled loop of gemm_bf16_kernel, three copies of whose body have to share the registers.
-// Not views that load element by element, which spill up to 900 registers there (us at 125,237 / 1,000,000 rows, the rolled
+// Not views that load element by element (but for the weights of the 256-wide tile: its input gradient 256 -> 256 at
+// 604,000 rows 914 against 779 us), which spill up to 900 registers there (us at 125,237 / 1,000,000 rows, the rolled
 // loop against the unrolled one: weight gradient of 2 x 150 -> 150 with ReLU 357 / 3,090 against 964 / 8,960, of
 // 2 x 90 -> 150 142 / 1,220 against 430 / 3,380); not PaddedRows (42 / 307 against 62 / 472, 130 -> 50); not gradients along k but for the
 // 256-wide tile (input gradient of 128 -> 128 41 / 275 against 48 / 342, of 2 x 100 -> 128 with ReLU 57 / 410 against
 // 72 / 524; the 256-wide one of 2 x 128 -> 256 with ReLU 73 / 515 against 68 / 484); not the forward product of two
 // weight matrices with a rest of k (2 x 100 -> 128 36 / 271 against 45 / 315; without a rest, 2 x 64 -> 120, 34 / 226
-// against 30 / 191).
+// against 30 / 191); and not weights in unaligned groups in the 128 x 128 tile (forward 128 -> 150 46 / 191 against 64 / 281 at
+// 125,237 / 600,000 rows).
 template <int kBN, class AL, class BL>
 struct SteadyLoop {
-    static constexpr bool value = AL::kGroups && BL::kGroups && !std::is_same<AL, PaddedRows>::value &&
-                                  !std::is_same<BL, CatWeightsRest>::value && !(AL::kMasks && AL::kContigK && kBN != 256);
+    static constexpr bool value = AL::kGroups && (BL::kGroups || kBN == 256) && !std::is_same<AL, PaddedRows>::value &&
+                                  !std::is_same<BL, CatWeightsRest>::value && !(kBN == 128 && UnalignedGroups<BL>::value) &&
+                                  !(AL::kMasks && AL::kContigK && kBN != 256);
 };
 
 // An optional member of an operand view: kPacksBf16 + packed(raw) say that the view's Raw already holds four bf16
@@ -1338,8 +1344,9 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_kernel(AL a, BL b, E
         };
         if constexpr (!kSteady) {
             // guarded loads: (two sources) they need no more registers than the others and fewer in all, 41 us against 50;
-            // (element by element) they are the only ones; (rows of no multiple of four) no range of theirs is whole slabs
-            if constexpr (TwoSourcesAlongK<AL>::value || !AL::kGroups || !BL::kGroups || std::is_same<AL, PaddedRows>::value)
+            // (element by element, unaligned groups) they are the only ones; (rows of no multiple of four) no range of theirs is whole slabs
+            if constexpr (TwoSourcesAlongK<AL>::value || !AL::kGroups || !BL::kGroups || UnalignedGroups<BL>::value ||
+                          std::is_same<AL, PaddedRows>::value)
                 one_loop(std::false_type{});
             else if ((t.k_end - t.k_begin) % BK != 0) one_loop(std::false_type{});
             else if constexpr (kLean || kDepth == 1) one_loop(std::true_type{});
