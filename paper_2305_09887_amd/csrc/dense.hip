@@ -19,8 +19,12 @@ struct DenseEpilogue {  // out = act(acc + b)  or  row_scale[row] * acc
     const float *bias;       // may be NULL
     const float *row_scale;  // read only with kRowScale
     bool relu;
+    int Fo;                  // columns from here on are stored as zeros
     __device__ __forceinline__ float col_aux(int col) const { return bias ? bias[col] : 0.0f; }
     __device__ __forceinline__ float row_aux(int64_t row) const { return kRowScale ? row_scale[row] : 0.0f; }
+    __device__ __forceinline__ const float *col_at(int col) const { return bias ? bias + col : kZeros; }
+    __device__ __forceinline__ const float *row_at(int64_t row) const { return row_scale + row; }
+    __device__ __forceinline__ bool padding(int col) const { return col >= Fo; }
     __device__ __forceinline__ float value(float v, float caux, float raux, int) const
     {
         v += caux;
@@ -37,36 +41,32 @@ struct DenseEpilogue {  // out = act(acc + b)  or  row_scale[row] * acc
 static int pad8(int32_t F) { return int(round_up(size_t(F), 8)); }
 
 // ---- forward ----------------------------------------------------------------
-// N_out >= F_out columns are written; those past F_out receive zeros (the weight view is zero there)
-template <typename T, bool kRowScale>
-static int dense_fwd_typed(int64_t n, const T *X, int64_t ldx, int32_t F_in, const float *W, const float *bias,
-                           const float *row_scale, int32_t F_out, int32_t N_out, bool relu, T *Y, int64_t ldy,
-                           hipStream_t s)
+// N_out >= F_out columns are written; those past F_out receive zeros
+template <bool kRowScale>
+static int dense_fwd_f32(int64_t n, const float *X, int64_t ldx, int32_t F_in, const float *W, const float *bias,
+                         const float *row_scale, int32_t F_out, int32_t N_out, bool relu, float *Y, int64_t ldy, hipStream_t s)
 {
-    DenseEpilogue<T, kRowScale> e{Y, ldy, bias, row_scale, relu};
+    launch_fwd_f32("gemm_dense_fwd", AsyncRows(X, ldx, X, ldx, F_in, F_in, n), AsyncWeights<false>{W, W, F_in, F_out, F_in, 0},
+                   DenseEpilogue<float, kRowScale>{Y, ldy, bias, row_scale, relu, F_out}, n, N_out, s);
+    return check_launch("dense gemm fwd");
+}
+
+template <bool kRowScale>
+static int dense_fwd_bf16(int64_t n, const uint16_t *X, int64_t ldx, int32_t F_in, const float *W, const float *bias,
+                          const float *row_scale, int32_t F_out, int32_t N_out, bool relu, uint16_t *Y, int64_t ldy,
+                          hipStream_t s)
+{
+    DenseEpilogue<uint16_t, kRowScale> e{Y, ldy, bias, row_scale, relu, F_out};
     const int64_t K = F_in, kps = int64_t(round_up(size_t(K), 32));
     // a group of four along k must not reach into row padding, nor a group of four columns past F_out
     const bool va = groups_ok(X, ldx, F_in);
     const bool vb = F_out % 4 == 0 && aligned(W, 16);
-    const char *name = kname<T>("gemm_dense_fwd", "gemm_dense_fwd_generic", "gemm_dense_fwd_bf16",
-                                "gemm_dense_fwd_bf16_generic", va);
-#define TMA_DENSE_FWD(VA_, VB_)                                                               \
-    do {                                                                                      \
-        CatRows<T, VA_> a{X, ldx, X, ldx, F_in, n, F_in};                                          \
-        SideWeights<VB_> b{W, W, F_in, F_out, pad8(F_out)};                                   \
-        if constexpr (sizeof(T) == 4) launch_fwd_f32<32>(name, a, b, e, n, N_out, K, s);      \
-        else launch_by_width<T, 32, false, VA_>(name, a, b, e, n, N_out, K, kps, 1, nullptr, s); \
-    } while (0)
+    const char *name = va ? "gemm_dense_fwd_bf16" : "gemm_dense_fwd_bf16_generic";
+#define TMA_DENSE_FWD(VA_, VB_)                                                                   do {                                                                                              CatRows<uint16_t, VA_> a{X, ldx, X, ldx, F_in, n, F_in};                                           SideWeights<VB_> b{W, W, F_in, F_out, pad8(F_out)};                                           launch_by_width<uint16_t, 32, false, VA_>(name, a, b, e, n, N_out, K, kps, 1, nullptr, s);     } while (0)
     // (va: F_in is a multiple of four, so W holds at least four elements and may be read in unaligned groups)
     if (va && vb) TMA_DENSE_FWD(true, kAligned4);
     else if (va) TMA_DENSE_FWD(true, kUnaligned4);
-    else if constexpr (sizeof(T) == 4) {
-        if (rows_u_ok(n, ldx, F_in) && weights_u_ok(F_in, F_out)) {
-            CatRowsU a{X, ldx, F_in, n};
-            SideWeights<kUnaligned4> b{W, W, F_in, F_out, pad8(F_out)};
-            launch_fwd_f32<32>(name, a, b, e, n, N_out, K, s);
-        } else TMA_DENSE_FWD(false, kElementwise);
-    } else TMA_DENSE_FWD(false, kElementwise);
+    else TMA_DENSE_FWD(false, kElementwise);
 #undef TMA_DENSE_FWD
     return check_launch("dense gemm fwd");
 }
@@ -82,14 +82,14 @@ int launch_dense_gemm_fwd(int64_t n, const void *X, int64_t ldx, int32_t F_in, c
     if (dtype == TMA_F32) {
         const float *x = static_cast<const float *>(X);
         float *y = static_cast<float *>(Y);
-        return row_scale ? dense_fwd_typed<float, true>(n, x, ldx, F_in, W, bias, row_scale, F_out, N_out, relu, y, ldy, s)
-                         : dense_fwd_typed<float, false>(n, x, ldx, F_in, W, bias, row_scale, F_out, N_out, relu, y, ldy, s);
+        return row_scale ? dense_fwd_f32<true>(n, x, ldx, F_in, W, bias, row_scale, F_out, N_out, relu, y, ldy, s)
+                         : dense_fwd_f32<false>(n, x, ldx, F_in, W, bias, row_scale, F_out, N_out, relu, y, ldy, s);
     }
     if (dtype == TMA_BF16) {
         const uint16_t *x = static_cast<const uint16_t *>(X);
         uint16_t *y = static_cast<uint16_t *>(Y);
-        return row_scale ? dense_fwd_typed<uint16_t, true>(n, x, ldx, F_in, W, bias, row_scale, F_out, N_out, relu, y, ldy, s)
-                         : dense_fwd_typed<uint16_t, false>(n, x, ldx, F_in, W, bias, row_scale, F_out, N_out, relu, y, ldy, s);
+        return row_scale ? dense_fwd_bf16<true>(n, x, ldx, F_in, W, bias, row_scale, F_out, N_out, relu, y, ldy, s)
+                         : dense_fwd_bf16<false>(n, x, ldx, F_in, W, bias, row_scale, F_out, N_out, relu, y, ldy, s);
     }
     return fail(TMA_ERR_UNSUPPORTED_DTYPE, "dense gemm fwd: dtype %d", dtype);
 }
@@ -99,7 +99,7 @@ template <typename T, bool kRowScale, bool kRelu>
 static int dense_bwd_data_typed(int64_t n, const T *g, const T *h, int64_t ld, const float *W, int32_t F_in,
                                 int32_t F_out, const float *row_scale, T *dX, int64_t ldx, hipStream_t s)
 {
-    DenseEpilogue<T, kRowScale> e{dX, ldx, nullptr, row_scale, false};
+    DenseEpilogue<T, kRowScale> e{dX, ldx, nullptr, row_scale, false, F_in};
     const int64_t K = F_out, kps = int64_t(round_up(size_t(K), 32));
     const bool va = padded_groups_ok(g, ld, F_out) && (!kRelu || padded_groups_ok(h, ld, F_out));
     const bool vb = groups_ok(W, F_out, F_out);

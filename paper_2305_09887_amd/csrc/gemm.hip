@@ -13,57 +13,36 @@
 
 namespace tma {
 
-// ---- forward ----------------------------------------------------------------
-template <typename T, bool VA, class AL, class BL>
-static void fwd_launch(const AL &a, const BL &b, const FwdEpilogue<T> &e, int64_t n, int F_out, int64_t K, int64_t kps,
+// ---- forward (fp32: launch_fwd_f32; these: bf16 storage) ----------------------
+template <bool VA, class AL, class BL>
+static void fwd_launch(const AL &a, const BL &b, const FwdEpilogue<uint16_t> &e, int64_t n, int F_out, int64_t K, int64_t kps,
                        hipStream_t s)
 {
-    if constexpr (sizeof(T) == 4)
-        launch_fwd_f32<16>(F_out <= 64 || few_tiles(n, F_out) ? (VA ? "gemm_fwd_128x64" : "gemm_fwd_128x64_generic")
-                                                              : (VA ? "gemm_fwd_128x128" : "gemm_fwd_128x128_generic"),
-                           a, b, e, n, F_out, K, s);   // (the name of its size class)
-    else if (F_out <= 64 || few_tiles(n, F_out))
-        launch_gemm<128, 64, 32, 4, 1, false, T>(VA ? "gemm_fwd_128x64_bf16" : "gemm_fwd_128x64_bf16_generic", a, b, e, n, F_out, K,
+    if (F_out <= 64 || few_tiles(n, F_out))
+        launch_gemm<128, 64, 32, 4, 1, false, uint16_t>(VA ? "gemm_fwd_128x64_bf16" : "gemm_fwd_128x64_bf16_generic", a, b, e, n, F_out, K,
                                                  kps, 1, nullptr, s);
     else if constexpr (VA) {
-        // bf16 storage: the product is bound by streaming [H | M]; a tile as wide as the output reads it once
+        // the product is bound by streaming [H | M]; a tile as wide as the output reads it once
         if (F_out > 128 && F_out <= 256)
-            launch_gemm<128, 256, 32, 2, 4, false, T>("gemm_fwd_128x256_bf16", a, b, e, n, F_out, K, kps, 1, nullptr, s);
+            launch_gemm<128, 256, 32, 2, 4, false, uint16_t>("gemm_fwd_128x256_bf16", a, b, e, n, F_out, K, kps, 1, nullptr, s);
         else if (std::is_same<BL, CatWeights<true>>::value && K % 32 != 0) {
             if constexpr (std::is_same<BL, CatWeights<true>>::value)
-                launch_gemm<128, 128, 32, 2, 2, false, T>("gemm_fwd_128x128_bf16", a, CatWeightsRest{b}, e, n, F_out, K, kps, 1, nullptr, s);
+                launch_gemm<128, 128, 32, 2, 2, false, uint16_t>("gemm_fwd_128x128_bf16", a, CatWeightsRest{b}, e, n, F_out, K, kps, 1, nullptr, s);
         } else
-            launch_gemm<128, 128, 32, 2, 2, false, T>("gemm_fwd_128x128_bf16", a, b, e, n, F_out, K, kps, 1, nullptr, s);
+            launch_gemm<128, 128, 32, 2, 2, false, uint16_t>("gemm_fwd_128x128_bf16", a, b, e, n, F_out, K, kps, 1, nullptr, s);
     } else
-        launch_gemm<128, 128, 32, 2, 2, false, T>("gemm_fwd_128x128_bf16_generic", a, b, e, n, F_out, K, kps, 1, nullptr, s);
+        launch_gemm<128, 128, 32, 2, 2, false, uint16_t>("gemm_fwd_128x128_bf16_generic", a, b, e, n, F_out, K, kps, 1, nullptr, s);
 }
 
-template <typename T, bool VA, bool VB>
-static void fwd_dispatch(int64_t n, const T *H, int64_t ldh, const T *M, int64_t ldm, int F_in, const float *W_self,
-                         const float *W_neigh, const FwdEpilogue<T> &e, int F_out, hipStream_t s)
+template <bool VA, bool VB>
+static void fwd_dispatch(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *M, int64_t ldm, int F_in, const float *W_self,
+                         const float *W_neigh, const FwdEpilogue<uint16_t> &e, int F_out, hipStream_t s)
 {
-    CatRows<T, VA> a{H, ldh, M, ldm, F_in, n, 2 * F_in};
+    CatRows<uint16_t, VA> a{H, ldh, M, ldm, F_in, n, 2 * F_in};
     const int64_t K = 2 * int64_t(F_in);
     const int64_t kps = int64_t(round_up(size_t(K), 32));
     CatWeights<VB> b{W_self, W_neigh, F_in, F_out};
-    fwd_launch<T, VA>(a, b, e, n, F_out, K, kps, s);
-}
-
-// fp32: groups of four at any 4-byte-aligned address.  Rows of [H | M] whose halves are no multiples of four are read
-// element by element: a group that straddles the halves could not be fetched whole, and halves padded to groups would
-// sum in another order (gemm_f32.hpp).
-static void fwd_dispatch_f32(int64_t n, const float *H, int64_t ldh, const float *M, int64_t ldm, int F_in,
-                             const float *W_self, const float *W_neigh, const FwdEpilogue<float> &e, int F_out, hipStream_t s)
-{
-    const int64_t K = 2 * int64_t(F_in);
-    const auto with_rows = [&](const auto &a, auto grouped_tag) {
-        constexpr bool VA = decltype(grouped_tag)::value;
-        if (F_out % 4 == 0) fwd_launch<float, VA>(a, CatWeights<true>{W_self, W_neigh, F_in, F_out}, e, n, F_out, K, K, s);
-        else if (weights_u_ok(F_in, F_out)) fwd_launch<float, VA>(a, CatWeightsU{W_self, W_neigh, F_in, F_out}, e, n, F_out, K, K, s);
-        else fwd_launch<float, VA>(a, CatWeights<false>{W_self, W_neigh, F_in, F_out}, e, n, F_out, K, K, s);
-    };
-    if (F_in % 4 == 0) with_rows(CatRows<float, true>{H, ldh, M, ldm, F_in, n, 2 * F_in}, std::true_type{});
-    else with_rows(CatRows<float, false>{H, ldh, M, ldm, F_in, n, 2 * F_in}, std::false_type{});
+    fwd_launch<VA>(a, b, e, n, F_out, K, kps, s);
 }
 
 // bf16 storage with the weights prepared as Wt[o][k] (bf16): both operands are rows of packed bf16, contiguous
@@ -74,7 +53,7 @@ static void fwd_prepared(int64_t n, const uint16_t *H, int64_t ldh, const uint16
     CatRows<uint16_t, true> a{H, ldh, M, ldm, F_in, n, 2 * F_in};
     CatRows<uint16_t, true> b{Wt, 2 * int64_t(F_in), Wt, 2 * int64_t(F_in), 2 * F_in, F_out, 2 * F_in};
     const int64_t K = 2 * int64_t(F_in);
-    fwd_launch<uint16_t, true>(a, b, e, n, F_out, K, int64_t(round_up(size_t(K), 32)), s);
+    fwd_launch<true>(a, b, e, n, F_out, K, int64_t(round_up(size_t(K), 32)), s);
 }
 
 __global__ __launch_bounds__(256) void narrow_transpose_weights_kernel(const float *__restrict__ Ws,
@@ -103,22 +82,27 @@ int launch_sage_prepare_weights_bf16(const float *W_self, const float *W_neigh, 
     return check_launch("prepare weights");
 }
 
-template <typename T>
-static int fwd_typed(int64_t n, const T *H, int64_t ldh, const T *M, int64_t ldm, int32_t F_in, const float *W_self,
-                     const float *W_neigh, const float *bias, int32_t F_out, int32_t act, T *Hnext, int64_t ld_next,
-                     hipStream_t stream)
+static int fwd_f32(int64_t n, const float *H, int64_t ldh, const float *M, int64_t ldm, int32_t F_in, const float *W_self,
+                   const float *W_neigh, const float *bias, int32_t F_out, int32_t act, float *Hnext, int64_t ld_next,
+                   hipStream_t stream)
 {
-    FwdEpilogue<T> e{Hnext, ld_next, bias, act == TMA_ACT_RELU};
-    if constexpr (sizeof(T) == 4) {
-        fwd_dispatch_f32(n, H, ldh, M, ldm, F_in, W_self, W_neigh, e, F_out, stream);
-    } else {
-        const bool va = vec4_ok(H, ldh) && vec4_ok(M, ldm) && F_in % 4 == 0;
-        const bool vb = vec4_ok(W_self, F_out) && vec4_ok(W_neigh, F_out);
-        if (va && vb) fwd_dispatch<T, true, true>(n, H, ldh, M, ldm, F_in, W_self, W_neigh, e, F_out, stream);
-        else if (va) fwd_dispatch<T, true, false>(n, H, ldh, M, ldm, F_in, W_self, W_neigh, e, F_out, stream);
-        else if (vb) fwd_dispatch<T, false, true>(n, H, ldh, M, ldm, F_in, W_self, W_neigh, e, F_out, stream);
-        else fwd_dispatch<T, false, false>(n, H, ldh, M, ldm, F_in, W_self, W_neigh, e, F_out, stream);
-    }
+    launch_fwd_f32(F_out <= 64 || few_tiles(n, F_out) ? "gemm_fwd_128x64" : "gemm_fwd_128x128",   // (the name of its size class)
+                   AsyncRows(H, ldh, M, ldm, F_in, 2 * F_in, n), AsyncWeights<false>{W_self, W_neigh, F_in, F_out, 2 * F_in, 0},
+                   FwdEpilogue<float>{Hnext, ld_next, bias, act == TMA_ACT_RELU}, n, F_out, stream);
+    return check_launch("sage gemm fwd");
+}
+
+static int fwd_bf16(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *M, int64_t ldm, int32_t F_in, const float *W_self,
+                    const float *W_neigh, const float *bias, int32_t F_out, int32_t act, uint16_t *Hnext, int64_t ld_next,
+                    hipStream_t stream)
+{
+    FwdEpilogue<uint16_t> e{Hnext, ld_next, bias, act == TMA_ACT_RELU};
+    const bool va = vec4_ok(H, ldh) && vec4_ok(M, ldm) && F_in % 4 == 0;
+    const bool vb = vec4_ok(W_self, F_out) && vec4_ok(W_neigh, F_out);
+    if (va && vb) fwd_dispatch<true, true>(n, H, ldh, M, ldm, F_in, W_self, W_neigh, e, F_out, stream);
+    else if (va) fwd_dispatch<true, false>(n, H, ldh, M, ldm, F_in, W_self, W_neigh, e, F_out, stream);
+    else if (vb) fwd_dispatch<false, true>(n, H, ldh, M, ldm, F_in, W_self, W_neigh, e, F_out, stream);
+    else fwd_dispatch<false, false>(n, H, ldh, M, ldm, F_in, W_self, W_neigh, e, F_out, stream);
     return check_launch("sage gemm fwd");
 }
 
@@ -137,10 +121,10 @@ int launch_sage_gemm_fwd(int64_t n, const void *H, int64_t ldh, const void *M, i
         }
     }
     if (dtype == TMA_F32)
-        return fwd_typed<float>(n, static_cast<const float *>(H), ldh, static_cast<const float *>(M), ldm, F_in, W_self,
+        return fwd_f32(n, static_cast<const float *>(H), ldh, static_cast<const float *>(M), ldm, F_in, W_self,
                                 W_neigh, bias, F_out, act, static_cast<float *>(Hnext), ld_next, stream);
     if (dtype == TMA_BF16)
-        return fwd_typed<uint16_t>(n, static_cast<const uint16_t *>(H), ldh, static_cast<const uint16_t *>(M), ldm, F_in,
+        return fwd_bf16(n, static_cast<const uint16_t *>(H), ldh, static_cast<const uint16_t *>(M), ldm, F_in,
                                    W_self, W_neigh, bias, F_out, act, static_cast<uint16_t *>(Hnext), ld_next, stream);
     return fail(TMA_ERR_UNSUPPORTED_DTYPE, "sage gemm fwd: dtype %d", dtype);
 }

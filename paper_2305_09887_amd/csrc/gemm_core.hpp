@@ -3,8 +3,9 @@
 //
 // Operands are described by small "view" structs that present concatenations ([H | M], [W_self ; W_neigh]), the ReLU
 // mask and transposes as plain A[m][k], B[k][n], and results by an epilogue struct; three kernel templates take them:
-// gemm_f32_kernel (gemm_f32.hpp) for the forward products of fp32 storage and backward ones of few rows, gemm_split_kernel
+// gemm_f32_kernel (gemm_f32.hpp) for the backward products of fp32 storage with few rows, gemm_split_kernel
 // (gemm_split.hpp) for the other backward ones, gemm_bf16_kernel below for bf16 (v_mfma_f32_32x32x16_bf16, fp32 accumulation).
+// The forward products of fp32 storage have a kernel with operands of its own (gemm_f32_async.hpp).
 //
 // Tiling of gemm_bf16_kernel.  BM x BN block tile, each wavefront owning a (BM/WM) x (BN/WN) patch of 32x32 MFMA
 // tiles; k is consumed in slabs of BK through two LDS buffers (one barrier per slab) while the next slab's global
@@ -962,6 +963,9 @@ struct FwdEpilogue {  // H' = act(acc + b)
     const float *bias;
     bool relu;
     __device__ __forceinline__ float col_aux(int col) const { return bias[col]; }
+    __device__ __forceinline__ const float *col_at(int col) const { return bias + col; }
+    __device__ __forceinline__ const float *row_at(int64_t) const { return nullptr; }
+    __device__ __forceinline__ bool padding(int) const { return false; }
     __device__ __forceinline__ float row_aux(int64_t) const { return 0.0f; }
     __device__ __forceinline__ float value(float v, float caux, float, int) const
     {
@@ -1003,12 +1007,15 @@ struct BwdDataEpilogue {  // columns [0,F): dH_self (leading dimension ldh) ; [F
 };
 
 template <typename T>
-struct HalvesEpilogue {  // columns [0,Fp): Y_self ; [Fp,2Fp): Y_neigh ; both [rows, ldy]
+struct HalvesEpilogue {  // columns [0,Fp): Y_self ; [Fp,2Fp): Y_neigh ; both [rows, ldy], of which Fo are not padding
     static constexpr bool kColAux = false, kRowAux = false;
     T *Ys;
     T *Yn;
     int64_t ldy;
-    int Fp;
+    int Fp, Fo;
+    __device__ __forceinline__ bool padding(int col) const { return col - (col < Fp ? 0 : Fp) >= Fo; }
+    __device__ __forceinline__ const float *col_at(int) const { return nullptr; }
+    __device__ __forceinline__ const float *row_at(int64_t) const { return nullptr; }
     __device__ __forceinline__ float col_aux(int) const { return 0.0f; }
     __device__ __forceinline__ float row_aux(int64_t) const { return 0.0f; }
     __device__ __forceinline__ float value(float v, float, float, int) const { return v; }
@@ -1473,6 +1480,7 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_kernel(AL a, BL b, E
 
 }  // namespace tma
 #include "gemm_f32.hpp"
+#include "gemm_f32_async.hpp"
 #include "gemm_split.hpp"
 namespace tma {
 
@@ -1562,12 +1570,29 @@ static void launch_f32(const char *name, const AL &a, const BL &b, const Epi &e,
                        dim3(WM * WN * 64), 0, s, a, b, e, M, N, K, k_per_split, n_tiles, tiles, total, colsum_partial);
 }
 
-template <int BK, class AL, class BL, class Epi>
-static void launch_fwd_f32(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K, hipStream_t s)
+// A forward product of fp32 storage (gemm_f32_async.hpp).  The tile: as wide as pads least, a padded column priced at what
+// the tile takes for one (us per column of 400,000 x 256: 64 wide 1.86, 96 1.66, 128 1.67, 160 1.61), of 128 rows
+// where that leaves enough tiles for the compute units.  us, 64 x 64 / 64 x 128 / as chosen by width:
+//   5,000 rows, 256 -> 256 and 128: 13.2 / 14.0 / 22.0 and 9.5 / 13.5 / 21.7;  12,000: 19.6 / 22.0 / 24.1 and 13.2 / 14.3 / 22.8
+//   30,000: 44.9 / 40.4 / 38.8 (470 tiles) and 22.5 / 21.5 / 23.6 (235);  30,000, 256 -> 96: 22.4 / - / 19.5 (235), 180 -> 150: 31.1 / - / 28.6
+//   125,237: 157 / 143 / 135 and 81 / 74 / 72;  180 -> 150: 104 / 128 / 84;  64 -> 32: 15.2 / - / 12.6 (64 x 32)
+template <class BL, class Epi>
+static void launch_fwd_f32(const char *name, const AsyncRows &a, const BL &b, const Epi &e, int64_t M, int N, hipStream_t s)
 {
-    if (N <= 64 || few_tiles(M, N)) launch_f32<128, 64, 32, 4, 1, false>(name, a, b, e, M, N, K, K, 1, nullptr, s);
-    else if (BK == 32 && N <= 96) launch_f32<128, 96, 32, 4, 1, false>(name, a, b, e, M, N, K, K, 1, nullptr, s);
-    else launch_f32<128, 128, BK, 2, 2, false>(name, a, b, e, M, N, K, K, 1, nullptr, s);
+    if (M <= 0 || N <= 0 || a.K <= 0) return;
+    const auto padded = [&](int width) { return int64_t(ceil_div(N, width)) * width; };
+    const auto tiles = [&](int rows, int width) { return ceil_div(M, int64_t(rows)) * ceil_div(N, width); };
+    const int widths[] = {128, 96, 160, 64}, prices[] = {167, 166, 161, 186};
+    int w = 0;
+    for (int i = 1; i < 4; ++i)
+        if (padded(widths[i]) * prices[i] < padded(widths[w]) * prices[w]) w = i;
+    if (N <= 32) launch_async<64, 32, 2, 1, 3, 4>(name, a, b, e, M, N, s);
+    else if (widths[w] == 160 && tiles(128, 160) >= 200) launch_async<128, 160, 4, 1, 3, 2>(name, a, b, e, M, N, s);
+    else if (widths[w] == 96 && tiles(128, 96) >= 200) launch_async<128, 96, 4, 1, 3, 3>(name, a, b, e, M, N, s);
+    else if (widths[w] == 64 && tiles(128, 64) >= kFewTiles) launch_async<128, 64, 4, 1, 3, 4>(name, a, b, e, M, N, s);
+    else if (widths[w] == 128 && tiles(128, 128) >= kFewTiles) launch_async<128, 128, 2, 2, 3, 3>(name, a, b, e, M, N, s);
+    else if (padded(128) == padded(64) && tiles(64, 128) >= kFewTiles) launch_async<64, 128, 2, 2, 3, 4>(name, a, b, e, M, N, s);
+    else launch_async<64, 64, 2, 2, 3, 4>(name, a, b, e, M, N, s);
 }
 
 // fp32 products with more than 96 columns.  The 256-wide tile of eight wavefronts reads the operand it is wide across

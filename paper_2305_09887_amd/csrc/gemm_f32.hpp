@@ -1,5 +1,5 @@
-// The tile product of fp32 storage on v_mfma_f32_32x32x2_f32, fp32 in, fp32 accumulate: forward products, and backward
-// products of few rows.
+// The tile product of fp32 storage on v_mfma_f32_32x32x2_f32, fp32 in, fp32 accumulate: backward products of few rows.  (The
+// forward products sum in the same order, in a kernel of their own: gemm_f32_async.hpp.)
 //
 // Why not the product of bf16 parts (gemm_split.hpp), which the other backward products take and which is faster: what a layer
 // puts out is compared with zero (ReLU, PReLU, in this layer or one that follows), and an input of such a comparison that
@@ -15,8 +15,6 @@
 // the orientation it has in memory:
 //   k-contiguous operand : LDS [mn][BK+4]; a lane fetches four k-values of its row with one 16-byte read, for four MFMAs;
 //   mn-contiguous operand: LDS [BK][MN+4]; a lane reads one element per k-value.
-// Bound by the fp32 matrix instruction (157 TFLOP/s) where the output is wide: 2 x 128 -> 256 at 125,237 rows takes
-// 174 us, where the product of bf16 parts took 116.
 #pragma once
 
 namespace tma {

@@ -61,35 +61,39 @@ __global__ __launch_bounds__(256) void reduce_splits_halves_kernel(const float *
 static int pad_cols(int32_t F_out, int32_t dtype) { return int(round_up(size_t(F_out), dtype == TMA_BF16 ? 8 : 4)); }
 
 
-template <typename T>
-static int tf_fwd_typed(int64_t n, const T *H, int64_t ldh, int32_t F_in, const float *W_self, const float *W_neigh,
-                        int32_t F_out, int Fp, T *Ys, T *Yn, int64_t ldy, hipStream_t s)
+static int tf_fwd_f32(int64_t n, const float *H, int64_t ldh, int32_t F_in, const float *W_self, const float *W_neigh,
+                      int32_t F_out, int Fp, float *Ys, float *Yn, int64_t ldy, hipStream_t s)
 {
-    HalvesEpilogue<T> e{Ys, Yn, ldy, Fp};
+    TMA_REQUIRE(int64_t(F_in) * F_out >= 4, TMA_ERR_INVALID_ARG, "sage gemm tf fwd: weight matrix below four elements");
+    launch_fwd_f32("gemm_tf_fwd", AsyncRows(H, ldh, H, ldh, F_in, F_in, n), AsyncWeights<true>{W_self, W_neigh, F_in, F_out, F_in, Fp},
+                   HalvesEpilogue<float>{Ys, Yn, ldy, Fp, F_out}, n, 2 * Fp, s);
+    return check_launch("sage gemm tf fwd");
+}
+
+static int tf_fwd_bf16(int64_t n, const uint16_t *H, int64_t ldh, int32_t F_in, const float *W_self, const float *W_neigh,
+                       int32_t F_out, int Fp, uint16_t *Ys, uint16_t *Yn, int64_t ldy, hipStream_t s)
+{
+    HalvesEpilogue<uint16_t> e{Ys, Yn, ldy, Fp, F_out};
     const int64_t K = F_in, kps = int64_t(round_up(size_t(K), 32));
     // The rows are the k side here: a group that reaches into their padding has to mask it (a NaN there would get through
     // the zero weights it meets), which the plain groups do not.
     const bool va = groups_ok(H, ldh, F_in);
-    const bool padded = sizeof(T) == 2 && !va && vec4_ok(H, ldh);
+    const bool padded = !va && vec4_ok(H, ldh);
     const bool vb = F_out % 4 == 0 && aligned(W_self, 16) && aligned(W_neigh, 16);
     TMA_REQUIRE(vb || int64_t(F_in) * F_out >= 4, TMA_ERR_INVALID_ARG, "sage gemm tf fwd: weight matrix below four elements");
-    const char *name = kname<T>("gemm_tf_fwd", "gemm_tf_fwd_generic", "gemm_tf_fwd_bf16", "gemm_tf_fwd_bf16_generic", va || padded);
+    const char *name = va || padded ? "gemm_tf_fwd_bf16" : "gemm_tf_fwd_bf16_generic";
     // weights whose rows are not multiples of four: 16-byte loads from 4-byte-aligned addresses
     // (the form is only chosen for F_in >= 8, so the matrices hold at least four elements)
     const auto with_rows = [&](const auto &a, auto grouped_tag) {
         const auto with_weights = [&](const auto &b) {
-            if constexpr (sizeof(T) == 4) launch_fwd_f32<32>(name, a, b, e, n, 2 * Fp, K, s);
-            else launch_by_width<T, 32, false, decltype(grouped_tag)::value>(name, a, b, e, n, 2 * Fp, K, kps, 1, nullptr, s);
+            launch_by_width<uint16_t, 32, false, decltype(grouped_tag)::value>(name, a, b, e, n, 2 * Fp, K, kps, 1, nullptr, s);
         };
         if (vb) with_weights(SideWeights<kAligned4>{W_self, W_neigh, F_in, F_out, Fp});
         else with_weights(SideWeights<kUnaligned4>{W_self, W_neigh, F_in, F_out, Fp});
     };
-    if (va) with_rows(CatRows<T, true>{H, ldh, H, ldh, F_in, n, F_in}, std::true_type{});
-    else if constexpr (sizeof(T) == 4) {
-        if (rows_u_ok(n, ldh, F_in)) with_rows(CatRowsU{H, ldh, F_in, n}, std::true_type{});
-        else with_rows(CatRows<T, false>{H, ldh, H, ldh, F_in, n, F_in}, std::false_type{});
-    } else if (padded) with_rows(PaddedRows{H, ldh, F_in, n}, std::true_type{});
-    else with_rows(CatRows<T, false>{H, ldh, H, ldh, F_in, n, F_in}, std::false_type{});
+    if (va) with_rows(CatRows<uint16_t, true>{H, ldh, H, ldh, F_in, n, F_in}, std::true_type{});
+    else if (padded) with_rows(PaddedRows{H, ldh, F_in, n}, std::true_type{});
+    else with_rows(CatRows<uint16_t, false>{H, ldh, H, ldh, F_in, n, F_in}, std::false_type{});
     return check_launch("sage gemm tf fwd");
 }
 
@@ -100,10 +104,10 @@ int launch_sage_tf_gemm_fwd(int64_t n, const void *H, int64_t ldh, int32_t F_in,
     if (n == 0) return TMA_OK;
     const int Fp = pad_cols(F_out, dtype);
     if (dtype == TMA_F32)
-        return tf_fwd_typed<float>(n, static_cast<const float *>(H), ldh, F_in, W_self, W_neigh, F_out, Fp,
+        return tf_fwd_f32(n, static_cast<const float *>(H), ldh, F_in, W_self, W_neigh, F_out, Fp,
                                    static_cast<float *>(Ys), static_cast<float *>(Yn), ldy, stream);
     if (dtype == TMA_BF16)
-        return tf_fwd_typed<uint16_t>(n, static_cast<const uint16_t *>(H), ldh, F_in, W_self, W_neigh, F_out, Fp,
+        return tf_fwd_bf16(n, static_cast<const uint16_t *>(H), ldh, F_in, W_self, W_neigh, F_out, Fp,
                                       static_cast<uint16_t *>(Ys), static_cast<uint16_t *>(Yn), ldy, stream);
     return fail(TMA_ERR_UNSUPPORTED_DTYPE, "sage gemm tf fwd: dtype %d", dtype);
 }

@@ -1,0 +1,89 @@
+// Every address that the operands of the fp32 forward products hand out lies inside their arrays, and every element comes
+// from its place: walked on the host as the kernel walks them, over arrays of exactly their size.
+#include "gemm_core.hpp"
+
+#include <cstdio>
+#include <cstdlib>
+
+namespace tma {
+KernelTimer::KernelTimer(const char *, hipStream_t) {}
+KernelTimer::~KernelTimer() {}
+}  // namespace tma
+using namespace tma;
+
+static int wrong = 0;
+static void expect(bool ok, const char *what, int a, int b, int c)
+{
+    if (!ok && ++wrong < 20) printf("%s at %d %d %d\n", what, a, b, c);
+}
+
+static void rows(int n, int F, int pitch, bool two)
+{
+    const int ld = F + pitch, K = two ? 2 * F : F;
+    const int64_t count = int64_t(n - 1) * ld + F;
+    float *H = static_cast<float *>(malloc(count * 4)), *M = static_cast<float *>(malloc(count * 4)), zero[4];
+    const AsyncRows a(H, ld, M, ld, F, K, n);
+    const auto check = [&](const float *p, int m, int k, int e) {
+        const float *want = k < F ? H + int64_t(m) * ld + k : M + int64_t(m) * ld + (k - F), *base = k < F ? H : M;
+        expect(p == want && p >= base && p + e <= base + count, "row", m, k, e);
+    };
+    for (int m = 0; m < n; ++m)
+        for (int kt = 0; kt < K; kt += kAsyncK) {
+            if (a.run(kt) > 0) {
+                const float *base = kt < F ? H + kt : M + (kt - F);
+                for (int k = kt; k < kt + kAsyncK; k += 4) check(base + int64_t(m) * ld + (k - kt), m, k, 4);
+            }
+            const int step = a.pieces() ? 4 : 1;
+            for (int k = kt; k < kt + kAsyncK; k += step) {
+                const float *p = a.at(m, k, zero);
+                if (k < K) check(p, m, k, step);
+                else expect(p == zero, "past k", m, k, step);
+            }
+        }
+    expect(a.at(n + 3, 0, zero) == a.at(n - 1, 0, zero), "past the rows", n, F, K);
+    free(H);
+    free(M);
+}
+
+template <bool kSide>
+static void weights(int R, int N, bool two)
+{
+    const int Np = (N + 3) / 4 * 4, K = kSide || !two ? R : 2 * R, columns = kSide ? 2 * Np : N;
+    const int64_t count = int64_t(R) * N;
+    float *W = static_cast<float *>(malloc(count * 4)), *V = static_cast<float *>(malloc(count * 4)), zero[4];
+    const AsyncWeights<kSide> b{W, V, R, N, K, kSide ? Np : 0};
+    for (int n = 0; n < (columns + 255) / 128 * 128; ++n)
+        for (int kt = 0; kt < K; kt += kAsyncK)
+            for (int k = kt; k < kt + kAsyncK; ++k) {
+                const int c = n - (kSide && n >= Np ? Np : 0);
+                const bool inside = n < columns && c < N;
+                const float *base = (kSide ? n >= Np && n < columns : k >= R) ? V : W;
+                const float *want = base + int64_t(!kSide && k >= R ? k - R : k) * N + c;
+                if (b.run(kt) > 0 && n % 4 == 0) {
+                    const float *p = kSide ? (b.half(n) ? V : W) + int64_t(k) * N + b.column(n) : b.first(kt) + int64_t(k - kt) * N + b.column(n);
+                    expect(p >= base && p + 4 <= base + count && (!inside || p == want), "piece", k, n, N);
+                }
+                const int step = b.pieces() ? 4 : 1;
+                if (n % step) continue;
+                const float *p = b.at(k, n, zero);
+                if (k >= K) expect(p == zero, "past k", k, n, N);
+                else expect(p >= base && p + step <= base + count && (!inside || p == want), "element", k, n, N);
+            }
+    free(W);
+    free(V);
+}
+
+int main()
+{
+    for (int F : {1, 2, 3, 4, 5, 7, 8, 12, 15, 16, 17, 20, 31, 32, 33, 48, 50, 63, 64, 90, 100, 128, 150}) {
+        for (int n : {1, 2, 5})
+            for (int pitch : {0, 1, 3, 4}) rows(n, F, pitch, false), rows(n, F, pitch, true);
+        for (int N : {1, 2, 3, 4, 5, 6, 7, 8, 31, 41, 47, 48, 64, 97, 130}) {
+            weights<false>(F, N, false);
+            weights<false>(F, N, true);
+            weights<true>(F, N, false);
+        }
+    }
+    printf("%d wrong\n", wrong);
+    return wrong ? 1 : 0;
+}
