@@ -50,6 +50,7 @@ static void fwd_dispatch(int64_t n, const uint16_t *H, int64_t ldh, const uint16
 static void fwd_prepared(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *M, int64_t ldm, int F_in,
                          const uint16_t *Wt, const FwdEpilogue<uint16_t> &e, int F_out, hipStream_t s)
 {
+    if (stream_sage_fwd(n, H, ldh, M, ldm, F_in, Wt, e.bias, F_out, e.relu, e.out, e.ld, s)) return;
     CatRows<uint16_t, true> a{H, ldh, M, ldm, F_in, n, 2 * F_in};
     CatRows<uint16_t, true> b{Wt, 2 * int64_t(F_in), Wt, 2 * int64_t(F_in), 2 * F_in, F_out, 2 * F_in};
     const int64_t K = 2 * int64_t(F_in);
@@ -189,9 +190,13 @@ static int bwd_data_typed(int64_t n, const T *g, const T *h, int64_t ld_next, co
 int launch_sage_gemm_bwd_data(int64_t n, const void *dHnext, const void *Hnext, int64_t ld_next,
                               const float *inv_deg, const float *W_self, const float *W_neigh, int32_t F_in,
                               int32_t F_out, int32_t act, int32_t dtype, void *dH_self_out, int64_t ldh,
-                              void *dM_scaled_out, hipStream_t stream)
+                              void *dM_scaled_out, hipStream_t stream, void *spare, size_t spare_bytes)
 {
     if (n == 0 || F_in == 0) return TMA_OK;
+    if (dtype == TMA_BF16 && stream_sage_bwd_data(n, static_cast<const uint16_t *>(dHnext), static_cast<const uint16_t *>(Hnext), ld_next, inv_deg,
+                                                  W_self, W_neigh, F_in, F_out, act == TMA_ACT_RELU, static_cast<uint16_t *>(dH_self_out), ldh,
+                                                  static_cast<uint16_t *>(dM_scaled_out), spare, spare_bytes, stream))
+        return check_launch("sage gemm bwd data");
     if (dtype == TMA_F32)
         return bwd_data_typed<float>(n, static_cast<const float *>(dHnext), static_cast<const float *>(Hnext), ld_next,
                                      inv_deg, W_self, W_neigh, F_in, F_out, act, static_cast<float *>(dH_self_out),

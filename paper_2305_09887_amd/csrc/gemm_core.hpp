@@ -989,6 +989,9 @@ struct BwdDataEpilogue {  // columns [0,F): dH_self (leading dimension ldh) ; [F
     int F;
     __device__ __forceinline__ float col_aux(int) const { return 0.0f; }
     __device__ __forceinline__ float row_aux(int64_t row) const { return inv_deg[row]; }
+    __device__ __forceinline__ const float *col_at(int) const { return nullptr; }
+    __device__ __forceinline__ const float *row_at(int64_t row) const { return inv_deg + row; }
+    __device__ __forceinline__ bool padding(int) const { return false; }
     __device__ __forceinline__ float value(float v, float, float raux, int col) const { return col < F ? v : v * raux; }
     __device__ __forceinline__ void store(int64_t row, int col, float v, int) const
     {
@@ -1040,6 +1043,9 @@ struct RowsEpilogue {  // plain [rows, ld] output
     static constexpr bool kColAux = false, kRowAux = false;
     T *out;
     int64_t ld;
+    __device__ __forceinline__ const float *col_at(int) const { return nullptr; }
+    __device__ __forceinline__ const float *row_at(int64_t) const { return nullptr; }
+    __device__ __forceinline__ bool padding(int) const { return false; }
     __device__ __forceinline__ float col_aux(int) const { return 0.0f; }
     __device__ __forceinline__ float row_aux(int64_t) const { return 0.0f; }
     __device__ __forceinline__ float value(float v, float, float, int) const { return v; }

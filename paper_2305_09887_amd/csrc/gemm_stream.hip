@@ -1,0 +1,118 @@
+// The products of bf16 storage over many nodes: operands, narrowed weights and tiles of gemm_bf16_async.hpp.
+#include "gemm_core.hpp"
+#include "gemm_bf16_async.hpp"
+
+namespace tma {
+
+// Which products come here.  From a tile of 256 rows per compute unit on, and from twice that for a product of few operations a row;
+// where a tile is padded, or slabs are fetched pair by pair, only where bytes alone count.  us, gemm_bf16_kernel -> here:
+//   forward, 65,536 / 125,237 rows: 128 -> 256 38 -> 32 / 66 -> 59, 256 -> 256 57 -> 49 / 97 -> 85; both at 12,500,000: 11,200 -> 7,780 (4.1 TB/s)
+//   64 -> 128 21 -> 21, 45 -> 39 at 181,000; 100 -> 120 72 -> 78 at 181,000, 555 -> 552 at 1,500,000; 96 -> 64 46 -> 48, 344 -> 347
+//   input gradient with ReLU (with the gather after it): 256 -> 256 85 -> 70 / 163 -> 134, alone at 12,500,000 11,520 -> 7,750; 128 -> 128
+//   without ReLU 37 -> 33 at 65,536; 96 -> 64 88 -> 83 at 181,000, 178 -> 184 at 400,000, 642 -> 580 at 1,500,000; 64 -> 128 (half the tile) 60 -> 89
+//   transformed first, forward 256 -> 47: 28 -> 27 / 48 -> 42 / 2,460 -> 1,820 (4.8 TB/s); 128 -> 47 23 -> 23 at 65,536, 49 -> 43 at 181,000
+//   transformed first, input gradient: 128 -> 47 14 -> 17 at 65,536, 30 -> 26 at 181,000; 256 -> 20 (slabs pair by pair) 85 -> 90 at
+//   400,000, 353 -> 303 at 1,500,000; 256 -> 47 3,850 -> 2,050 (4.3 TB/s) at 12,500,000
+constexpr int64_t kManyRows = 65536, kTransformRows = 98304, kStreamRows = int64_t(1) << 20;
+template <bool kMask, class Epi>
+static void launch_rows16(const char *name, const AsyncRows16 &a, const uint16_t *mask, const AsyncRows16 &b, const Epi &e, int64_t M, int N, hipStream_t s)
+{
+    if constexpr (kMask) {
+        launch_async16<256, 256, 4, 2, 3, true>(name, a, mask, b, e, M, N, s);
+    } else {
+        if (N <= 96) launch_async16<256, 96, 4, 1, 3, false>(name, a, mask, b, e, M, N, s);
+        else if (N <= 128) launch_async16<256, 128, 4, 1, 3, false>(name, a, mask, b, e, M, N, s);
+        else launch_async16<256, 256, 4, 2, 4, false>(name, a, mask, b, e, M, N, s);
+    }
+}
+// rows of narrowed weights beside what a product reads them for: out[r][c], c < pitch
+struct NarrowStack {   // [W0 ; W1] of R rows each, N columns, zeros up to the pitch
+    const float *W0, *W1;
+    int R, N;
+    __device__ __forceinline__ float at(int r, int c) const { return c < N ? (r < R ? W0 + int64_t(r) * N : W1 + int64_t(r - R) * N)[c] : 0.0f; }
+};
+struct NarrowSides {   // [W0 | W1], N columns each padded with zeros to Np
+    const float *W0, *W1;
+    int N, Np;
+    __device__ __forceinline__ float at(int r, int c) const
+    {
+        const int cc = c < Np ? c : c - Np;
+        return cc < N ? (c < Np ? W0 : W1)[int64_t(r) * N + cc] : 0.0f;
+    }
+};
+struct NarrowSidesT {  // the transpose of [W0 | W1]: row r is column r, R long, zeros up to the pitch
+    const float *W0, *W1;
+    int N, Np, R;
+    __device__ __forceinline__ float at(int r, int c) const
+    {
+        const int col = r < Np ? r : r - Np;
+        return col < N && c < R ? (r < Np ? W0 : W1)[int64_t(c) * N + col] : 0.0f;
+    }
+};
+template <class From>
+static __global__ __launch_bounds__(256) void narrow_rows_kernel(From from, int rows, int pitch, uint16_t *__restrict__ out)
+{
+    const int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x;
+    if (i < int64_t(rows) * pitch) out[i] = f32_to_bf16(from.at(int(i / pitch), int(i % pitch)));
+}
+template <class From>
+static AsyncRows16 narrow_rows(const From &from, int rows, int K, int pitch, void *out, hipStream_t s)
+{
+    TMA_TIMED("prepare_weights_bf16", s);
+    uint16_t *w = static_cast<uint16_t *>(out);
+    hipLaunchKernelGGL(narrow_rows_kernel<From>, dim3(unsigned(ceil_div(int64_t(rows) * pitch, 256))), dim3(256), 0, s, from, rows, pitch, w);
+    return AsyncRows16{w, pitch, w, pitch, K, K, K, rows};
+}
+
+bool stream_sage_fwd(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *M, int64_t ldm, int F_in, const uint16_t *Wt, const float *bias,
+                     int F_out, bool relu, uint16_t *Hnext, int64_t ld_next, hipStream_t s)
+{
+    const int K = 2 * F_in;
+    const AsyncRows16 a{H, ldh, M, ldm, F_in, F_in, K, n};
+    if (n < kManyRows || !a.ok() || F_out <= 64 || (F_out <= 128 && F_in % kAsyncK16 != 0 && n < kStreamRows)) return false;
+    launch_rows16<false>(F_out > 128 ? "gemm_fwd_128x256_bf16" : "gemm_fwd_128x128_bf16", a, nullptr,
+                         AsyncRows16{Wt, K, Wt, K, K, K, K, F_out}, FwdEpilogue<uint16_t>{Hnext, ld_next, bias, relu}, n, F_out, s);
+    return true;
+}
+
+bool stream_sage_bwd_data(int64_t n, const uint16_t *dHnext, const uint16_t *Hnext, int64_t ld_next, const float *inv_deg, const float *W_self,
+                          const float *W_neigh, int F_in, int F_out, bool relu, uint16_t *dH_self_out, int64_t ldh, uint16_t *dM_scaled_out,
+                          void *spare, size_t spare_bytes, hipStream_t s)
+{
+    const int N = 2 * F_in, pitch = int(round_up(size_t(F_out), 8));
+    const AsyncRows16 a{dHnext, ld_next, dHnext, ld_next, F_out, F_out, F_out, n};
+    if (n < kManyRows || (N < 256 && n < kStreamRows) || N <= (relu ? 128 : 64)) return false;
+    if (!a.ok() || (relu && !aligned(Hnext, 4)) || !spare || size_t(N) * pitch * 2 > spare_bytes) return false;
+    const AsyncRows16 b = narrow_rows(NarrowStack{W_self, W_neigh, F_in, F_out}, N, F_out, pitch, spare, s);
+    const BwdDataEpilogue<uint16_t> e{dH_self_out, ldh, dM_scaled_out, inv_deg, F_in};
+    const char *name = N >= 256 ? "gemm_bwd_data_128x256_bf16" : "gemm_bwd_data_128x128_bf16";
+    if (relu) launch_rows16<true>(name, a, Hnext, b, e, n, N, s);
+    else launch_rows16<false>(name, a, nullptr, b, e, n, N, s);
+    return true;
+}
+
+bool stream_sage_tf_fwd(int64_t n, const uint16_t *H, int64_t ldh, int F_in, const float *W_self, const float *W_neigh, int F_out, int Fp,
+                        uint16_t *Ys, uint16_t *Yn, int64_t ldy, void *spare, size_t spare_bytes, hipStream_t s)
+{
+    const AsyncRows16 a{H, ldh, H, ldh, F_in, F_in, F_in, n};
+    const int pitch = int(round_up(size_t(F_in), 8));
+    if (n < kTransformRows || (F_in % kAsyncK16 != 0 && n < kStreamRows)) return false;
+    if (!a.ok() || !spare || size_t(2) * Fp * pitch * 2 > spare_bytes) return false;
+    const AsyncRows16 b = narrow_rows(NarrowSidesT{W_self, W_neigh, F_out, Fp, F_in}, 2 * Fp, F_in, pitch, spare, s);
+    launch_rows16<false>("gemm_tf_fwd_bf16", a, nullptr, b, HalvesEpilogue<uint16_t>{Ys, Yn, ldy, Fp, F_out}, n, 2 * Fp, s);
+    return true;
+}
+
+bool stream_sage_tf_bwd_data(int64_t n, const uint16_t *dHnext, int64_t ld_next, const uint16_t *dYn, int64_t ldy, const float *W_self,
+                             const float *W_neigh, int F_in, int F_out, int Fp, uint16_t *dH, int64_t ldh, void *spare, size_t spare_bytes,
+                             hipStream_t s)
+{
+    const AsyncRows16 a{dHnext, ld_next, dYn, ldy, Fp, F_out, 2 * Fp, n};
+    if (n < kTransformRows || (Fp < 32 && n < kStreamRows)) return false;
+    if (!a.ok() || !spare || size_t(F_in) * 2 * Fp * 2 > spare_bytes) return false;
+    const AsyncRows16 b = narrow_rows(NarrowSides{W_self, W_neigh, F_out, Fp}, F_in, 2 * Fp, 2 * Fp, spare, s);
+    launch_rows16<false>("gemm_tf_bwd_data_bf16", a, nullptr, b, RowsEpilogue<uint16_t>{dH, ldh}, n, F_in, s);
+    return true;
+}
+
+}  // namespace tma

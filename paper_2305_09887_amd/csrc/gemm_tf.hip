@@ -71,9 +71,10 @@ static int tf_fwd_f32(int64_t n, const float *H, int64_t ldh, int32_t F_in, cons
 }
 
 static int tf_fwd_bf16(int64_t n, const uint16_t *H, int64_t ldh, int32_t F_in, const float *W_self, const float *W_neigh,
-                       int32_t F_out, int Fp, uint16_t *Ys, uint16_t *Yn, int64_t ldy, hipStream_t s)
+                       int32_t F_out, int Fp, uint16_t *Ys, uint16_t *Yn, int64_t ldy, hipStream_t s, void *spare, size_t spare_bytes)
 {
     HalvesEpilogue<uint16_t> e{Ys, Yn, ldy, Fp, F_out};
+    if (stream_sage_tf_fwd(n, H, ldh, F_in, W_self, W_neigh, F_out, Fp, Ys, Yn, ldy, spare, spare_bytes, s)) return check_launch("sage gemm tf fwd");
     const int64_t K = F_in, kps = int64_t(round_up(size_t(K), 32));
     // The rows are the k side here: a group that reaches into their padding has to mask it (a NaN there would get through
     // the zero weights it meets), which the plain groups do not.
@@ -99,7 +100,7 @@ static int tf_fwd_bf16(int64_t n, const uint16_t *H, int64_t ldh, int32_t F_in, 
 
 int launch_sage_tf_gemm_fwd(int64_t n, const void *H, int64_t ldh, int32_t F_in, const float *W_self,
                             const float *W_neigh, int32_t F_out, int32_t dtype, void *Ys, void *Yn, int64_t ldy,
-                            hipStream_t stream)
+                            hipStream_t stream, void *spare, size_t spare_bytes)
 {
     if (n == 0) return TMA_OK;
     const int Fp = pad_cols(F_out, dtype);
@@ -108,7 +109,7 @@ int launch_sage_tf_gemm_fwd(int64_t n, const void *H, int64_t ldh, int32_t F_in,
                                    static_cast<float *>(Ys), static_cast<float *>(Yn), ldy, stream);
     if (dtype == TMA_BF16)
         return tf_fwd_bf16(n, static_cast<const uint16_t *>(H), ldh, F_in, W_self, W_neigh, F_out, Fp,
-                                      static_cast<uint16_t *>(Ys), static_cast<uint16_t *>(Yn), ldy, stream);
+                                      static_cast<uint16_t *>(Ys), static_cast<uint16_t *>(Yn), ldy, stream, spare, spare_bytes);
     return fail(TMA_ERR_UNSUPPORTED_DTYPE, "sage gemm tf fwd: dtype %d", dtype);
 }
 
@@ -244,11 +245,15 @@ static int tf_bwd_data_typed(int64_t n, const T *g, const T *h, int64_t ld_next,
 
 int launch_sage_tf_gemm_bwd_data(int64_t n, const void *dHnext, const void *Hnext, int64_t ld_next, const void *dYn,
                                  int64_t ldy, const float *W_self, const float *W_neigh, int32_t F_in, int32_t F_out,
-                                 int32_t act, int32_t dtype, void *dH, int64_t ldh, hipStream_t stream)
+                                 int32_t act, int32_t dtype, void *dH, int64_t ldh, hipStream_t stream, void *spare, size_t spare_bytes)
 {
     if (n == 0) return TMA_OK;
     const int Fp = pad_cols(F_out, dtype);
     const bool relu = act == TMA_ACT_RELU;
+    if (dtype == TMA_BF16 && !relu && stream_sage_tf_bwd_data(n, static_cast<const uint16_t *>(dHnext), ld_next, static_cast<const uint16_t *>(dYn), ldy,
+                                                              W_self, W_neigh, F_in, F_out, Fp, static_cast<uint16_t *>(dH), ldh, spare, spare_bytes,
+                                                              stream))
+        return check_launch("sage gemm tf bwd data");
     if (dtype == TMA_F32)
         return tf_bwd_data_typed<float>(n, static_cast<const float *>(dHnext), static_cast<const float *>(Hnext),
                                         ld_next, static_cast<const float *>(dYn), ldy, W_self, W_neigh, F_in, F_out, Fp,

@@ -53,11 +53,13 @@ size_t sage_weights_bf16_bytes(int32_t F_in, int32_t F_out);
 int launch_sage_prepare_weights_bf16(const float *W_self, const float *W_neigh, int32_t F_in, int32_t F_out, void *Wt_out,
                                      hipStream_t stream);
 
+// `spare` of the products below (may be NULL): 16-byte-aligned device memory that the call may overwrite, for narrowed weights
+
 // [dH_self | inv_deg * dM] = dZ [W_self^T | W_neigh^T],  dZ = dHnext (.) act'(Hnext)
 int launch_sage_gemm_bwd_data(int64_t n, const void *dHnext, const void *Hnext, int64_t ld_next,
                               const float *inv_deg, const float *W_self, const float *W_neigh, int32_t F_in,
                               int32_t F_out, int32_t act, int32_t dtype, void *dH_self_out, int64_t ldh,
-                              void *dM_scaled_out, hipStream_t stream);
+                              void *dM_scaled_out, hipStream_t stream, void *spare = nullptr, size_t spare_bytes = 0);
 
 // [dW_self ; dW_neigh] = [H | M]^T dZ,  dbias = 1^T dZ   (split over nodes, two-stage fixed-order reduction)
 size_t sage_gemm_bwd_weight_workspace_bytes(int64_t n, int32_t F_in, int32_t F_out);
@@ -74,7 +76,7 @@ int launch_sage_gemm_bwd_weight(int64_t n, const void *H, int64_t ldh, const voi
 // Ys, Yn, dYn: [n, Fp] blocks with leading dimension ldy, Fp = F_out padded to 16 bytes.
 int launch_sage_tf_gemm_fwd(int64_t n, const void *H, int64_t ldh, int32_t F_in, const float *W_self,
                             const float *W_neigh, int32_t F_out, int32_t dtype, void *Ys, void *Yn, int64_t ldy,
-                            hipStream_t stream);
+                            hipStream_t stream, void *spare = nullptr, size_t spare_bytes = 0);
 size_t sage_tf_gemm_bwd_weight_workspace_bytes(int64_t n, int32_t F_in, int32_t F_out, int32_t dtype);
 int launch_sage_tf_gemm_bwd_weight(int64_t n, const void *H, int64_t ldh, const void *dHnext, const void *Hnext,
                                    int64_t ld_next, const void *dYn, int64_t ldy, int32_t F_in, int32_t F_out,
@@ -82,7 +84,21 @@ int launch_sage_tf_gemm_bwd_weight(int64_t n, const void *H, int64_t ldh, const 
                                    size_t ws_bytes, hipStream_t stream);
 int launch_sage_tf_gemm_bwd_data(int64_t n, const void *dHnext, const void *Hnext, int64_t ld_next, const void *dYn,
                                  int64_t ldy, const float *W_self, const float *W_neigh, int32_t F_in, int32_t F_out,
-                                 int32_t act, int32_t dtype, void *dH, int64_t ldh, hipStream_t stream);
+                                 int32_t act, int32_t dtype, void *dH, int64_t ldh, hipStream_t stream, void *spare = nullptr,
+                                 size_t spare_bytes = 0);
+
+// The products of bf16 storage over many nodes (gemm_stream.hip); false: not one of theirs, nothing was launched.  Arguments as
+// of the calls above.
+bool stream_sage_fwd(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *M, int64_t ldm, int F_in, const uint16_t *Wt, const float *bias,
+                     int F_out, bool relu, uint16_t *Hnext, int64_t ld_next, hipStream_t stream);
+bool stream_sage_bwd_data(int64_t n, const uint16_t *dHnext, const uint16_t *Hnext, int64_t ld_next, const float *inv_deg, const float *W_self,
+                          const float *W_neigh, int F_in, int F_out, bool relu, uint16_t *dH_self_out, int64_t ldh, uint16_t *dM_scaled_out,
+                          void *spare, size_t spare_bytes, hipStream_t stream);
+bool stream_sage_tf_fwd(int64_t n, const uint16_t *H, int64_t ldh, int F_in, const float *W_self, const float *W_neigh, int F_out, int Fp,
+                        uint16_t *Ys, uint16_t *Yn, int64_t ldy, void *spare, size_t spare_bytes, hipStream_t stream);
+bool stream_sage_tf_bwd_data(int64_t n, const uint16_t *dHnext, int64_t ld_next, const uint16_t *dYn, int64_t ldy, const float *W_self,
+                             const float *W_neigh, int F_in, int F_out, int Fp, uint16_t *dH, int64_t ldh, void *spare, size_t spare_bytes,
+                             hipStream_t stream);
 
 // Second stage of a split weight-gradient product, fixed order: partial is [n_splits][halves * F][N] and
 // colsum_partial [n_splits][N]; rows [0, F) go to dW_first, rows [F, 2F) (halves = 2) to dW_second, the

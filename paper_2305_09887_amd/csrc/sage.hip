@@ -63,7 +63,11 @@ static int sage_layer_fwd(const char *fn, int64_t n, const int32_t *rowptr, cons
     void *Ys = scratch;
     void *Yn = scratch + size_t(n) * size_t(Fp) * elem_size(dtype);
     TMA_REQUIRE(aligned(M_out, 16), TMA_ERR_INVALID_ARG, "%s: M_out must be 16-byte aligned", fn);
-    if (int rc = launch_sage_tf_gemm_fwd(n, H, ldh, F_in, W_self, W_neigh, F_out, dtype, Ys, Yn, Fp, s)) return rc;
+    // (what the two blocks leave of the buffer)
+    const size_t taken = round_up(2 * size_t(n) * size_t(Fp) * elem_size(dtype), 16), held = size_t(n) * size_t(F_in) * elem_size(dtype);
+    if (int rc = launch_sage_tf_gemm_fwd(n, H, ldh, F_in, W_self, W_neigh, F_out, dtype, Ys, Yn, Fp, s, scratch + taken,
+                                         held > taken ? held - taken : 0))
+        return rc;
     if (ld_next >= Fp)   // whole padded rows (vector path); the padding columns of Hnext receive zeros
         return launch_spmm_combine(n, rowptr, colidx, inv_deg, Yn, Fp, Fp, dtype, Hnext_out, ld_next, false, Ys, Fp,
                                    bias, F_out, act == TMA_ACT_RELU, false, nullptr, s);
@@ -198,7 +202,7 @@ extern "C" int tma_sage_layer_bwd(int64_t n, const int32_t *rowptr_T, const int3
             return rc;
         if (!need_dH || n == 0) return TMA_OK;
         return launch_sage_tf_gemm_bwd_data(n, dHnext, Hnext, ld_next, dYn, Fp, W_self, W_neigh, F_in, F_out, act,
-                                            dtype, dH_out, ldh, s);
+                                            dtype, dH_out, ldh, s, wws, w.weight_bytes);   // (the partial sums are spent)
     }
     if (int rc = launch_sage_gemm_bwd_weight(n, H, ldh, M, ldm, dHnext, Hnext, ld_next, F_in, F_out, act, dtype, dW_self,
                                              dW_neigh, dbias, wws, w.weight_bytes, s))
@@ -206,7 +210,7 @@ extern "C" int tma_sage_layer_bwd(int64_t n, const int32_t *rowptr_T, const int3
     if (!need_dH || n == 0) return TMA_OK;
     // dH = dZ W_self^T  (written by the transform)  +  A^T (D^-1 dZ W_neigh^T)  (gathered on top of it)
     if (int rc = launch_sage_gemm_bwd_data(n, dHnext, Hnext, ld_next, inv_deg, W_self, W_neigh, F_in, F_out, act, dtype,
-                                           dH_out, ldh, dMs, s))
+                                           dH_out, ldh, dMs, s, wws, w.weight_bytes))
         return rc;
     return launch_spmm(n, rowptr_T, colidx_T, nullptr, dMs, F_in, F_in, dtype, dH_out, ldh, true, s);
 }

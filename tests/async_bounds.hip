@@ -1,6 +1,7 @@
 // Every address that the operands of the fp32 forward products hand out lies inside their arrays, and every element comes
 // from its place: walked on the host as the kernel walks them, over arrays of exactly their size.
 #include "gemm_core.hpp"
+#include "gemm_bf16_async.hpp"
 
 #include <cstdio>
 #include <cstdlib>
@@ -73,8 +74,41 @@ static void weights(int R, int N, bool two)
     free(V);
 }
 
+// rows of bf16: the whole slabs of a run and the pairs of the others, as Fetch16 walks them
+static void rows16(int n, int F, int Fv, int pitch, bool two)
+{
+    const int ld = F + pitch, K = two ? 2 * F : F;
+    const int64_t count = int64_t(n - 1) * ld + F;      // (padding up to an even width is the rows' own)
+    uint16_t *H = static_cast<uint16_t *>(malloc(count * 2)), *M = static_cast<uint16_t *>(malloc(count * 2)), zero[8];
+    const AsyncRows16 a{H, ld, M, ld, F, Fv, K, n};
+    expect(a.ok(), "form", n, F, ld);
+    for (int m = 0; m < n + 2; ++m)
+        for (int kt = 0; kt < K; kt += kAsyncK16) {
+            const int row = m < n ? m : n - 1;
+            const uint16_t *base = kt < F ? H : M;
+            if (a.run(kt) > 0) {
+                const uint16_t *p = base + int64_t(row) * ld + (kt < F ? kt : kt - F);
+                expect(kt + kAsyncK16 <= (kt < F ? Fv : K) && p >= base && p + kAsyncK16 <= base + count, "slab", m, kt, F);
+            }
+            for (int k = kt; k < kt + kAsyncK16; k += 2) {
+                const uint16_t *p = a.at(m, k, zero);
+                if (k >= K || (k >= Fv && k < F)) expect(p == zero, "outside", m, k, F);
+                else expect(p == (k < F ? H + int64_t(row) * ld + k : M + int64_t(row) * ld + (k - F)) && p + 2 <= (k < F ? H : M) + count, "pair", m, k, F);
+            }
+        }
+    free(H);
+    free(M);
+}
+
 int main()
 {
+    for (int F : {2, 8, 16, 30, 32, 34, 48, 50, 64, 96, 100, 150, 256})
+        for (int n : {1, 3})
+            for (int pitch : {0, 2, 6})
+                for (int less : {0, 1, 7}) {
+                    if (less < F) rows16(n, F, F - less, pitch, true);
+                    rows16(n, F, F, pitch, false);
+                }
     for (int F : {1, 2, 3, 4, 5, 7, 8, 12, 15, 16, 17, 20, 31, 32, 33, 48, 50, 63, 64, 90, 100, 128, 150}) {
         for (int n : {1, 2, 5})
             for (int pitch : {0, 1, 3, 4}) rows(n, F, pitch, false), rows(n, F, pitch, true);

@@ -1,0 +1,83 @@
+"""The bf16 products over many rows at the edges of their tiles and slabs of 32 k-values: the last tile of 256 rows whole, cut and
+of one row; widths of every tile; halves that end at every kind of place of a slab; padding that holds NaN and must reach nothing.
+Bounds as in test_gpu_bf16_products.py."""
+import pytest
+
+from test_gpu_bf16_products import B, bf16, within  # noqa: F401  (B: the fixture)
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def inside(a, pitch, before):
+    """`a` on the GPU at an offset of `before` elements, rows `pitch` apart, NaN around and between the rows."""
+    n, f = a.shape
+    t = torch.full((before + n * pitch + 8,), float("nan"), dtype=a.dtype, device="cuda")
+    view = t[before:before + n * pitch].view(n, pitch)[:, :f]
+    view.copy_(a)
+    return view
+
+
+def ring(n):
+    """Every node's one neighbour is the next: aggregating rolls the rows."""
+    nodes = torch.arange(n, dtype=torch.int32)
+    return torch.arange(n + 1, dtype=torch.int32).cuda(), ((nodes + 1) % n).cuda(), torch.ones(n, device="cuda")
+
+
+def even(x):
+    return (x + 1) // 2 * 2
+
+
+# aggregated first: forward [H | M] [W_self ; W_neigh] + b, backward dZ [W_self^T | W_neigh^T] with and without the mask
+@pytest.mark.parametrize("n,fi,fo", [(65536, 64, 72), (65537, 32, 96), (65792, 96, 128), (65535 + 256, 128, 256), (65600, 32, 70), (65600, 160, 98),
+                                     (65664, 16, 130), (65540, 150, 150), (65540, 66, 300), (65540, 200, 258), (65601, 100, 256)])
+@pytest.mark.parametrize("relu", [False, True])
+def test_layer(B, n, fi, fo, relu):
+    assert B.tma_sage_layer_aggregates_first(fi, fo, B.TMA_BF16)
+    act = B.TMA_ACT_RELU if relu else B.TMA_ACT_NONE
+    rowptr, col, inv = ring(n)
+    X, Ws, Wn, g = bf16(1, n, fi), bf16(2, fi, fo), bf16(3, fi, fo), bf16(4, n, fo)
+    pitch = even(fi) + 2
+    H = inside(X, pitch, 2)
+    M, out = inside(torch.zeros_like(X), pitch, 4), inside(torch.zeros(n, fo).bfloat16(), even(fo) + 4, 2)
+    w = Ws.float().cuda(), Wn.float().cuda()
+    B.tma_sage_layer_fwd(rowptr, col, inv, H, *w, torch.zeros(fo, device="cuda"), act, M_out=M, Hnext_out=out,
+                         Wt=B.tma_sage_prepare_weights_bf16(*w))
+    Z = torch.cat([X, X.roll(-1, 0)], 1), torch.cat([Ws, Wn])
+    if not relu:
+        within(out, *Z, True, "forward")
+    h = bf16(5, n, fo)
+    h[::7, 1], h[::5, 0] = float("nan"), float("inf")      # not above zero, and above
+    h[::3, fo - 1] = 0.0
+    d = torch.where(h > 0, g, torch.zeros(()).bfloat16()) if relu else g
+    dH = inside(torch.zeros_like(X), pitch, 2)
+    back = torch.zeros(n + 1, dtype=torch.int32, device="cuda")          # no entries: dH is dZ W_self^T
+    B.tma_sage_layer_bwd(back, col, inv, H, M, inside(h, even(fo) + 4, 2), inside(g, even(fo) + 4, 2), *w, act, dH_out=dH)
+    within(dH, d, Ws.T, True, "input gradient")
+    into = (torch.arange(n, dtype=torch.int32) - 1) % n                  # the transposed ring
+    B.tma_sage_layer_bwd(rowptr, into.int().cuda(), inv, H, M, inside(h, even(fo) + 4, 2), inside(g, even(fo) + 4, 2), *w, act, dH_out=dH)
+    # (two roundings more on the way: of dZ W_neigh^T and of the first part of the sum)
+    got, a, b = dH.double().cpu(), torch.cat([d, d.roll(1, 0)], 1).double(), torch.cat([Ws.T, Wn.T]).double()
+    bound = 3 * 2.0 ** -8 * ((d.double() @ Ws.T.double()).abs() + (d.roll(1, 0).double() @ Wn.T.double()).abs()) + 2.0 ** -20 * (a.abs() @ b.abs()) + 1e-30
+    assert torch.all((got - a @ b).abs() <= bound)
+
+
+# transformed first: H [W_self | W_neigh], and [dZ | dYn] [W_self | W_neigh]^T, with outputs of odd width too
+@pytest.mark.parametrize("n,fi,fo", [(98304, 256, 47), (98305, 128, 41), (98560, 64, 5), (98400, 96, 48), (98432, 96, 33), (98500, 320, 140),
+                                     (98310, 128, 50)])
+def test_transform_first(B, n, fi, fo):
+    assert not B.tma_sage_layer_aggregates_first(fi, fo, B.TMA_BF16)
+    rowptr, col, inv = ring(n)
+    X, Ws, Wn, g = bf16(1, n, fi), bf16(2, fi, fo), bf16(3, fi, fo), bf16(4, n, fo)
+    w = Ws.float().cuda(), Wn.float().cuda()
+    pitch = even(fi) + 2
+    H = inside(X, pitch, 2)
+    out = B.tma_sage_layer_fwd(rowptr, col, inv, H, *w, torch.zeros(fo, device="cuda"), B.TMA_ACT_NONE)[1]
+    x, y = X.double() @ Ws.double(), X.roll(-1, 0).double() @ Wn.double()
+    sums = X.abs().double() @ Ws.abs().double() + X.roll(-1, 0).abs().double() @ Wn.abs().double()
+    assert torch.all((out.double().cpu() - x - y).abs() <= 2 * 2.0 ** -8 * (x.abs() + y.abs()) + 2.0 ** -20 * sums + 1e-30)
+    into = (torch.arange(n, dtype=torch.int32) - 1) % n
+    dH = inside(torch.zeros_like(X), pitch, 2)
+    room = inside(g, (fo + 7) // 8 * 8, 8)
+    B.tma_sage_layer_bwd(rowptr, into.int().cuda(), inv, H, H, None, room, *w, B.TMA_ACT_NONE, dH_out=dH)
+    within(dH, torch.cat([g, g.roll(1, 0)], 1), torch.cat([Ws.T, Wn.T]), True, "input gradient")
