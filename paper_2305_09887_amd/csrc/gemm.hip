@@ -50,7 +50,6 @@ static void fwd_dispatch(int64_t n, const uint16_t *H, int64_t ldh, const uint16
 static void fwd_prepared(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *M, int64_t ldm, int F_in,
                          const uint16_t *Wt, const FwdEpilogue<uint16_t> &e, int F_out, hipStream_t s)
 {
-    if (stream_sage_fwd(n, H, ldh, M, ldm, F_in, Wt, e.bias, F_out, e.relu, e.out, e.ld, s)) return;
     CatRows<uint16_t, true> a{H, ldh, M, ldm, F_in, n, 2 * F_in};
     CatRows<uint16_t, true> b{Wt, 2 * int64_t(F_in), Wt, 2 * int64_t(F_in), 2 * F_in, F_out, 2 * F_in};
     const int64_t K = 2 * int64_t(F_in);
@@ -114,6 +113,9 @@ int launch_sage_gemm_fwd(int64_t n, const void *H, int64_t ldh, const void *M, i
     if (n == 0 || F_out == 0) return TMA_OK;
     if (Wt_bf16 && dtype == TMA_BF16) {
         const uint16_t *h = static_cast<const uint16_t *>(H), *m = static_cast<const uint16_t *>(M);
+        if (stream_sage_fwd(n, h, ldh, m, ldm, F_in, static_cast<const uint16_t *>(Wt_bf16), bias, F_out, act == TMA_ACT_RELU,
+                            static_cast<uint16_t *>(Hnext), ld_next, stream))
+            return check_launch("sage gemm fwd");
         // the packed path needs groups of four bf16 at 8-byte aligned addresses in both operands
         if (vec4_ok(h, ldh) && vec4_ok(m, ldm) && F_in % 4 == 0 && aligned(Wt_bf16, 8)) {
             FwdEpilogue<uint16_t> e{static_cast<uint16_t *>(Hnext), ld_next, bias, act == TMA_ACT_RELU};

@@ -77,13 +77,16 @@ struct Fetch16 {
     }
 };
 
-// the values of g where h > 0 (h NaN: not), zeros elsewhere; two bf16 in a word
+// The values of g where h > 0 (h NaN: not), zeros elsewhere; two bf16 in a word.  In assembler: the compiler makes compares and selects
+// of it, half by half, eight instructions with waits between them.
 __device__ __forceinline__ uint32_t where_positive(uint32_t g, uint32_t h)
 {
-    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-    const u16x2 bits = __builtin_bit_cast(u16x2, h) - u16x2{1, 1};              // 0 .. 0x7F7F: positive, up to infinity
-    const u16x2 one = __builtin_elementwise_min(__builtin_elementwise_sub_sat(u16x2{0x7F80, 0x7F80}, bits), u16x2{1, 1});
-    return __builtin_bit_cast(uint32_t, u16x2(__builtin_bit_cast(u16x2, g) * one));
+    uint32_t bits, under, one, out;
+    asm("v_pk_sub_u16 %0, %1, %2" : "=v"(bits) : "v"(h), "s"(0x00010001u));                   // 0 .. 0x7F7F: positive, up to infinity
+    asm("v_pk_sub_u16 %0, %1, %2 clamp" : "=v"(under) : "s"(0x7F807F80u), "v"(bits));          // above zero for those
+    asm("v_pk_min_u16 %0, %1, %2" : "=v"(one) : "v"(under), "s"(0x00010001u));
+    asm("v_pk_mul_lo_u16 %0, %1, %2" : "=v"(out) : "v"(g), "v"(one));
+    return out;
 }
 
 // C[M,N] = A[M,K] B[N,K]^T.  kMask: A's elements count where `mask`, an array like A's only part, is positive.  Persistent blocks
@@ -307,6 +310,276 @@ static void launch_async16(const char *name, const AsyncRows16 &a, const uint16_
     TMA_TIMED(name, s);
     hipLaunchKernelGGL((gemm_bf16_async_kernel<BM, BN, WM, WN, kStages, kMask, Epi>), dim3(unsigned(blocks_per_die * kXcds)), dim3(WM * WN * 64), 0, s, a,
                        mask, b, e, M, N, n_tiles, total);
+}
+
+// ---------------------------------------------------------------------------
+// Weight gradients of bf16 storage: C[M,N] = A^T B summed over nodes, the k side, both operands rows of nodes.  They come into LDS as
+// they lie, [32 nodes][columns], and ds_read_b64_tr_b16 turns them: of four nodes' 16 columns, which the lanes of a quarter
+// wavefront address in pieces of four, each lane receives one column.  (gemm_bf16_kernel gathers the same fragments in eight
+// 2-byte reads.)  The rest as in gemm_bf16_async_kernel: tiles of 256 rows of the result, so that the nodes' rows are read once or
+// twice, and a ring of slabs that is bound by the memory alone.
+// ---------------------------------------------------------------------------
+
+// X[k][c], columns of one or two parts of F each, padded to Fq (a multiple of eight): c < Fq ? P0[k][c] : P1[k][c-Fq].  What is read in the
+// place of padding is anything: it reaches only results of its own column, which are not stored.
+struct AsyncCols16 {
+    const uint16_t *P0;
+    int64_t ld0;
+    const uint16_t *P1;
+    int64_t ld1;
+    int F, Fq, width;      // width: Fq or 2 Fq
+    int64_t rows;
+    __host__ __device__ __forceinline__ bool second(int c) const { return c >= Fq && c < width; }
+    __host__ __device__ __forceinline__ int column(int c) const
+    {
+        const int cc = c - (second(c) ? Fq : 0);
+        return cc < F ? cc : 0;
+    }
+    __host__ __device__ __forceinline__ int64_t ld(int c) const { return second(c) ? ld1 : ld0; }
+    // column c of node k; eight from there on may be read if another row follows
+    __host__ __device__ __forceinline__ const uint16_t *piece(int64_t k, int c) const { return (second(c) ? P1 : P0) + k * ld(c) + column(c); }
+    // the pair of columns c, c + 1 (c even)
+    __host__ __device__ __forceinline__ const uint16_t *at(int64_t k, int c, const void *zeros) const
+    {
+        return k < rows ? piece(k, c) : static_cast<const uint16_t *>(zeros);
+    }
+    __host__ bool ok() const
+    {
+        const auto even = [&](const uint16_t *p, int64_t l) { return (reinterpret_cast<uintptr_t>(p) & 3) == 0 && l % 2 == 0 && l >= F + F % 2 && l <= (1 << 21); };
+        return F >= 8 && even(P0, ld0) && (width == Fq || even(P1, ld1));
+    }
+};
+
+// A slab of 32 nodes and COLS columns on its way into LDS, [32][COLS], the groups of four pieces of a node's row exchanged by its number.
+template <int COLS, int kWaves>
+struct FetchCols16 {
+    static constexpr int kPieces = COLS / 8, kI = kPieces / 2, kLoads = kI / kWaves;
+    static_assert(kI % kWaves == 0 && kPieces >= 16 && (kPieces & (kPieces - 1)) == 0, "columns of a slab");
+    const char *from[kLoads];
+    uint32_t step[kLoads];
+    // (16-byte place in the slab: its node, its first column)
+    static __device__ __forceinline__ int node(int place) { return place / kPieces; }
+    static __device__ __forceinline__ int column(int place) { return ((place % kPieces) ^ (4 * (node(place) & 3))) * 8; }
+    __device__ __forceinline__ void enter(const AsyncCols16 &x, int64_t k, int c0, int wave, int lane)
+    {
+#pragma unroll
+        for (int v = 0; v < kLoads; ++v) {
+            const int place = (v * kWaves + wave) * 64 + lane, c = c0 + column(place);
+            from[v] = reinterpret_cast<const char *>(x.piece(k + node(place), c));
+            step[v] = uint32_t(x.ld(c)) * 2u * uint32_t(kAsyncK16);
+        }
+    }
+    __device__ __forceinline__ void whole(uint32_t to, int64_t shift, int wave) const
+    {
+#pragma unroll
+        for (int v = 0; v < kLoads; ++v) lds_fetch<4>(to + uint32_t(v * kWaves + wave) * 1024u, reinterpret_cast<const float *>(from[v] + shift));
+    }
+    __device__ __forceinline__ void advance()
+    {
+#pragma unroll
+        for (int v = 0; v < kLoads; ++v) from[v] += step[v];
+    }
+    // any nodes, pair by pair
+    __device__ __forceinline__ static void slowly(const AsyncCols16 &x, int64_t k, int c0, uint32_t to, int wave, int lane)
+    {
+#pragma unroll 1
+        for (int v = 0; v < 4 * kLoads; ++v) {
+            const int q = v * kWaves + wave, place = q * 16 + lane / 4;
+            lds_fetch<1>(to + uint32_t(q) * 256u, reinterpret_cast<const float *>(x.at(k + node(place), c0 + column(place) + (lane & 3) * 2, kZeros)));
+        }
+    }
+};
+
+typedef short shortx4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) shortx4 lds_shortx4;
+// eight k-values of a lane's column: of nodes 0..3 and 4..7 from `at` on, `row` elements apart
+__device__ __forceinline__ uint4 turned(const uint16_t *at, int row)
+{
+    const uint2 lo = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(at)));
+    const uint2 hi = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_shortx4 *)(at + 4 * row)));
+    return make_uint4(lo.x, lo.y, hi.x, hi.y);
+}
+__device__ __forceinline__ float sum_of(const uint4 &v)
+{
+    const auto two = [](uint32_t w) { return __uint_as_float(w << 16) + __uint_as_float(w & 0xFFFF0000u); };
+    return (two(v.x) + two(v.y)) + (two(v.z) + two(v.w));
+}
+
+// partial[split][m][n] and colsum_partial[split][n] (the sums over nodes of B); work items (split, m-tile, n-tile) numbered as in gemm_bf16_kernel
+template <int BN, int WN, int kStages, bool kMask>
+__global__ __launch_bounds__(256 * WN, WN == 2 ? 2 : 1) void gemm_bf16_weight_kernel(AsyncCols16 a, AsyncCols16 b, const uint16_t *mask,
+                                                                                    int64_t k_per_split, int N, int n_tiles, int tiles,
+                                                                                    int64_t total_work, float *__restrict__ partial,
+                                                                                    float *__restrict__ colsum_partial)
+{
+    constexpr int BM = 256, kWaves = 4 * WN, TM = 2, TN = BN / WN / 32;
+    typedef FetchCols16<BM, kWaves> FA;
+    typedef FetchCols16<BN, kWaves> FB;
+    constexpr int kA = BM * kAsyncK16, kB = BN * kAsyncK16;
+    constexpr int kLoads = FA::kLoads + (kMask ? 2 : 1) * FB::kLoads, kAhead = kStages - 1, kYoung = (kAhead - 1) * kLoads;
+    static_assert(TN == 4 && kYoung <= 63, "wavefront (m, n) sums column block m of its four");
+
+    __shared__ __attribute__((aligned(1024))) uint16_t As[kStages][kA];
+    __shared__ __attribute__((aligned(1024))) uint16_t Bs[kStages][kB];
+    __shared__ __attribute__((aligned(1024))) uint16_t Ms[kMask ? kStages : 1][kMask ? kB : 8];
+
+    const int tid = threadIdx.x, lane = tid & 63, l31 = lane & 31, hi = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave / WN, wn = wave % WN;
+
+    const int64_t blocks_per_die = gridDim.x / kXcds;
+    const int64_t per_die = (total_work + kXcds - 1) / kXcds;
+    const int64_t die = blockIdx.x % kXcds;
+    int64_t die_end = (die + 1) * per_die;
+    if (die_end > total_work) die_end = total_work;
+    int64_t work = die * per_die + blockIdx.x / kXcds;
+    if (work >= die_end) return;
+
+    const uint32_t as0 = lds_address(&As[0][0]), bs0 = lds_address(&Bs[0][0]), ms0 = lds_address(&Ms[0][0]);
+    const int64_t nodes = a.rows, to_mask = kMask ? reinterpret_cast<intptr_t>(mask) - reinterpret_cast<intptr_t>(b.P0) : 0;
+    auto end_of = [&](int64_t split) { return (split + 1) * k_per_split < nodes ? (split + 1) * k_per_split : nodes; };
+    // ---- the cursor: the slab that is fetched next
+    int64_t c_work = work, c_k = 0, c_end = 0;
+    int c_m0 = 0, c_n0 = 0;
+    uint32_t c_stage = 0;
+    bool c_open = true, c_fresh = true;
+    FA fa;
+    FB fb;
+    auto fetch_next = [&]() {
+        if (!c_open) return;
+        const uint32_t a_to = as0 + c_stage * uint32_t(kA * 2), b_to = bs0 + c_stage * uint32_t(kB * 2), m_to = ms0 + c_stage * uint32_t(kB * 2);
+        if (c_fresh) {
+            const int64_t split = c_work / tiles;
+            const int tile = int(c_work % tiles);
+            c_m0 = tile / n_tiles * BM;
+            c_n0 = tile % n_tiles * BN;
+            c_k = split * k_per_split;
+            c_end = end_of(split);
+            fa.enter(a, c_k, c_m0, wave, lane);
+            fb.enter(b, c_k, c_n0, wave, lane);
+            c_fresh = false;
+        }
+        if (c_k + kAsyncK16 < nodes) {     // (a piece may run past the end of its row: not in the last one)
+            fa.whole(a_to, 0, wave);
+            fb.whole(b_to, 0, wave);
+            if constexpr (kMask) fb.whole(m_to, to_mask, wave);
+            fa.advance();
+            fb.advance();
+        } else {
+            FA::slowly(a, c_k, c_m0, a_to, wave, lane);
+            FB::slowly(b, c_k, c_n0, b_to, wave, lane);
+            if constexpr (kMask) {
+                AsyncCols16 m = b;
+                m.P0 = mask;
+                FB::slowly(m, c_k, c_n0, m_to, wave, lane);
+            }
+        }
+        c_stage = c_stage == kStages - 1 ? 0 : c_stage + 1;
+        c_k += kAsyncK16;
+        if (c_k >= c_end) {
+            c_work += blocks_per_die;
+            c_open = c_work < die_end;
+            c_fresh = true;
+        }
+    };
+#pragma unroll
+    for (int s = 0; s < kAhead; ++s) fetch_next();
+
+    // this lane's place in its quarter wavefront's 4 x 16 block, of nodes and columns as the fragment of a group wants them
+    const int quarter = lane >> 4, i = lane & 15, swap = i >> 2;
+    const int node0 = 8 * (quarter >> 1) + (i >> 2), col0 = 16 * (quarter & 1) + 4 * (i & 3);
+    auto offset = [&](int block, int row) { return node0 * row + (((block & ~3) | ((block & 3) ^ swap)) * 32) + col0; };   // block: 32 columns
+    int a_at[TM], b_at[TN];
+#pragma unroll
+    for (int t = 0; t < TM; ++t) a_at[t] = offset(wm * TM + t, BM);
+#pragma unroll
+    for (int t = 0; t < TN; ++t) b_at[t] = offset(wn * TN + t, BN);
+    int stage = 0;
+    for (;; work += blocks_per_die) {
+        const int64_t split = work / tiles;
+        const int tile = int(work % tiles), m0 = tile / n_tiles * BM, n0 = tile % n_tiles * BN;
+        const int n_slabs = int((end_of(split) - split * k_per_split + kAsyncK16 - 1) / kAsyncK16);
+        const bool sums = m0 == 0;
+        float colsum = 0.0f;
+        floatx16 acc[TM][TN];
+#pragma unroll
+        for (int t = 0; t < TM; ++t)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[t][j][r] = 0.0f;
+
+        for (int s = 0; s < n_slabs; ++s) {
+            if (!c_open) wait_and_meet<0>();
+            else wait_and_meet<kYoung>();
+            fetch_next();       // into the buffer that every wavefront has read before this meeting
+            const uint16_t *A0 = &As[0][0] + stage * kA, *B0 = &Bs[0][0] + stage * kB, *M0 = &Ms[0][0] + (kMask ? stage * kB : 0);
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+                uint4 xa[TM], xb[TN];
+#pragma unroll
+                for (int t = 0; t < TM; ++t) xa[t] = turned(A0 + a_at[t] + g * 16 * BM, BM);
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    xb[j] = turned(B0 + b_at[j] + g * 16 * BN, BN);
+                    if constexpr (kMask) {
+                        const uint4 h = turned(M0 + b_at[j] + g * 16 * BN, BN);
+                        xb[j] = make_uint4(where_positive(xb[j].x, h.x), where_positive(xb[j].y, h.y), where_positive(xb[j].z, h.z),
+                                           where_positive(xb[j].w, h.w));
+                    }
+                }
+#pragma unroll
+                for (int t = 0; t < TM; ++t)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        acc[t][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, xa[t]), __builtin_bit_cast(bf16x8, xb[j]),
+                                                                            acc[t][j], 0, 0, 0);
+                if (sums) {
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        if (wm == j) colsum += sum_of(xb[j]);
+                }
+            }
+            stage = stage == kStages - 1 ? 0 : stage + 1;
+        }
+
+        // MFMA 32x32 result layout: register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4, column l%32.
+        float *out = partial + split * int64_t(a.width == a.Fq ? a.F : 2 * a.F) * N;
+#pragma unroll
+        for (int t = 0; t < TM; ++t)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int m = m0 + (wm * TM + t) * 32 + 8 * (r / 4) + 4 * hi + r % 4;
+                const int c = m - (a.second(m) ? a.Fq : 0);
+                if (c < a.F && m < a.width) {
+                    float *row = out + (c + (a.second(m) ? a.F : 0)) * int64_t(N);
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        const int n = n0 + (wn * TN + j) * 32 + l31;
+                        if (n < N) row[n] = acc[t][j][r];
+                    }
+                }
+            }
+        if (sums) {
+            colsum += __shfl_xor(colsum, 32, kWave);
+            const int n = n0 + (wn * TN + wm) * 32 + l31;
+            if (hi == 0 && n < N) colsum_partial[split * N + n] = colsum;
+        }
+        if (work + blocks_per_die >= die_end) break;
+    }
+}
+
+template <int BN, int WN, int kStages, bool kMask>
+static void launch_weight16(const char *name, const AsyncCols16 &a, const AsyncCols16 &b, const uint16_t *mask, int N, int64_t k_per_split,
+                            int n_splits, float *partial, float *colsum, hipStream_t s)
+{
+    static_assert(kStages * (256 + (kMask ? 2 : 1) * BN) * 64 <= 152 * 1024, "LDS of a unit");
+    const int n_tiles = int(ceil_div(N, BN)), tiles = int(ceil_div(a.width, 256)) * n_tiles;
+    const int64_t total = int64_t(tiles) * n_splits;
+    int64_t blocks_per_die = ceil_div(total, kXcds);
+    if (blocks_per_die > 32) blocks_per_die = 32;
+    TMA_TIMED(name, s);
+    hipLaunchKernelGGL((gemm_bf16_weight_kernel<BN, WN, kStages, kMask>), dim3(unsigned(blocks_per_die * kXcds)), dim3(256 * WN), 0, s, a, b, mask,
+                       k_per_split, N, n_tiles, tiles, total, partial, colsum);
 }
 
 }  // namespace tma

@@ -1660,10 +1660,4 @@ static void launch_by_width(const char *name, const AL &a, const BL &b, const Ep
     else launch_gemm<128, 128, BK, 2, 2, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
 }
 
-struct WeightSplit {
-    int n_splits;
-    int64_t k_per_split;
-    size_t partial_bytes, colsum_bytes;
-};
-
 }  // namespace tma

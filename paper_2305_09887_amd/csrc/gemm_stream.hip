@@ -115,4 +115,56 @@ bool stream_sage_tf_bwd_data(int64_t n, const uint16_t *dHnext, int64_t ld_next,
     return true;
 }
 
+// ---- weight gradients
+// A tile of 256 rows per compute unit and twice that from kStreamRows on, where the partial results are a small part of the bytes; not
+// where most of a tile is padding.  us, gemm_bf16_kernel -> here, both with the second stage:
+//   with ReLU, 65,536 / 181,000 / 1,500,000 nodes: 128 -> 256 64 -> 52 / 125 -> 77 / 569 -> 480, 256 -> 256 92 -> 56 / 211 -> 110 / 941 -> 751,
+//   100 -> 128 50 -> 39 / 79 -> 55 / 421 -> 295, 120 -> 64 31 -> 37 / 55 -> 51 / 326 -> 266, 64 -> 64 35 -> 36 / 46 -> 54 / 181 -> 306;
+//   150 -> 150, element by element before, 195 -> 50 / 503 -> 88 / 4,850 -> 647; 256 -> 256 without ReLU 84 -> 46 / 191 -> 78 / 846 -> 472 (4.9 TB/s)
+//   transformed first: 256 -> 47 49 -> 43 / 87 -> 65 / 434 -> 301, 128 -> 47 38 -> 47 / 69 -> 69 / 271 -> 251, 128 -> 20 83 -> 89 at 400,000
+bool plan_stream_weight(int64_t n, int32_t F_in, int32_t F_out, size_t ws_bytes, WeightSplit &w)
+{
+    if (F_in < 8 || F_out < 8 || (F_in <= 64 && F_out <= 64) || n < (F_out <= 64 ? 2 * kManyRows : kManyRows)) return false;
+    const int64_t tiles = ceil_div(2 * round_up(size_t(F_in), 8), 256) * ceil_div(F_out, F_out > 128 ? 256 : 128);
+    int64_t want = (n >= kStreamRows ? 512 : 256) / tiles;
+    if (want < 1) want = 1;
+    const size_t per_split = size_t(2) * F_in * F_out * 4 + size_t(F_out) * 4;
+    if (ws_bytes < 512 + per_split) return false;
+    if (size_t(want) > (ws_bytes - 512) / per_split) want = int64_t((ws_bytes - 512) / per_split);
+    w.k_per_split = int64_t(round_up(size_t(ceil_div(n, want)), kAsyncK16));
+    w.n_splits = int(ceil_div(n, w.k_per_split));
+    w.partial_bytes = round_up(size_t(w.n_splits) * 2 * size_t(F_in) * size_t(F_out) * 4, 256);
+    w.colsum_bytes = round_up(size_t(w.n_splits) * size_t(F_out) * 4, 256);
+    return true;
+}
+
+bool stream_sage_bwd_weight(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *M, int64_t ldm, const uint16_t *dHnext, const uint16_t *Hnext,
+                            int64_t ld_next, int F_in, int F_out, bool relu, const WeightSplit &w, float *partial, float *colsum, hipStream_t s)
+{
+    const int Fq = int(round_up(size_t(F_in), 8)), No = int(round_up(size_t(F_out), 8));
+    const AsyncCols16 a{H, ldh, M, ldm, F_in, Fq, 2 * Fq, n}, b{dHnext, ld_next, dHnext, ld_next, F_out, No, No, n};
+    if (!a.ok() || !b.ok() || (relu && !aligned(Hnext, 4))) return false;
+    if (F_out > 128) {
+        const char *name = "gemm_bwd_weight_256x256_bf16";
+        if (relu) launch_weight16<256, 2, 3, true>(name, a, b, Hnext, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
+        else launch_weight16<256, 2, 4, false>(name, a, b, nullptr, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
+    } else {
+        const char *name = F_out <= 64 ? "gemm_bwd_weight_128x64_bf16" : "gemm_bwd_weight_128x128_bf16";
+        if (relu) launch_weight16<128, 1, 4, true>(name, a, b, Hnext, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
+        else launch_weight16<128, 1, 6, false>(name, a, b, nullptr, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
+    }
+    return true;
+}
+
+bool stream_sage_tf_bwd_weight(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *dHnext, int64_t ld_next, const uint16_t *dYn, int64_t ldy,
+                               int F_in, int F_out, int Fp, const WeightSplit &w, float *partial, float *colsum, hipStream_t s)
+{
+    const int Fq = int(round_up(size_t(F_in), 8));
+    const AsyncCols16 a{H, ldh, H, ldh, F_in, Fq, Fq, n}, b{dHnext, ld_next, dYn, ldy, F_out, Fp, 2 * Fp, n};
+    if (n < (F_in <= 128 ? kStreamRows : kManyRows) || !a.ok() || !b.ok()) return false;
+    if (2 * Fp > 128) launch_weight16<256, 2, 4, false>("gemm_tf_bwd_weight_bf16", a, b, nullptr, 2 * Fp, w.k_per_split, w.n_splits, partial, colsum, s);
+    else launch_weight16<128, 1, 6, false>("gemm_tf_bwd_weight_bf16", a, b, nullptr, 2 * Fp, w.k_per_split, w.n_splits, partial, colsum, s);
+    return true;
+}
+
 }  // namespace tma

@@ -192,6 +192,10 @@ int launch_sage_tf_gemm_bwd_weight(int64_t n, const void *H, int64_t ldh, const 
     int rc = TMA_OK;
     if (n == 0) {
         // no rows: nothing to multiply (operands may be NULL); the second stage writes the zero gradients
+    } else if (dtype == TMA_BF16 && !relu &&
+               stream_sage_tf_bwd_weight(n, static_cast<const uint16_t *>(H), ldh, static_cast<const uint16_t *>(dHnext), ld_next,
+                                         static_cast<const uint16_t *>(dYn), ldy, F_in, F_out, Fp, w, partial, colsum, stream)) {
+        rc = check_launch("sage gemm tf bwd weight");
     } else if (dtype == TMA_F32)
         rc = tf_bwd_weight_typed<float>(n, static_cast<const float *>(H), ldh, static_cast<const float *>(dHnext),
                                         static_cast<const float *>(Hnext), ld_next, static_cast<const float *>(dYn),

@@ -70,27 +70,12 @@ int launch_reduce_splits(const float *partial, const float *colsum_partial, int 
 
 // ---- backward: weights ------------------------------------------------------
 
-// wide: 256 x 256 tiles (bf16 storage with F_out > 128: the product is bound by streaming its two operands, which
-// 128 x 128 tiles read two and four times: 54 GB instead of 16 GB per launch on a 12.5 M-row part); fewer tiles then
-// need more splits to fill the chip, capped so that the partial results stay under a quarter of the operands'
-// bytes.  Below some 4e5 rows that cap leaves too few work items and the narrow tiles are faster (95 vs 109 us at
-// 125 k rows), above it the wide ones are (2 M rows: 1.17 -> 0.73 ms for 128 -> 256, 2.47 -> 1.42 ms for 256 -> 256).
-static bool wide_weight_tiles(int64_t n, int32_t F_in, int32_t F_out, int elem_bytes)
+static WeightSplit plan_weight_split(int64_t n, int32_t F_in, int32_t F_out)
 {
-    return elem_bytes == 2 && F_out > 128 && F_out <= 256 && F_in >= 128 && n >= 400000;
-}
-
-static WeightSplit plan_weight_split(int64_t n, int32_t F_in, int32_t F_out, bool wide = false)
-{
-    const int bn = wide ? 256 : (F_out <= 64 ? 64 : 128);
-    const int64_t tiles = ceil_div(2 * int64_t(F_in), wide ? 256 : 128) * ceil_div(F_out, bn);
+    const int64_t tiles = ceil_div(2 * int64_t(F_in), 128) * ceil_div(F_out, F_out <= 64 ? 64 : 128);
     int64_t want = ceil_div(512, tiles > 0 ? tiles : 1);
     const int64_t max_useful = ceil_div(n > 0 ? n : 1, 128);
     if (want > max_useful) want = max_useful;
-    if (wide) {
-        const int64_t cap = (n > 0 ? n : 1) * (2 * int64_t(F_in) + F_out) * 2 / 4 / (2 * int64_t(F_in) * F_out * 4);
-        if (want > cap) want = cap;
-    }
     if (want < 1) want = 1;
     WeightSplit w;
     w.k_per_split = int64_t(round_up(size_t(ceil_div(n > 0 ? n : 1, want)), 32));
@@ -100,14 +85,12 @@ static WeightSplit plan_weight_split(int64_t n, int32_t F_in, int32_t F_out, boo
     return w;
 }
 
-size_t sage_gemm_bwd_weight_workspace_bytes(int64_t n, int32_t F_in, int32_t F_out)
+size_t sage_gemm_bwd_weight_workspace_bytes(int64_t n, int32_t F_in, int32_t F_out, bool least)
 {
     const WeightSplit w = plan_weight_split(n, F_in, F_out);
     size_t bytes = w.partial_bytes + w.colsum_bytes;
-    if (wide_weight_tiles(n, F_in, F_out, 2)) {   // the query does not know the storage type: room for either plan
-        const WeightSplit v = plan_weight_split(n, F_in, F_out, true);
-        if (v.partial_bytes + v.colsum_bytes > bytes) bytes = v.partial_bytes + v.colsum_bytes;
-    }
+    WeightSplit u;
+    if (!least && plan_stream_weight(n, F_in, F_out, SIZE_MAX, u) && u.partial_bytes + u.colsum_bytes > bytes) bytes = u.partial_bytes + u.colsum_bytes;
     return bytes;
 }
 
@@ -122,16 +105,9 @@ static void bwd_weight_launch(const AView &a, const BView &b, const Epi &e, int6
     else if (F_out <= 64)
         launch_gemm<128, 64, 32, 4, 1, true, T>(V ? "gemm_bwd_weight_128x64_bf16" : "gemm_bwd_weight_128x64_bf16_generic", a, b, e,
                                                 Mtot, F_out, n, w.k_per_split, w.n_splits, colsum, s);
-    else if constexpr (V) {
-        if (wide_weight_tiles(n, F_in, F_out, 2))
-            launch_gemm<256, 256, 32, 4, 2, true, T>("gemm_bwd_weight_256x256_bf16", a, b, e, Mtot, F_out, n, w.k_per_split,
-                                                     w.n_splits, colsum, s);
-        else
-            launch_gemm<128, 128, 32, 2, 2, true, T>("gemm_bwd_weight_128x128_bf16", a, b, e, Mtot, F_out, n, w.k_per_split,
-                                                     w.n_splits, colsum, s);
-    } else
-        launch_gemm<128, 128, 32, 2, 2, true, T>("gemm_bwd_weight_128x128_bf16_generic", a, b, e, Mtot, F_out, n, w.k_per_split,
-                                                 w.n_splits, colsum, s);
+    else
+        launch_gemm<128, 128, 32, 2, 2, true, T>(V ? "gemm_bwd_weight_128x128_bf16" : "gemm_bwd_weight_128x128_bf16_generic", a, b, e,
+                                                 Mtot, F_out, n, w.k_per_split, w.n_splits, colsum, s);
 }
 
 template <typename T, bool VA, bool VB, bool kRelu>
@@ -185,11 +161,7 @@ int launch_sage_gemm_bwd_weight(int64_t n, const void *H, int64_t ldh, const voi
     if (dtype != TMA_F32 && dtype != TMA_BF16) return fail(TMA_ERR_UNSUPPORTED_DTYPE, "sage gemm bwd: dtype %d", dtype);
     if (F_out == 0) return TMA_OK;
     const bool relu_ = act == TMA_ACT_RELU;
-    const bool all_vec = dtype == TMA_BF16 && vec4_ok(static_cast<const uint16_t *>(H), ldh) &&
-                         vec4_ok(static_cast<const uint16_t *>(M), ldm) && F_in % 4 == 0 &&
-                         vec4_ok(static_cast<const uint16_t *>(dHnext), ld_next) &&
-                         (!relu_ || vec4_ok(static_cast<const uint16_t *>(Hnext), ld_next));
-    const WeightSplit w = plan_weight_split(n, F_in, F_out, all_vec && wide_weight_tiles(n, F_in, F_out, 2));
+    const WeightSplit w = plan_weight_split(n, F_in, F_out);
     if (ws_bytes < w.partial_bytes + w.colsum_bytes)
         return fail(TMA_ERR_WORKSPACE_TOO_SMALL, "sage gemm bwd weight: workspace %zu < %zu", ws_bytes,
                     w.partial_bytes + w.colsum_bytes);
@@ -200,6 +172,16 @@ int launch_sage_gemm_bwd_weight(int64_t n, const void *H, int64_t ldh, const voi
     // An empty node set leaves nothing to multiply: the operands may then be NULL, and the kernel's clamped
     // loads would have no valid row to fall back to.  The second stage alone writes the zero gradients.
     const bool have_rows = F_in > 0 && n > 0;
+    WeightSplit u;
+    if (dtype == TMA_BF16 && have_rows && plan_stream_weight(n, F_in, F_out, ws_bytes, u)) {
+        colsum = reinterpret_cast<float *>(static_cast<char *>(ws) + u.partial_bytes);
+        if (stream_sage_bwd_weight(n, static_cast<const uint16_t *>(H), ldh, static_cast<const uint16_t *>(M), ldm, static_cast<const uint16_t *>(dHnext),
+                                   static_cast<const uint16_t *>(Hnext), ld_next, F_in, F_out, relu_, u, partial, colsum, stream)) {
+            if (int rc = check_launch("sage gemm bwd weight")) return rc;
+            return launch_reduce_splits(partial, colsum, u.n_splits, F_in, F_out, 2, dW_self, dW_neigh, dbias, stream);
+        }
+        colsum = reinterpret_cast<float *>(static_cast<char *>(ws) + w.partial_bytes);
+    }
     if (have_rows) {
         int rc;
         if (dtype == TMA_F32)

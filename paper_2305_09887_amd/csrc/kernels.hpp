@@ -62,7 +62,8 @@ int launch_sage_gemm_bwd_data(int64_t n, const void *dHnext, const void *Hnext, 
                               void *dM_scaled_out, hipStream_t stream, void *spare = nullptr, size_t spare_bytes = 0);
 
 // [dW_self ; dW_neigh] = [H | M]^T dZ,  dbias = 1^T dZ   (split over nodes, two-stage fixed-order reduction)
-size_t sage_gemm_bwd_weight_workspace_bytes(int64_t n, int32_t F_in, int32_t F_out);
+// least: what the call needs; else what it makes use of
+size_t sage_gemm_bwd_weight_workspace_bytes(int64_t n, int32_t F_in, int32_t F_out, bool least = true);
 int launch_sage_gemm_bwd_weight(int64_t n, const void *H, int64_t ldh, const void *M, int64_t ldm, const void *dHnext,
                                 const void *Hnext, int64_t ld_next, int32_t F_in, int32_t F_out, int32_t act,
                                 int32_t dtype,
@@ -94,6 +95,18 @@ bool stream_sage_fwd(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *
 bool stream_sage_bwd_data(int64_t n, const uint16_t *dHnext, const uint16_t *Hnext, int64_t ld_next, const float *inv_deg, const float *W_self,
                           const float *W_neigh, int F_in, int F_out, bool relu, uint16_t *dH_self_out, int64_t ldh, uint16_t *dM_scaled_out,
                           void *spare, size_t spare_bytes, hipStream_t stream);
+struct WeightSplit {   // of a weight gradient: ranges of nodes with a partial result each
+    int n_splits;
+    int64_t k_per_split;
+    size_t partial_bytes, colsum_bytes;
+};
+// in ws_bytes of partial results at most; false: too few nodes, or columns
+bool plan_stream_weight(int64_t n, int32_t F_in, int32_t F_out, size_t ws_bytes, WeightSplit &w);
+bool stream_sage_bwd_weight(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *M, int64_t ldm, const uint16_t *dHnext, const uint16_t *Hnext,
+                            int64_t ld_next, int F_in, int F_out, bool relu, const WeightSplit &w, float *partial, float *colsum,
+                            hipStream_t stream);
+bool stream_sage_tf_bwd_weight(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *dHnext, int64_t ld_next, const uint16_t *dYn, int64_t ldy,
+                               int F_in, int F_out, int Fp, const WeightSplit &w, float *partial, float *colsum, hipStream_t stream);
 bool stream_sage_tf_fwd(int64_t n, const uint16_t *H, int64_t ldh, int F_in, const float *W_self, const float *W_neigh, int F_out, int Fp,
                         uint16_t *Ys, uint16_t *Yn, int64_t ldy, void *spare, size_t spare_bytes, hipStream_t stream);
 bool stream_sage_tf_bwd_data(int64_t n, const uint16_t *dHnext, int64_t ld_next, const uint16_t *dYn, int64_t ldy, const float *W_self,

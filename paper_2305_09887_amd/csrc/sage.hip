@@ -20,13 +20,14 @@ struct BwdWorkspace {
 static int pad_cols(int32_t F_out, int32_t dtype) { return int(round_up(size_t(F_out), dtype == TMA_BF16 ? 8 : 4)); }
 static bool aggregates_first(int32_t F_in, int32_t F_out, int32_t dtype) { return 2 * pad_cols(F_out, dtype) > F_in; }
 
-static BwdWorkspace plan_bwd(int64_t n, int32_t F_in, int32_t F_out, int32_t dtype, bool need_dH)
+// least: what the call needs; else what it makes use of
+static BwdWorkspace plan_bwd(int64_t n, int32_t F_in, int32_t F_out, int32_t dtype, bool need_dH, bool least)
 {
     BwdWorkspace w;
     const size_t rows = size_t(n > 0 ? n : 1);
     if (aggregates_first(F_in, F_out, dtype)) {
         w.dm_bytes = need_dH ? round_up(rows * size_t(F_in) * elem_size(dtype), 256) : 0;
-        w.weight_bytes = sage_gemm_bwd_weight_workspace_bytes(n, F_in, F_out);
+        w.weight_bytes = sage_gemm_bwd_weight_workspace_bytes(n, F_in, F_out, least || dtype != TMA_BF16);
     } else {  // scaled dZ and dYn, [n, Fp] each
         w.dm_bytes = 2 * round_up(rows * size_t(pad_cols(F_out, dtype)) * elem_size(dtype), 256);
         w.weight_bytes = sage_tf_gemm_bwd_weight_workspace_bytes(n, F_in, F_out, dtype);
@@ -127,7 +128,7 @@ extern "C" size_t tma_sage_layer_bwd_workspace_bytes(int64_t n, int32_t F_in, in
                                                      int32_t need_dH)
 {
     if (n < 0 || F_in < 1 || F_out < 1) return 0;
-    return tma::plan_bwd(n, F_in, F_out, dtype, need_dH != 0).total();
+    return tma::plan_bwd(n, F_in, F_out, dtype, need_dH != 0, false).total();
 }
 
 extern "C" int tma_sage_layer_bwd(int64_t n, const int32_t *rowptr_T, const int32_t *colidx_T, const float *inv_deg,
@@ -146,9 +147,10 @@ extern "C" int tma_sage_layer_bwd(int64_t n, const int32_t *rowptr_T, const int3
     TMA_REQUIRE(dW_self && dW_neigh && dbias, TMA_ERR_INVALID_ARG, "%s: gradient output is NULL", fn);
     TMA_REQUIRE(ws && aligned(ws, 256), TMA_ERR_INVALID_ARG, "%s: workspace NULL or not 256-byte aligned", fn);
     const bool need_dH = dH_out != nullptr;
-    const BwdWorkspace w = plan_bwd(n, F_in, F_out, dtype, need_dH);
+    BwdWorkspace w = plan_bwd(n, F_in, F_out, dtype, need_dH, true);
     TMA_REQUIRE(ws_bytes >= w.total(), TMA_ERR_WORKSPACE_TOO_SMALL, "%s: workspace %zu < %zu bytes", fn, ws_bytes,
                 w.total());
+    w.weight_bytes = ws_bytes - w.dm_bytes;
     const bool agg_first = aggregates_first(F_in, F_out, dtype);
     if (n > 0) {
         TMA_REQUIRE(H && (M || !agg_first) && dHnext && W_self && W_neigh, TMA_ERR_INVALID_ARG, "%s: NULL argument", fn);

@@ -100,8 +100,47 @@ static void rows16(int n, int F, int Fv, int pitch, bool two)
     free(M);
 }
 
+// columns of bf16 nodes as FetchCols16 walks them: whole slabs before the one that holds the last node, pairs in that one
+template <int COLS>
+static void cols16(int n, int F, int pitch, bool two)
+{
+    typedef FetchCols16<COLS, 4> Fetch;
+    const int ld = F + F % 2 + pitch, Fq = (F + 7) / 8 * 8, width = two ? 2 * Fq : Fq;
+    const int64_t count = int64_t(n - 1) * ld + F + F % 2;
+    uint16_t *H = static_cast<uint16_t *>(malloc(count * 2)), *M = static_cast<uint16_t *>(malloc(count * 2)), zero[8];
+    const AsyncCols16 x{H, ld, M, ld, F, Fq, width, n};
+    expect(x.ok(), "form", n, F, ld);
+    for (int c0 = 0; c0 < width; c0 += COLS)
+        for (int k = 0; k < n; k += kAsyncK16)
+            for (int place = 0; place < COLS * kAsyncK16 / 8; ++place) {
+                const int node = k + place / Fetch::kPieces, c = c0 + ((place % Fetch::kPieces) ^ (4 * (place / Fetch::kPieces & 3))) * 8;
+                const bool second = c >= Fq && c < width, inside = c < width && c - (second ? Fq : 0) < F;
+                const uint16_t *base = second ? M : H, *want = base + int64_t(node) * ld + (c - (second ? Fq : 0));
+                if (k + kAsyncK16 < n) {
+                    const uint16_t *p = x.piece(node, c);
+                    expect(p >= base && p + 8 <= base + count && (!inside || p == want), "piece", node, c, F);
+                } else {
+                    for (int e = 0; e < 8; e += 2) {
+                        const uint16_t *p = x.at(node, c + e, zero);
+                        const bool own = c < width && c + e - (second ? Fq : 0) < F;
+                        if (node >= n) expect(p == zero, "past the nodes", node, c, F);
+                        else expect(p >= base && p + 2 <= base + count && (!own || p == want + e), "pair", node, c, F);
+                    }
+                }
+            }
+    free(H);
+    free(M);
+}
+
 int main()
 {
+    for (int F : {8, 9, 30, 47, 48, 64, 100, 128, 150, 256, 300})
+        for (int n : {1, 31, 32, 33, 64, 97})
+            for (int pitch : {0, 2, 6}) {
+                cols16<256>(n, F, pitch, false);
+                cols16<256>(n, F, pitch, true);
+                cols16<128>(n, F, pitch, true);
+            }
     for (int F : {2, 8, 16, 30, 32, 34, 48, 50, 64, 96, 100, 150, 256})
         for (int n : {1, 3})
             for (int pitch : {0, 2, 6})

@@ -1,4 +1,4 @@
-"""The bf16 products over many rows at the edges of their tiles and slabs of 32 k-values: the last tile of 256 rows whole, cut and
+"""The bf16 products over many rows at the edges of their tiles and slabs of 32 k-values (32 nodes in a weight gradient): the last tile of 256 rows whole, cut and
 of one row; widths of every tile; halves that end at every kind of place of a slab; padding that holds NaN and must reach nothing.
 Bounds as in test_gpu_bf16_products.py."""
 import pytest
@@ -52,8 +52,10 @@ def test_layer(B, n, fi, fo, relu):
     d = torch.where(h > 0, g, torch.zeros(()).bfloat16()) if relu else g
     dH = inside(torch.zeros_like(X), pitch, 2)
     back = torch.zeros(n + 1, dtype=torch.int32, device="cuda")          # no entries: dH is dZ W_self^T
-    B.tma_sage_layer_bwd(back, col, inv, H, M, inside(h, even(fo) + 4, 2), inside(g, even(fo) + 4, 2), *w, act, dH_out=dH)
+    dW = B.tma_sage_layer_bwd(back, col, inv, H, M, inside(h, even(fo) + 4, 2), inside(g, even(fo) + 4, 2), *w, act, dH_out=dH)
     within(dH, d, Ws.T, True, "input gradient")
+    within(torch.cat(dW[:2]), Z[0].T, d, False, "weight gradient")
+    within(dW[2].reshape(1, -1), torch.ones((1, n)).bfloat16(), d, False, "bias gradient")
     into = (torch.arange(n, dtype=torch.int32) - 1) % n                  # the transposed ring
     B.tma_sage_layer_bwd(rowptr, into.int().cuda(), inv, H, M, inside(h, even(fo) + 4, 2), inside(g, even(fo) + 4, 2), *w, act, dH_out=dH)
     # (two roundings more on the way: of dZ W_neigh^T and of the first part of the sum)
@@ -79,5 +81,7 @@ def test_transform_first(B, n, fi, fo):
     into = (torch.arange(n, dtype=torch.int32) - 1) % n
     dH = inside(torch.zeros_like(X), pitch, 2)
     room = inside(g, (fo + 7) // 8 * 8, 8)
-    B.tma_sage_layer_bwd(rowptr, into.int().cuda(), inv, H, H, None, room, *w, B.TMA_ACT_NONE, dH_out=dH)
+    dW = B.tma_sage_layer_bwd(rowptr, into.int().cuda(), inv, H, H, None, room, *w, B.TMA_ACT_NONE, dH_out=dH)
+    within(torch.cat(dW[:2], 1), X.T, torch.cat([g, g.roll(1, 0)], 1), False, "weight gradient")
+    within(dW[2].reshape(1, -1), torch.ones((1, n)).bfloat16(), g, False, "bias gradient")
     within(dH, torch.cat([g, g.roll(1, 0)], 1), torch.cat([Ws.T, Wn.T]), True, "input gradient")
