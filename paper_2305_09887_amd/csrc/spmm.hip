@@ -203,20 +203,28 @@ __device__ __forceinline__ void issue_ids(const int32_t *__restrict__ ids, int32
     // an unused slot repeats the step's last entry; a step without entries reads any valid entry
     const int32_t filler = s.hi > s.lo ? s.hi - 1 : (s.lo < last_entry ? s.lo : last_entry);
 #pragma unroll
-    for (int q = 0; q < U; ++q) I[q] = ids[s.lo + q < s.hi ? s.lo + q : filler];
+    for (int q = 0; q < U; ++q) I[q] = ids[uint32_t(s.lo + q < s.hi ? s.lo + q : filler)];
 }
+
+// The rows of a matrix as a lane reads them: its chunk of row 0, and the rows' pitch in bytes.  Ids are not negative and a
+// pitch fits 32 bits (launch_typed), so that an address is one 32 x 32 + 64 bit multiplication: with 64-bit factors the
+// addresses were a third of the instructions (four of a quarter of the rate each, and sign extensions).
+struct LaneRows {
+    const char *first;
+    uint32_t pitch;
+    __device__ __forceinline__ const char *at(int32_t id) const { return first + uint64_t(uint32_t(id)) * pitch; }
+};
 
 // kEdge: every neighbour row comes with a weight edge_scale[id], fetched next to the row
 template <typename T, int U, bool kEdge>
-__device__ __forceinline__ void issue_gathers(const T *__restrict__ in, int64_t ld, const float *__restrict__ edge_scale,
-                                              const Step &s, const int32_t (&I)[U], int32_t &recent, int col,
-                                              uint4 (&V)[U], float (&Wt)[U])
+__device__ __forceinline__ void issue_gathers(const LaneRows &in, const float *__restrict__ edge_scale, const Step &s, const int32_t (&I)[U],
+                                              int32_t &recent, uint4 (&V)[U], float (&Wt)[U])
 {
 #pragma unroll
     for (int q = 0; q < U; ++q) {
         recent = s.lo + q < s.hi ? I[q] : recent;   // unused slot: a row this group fetched a moment ago
-        V[q] = load_chunk(in + int64_t(recent) * ld + col);
-        if constexpr (kEdge) Wt[q] = edge_scale[recent];
+        V[q] = load_chunk(reinterpret_cast<const T *>(in.at(recent)));
+        if constexpr (kEdge) Wt[q] = edge_scale[uint32_t(recent)];
     }
 }
 
@@ -225,7 +233,7 @@ __device__ __forceinline__ void issue_gathers(const T *__restrict__ in, int64_t 
 // gradient and more: which of the two, and the order of the additions, is part of the result (see launch_typed).
 enum class Weighting { kNone, kRounded, kFused };
 
-template <typename T, int U, Weighting kW>
+template <typename T, int U, Weighting kW, bool kFull>
 __device__ __forceinline__ void consume(const Step &s, const uint4 (&V)[U], const float (&Wt)[U],
                                         float (&acc)[Chunk<T>::kElems])
 {
@@ -233,8 +241,9 @@ __device__ __forceinline__ void consume(const Step &s, const uint4 (&V)[U], cons
     constexpr int E = Chunk<T>::kElems;
 #pragma unroll
     for (int q = 0; q < U; ++q) {
-        // an unused slot's chunk is cleared as it came (four words, whatever the type), so that the sums need no selects
-        const bool used = s.lo + q < s.hi;
+        // an unused slot's chunk is cleared as it came (four words, whatever the type), so that the sums need no selects;
+        // kFull: there is none in any group of the wavefront
+        const bool used = kFull || s.lo + q < s.hi;
         float v[E];
         Chunk<T>::widen(make_uint4(used ? V[q].x : 0u, used ? V[q].y : 0u, used ? V[q].z : 0u, used ? V[q].w : 0u), v);
 #pragma unroll
@@ -255,13 +264,16 @@ struct RowExtra {
 // Runs the steps that `gen` hands out through the ids -> gathers -> additions pipeline.  `extra(seg, X)`
 // issues the loads a closing step needs (or nothing); `emit(seg, acc, X)` takes a finished segment.
 template <typename T, Weighting kW, typename Gen, typename Extra, typename Emit>
-__device__ __forceinline__ void stream_segments(const T *__restrict__ in, int64_t ld, const int32_t *__restrict__ ids,
-                                                const float *__restrict__ edge_scale, int32_t last_entry, int col,
-                                                int32_t recent, Gen &&gen, Extra &&extra, Emit &&emit)
+__device__ __forceinline__ void stream_segments(const LaneRows &in, const int32_t *__restrict__ ids,
+                                                const float *__restrict__ edge_scale, int32_t last_entry, int32_t recent, bool few_groups,
+                                                Gen &&gen, Extra &&extra, Emit &&emit)
 {
     constexpr int E = Chunk<T>::kElems;
     constexpr int U = kStreamU;
     constexpr bool kEdge = kW != Weighting::kNone;
+    // Steps without an unused slot, where most of them are (wide bf16 rows of dense graphs: two groups or four to a wavefront);
+    // the second copy of the additions costs the others (fp32 rows of 48 with the own row: 34 -> 39 us).
+    constexpr bool kTestFull = sizeof(T) == 2;
     int32_t I0[U], I1[U];
     uint4 V0[U], V1[U];
     float W0[U], W1[U];
@@ -274,16 +286,17 @@ __device__ __forceinline__ void stream_segments(const T *__restrict__ in, int64_
     issue_ids<U>(ids, last_entry, a, I0);
     Step b = gen();
     issue_ids<U>(ids, last_entry, b, I1);
-    issue_gathers<T, U, kEdge>(in, ld, edge_scale, a, I0, recent, col, V0, W0);
+    issue_gathers<T, U, kEdge>(in, edge_scale, a, I0, recent, V0, W0);
     extra(a.seg, X0);
     // entering a half: step a has its gathers in flight (V0/X0 in the first half), step b its ids (I1)
     auto half = [&](int32_t (&Ia)[U], int32_t (&Ib)[U], uint4 (&Va)[U], uint4 (&Vb)[U], float (&Wa)[U],
                     float (&Wb)[U], RowExtra &Xa, RowExtra &Xb) __attribute__((always_inline)) {
         const Step c = gen();
         issue_ids<U>(ids, last_entry, c, Ia);
-        issue_gathers<T, U, kEdge>(in, ld, edge_scale, b, Ib, recent, col, Vb, Wb);
+        issue_gathers<T, U, kEdge>(in, edge_scale, b, Ib, recent, Vb, Wb);
         extra(b.seg, Xb);
-        consume<T, U, kW>(a, Va, Wa, acc);
+        if (kTestFull && few_groups && __all(a.hi - a.lo == U)) consume<T, U, kW, true>(a, Va, Wa, acc);
+        else consume<T, U, kW, false>(a, Va, Wa, acc);
         if (a.last) {
             emit(a.seg, acc, Xa);
 #pragma unroll
@@ -413,8 +426,8 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, co
     };
     // a row that exists in the gathered matrix, for the loads of slots that carry nothing yet
     const int32_t filler_row = int32_t((base + r_first) < o.in_rows ? (base + r_first) : o.in_rows - 1);
-    stream_segments<T, kW>(in, ld_in, ids, o.edge_scale, last_entry, col, filler_row, next_row_step, row_extra,
-                              finish);
+    const LaneRows rows{reinterpret_cast<const char *>(in + col), uint32_t(ld_in) * uint32_t(sizeof(T))};
+    stream_segments<T, kW>(rows, ids, o.edge_scale, last_entry, filler_row, gpw <= 4, next_row_step, row_extra, finish);
     __syncthreads();
 
     // ---- deferred rows, kHubsPerPass at a time: group g sums the g-th share of each, then a fixed-order combine
@@ -454,8 +467,7 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, co
 #pragma unroll
                 for (int i = 0; i < E; ++i) partial[(seg * NG + grp) * width + sub * E + i] = acc[i];
             };
-            stream_segments<T, kW>(in, ld_in, ids, o.edge_scale, last_entry, col, filler_row, next_share_step,
-                                      no_extra, to_lds);
+            stream_segments<T, kW>(rows, ids, o.edge_scale, last_entry, filler_row, gpw <= 4, next_share_step, no_extra, to_lds);
         }
         __syncthreads();
         if (live && grp < h_end - h0) {
@@ -664,7 +676,8 @@ static int launch_typed(int64_t n, const int32_t *rowptr, const int32_t *colidx,
     // self, scale and accumulation
     const bool edge_self = o.edge_scale && o.self && o.inv_deg == o.edge_scale;
     const bool edge_plain = o.edge_scale && !o.self && !o.inv_deg && !o.accumulate;
-    if ((!vec_ok && !overlap) || (o.edge_scale && !edge_self && !edge_plain && row_bytes / 16 <= 64)) {
+    const bool far = size_t(ld_in) * sizeof(T) > UINT32_MAX;   // (see LaneRows)
+    if ((!vec_ok && !overlap) || (far && row_bytes / 16 <= 64) || (o.edge_scale && !edge_self && !edge_plain && row_bytes / 16 <= 64)) {
         TMA_TIMED(o.gate.side ? "gated_spmm_generic" : o.self ? "spmm_combine_generic" : (o.inv_deg ? "spmm_mean_generic" : "spmm_sum_generic"), s);
         hipLaunchKernelGGL((spmm_rows_generic_kernel<T>), dim3(unsigned(ceil_div(n, kSpmmThreads / kWave))),
                            dim3(kSpmmThreads), 0, s, n, rowptr, colidx, in, ld_in, o, F);
