@@ -8,35 +8,9 @@
 // Same kernel template as the GraphSAGE transforms; the operand views that
 // present concatenations there are used here with the first part only.
 #include "gemm_core.hpp"
+#include "dense_epilogue.hpp"
 
 namespace tma {
-
-template <typename T, bool kRowScale>
-struct DenseEpilogue {  // out = act(acc + b)  or  row_scale[row] * acc
-    static constexpr bool kColAux = true, kRowAux = kRowScale;
-    T *out;
-    int64_t ld;
-    const float *bias;       // may be NULL
-    const float *row_scale;  // read only with kRowScale
-    bool relu;
-    int Fo;                  // columns from here on are stored as zeros
-    __device__ __forceinline__ float col_aux(int col) const { return bias ? bias[col] : 0.0f; }
-    __device__ __forceinline__ float row_aux(int64_t row) const { return kRowScale ? row_scale[row] : 0.0f; }
-    __device__ __forceinline__ const float *col_at(int col) const { return bias ? bias + col : kZeros; }
-    __device__ __forceinline__ const float *row_at(int64_t row) const { return row_scale + row; }
-    __device__ __forceinline__ bool padding(int col) const { return col >= Fo; }
-    __device__ __forceinline__ float value(float v, float caux, float raux, int) const
-    {
-        v += caux;
-        if (kRowScale) v *= raux;
-        if (relu) v = v > 0.0f ? v : 0.0f;
-        return v;
-    }
-    __device__ __forceinline__ void store(int64_t row, int col, float v, int) const { narrow1(out + row * ld + col, v); }
-    static constexpr bool kPairs = sizeof(T) == 2;
-    __device__ __forceinline__ bool pairs_ok() const { return ld % 2 == 0 && word_aligned(out); }
-    __device__ __forceinline__ T *at(int64_t row, int col) const { return out + row * ld + col; }
-};
 
 static int pad8(int32_t F) { return int(round_up(size_t(F), 8)); }
 
@@ -137,10 +111,13 @@ static int dense_bwd_data_any(int64_t n, const void *dY, const void *Y, int64_t 
 
 int launch_dense_gemm_bwd_data(int64_t n, const void *dY, const void *Y, int64_t ld, const float *W, int32_t F_in,
                                int32_t F_out, int32_t act, int32_t dtype, const float *row_scale, void *dX,
-                               int64_t ldx, hipStream_t s)
+                               int64_t ldx, hipStream_t s, void *spare, size_t spare_bytes)
 {
     if (n == 0 || F_in == 0) return TMA_OK;
     const bool relu = act == TMA_ACT_RELU;
+    if (dtype == TMA_BF16 && stream_dense_bwd_data(n, static_cast<const uint16_t *>(dY), static_cast<const uint16_t *>(Y), ld, W, F_in, F_out, relu,
+                                                   row_scale, static_cast<uint16_t *>(dX), ldx, spare, spare_bytes, s))
+        return check_launch("dense gemm bwd data");
     if (dtype == TMA_F32) return dense_bwd_data_any<float>(n, dY, Y, ld, W, F_in, F_out, relu, row_scale, dX, ldx, s);
     if (dtype == TMA_BF16)
         return dense_bwd_data_any<uint16_t>(n, dY, Y, ld, W, F_in, F_out, relu, row_scale, dX, ldx, s);
@@ -215,7 +192,10 @@ int launch_dense_gemm_bwd_weight(int64_t n, const void *X, int64_t ldx, const vo
     // without rows there is nothing to multiply (the operands may be NULL); the second stage writes zeros
     if (n > 0) {
         int rc;
-        if (dtype == TMA_F32) {
+        if (dtype == TMA_BF16 && stream_dense_bwd_weight(n, static_cast<const uint16_t *>(X), ldx, static_cast<const uint16_t *>(dY),
+                                                         static_cast<const uint16_t *>(Y), ld, F_in, F_out, relu, w, partial, colsum, s)) {
+            rc = check_launch("dense gemm bwd weight");
+        } else if (dtype == TMA_F32) {
             const float *x = static_cast<const float *>(X), *g = static_cast<const float *>(dY),
                         *h = static_cast<const float *>(Y);
             rc = relu ? dense_bwd_weight_typed<float, true>(n, x, ldx, g, h, ld, F_in, F_out, w, partial, colsum, s)

@@ -314,7 +314,7 @@ extern "C" int tma_gcn_layer_bwd(int64_t n, const int32_t *rowptr_T, const int32
             return rc;
         if (!need_dH || n == 0) return TMA_OK;
         void *P = base;
-        if ((rc = launch_dense_gemm_bwd_data(n, dHnext, Hnext, ld_next, W, F_in, F_out, act, dtype, s_norm, P, F_in, s)))
+        if ((rc = launch_dense_gemm_bwd_data(n, dHnext, Hnext, ld_next, W, F_in, F_out, act, dtype, s_norm, P, F_in, s, wws, w.weight_bytes)))
             return rc;
         return launch_spmm_combine(n, rowptr_T, colidx_T, s_norm, P, F_in, F_in, dtype, dH_out, ldh, false, P, F_in,
                                    nullptr, F_in, false, true, nullptr, s);
@@ -339,7 +339,7 @@ extern "C" int tma_gcn_layer_bwd(int64_t n, const int32_t *rowptr_T, const int32
                                            w.weight_bytes, s)))
         return rc;
     if (!need_dH || n == 0) return TMA_OK;
-    return launch_dense_gemm_bwd_data(n, G, nullptr, Fp, W, F_in, F_out, TMA_ACT_NONE, dtype, nullptr, dH_out, ldh, s);
+    return launch_dense_gemm_bwd_data(n, G, nullptr, Fp, W, F_in, F_out, TMA_ACT_NONE, dtype, nullptr, dH_out, ldh, s, wws, w.weight_bytes);
 }
 
 extern "C" int tma_dense_fwd(int64_t n, const void *X, int64_t ldx, int32_t F_in, const float *W, const float *bias,
@@ -388,5 +388,5 @@ extern "C" int tma_dense_bwd(int64_t n, const void *X, int64_t ldx, const void *
     if (int rc = launch_dense_gemm_bwd_weight(n, X, ldx, dY, Y, ldy, F_in, F_out, act, dtype, dW, dbias, ws, ws_bytes, s))
         return rc;
     if (!dX_out || n == 0) return TMA_OK;
-    return launch_dense_gemm_bwd_data(n, dY, Y, ldy, W, F_in, F_out, act, dtype, nullptr, dX_out, ld_dx, s);
+    return launch_dense_gemm_bwd_data(n, dY, Y, ldy, W, F_in, F_out, act, dtype, nullptr, dX_out, ld_dx, s, ws, ws_bytes);   // (the partial sums are spent)
 }

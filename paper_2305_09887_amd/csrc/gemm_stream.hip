@@ -1,5 +1,6 @@
 // The products of bf16 storage over many nodes: operands, narrowed weights and tiles of gemm_bf16_async.hpp.
 #include "gemm_core.hpp"
+#include "dense_epilogue.hpp"
 #include "gemm_bf16_async.hpp"
 
 namespace tma {
@@ -10,6 +11,8 @@ namespace tma {
 //   64 -> 128 21 -> 21, 45 -> 39 at 181,000; 100 -> 120 72 -> 78 at 181,000, 555 -> 552 at 1,500,000; 96 -> 64 46 -> 48, 344 -> 347
 //   input gradient with ReLU (with the gather after it): 256 -> 256 85 -> 70 / 163 -> 134, alone at 12,500,000 11,520 -> 7,750; 128 -> 128
 //   without ReLU 37 -> 33 at 65,536; 96 -> 64 88 -> 83 at 181,000, 178 -> 184 at 400,000, 642 -> 580 at 1,500,000; 64 -> 128 (half the tile) 60 -> 89
+//   dense input gradient, 98,304 / 181,000 / 1,500,000 rows: 256 <- 256 46 -> 36 / 86 -> 56 / 680 -> 395, with ReLU 70 -> 47 / 127 -> 69 / 958 -> 511;
+//   256 <- 64 39 -> 27 / 72 -> 43 / 565 -> 326; 256 <- 47 (slabs pair by pair) 26 -> 25 / 45 -> 45 / 373 -> 414
 //   transformed first, forward 256 -> 47: 28 -> 27 / 48 -> 42 / 2,460 -> 1,820 (4.8 TB/s); 128 -> 47 23 -> 23 at 65,536, 49 -> 43 at 181,000
 //   transformed first, input gradient: 128 -> 47 14 -> 17 at 65,536, 30 -> 26 at 181,000; 256 -> 20 (slabs pair by pair) 85 -> 90 at
 //   400,000, 353 -> 303 at 1,500,000; 256 -> 47 3,850 -> 2,050 (4.3 TB/s) at 12,500,000
@@ -91,6 +94,24 @@ bool stream_sage_bwd_data(int64_t n, const uint16_t *dHnext, const uint16_t *Hne
     return true;
 }
 
+bool stream_dense_bwd_data(int64_t n, const uint16_t *dY, const uint16_t *Y, int64_t ld, const float *W, int F_in, int F_out, bool relu,
+                           const float *row_scale, uint16_t *dX, int64_t ldx, void *spare, size_t spare_bytes, hipStream_t s)
+{
+    const int pitch = int(round_up(size_t(F_out), 8));
+    const AsyncRows16 a{dY, ld, dY, ld, F_out, F_out, F_out, n};
+    if (n < kTransformRows || (F_in < 256 && n < kStreamRows) || F_in <= 128 || F_out < 64) return false;
+    if (!a.ok() || (relu && !aligned(Y, 4)) || !spare || !aligned(spare, 16) || size_t(F_in) * pitch * 2 > spare_bytes) return false;
+    const AsyncRows16 b = narrow_rows(NarrowStack{W, W, F_in, F_out}, F_in, F_out, pitch, spare, s);
+    const char *name = "gemm_dense_bwd_data_bf16";
+    const auto launch = [&](const auto &e) {
+        if (relu) launch_rows16<true>(name, a, Y, b, e, n, F_in, s);
+        else launch_rows16<false>(name, a, nullptr, b, e, n, F_in, s);
+    };
+    if (row_scale) launch(DenseEpilogue<uint16_t, true>{dX, ldx, nullptr, row_scale, false, F_in});
+    else launch(DenseEpilogue<uint16_t, false>{dX, ldx, nullptr, nullptr, false, F_in});
+    return true;
+}
+
 bool stream_sage_tf_fwd(int64_t n, const uint16_t *H, int64_t ldh, int F_in, const float *W_self, const float *W_neigh, int F_out, int Fp,
                         uint16_t *Ys, uint16_t *Yn, int64_t ldy, void *spare, size_t spare_bytes, hipStream_t s)
 {
@@ -151,6 +172,30 @@ bool stream_sage_bwd_weight(int64_t n, const uint16_t *H, int64_t ldh, const uin
     } else {
         const char *name = F_out <= 64 ? "gemm_bwd_weight_128x64_bf16" : "gemm_bwd_weight_128x128_bf16";
         if (relu) launch_weight16<128, 1, 4, true>(name, a, b, Hnext, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
+        else launch_weight16<128, 1, 6, false>(name, a, b, nullptr, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
+    }
+    return true;
+}
+
+// The dense layer's, in the ranges of nodes that it plans: where they make an item for half of the compute units or more, and not where
+// much of a narrow tile is padding.  us, gemm_bf16_kernel -> here, both with the second stage, 98,304 / 181,000 / 1,500,000 nodes:
+//   256 -> 256 72 -> 46 / 109 -> 62 / 712 -> 339 (128 items), with ReLU 83 -> 62 / 125 -> 94 / 790 -> 595; 128 -> 256 62 -> 48 / 86 -> 62 /
+//   432 -> 359; 256 -> 47 37 -> 36 / 54 -> 41 / 308 -> 172; 150 -> 150, element by element before, 148 -> 44 / 279 -> 58 / 2,352 -> 324;
+//   300 -> 47 58 -> 56 / 71 -> 78 / 605 -> 433
+bool stream_dense_bwd_weight(int64_t n, const uint16_t *X, int64_t ldx, const uint16_t *dY, const uint16_t *Y, int64_t ld, int F_in, int F_out,
+                             bool relu, const WeightSplit &w, float *partial, float *colsum, hipStream_t s)
+{
+    const int Fq = int(round_up(size_t(F_in), 8)), No = int(round_up(size_t(F_out), 8));
+    const AsyncCols16 a{X, ldx, X, ldx, F_in, Fq, Fq, n}, b{dY, ld, dY, ld, F_out, No, No, n};
+    const int64_t items = ceil_div(Fq, 256) * ceil_div(F_out, F_out > 128 ? 256 : 128) * w.n_splits;
+    if (n < kManyRows || items < 112 || (F_in <= 128 && F_out <= 128 && n < kStreamRows) ||
+        (F_out <= 64 && ceil_div(Fq, 256) * 256 * 2 > 3 * Fq && n < kStreamRows) || !a.ok() || !b.ok() || (relu && !aligned(Y, 4))) return false;
+    const char *name = "gemm_dense_bwd_weight_bf16";
+    if (F_out > 128) {
+        if (relu) launch_weight16<256, 2, 3, true>(name, a, b, Y, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
+        else launch_weight16<256, 2, 4, false>(name, a, b, nullptr, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
+    } else {
+        if (relu) launch_weight16<128, 1, 4, true>(name, a, b, Y, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
         else launch_weight16<128, 1, 6, false>(name, a, b, nullptr, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
     }
     return true;

@@ -107,6 +107,10 @@ bool stream_sage_bwd_weight(int64_t n, const uint16_t *H, int64_t ldh, const uin
                             hipStream_t stream);
 bool stream_sage_tf_bwd_weight(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *dHnext, int64_t ld_next, const uint16_t *dYn, int64_t ldy,
                                int F_in, int F_out, int Fp, const WeightSplit &w, float *partial, float *colsum, hipStream_t stream);
+bool stream_dense_bwd_data(int64_t n, const uint16_t *dY, const uint16_t *Y, int64_t ld, const float *W, int F_in, int F_out, bool relu,
+                           const float *row_scale, uint16_t *dX, int64_t ldx, void *spare, size_t spare_bytes, hipStream_t stream);
+bool stream_dense_bwd_weight(int64_t n, const uint16_t *X, int64_t ldx, const uint16_t *dY, const uint16_t *Y, int64_t ld, int F_in, int F_out,
+                             bool relu, const WeightSplit &w, float *partial, float *colsum, hipStream_t stream);
 bool stream_sage_tf_fwd(int64_t n, const uint16_t *H, int64_t ldh, int F_in, const float *W_self, const float *W_neigh, int F_out, int Fp,
                         uint16_t *Ys, uint16_t *Yn, int64_t ldy, void *spare, size_t spare_bytes, hipStream_t stream);
 bool stream_sage_tf_bwd_data(int64_t n, const uint16_t *dHnext, int64_t ld_next, const uint16_t *dYn, int64_t ldy, const float *W_self,
@@ -130,7 +134,7 @@ int launch_dense_gemm_fwd(int64_t n, const void *X, int64_t ldx, int32_t F_in, c
                           int64_t ldy, hipStream_t s);
 int launch_dense_gemm_bwd_data(int64_t n, const void *dY, const void *Y, int64_t ld, const float *W, int32_t F_in,
                                int32_t F_out, int32_t act, int32_t dtype, const float *row_scale, void *dX,
-                               int64_t ldx, hipStream_t s);
+                               int64_t ldx, hipStream_t s, void *spare = nullptr, size_t spare_bytes = 0);
 size_t dense_gemm_bwd_weight_workspace_bytes(int64_t n, int32_t F_in, int32_t F_out);
 int launch_dense_gemm_bwd_weight(int64_t n, const void *X, int64_t ldx, const void *dY, const void *Y, int64_t ld,
                                  int32_t F_in, int32_t F_out, int32_t act, int32_t dtype, float *dW, float *dbias,

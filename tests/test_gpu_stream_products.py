@@ -85,3 +85,18 @@ def test_transform_first(B, n, fi, fo):
     within(torch.cat(dW[:2], 1), X.T, torch.cat([g, g.roll(1, 0)], 1), False, "weight gradient")
     within(dW[2].reshape(1, -1), torch.ones((1, n)).bfloat16(), g, False, "bias gradient")
     within(dH, torch.cat([g, g.roll(1, 0)], 1), torch.cat([Ws.T, Wn.T]), True, "input gradient")
+
+
+# single-operand backward products, with the row scale that a GCN layer puts into its input gradient left out
+@pytest.mark.parametrize("n,fi,fo", [(98304, 256, 64), (98305, 256, 47), (98400, 130, 256), (98320, 264, 130), (98310, 128, 258)])
+@pytest.mark.parametrize("relu", [False, True])
+def test_dense_backward(B, n, fi, fo, relu):
+    X, W, g, h = bf16(1, n, fi), bf16(2, fi, fo), bf16(3, n, fo), bf16(4, n, fo)
+    h[::7, 1], h[::3, fo - 1] = float("nan"), 0.0
+    pitch = (fo + 3) // 4 * 4
+    x, w = X.cuda(), W.float().cuda()
+    dW, db, dX = B.tma_dense_bwd(x, inside(h, pitch, 4), inside(g, pitch, 4), w, B.TMA_ACT_RELU if relu else B.TMA_ACT_NONE)[:3]
+    d = torch.where(h > 0, g, torch.zeros(()).bfloat16()) if relu else g
+    within(dX, d, W.T, True, "input gradient")
+    within(dW, X.T, d, False, "weight gradient")
+    within(db.reshape(1, -1), torch.ones((1, n)).bfloat16(), d, False, "bias gradient")
