@@ -256,8 +256,11 @@ int tma_sage_layer_fwd_prepared(int64_t n, const int32_t *rowptr, const int32_t 
  *   dH_out [n, F_in] dtype with the leading dimension of H (ldh), or NULL to
  *            skip the input gradient (first layer).
  * Workspace: tma_sage_layer_bwd_workspace_bytes(n, F_in, F_out, dtype,
- * dH_out != NULL), 256-byte aligned.  Results are deterministic (fixed
- * reduction order, no floating-point atomics).
+ * dH_out != NULL), 256-byte aligned: what the call makes use of.  With bf16
+ * storage and many nodes it also runs, more slowly, in less (a weight gradient
+ * then comes from fewer partial sums; TMA_ERR_WORKSPACE_TOO_SMALL below what it
+ * needs).  Results are deterministic (fixed reduction order, no floating-point
+ * atomics) for one size of the workspace.
  * ---------------------------------------------------------------------- */
 size_t tma_sage_layer_bwd_workspace_bytes(int64_t n, int32_t F_in, int32_t F_out,
                                           int32_t dtype, int32_t need_dH);

@@ -100,3 +100,19 @@ def test_dense_backward(B, n, fi, fo, relu):
     within(dX, d, W.T, True, "input gradient")
     within(dW, X.T, d, False, "weight gradient")
     within(db.reshape(1, -1), torch.ones((1, n)).bfloat16(), d, False, "bias gradient")
+
+
+# a workspace below what the query asks for: fewer ranges of nodes, the same sums; far below: an error
+def test_smaller_workspace(B):
+    n, fi, fo = 65600, 128, 256
+    X, M, g = bf16(1, n, fi), bf16(2, n, fi), bf16(3, n, fo)
+    rowptr, col, inv = ring(n)
+    w = torch.zeros(fi, fo, device="cuda"), torch.zeros(fi, fo, device="cuda")
+    asked = B.tma_sage_layer_bwd_workspace_bytes(n, fi, fo, B.TMA_BF16, False)
+    for share in (1.0, 0.6):
+        ws = torch.empty(int(asked * share) // 256 * 256, dtype=torch.uint8, device="cuda")
+        dW = B.tma_sage_layer_bwd(rowptr, col, inv, X.cuda(), M.cuda(), None, g.cuda(), *w, B.TMA_ACT_NONE, need_dH=False, ws=ws)
+        within(torch.cat(dW[:2]), torch.cat([X, M], 1).T, g, False, "weight gradient")
+        within(dW[2].reshape(1, -1), torch.ones((1, n)).bfloat16(), g, False, "bias gradient")
+    with pytest.raises(B.TmaError):
+        B.tma_sage_layer_bwd(rowptr, col, inv, X.cuda(), M.cuda(), None, g.cuda(), *w, B.TMA_ACT_NONE, need_dH=False, ws=ws[:1 << 20])
