@@ -80,16 +80,16 @@ struct Fetch16 {
     }
 };
 
-// The values of g where h > 0 (h NaN: not), zeros elsewhere; two bf16 in a word.  In assembler: the compiler makes compares and selects
-// of it, half by half, eight instructions with waits between them.
-__device__ __forceinline__ uint32_t where_positive(uint32_t g, uint32_t h)
+// The values of g where h > 0 (h NaN: not), zeros elsewhere; two bf16 in a word.  With a comparison the compiler makes selects of it,
+// half by half, eight instructions with waits between them; so it makes four packed ones.  Not in assembler: between a vector instruction
+// and the matrix instruction that reads its result two others have to pass, and the compiler only counts those that it knows.
+typedef unsigned short ushortx2 __attribute__((ext_vector_type(2)));
+typedef short shortx2 __attribute__((ext_vector_type(2)));
+__host__ __device__ __forceinline__ uint32_t where_positive(uint32_t g, uint32_t h)
 {
-    uint32_t bits, under, one, out;
-    asm("v_pk_sub_u16 %0, %1, %2" : "=v"(bits) : "v"(h), "s"(0x00010001u));                   // 0 .. 0x7F7F: positive, up to infinity
-    asm("v_pk_sub_u16 %0, %1, %2 clamp" : "=v"(under) : "s"(0x7F807F80u), "v"(bits));          // above zero for those
-    asm("v_pk_min_u16 %0, %1, %2" : "=v"(one) : "v"(under), "s"(0x00010001u));
-    asm("v_pk_mul_lo_u16 %0, %1, %2" : "=v"(out) : "v"(g), "v"(one));
-    return out;
+    const ushortx2 below = __builtin_bit_cast(ushortx2, h) - ushortx2{1, 1};                     // 0 .. 0x7F7F: positive, up to infinity
+    const ushortx2 top = __builtin_elementwise_add_sat(below, ushortx2{0x80, 0x80});             // its top bit: clear for those
+    return g & ~__builtin_bit_cast(uint32_t, __builtin_bit_cast(shortx2, top) >> shortx2{15, 15});
 }
 
 // C[M,N] = A[M,K] B[N,K]^T.  kMask: A's elements count where `mask`, an array like A's only part, is positive.  Persistent blocks

@@ -1,5 +1,5 @@
-// Every address that the operands of the fp32 forward products hand out lies inside their arrays, and every element comes
-// from its place: walked on the host as the kernel walks them, over arrays of exactly their size.
+// Every address that the operands of the fp32 forward products and of the bf16 products over many nodes hand out lies inside their
+// arrays, and every element comes from its place: walked on the host as the kernels walk them, over arrays of exactly their size.
 #include "gemm_core.hpp"
 #include "gemm_bf16_async.hpp"
 
@@ -132,8 +132,19 @@ static void cols16(int n, int F, int pitch, bool two)
     free(M);
 }
 
+// the mask of a ReLU, for every value of it
+static void positive()
+{
+    for (uint32_t h = 0; h < 65536; ++h) {
+        const bool above = __builtin_bit_cast(float, h << 16) > 0.0f;
+        expect(where_positive(0xABCD8001u, h << 16 | (65535 - h)) >> 16 == (above ? 0xABCDu : 0u), "mask, upper half", int(h), 0, 0);
+        expect((where_positive(0xABCD8001u, (65535 - h) << 16 | h) & 0xFFFFu) == (above ? 0x8001u : 0u), "mask, lower half", int(h), 0, 0);
+    }
+}
+
 int main()
 {
+    positive();
     for (int F : {8, 9, 30, 47, 48, 64, 100, 128, 150, 256, 300})
         for (int n : {1, 31, 32, 33, 64, 97})
             for (int pitch : {0, 2, 6}) {

@@ -1,4 +1,5 @@
-"""The addresses that the fp32 forward products fetch from, checked on the host (async_bounds.hip)."""
+"""The addresses that the products fetch from straight into LDS, and the bf16 ReLU mask of every value, checked on the host
+(async_bounds.hip)."""
 import os
 import subprocess
 
