@@ -69,9 +69,10 @@ def cpu_baseline_leg(sample):
 
 
 def canonical(name, s):
-    """Kernel name as the work tables spell it: without the storage / path suffixes, and with a gather's
-    16-byte pieces per row counted as for fp32 rows (a bf16 row of the same width has half as many)."""
-    name = name.replace("_generic", "")
+    """Kernel name as the work tables spell it: without the storage / path suffixes and the tile of a product that
+    has only some in its name, and with a gather's 16-byte pieces per row counted as for fp32 rows (a bf16 row of the
+    same width has half as many)."""
+    name = re.sub(r"^(gemm_(?:tf|dense)_[a-z_]+)_\d+x\d+", r"\1", name.replace("_generic", ""))
     m = re.match(r"(spmm_[a-z]+)_(?:f32|bf16)_g(\d+)x1$", name)
     if m:
         return "%s_f32_g%dx1" % (m.group(1), int(m.group(2)) * 4 // s)

@@ -13,6 +13,8 @@
 // Sums: groups of 16 k-values in order, one accumulator, as in gemm_bf16_kernel: the same bits.
 #pragma once
 
+#include <cstdio>
+
 namespace tma {
 
 constexpr int kAsyncK16 = 32;          // k-values of a slab: 64 bytes of a row
@@ -302,7 +304,7 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_async_kernel(AsyncRo
 }
 
 template <int BM, int BN, int WM, int WN, int kStages, bool kMask, class Epi>
-static void launch_async16(const char *name, const AsyncRows16 &a, const uint16_t *mask, const AsyncRows16 &b, const Epi &e, int64_t M, int N, hipStream_t s)
+static void launch_async16(const char *what, const AsyncRows16 &a, const uint16_t *mask, const AsyncRows16 &b, const Epi &e, int64_t M, int N, hipStream_t s)
 {
     constexpr int kPerCu = 8 / (WM * WN);
     static_assert(kPerCu * kStages * ((kMask ? 2 : 1) * BM + BN) * 64 <= 152 * 1024, "LDS of the blocks of a unit");
@@ -310,6 +312,8 @@ static void launch_async16(const char *name, const AsyncRows16 &a, const uint16_
     const int64_t total = ceil_div(M, BM) * n_tiles;
     int64_t blocks_per_die = ceil_div(total, kXcds);
     if (blocks_per_die > 32 * kPerCu) blocks_per_die = 32 * kPerCu;
+    char name[48];
+    snprintf(name, sizeof(name), "%s_%dx%d_bf16", what, BM, BN);
     TMA_TIMED(name, s);
     hipLaunchKernelGGL((gemm_bf16_async_kernel<BM, BN, WM, WN, kStages, kMask, Epi>), dim3(unsigned(blocks_per_die * kXcds)), dim3(WM * WN * 64), 0, s, a,
                        mask, b, e, M, N, n_tiles, total);
@@ -573,7 +577,7 @@ __global__ __launch_bounds__(256 * WN, WN == 2 ? 2 : 1) void gemm_bf16_weight_ke
 }
 
 template <int BN, int WN, int kStages, bool kMask>
-static void launch_weight16(const char *name, const AsyncCols16 &a, const AsyncCols16 &b, const uint16_t *mask, int N, int64_t k_per_split,
+static void launch_weight16(const char *what, const AsyncCols16 &a, const AsyncCols16 &b, const uint16_t *mask, int N, int64_t k_per_split,
                             int n_splits, float *partial, float *colsum, hipStream_t s)
 {
     static_assert(kStages * (256 + (kMask ? 2 : 1) * BN) * 64 <= 152 * 1024, "LDS of a unit");
@@ -581,6 +585,8 @@ static void launch_weight16(const char *name, const AsyncCols16 &a, const AsyncC
     const int64_t total = int64_t(tiles) * n_splits;
     int64_t blocks_per_die = ceil_div(total, kXcds);
     if (blocks_per_die > 32) blocks_per_die = 32;
+    char name[48];
+    snprintf(name, sizeof(name), "%s_256x%d_bf16", what, BN);
     TMA_TIMED(name, s);
     hipLaunchKernelGGL((gemm_bf16_weight_kernel<BN, WN, kStages, kMask>), dim3(unsigned(blocks_per_die * kXcds)), dim3(256 * WN), 0, s, a, b, mask,
                        k_per_split, N, n_tiles, tiles, total, partial, colsum);

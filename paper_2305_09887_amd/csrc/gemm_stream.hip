@@ -18,14 +18,14 @@ namespace tma {
 //   400,000, 353 -> 303 at 1,500,000; 256 -> 47 3,850 -> 2,050 (4.3 TB/s) at 12,500,000
 constexpr int64_t kManyRows = 65536, kTransformRows = 98304, kStreamRows = int64_t(1) << 20;
 template <bool kMask, class Epi>
-static void launch_rows16(const char *name, const AsyncRows16 &a, const uint16_t *mask, const AsyncRows16 &b, const Epi &e, int64_t M, int N, hipStream_t s)
+static void launch_rows16(const char *what, const AsyncRows16 &a, const uint16_t *mask, const AsyncRows16 &b, const Epi &e, int64_t M, int N, hipStream_t s)
 {
     if constexpr (kMask) {
-        launch_async16<256, 256, 4, 2, 3, true>(name, a, mask, b, e, M, N, s);
+        launch_async16<256, 256, 4, 2, 3, true>(what, a, mask, b, e, M, N, s);
     } else {
-        if (N <= 96) launch_async16<256, 96, 4, 1, 3, false>(name, a, mask, b, e, M, N, s);
-        else if (N <= 128) launch_async16<256, 128, 4, 1, 3, false>(name, a, mask, b, e, M, N, s);
-        else launch_async16<256, 256, 4, 2, 4, false>(name, a, mask, b, e, M, N, s);
+        if (N <= 96) launch_async16<256, 96, 4, 1, 3, false>(what, a, mask, b, e, M, N, s);
+        else if (N <= 128) launch_async16<256, 128, 4, 1, 3, false>(what, a, mask, b, e, M, N, s);
+        else launch_async16<256, 256, 4, 2, 4, false>(what, a, mask, b, e, M, N, s);
     }
 }
 // rows of narrowed weights beside what a product reads them for: out[r][c], c < pitch
@@ -73,7 +73,7 @@ bool stream_sage_fwd(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *
     const int K = 2 * F_in;
     const AsyncRows16 a{H, ldh, M, ldm, F_in, F_in, K, n};
     if (n < kManyRows || !a.ok() || F_out <= 64 || (F_out <= 128 && F_in % kAsyncK16 != 0 && n < kStreamRows)) return false;
-    launch_rows16<false>(F_out > 128 ? "gemm_fwd_128x256_bf16" : "gemm_fwd_128x128_bf16", a, nullptr,
+    launch_rows16<false>("gemm_fwd", a, nullptr,
                          AsyncRows16{Wt, K, Wt, K, K, K, K, F_out}, FwdEpilogue<uint16_t>{Hnext, ld_next, bias, relu}, n, F_out, s);
     return true;
 }
@@ -88,9 +88,8 @@ bool stream_sage_bwd_data(int64_t n, const uint16_t *dHnext, const uint16_t *Hne
     if (!a.ok() || (relu && !aligned(Hnext, 4)) || !spare || size_t(N) * pitch * 2 > spare_bytes) return false;
     const AsyncRows16 b = narrow_rows(NarrowStack{W_self, W_neigh, F_in, F_out}, N, F_out, pitch, spare, s);
     const BwdDataEpilogue<uint16_t> e{dH_self_out, ldh, dM_scaled_out, inv_deg, F_in};
-    const char *name = N >= 256 ? "gemm_bwd_data_128x256_bf16" : "gemm_bwd_data_128x128_bf16";
-    if (relu) launch_rows16<true>(name, a, Hnext, b, e, n, N, s);
-    else launch_rows16<false>(name, a, nullptr, b, e, n, N, s);
+    if (relu) launch_rows16<true>("gemm_bwd_data", a, Hnext, b, e, n, N, s);
+    else launch_rows16<false>("gemm_bwd_data", a, nullptr, b, e, n, N, s);
     return true;
 }
 
@@ -102,10 +101,9 @@ bool stream_dense_bwd_data(int64_t n, const uint16_t *dY, const uint16_t *Y, int
     if (n < kTransformRows || (F_in < 256 && n < kStreamRows) || F_in <= 128 || F_out < 64) return false;
     if (!a.ok() || (relu && !aligned(Y, 4)) || !spare || !aligned(spare, 16) || size_t(F_in) * pitch * 2 > spare_bytes) return false;
     const AsyncRows16 b = narrow_rows(NarrowStack{W, W, F_in, F_out}, F_in, F_out, pitch, spare, s);
-    const char *name = "gemm_dense_bwd_data_bf16";
     const auto launch = [&](const auto &e) {
-        if (relu) launch_rows16<true>(name, a, Y, b, e, n, F_in, s);
-        else launch_rows16<false>(name, a, nullptr, b, e, n, F_in, s);
+        if (relu) launch_rows16<true>("gemm_dense_bwd_data", a, Y, b, e, n, F_in, s);
+        else launch_rows16<false>("gemm_dense_bwd_data", a, nullptr, b, e, n, F_in, s);
     };
     if (row_scale) launch(DenseEpilogue<uint16_t, true>{dX, ldx, nullptr, row_scale, false, F_in});
     else launch(DenseEpilogue<uint16_t, false>{dX, ldx, nullptr, nullptr, false, F_in});
@@ -120,7 +118,7 @@ bool stream_sage_tf_fwd(int64_t n, const uint16_t *H, int64_t ldh, int F_in, con
     if (n < kTransformRows || (F_in % kAsyncK16 != 0 && n < kStreamRows)) return false;
     if (!a.ok() || !spare || size_t(2) * Fp * pitch * 2 > spare_bytes) return false;
     const AsyncRows16 b = narrow_rows(NarrowSidesT{W_self, W_neigh, F_out, Fp, F_in}, 2 * Fp, F_in, pitch, spare, s);
-    launch_rows16<false>("gemm_tf_fwd_bf16", a, nullptr, b, HalvesEpilogue<uint16_t>{Ys, Yn, ldy, Fp, F_out}, n, 2 * Fp, s);
+    launch_rows16<false>("gemm_tf_fwd", a, nullptr, b, HalvesEpilogue<uint16_t>{Ys, Yn, ldy, Fp, F_out}, n, 2 * Fp, s);
     return true;
 }
 
@@ -132,7 +130,7 @@ bool stream_sage_tf_bwd_data(int64_t n, const uint16_t *dHnext, int64_t ld_next,
     if (n < kTransformRows || (Fp < 32 && n < kStreamRows)) return false;
     if (!a.ok() || !spare || size_t(F_in) * 2 * Fp * 2 > spare_bytes) return false;
     const AsyncRows16 b = narrow_rows(NarrowSides{W_self, W_neigh, F_out, Fp}, F_in, 2 * Fp, 2 * Fp, spare, s);
-    launch_rows16<false>("gemm_tf_bwd_data_bf16", a, nullptr, b, RowsEpilogue<uint16_t>{dH, ldh}, n, F_in, s);
+    launch_rows16<false>("gemm_tf_bwd_data", a, nullptr, b, RowsEpilogue<uint16_t>{dH, ldh}, n, F_in, s);
     return true;
 }
 
@@ -166,13 +164,11 @@ bool stream_sage_bwd_weight(int64_t n, const uint16_t *H, int64_t ldh, const uin
     const AsyncCols16 a{H, ldh, M, ldm, F_in, Fq, 2 * Fq, n}, b{dHnext, ld_next, dHnext, ld_next, F_out, No, No, n};
     if (!a.ok() || !b.ok() || (relu && !aligned(Hnext, 4))) return false;
     if (F_out > 128) {
-        const char *name = "gemm_bwd_weight_256x256_bf16";
-        if (relu) launch_weight16<256, 2, 3, true>(name, a, b, Hnext, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
-        else launch_weight16<256, 2, 4, false>(name, a, b, nullptr, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
+        if (relu) launch_weight16<256, 2, 3, true>("gemm_bwd_weight", a, b, Hnext, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
+        else launch_weight16<256, 2, 4, false>("gemm_bwd_weight", a, b, nullptr, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
     } else {
-        const char *name = F_out <= 64 ? "gemm_bwd_weight_128x64_bf16" : "gemm_bwd_weight_128x128_bf16";
-        if (relu) launch_weight16<128, 1, 4, true>(name, a, b, Hnext, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
-        else launch_weight16<128, 1, 6, false>(name, a, b, nullptr, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
+        if (relu) launch_weight16<128, 1, 4, true>("gemm_bwd_weight", a, b, Hnext, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
+        else launch_weight16<128, 1, 6, false>("gemm_bwd_weight", a, b, nullptr, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
     }
     return true;
 }
@@ -190,13 +186,12 @@ bool stream_dense_bwd_weight(int64_t n, const uint16_t *X, int64_t ldx, const ui
     const int64_t items = ceil_div(Fq, 256) * ceil_div(F_out, F_out > 128 ? 256 : 128) * w.n_splits;
     if (n < kManyRows || items < 112 || (F_in <= 128 && F_out <= 128 && n < kStreamRows) ||
         (F_out <= 64 && ceil_div(Fq, 256) * 256 * 2 > 3 * Fq && n < kStreamRows) || !a.ok() || !b.ok() || (relu && !aligned(Y, 4))) return false;
-    const char *name = "gemm_dense_bwd_weight_bf16";
     if (F_out > 128) {
-        if (relu) launch_weight16<256, 2, 3, true>(name, a, b, Y, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
-        else launch_weight16<256, 2, 4, false>(name, a, b, nullptr, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
+        if (relu) launch_weight16<256, 2, 3, true>("gemm_dense_bwd_weight", a, b, Y, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
+        else launch_weight16<256, 2, 4, false>("gemm_dense_bwd_weight", a, b, nullptr, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
     } else {
-        if (relu) launch_weight16<128, 1, 4, true>(name, a, b, Y, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
-        else launch_weight16<128, 1, 6, false>(name, a, b, nullptr, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
+        if (relu) launch_weight16<128, 1, 4, true>("gemm_dense_bwd_weight", a, b, Y, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
+        else launch_weight16<128, 1, 6, false>("gemm_dense_bwd_weight", a, b, nullptr, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
     }
     return true;
 }
@@ -207,8 +202,8 @@ bool stream_sage_tf_bwd_weight(int64_t n, const uint16_t *H, int64_t ldh, const 
     const int Fq = int(round_up(size_t(F_in), 8));
     const AsyncCols16 a{H, ldh, H, ldh, F_in, Fq, Fq, n}, b{dHnext, ld_next, dYn, ldy, F_out, Fp, 2 * Fp, n};
     if (n < (F_in <= 128 ? kStreamRows : kManyRows) || !a.ok() || !b.ok()) return false;
-    if (2 * Fp > 128) launch_weight16<256, 2, 4, false>("gemm_tf_bwd_weight_bf16", a, b, nullptr, 2 * Fp, w.k_per_split, w.n_splits, partial, colsum, s);
-    else launch_weight16<128, 1, 6, false>("gemm_tf_bwd_weight_bf16", a, b, nullptr, 2 * Fp, w.k_per_split, w.n_splits, partial, colsum, s);
+    if (2 * Fp > 128) launch_weight16<256, 2, 4, false>("gemm_tf_bwd_weight", a, b, nullptr, 2 * Fp, w.k_per_split, w.n_splits, partial, colsum, s);
+    else launch_weight16<128, 1, 6, false>("gemm_tf_bwd_weight", a, b, nullptr, 2 * Fp, w.k_per_split, w.n_splits, partial, colsum, s);
     return true;
 }
 
