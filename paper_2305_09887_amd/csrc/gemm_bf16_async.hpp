@@ -94,9 +94,12 @@ __host__ __device__ __forceinline__ uint32_t where_positive(uint32_t g, uint32_t
     return g & ~__builtin_bit_cast(uint32_t, __builtin_bit_cast(shortx2, top) >> shortx2{15, 15});
 }
 
-// C[M,N] = A[M,K] B[N,K]^T.  kMask: A's elements count where `mask`, an array like A's only part, is positive.  Persistent blocks
-// over tiles numbered as in gemm_bf16_kernel, m then n.
-template <int BM, int BN, int WM, int WN, int kStages, bool kMask, class Epi>
+// C[M,N] = A[M,K] B[N,K]^T.  kMask: A's elements count where `mask`, an array like A's only part, is positive.  kCut: the last column
+// cuts a tile, whose results are then stored in pairs too (element by element a cut tile of 256 was dearer than the whole ones of 128
+// that it replaced: input gradient of 384 columns from 64 with ReLU, 181,000 rows, 102 -> 74 us against 92); in a kernel of its own, for
+// the comparisons slow the others (128 -> 256 with ReLU at 400,000 rows 156 -> 163).  Persistent blocks over tiles numbered as in
+// gemm_bf16_kernel, m then n.
+template <int BM, int BN, int WM, int WN, int kStages, bool kMask, bool kCut, class Epi>
 __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_async_kernel(AsyncRows16 a, const uint16_t *mask, AsyncRows16 b, Epi epi, int64_t M, int N,
                                                                          int n_tiles, int64_t total_work)
 {
@@ -267,7 +270,7 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_async_kernel(AsyncRo
 #pragma unroll
         for (int j = 0; j < TN; ++j) caux[j] = Epi::kColAux ? col_aux[aux][wn0 + j * 32 + l31] : 0.0f;
         const bool whole = m0 + BM <= M && n0 + BN <= N;
-        const bool pairs = whole && pairs_ok_of(epi);
+        const bool pairs = (kCut ? m0 + BM <= M && N % 2 == 0 : whole) && pairs_ok_of(epi);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             float raux[16];
@@ -285,7 +288,7 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_async_kernel(AsyncRo
                         const float v0 = epi.value(padding ? 0.0f : acc[i][j][r], caux[j], raux[r], col);
                         const float v1 = epi.value(padding ? 0.0f : acc[i][j][r + 1], caux[j], raux[r + 1], col);
                         const float got = __shfl_xor(odd ? v0 : v1, 1, kWave);
-                        store_pair(epi, row0 + 8 * (r / 4) + r % 4 + odd, col - odd, odd ? pack_bf16(got, v1) : pack_bf16(v0, got));
+                        if (!kCut || col < N) store_pair(epi, row0 + 8 * (r / 4) + r % 4 + odd, col - odd, odd ? pack_bf16(got, v1) : pack_bf16(v0, got));
                     }
                 } else if (col < N) {
 #pragma unroll
@@ -315,8 +318,11 @@ static void launch_async16(const char *what, const AsyncRows16 &a, const uint16_
     char name[48];
     snprintf(name, sizeof(name), "%s_%dx%d_bf16", what, BM, BN);
     TMA_TIMED(name, s);
-    hipLaunchKernelGGL((gemm_bf16_async_kernel<BM, BN, WM, WN, kStages, kMask, Epi>), dim3(unsigned(blocks_per_die * kXcds)), dim3(WM * WN * 64), 0, s, a,
-                       mask, b, e, M, N, n_tiles, total);
+    const dim3 grid(unsigned(blocks_per_die * kXcds)), block(WM * WN * 64);
+    if (N % BN == 0)
+        hipLaunchKernelGGL((gemm_bf16_async_kernel<BM, BN, WM, WN, kStages, kMask, false, Epi>), grid, block, 0, s, a, mask, b, e, M, N, n_tiles, total);
+    else
+        hipLaunchKernelGGL((gemm_bf16_async_kernel<BM, BN, WM, WN, kStages, kMask, true, Epi>), grid, block, 0, s, a, mask, b, e, M, N, n_tiles, total);
 }
 
 // ---------------------------------------------------------------------------
