@@ -24,7 +24,9 @@ static void launch_rows16(const char *what, const AsyncRows16 &a, const uint16_t
         launch_async16<256, 256, 4, 2, 3, true>(what, a, mask, b, e, M, N, s);
     } else {
         if (N <= 96) launch_async16<256, 96, 4, 1, 3, false>(what, a, mask, b, e, M, N, s);
-        else if (N <= 128) launch_async16<256, 128, 4, 1, 3, false>(what, a, mask, b, e, M, N, s);
+        // (and where tiles of 256 would reach past more columns.  us, with them / so / gemm_bf16_kernel, 181,000 rows: forward 256 -> 300
+        // 168 / 150 / 195, 64 -> 384 80 / 64 / 80; input gradient of 300 from 256 96 / 78 / 118.  The mask is better applied once to 256.)
+        else if (N <= 128 || ceil_div(N, 128) % 2 == 1) launch_async16<256, 128, 4, 1, 3, false>(what, a, mask, b, e, M, N, s);
         else launch_async16<256, 256, 4, 2, 4, false>(what, a, mask, b, e, M, N, s);
     }
 }

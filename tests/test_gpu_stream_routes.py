@@ -1,0 +1,68 @@
+"""Which kernel runs a bf16 product, on both sides of the lines of the dispatch: each was drawn where the one became the faster of the two.  The name of a
+launch says the tile: 256 rows for the streamed products, none or 128 for the others.  (What they return: test_gpu_stream_products.py.)"""
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2305_09887_amd import binding
+    binding.lib()
+    return binding
+
+
+def rows(n, f):
+    return torch.zeros(n, (f + 7) // 8 * 8, dtype=torch.bfloat16, device="cuda")[:, :f]
+
+
+def launches(B, call):
+    B.tma_profile_begin(None)
+    call()
+    return {name for name in B.tma_profile_end() if name.startswith("gemm_")}
+
+
+def graph(n):
+    return torch.zeros(n + 1, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"), torch.ones(n, device="cuda")
+
+
+def weights(fi, fo):
+    return torch.zeros(fi, fo, device="cuda"), torch.zeros(fi, fo, device="cuda")
+
+
+def forward(B, n, fi, fo):
+    w = weights(fi, fo)
+    Wt = B.tma_sage_prepare_weights_bf16(*w) if B.tma_sage_layer_aggregates_first(fi, fo, B.TMA_BF16) else None
+    return launches(B, lambda: B.tma_sage_layer_fwd(*graph(n), rows(n, fi), *w, torch.zeros(fo, device="cuda"), B.TMA_ACT_NONE, Wt=Wt))
+
+
+def backward(B, n, fi, fo, relu, what):
+    act = B.TMA_ACT_RELU if relu else B.TMA_ACT_NONE
+    got = launches(B, lambda: B.tma_sage_layer_bwd(*graph(n), rows(n, fi), rows(n, fi), rows(n, fo), rows(n, fo), *weights(fi, fo), act))
+    return {name for name in got if what in name}
+
+
+def dense(B, n, fi, fo, relu, what):
+    act = B.TMA_ACT_RELU if relu else B.TMA_ACT_NONE
+    got = launches(B, lambda: B.tma_dense_bwd(rows(n, fi), rows(n, fo), rows(n, fo), weights(fi, fo)[0], act))
+    return {name for name in got if what in name}
+
+
+@pytest.mark.parametrize("n,fi,fo,name", [(65536, 128, 256, "gemm_fwd_256x256_bf16"), (65536, 128, 260, "gemm_fwd_256x128_bf16"),
+                                          (65536, 128, 384, "gemm_fwd_256x128_bf16"), (65536, 128, 385, "gemm_fwd_256x256_bf16")])
+def test_forward(B, n, fi, fo, name):
+    assert forward(B, n, fi, fo) == {name}
+
+
+@pytest.mark.parametrize("n,fi,fo,relu,name", [(65536, 150, 128, False, "gemm_bwd_data_256x128_bf16"), (65536, 150, 128, True, "gemm_bwd_data_256x256_bf16")])
+def test_input_gradient(B, n, fi, fo, relu, name):
+    assert backward(B, n, fi, fo, relu, "bwd_data") == {name}
+
+
+@pytest.mark.parametrize("n,fi,fo,relu,name", [(98304, 384, 256, False, "gemm_dense_bwd_data_256x128_bf16"),
+                                               (98304, 384, 256, True, "gemm_dense_bwd_data_256x256_bf16")])
+def test_dense_input_gradient(B, n, fi, fo, relu, name):
+    assert dense(B, n, fi, fo, relu, "bwd_data") == {name}
