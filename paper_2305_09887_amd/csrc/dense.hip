@@ -182,7 +182,7 @@ int launch_dense_gemm_bwd_weight(int64_t n, const void *X, int64_t ldx, const vo
     if (dtype != TMA_F32 && dtype != TMA_BF16)
         return fail(TMA_ERR_UNSUPPORTED_DTYPE, "dense gemm bwd weight: dtype %d", dtype);
     if (F_out == 0 || F_in == 0) return TMA_OK;
-    const WeightSplit w = plan_dense_weight_split(n, F_in, F_out);
+    WeightSplit w = plan_dense_weight_split(n, F_in, F_out);
     if (ws_bytes < w.partial_bytes + w.colsum_bytes)
         return fail(TMA_ERR_WORKSPACE_TOO_SMALL, "dense gemm bwd weight: workspace %zu < %zu", ws_bytes,
                     w.partial_bytes + w.colsum_bytes);

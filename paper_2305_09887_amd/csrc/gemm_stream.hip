@@ -175,19 +175,31 @@ bool stream_sage_bwd_weight(int64_t n, const uint16_t *H, int64_t ldh, const uin
     return true;
 }
 
+// A plan made for tiles of 128 may leave a last round of items that few of the compute units have one of (three of those tiles: 171 ranges, 342
+// items of two of these): fewer ranges of nodes then, so that every unit has as many.  us at 181,000 nodes, gemm_bf16_kernel / as planned / so:
+//   dense with ReLU 264 -> 66 94 / 106 / 73, 384 -> 47 75 / 104 / 71, 100 -> 300 109 / 124 / 88; transformed first 264 -> 20 86 / 90 / 69
+static void whole_rounds(int64_t n, int64_t tiles, WeightSplit &w)
+{
+    const int64_t items = tiles * w.n_splits, ranges = items / 256 * 256 / tiles;
+    if (items <= 256 || ranges < 1) return;
+    w.k_per_split = int64_t(round_up(size_t(ceil_div(n, ranges)), kAsyncK16));
+    w.n_splits = int(ceil_div(n, w.k_per_split));
+}
+
 // The dense layer's, in the ranges of nodes that it plans: where they make an item for half of the compute units or more, and not where
 // much of a narrow tile is padding.  us, gemm_bf16_kernel -> here, both with the second stage, 98,304 / 181,000 / 1,500,000 nodes:
 //   256 -> 256 72 -> 46 / 109 -> 62 / 712 -> 339 (128 items), with ReLU 83 -> 62 / 125 -> 94 / 790 -> 595; 128 -> 256 62 -> 48 / 86 -> 62 /
 //   432 -> 359; 256 -> 47 37 -> 36 / 54 -> 41 / 308 -> 172; 150 -> 150, element by element before, 148 -> 44 / 279 -> 58 / 2,352 -> 324;
 //   300 -> 47 58 -> 56 / 71 -> 78 / 605 -> 433
 bool stream_dense_bwd_weight(int64_t n, const uint16_t *X, int64_t ldx, const uint16_t *dY, const uint16_t *Y, int64_t ld, int F_in, int F_out,
-                             bool relu, const WeightSplit &w, float *partial, float *colsum, hipStream_t s)
+                             bool relu, WeightSplit &w, float *partial, float *colsum, hipStream_t s)
 {
     const int Fq = int(round_up(size_t(F_in), 8)), No = int(round_up(size_t(F_out), 8));
     const AsyncCols16 a{X, ldx, X, ldx, F_in, Fq, Fq, n}, b{dY, ld, dY, ld, F_out, No, No, n};
-    const int64_t items = ceil_div(Fq, 256) * ceil_div(F_out, F_out > 128 ? 256 : 128) * w.n_splits;
-    if (n < kManyRows || items < 112 || (F_in <= 128 && F_out <= 128 && n < kStreamRows) ||
+    const int64_t tiles = ceil_div(Fq, 256) * ceil_div(F_out, F_out > 128 ? 256 : 128);
+    if (n < kManyRows || tiles * w.n_splits < 112 || (F_in <= 128 && F_out <= 128 && n < kStreamRows) ||
         (F_out <= 64 && ceil_div(Fq, 256) * 256 * 2 > 3 * Fq && n < kStreamRows) || !a.ok() || !b.ok() || (relu && !aligned(Y, 4))) return false;
+    whole_rounds(n, tiles, w);
     if (F_out > 128) {
         if (relu) launch_weight16<256, 2, 3, true>("gemm_dense_bwd_weight", a, b, Y, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
         else launch_weight16<256, 2, 4, false>("gemm_dense_bwd_weight", a, b, nullptr, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
@@ -199,11 +211,12 @@ bool stream_dense_bwd_weight(int64_t n, const uint16_t *X, int64_t ldx, const ui
 }
 
 bool stream_sage_tf_bwd_weight(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *dHnext, int64_t ld_next, const uint16_t *dYn, int64_t ldy,
-                               int F_in, int F_out, int Fp, const WeightSplit &w, float *partial, float *colsum, hipStream_t s)
+                               int F_in, int F_out, int Fp, WeightSplit &w, float *partial, float *colsum, hipStream_t s)
 {
     const int Fq = int(round_up(size_t(F_in), 8));
     const AsyncCols16 a{H, ldh, H, ldh, F_in, Fq, Fq, n}, b{dHnext, ld_next, dYn, ldy, F_out, Fp, 2 * Fp, n};
     if (n < (F_in <= 128 ? kStreamRows : kManyRows) || !a.ok() || !b.ok()) return false;
+    whole_rounds(n, ceil_div(Fq, 256) * ceil_div(2 * Fp, 2 * Fp > 128 ? 256 : 128), w);
     if (2 * Fp > 128) launch_weight16<256, 2, 4, false>("gemm_tf_bwd_weight", a, b, nullptr, 2 * Fp, w.k_per_split, w.n_splits, partial, colsum, s);
     else launch_weight16<128, 1, 6, false>("gemm_tf_bwd_weight", a, b, nullptr, 2 * Fp, w.k_per_split, w.n_splits, partial, colsum, s);
     return true;

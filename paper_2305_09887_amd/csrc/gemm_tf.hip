@@ -182,7 +182,7 @@ int launch_sage_tf_gemm_bwd_weight(int64_t n, const void *H, int64_t ldh, const 
 {
     if (dtype != TMA_F32 && dtype != TMA_BF16) return fail(TMA_ERR_UNSUPPORTED_DTYPE, "sage gemm tf bwd: dtype %d", dtype);
     const int Fp = pad_cols(F_out, dtype);
-    const WeightSplit w = plan_tf_weight_split(n, F_in, Fp);
+    WeightSplit w = plan_tf_weight_split(n, F_in, Fp);
     if (ws_bytes < w.partial_bytes + w.colsum_bytes)
         return fail(TMA_ERR_WORKSPACE_TOO_SMALL, "sage gemm tf bwd weight: workspace %zu < %zu", ws_bytes,
                     w.partial_bytes + w.colsum_bytes);

@@ -100,17 +100,17 @@ struct WeightSplit {   // of a weight gradient: ranges of nodes with a partial r
     int64_t k_per_split;
     size_t partial_bytes, colsum_bytes;
 };
-// in ws_bytes of partial results at most; false: too few nodes, or columns
+// in ws_bytes of partial results at most; false: too few nodes, or columns.  (The other two take a plan and may put fewer ranges into it.)
 bool plan_stream_weight(int64_t n, int32_t F_in, int32_t F_out, size_t ws_bytes, WeightSplit &w);
 bool stream_sage_bwd_weight(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *M, int64_t ldm, const uint16_t *dHnext, const uint16_t *Hnext,
                             int64_t ld_next, int F_in, int F_out, bool relu, const WeightSplit &w, float *partial, float *colsum,
                             hipStream_t stream);
 bool stream_sage_tf_bwd_weight(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *dHnext, int64_t ld_next, const uint16_t *dYn, int64_t ldy,
-                               int F_in, int F_out, int Fp, const WeightSplit &w, float *partial, float *colsum, hipStream_t stream);
+                               int F_in, int F_out, int Fp, WeightSplit &w, float *partial, float *colsum, hipStream_t stream);
 bool stream_dense_bwd_data(int64_t n, const uint16_t *dY, const uint16_t *Y, int64_t ld, const float *W, int F_in, int F_out, bool relu,
                            const float *row_scale, uint16_t *dX, int64_t ldx, void *spare, size_t spare_bytes, hipStream_t stream);
 bool stream_dense_bwd_weight(int64_t n, const uint16_t *X, int64_t ldx, const uint16_t *dY, const uint16_t *Y, int64_t ld, int F_in, int F_out,
-                             bool relu, const WeightSplit &w, float *partial, float *colsum, hipStream_t stream);
+                             bool relu, WeightSplit &w, float *partial, float *colsum, hipStream_t stream);
 bool stream_sage_tf_fwd(int64_t n, const uint16_t *H, int64_t ldh, int F_in, const float *W_self, const float *W_neigh, int F_out, int Fp,
                         uint16_t *Ys, uint16_t *Yn, int64_t ldy, void *spare, size_t spare_bytes, hipStream_t stream);
 bool stream_sage_tf_bwd_data(int64_t n, const uint16_t *dHnext, int64_t ld_next, const uint16_t *dYn, int64_t ldy, const float *W_self,

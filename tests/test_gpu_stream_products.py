@@ -65,7 +65,7 @@ def test_layer(B, n, fi, fo, relu):
 
 
 # transformed first: H [W_self | W_neigh], and [dZ | dYn] [W_self | W_neigh]^T, with outputs of odd width too
-@pytest.mark.parametrize("n,fi,fo", [(98304, 256, 47), (98305, 128, 41), (98560, 64, 5), (98400, 96, 48), (98432, 96, 33), (98500, 320, 140),
+@pytest.mark.parametrize("n,fi,fo", [(98304, 256, 47), (98305, 128, 41), (98560, 64, 5), (98400, 96, 48), (98432, 96, 33), (98500, 320, 140), (65570, 264, 20),
                                      (98310, 128, 50)])
 def test_transform_first(B, n, fi, fo):
     assert not B.tma_sage_layer_aggregates_first(fi, fo, B.TMA_BF16)
@@ -88,7 +88,8 @@ def test_transform_first(B, n, fi, fo):
 
 
 # single-operand backward products, with the row scale that a GCN layer puts into its input gradient left out
-@pytest.mark.parametrize("n,fi,fo", [(98304, 256, 64), (98305, 256, 47), (98400, 130, 256), (98320, 264, 130), (98310, 128, 258)])
+@pytest.mark.parametrize("n,fi,fo", [(98304, 256, 64), (98305, 256, 47), (98400, 130, 256), (98320, 264, 130), (98310, 128, 258),
+                                     (65600, 264, 66), (65570, 600, 48)])
 @pytest.mark.parametrize("relu", [False, True])
 def test_dense_backward(B, n, fi, fo, relu):
     X, W, g, h = bf16(1, n, fi), bf16(2, fi, fo), bf16(3, n, fo), bf16(4, n, fo)
