@@ -74,7 +74,9 @@ bool stream_sage_fwd(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *
 {
     const int K = 2 * F_in;
     const AsyncRows16 a{H, ldh, M, ldm, F_in, F_in, K, n};
-    if (n < kManyRows || !a.ok() || F_out <= 64 || (F_out <= 128 && F_in % kAsyncK16 != 0 && n < kStreamRows)) return false;
+    if (n < kManyRows || !a.ok() || F_out <= 64) return false;
+    // (halves that end inside a slab: 100 -> 260 and 640 60 -> 60, 80 -> 86 at 80,000 rows, 155 -> 148, 266 -> 253 at 262,144)
+    if (F_in % kAsyncK16 != 0 && (F_out <= 128 ? n < kStreamRows : F_out > 256 && F_in % 4 == 0 && n < 2 * kManyRows)) return false;
     launch_rows16<false>("gemm_fwd", a, nullptr,
                          AsyncRows16{Wt, K, Wt, K, K, K, K, F_out}, FwdEpilogue<uint16_t>{Hnext, ld_next, bias, relu}, n, F_out, s);
     return true;
