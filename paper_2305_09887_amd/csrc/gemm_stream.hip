@@ -89,6 +89,9 @@ bool stream_sage_bwd_data(int64_t n, const uint16_t *dHnext, const uint16_t *Hne
     const int N = 2 * F_in, pitch = int(round_up(size_t(F_out), 8));
     const AsyncRows16 a{dHnext, ld_next, dHnext, ld_next, F_out, F_out, F_out, n};
     if (n < kManyRows || (N < 256 && n < kStreamRows) || N <= (relu ? 128 : 64)) return false;
+    // (a last slab pair by pair, where gemm_bf16_kernel reads groups of four: 128 -> 100 32 -> 38 at 98,304 rows, 41 -> 40 at 131,072, 130 -> 110 at
+    // 400,000; with ReLU 69 -> 76 at 181,000 and 155 -> 148)
+    if (F_out % kAsyncK16 != 0 && F_out % 4 == 0 && n < (relu ? 4 : 2) * kManyRows) return false;
     if (!a.ok() || (relu && !aligned(Hnext, 4)) || !spare || size_t(N) * pitch * 2 > spare_bytes) return false;
     const AsyncRows16 b = narrow_rows(NarrowStack{W_self, W_neigh, F_in, F_out}, N, F_out, pitch, spare, s);
     const BwdDataEpilogue<uint16_t> e{dH_self_out, ldh, dM_scaled_out, inv_deg, F_in};
