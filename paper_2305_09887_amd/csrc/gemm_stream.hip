@@ -106,6 +106,9 @@ bool stream_dense_bwd_data(int64_t n, const uint16_t *dY, const uint16_t *Y, int
     const int pitch = int(round_up(size_t(F_out), 8));
     const AsyncRows16 a{dY, ld, dY, ld, F_out, F_out, F_out, n};
     if (n < kTransformRows || (F_in < 256 && n < kStreamRows) || F_in <= 128 || F_out < 64) return false;
+    // (a last slab pair by pair: 256 <- 66 and 100 32 -> 36, 33 -> 39 at 98,304 rows, 41 -> 37, 42 -> 40 at 131,072; with ReLU in tiles of 256 that the last
+    // column cuts 384 <- 66 86 -> 104 at 181,000, 192 -> 212 at 400,000, 508 -> 500 at 1,048,576)
+    if (F_out % kAsyncK16 != 0 && n < (relu && F_in > 256 ? kStreamRows / 2 : 2 * kManyRows)) return false;
     if (!a.ok() || (relu && !aligned(Y, 4)) || !spare || !aligned(spare, 16) || size_t(F_in) * pitch * 2 > spare_bytes) return false;
     const AsyncRows16 b = narrow_rows(NarrowStack{W, W, F_in, F_out}, F_in, F_out, pitch, spare, s);
     const auto launch = [&](const auto &e) {

@@ -68,6 +68,8 @@ def test_input_gradient(B, n, fi, fo, relu, name):
 
 
 @pytest.mark.parametrize("n,fi,fo,relu,name", [(98304, 384, 256, False, "gemm_dense_bwd_data_256x128_bf16"),
-                                               (98304, 384, 256, True, "gemm_dense_bwd_data_256x256_bf16")])
+                                               (98304, 384, 256, True, "gemm_dense_bwd_data_256x256_bf16"),
+                                               (131071, 256, 100, False, "gemm_dense_bwd_data_bf16"), (131072, 256, 100, True, "gemm_dense_bwd_data_256x256_bf16"),
+                                               (524287, 384, 66, True, "gemm_dense_bwd_data_bf16"), (524288, 384, 66, True, "gemm_dense_bwd_data_256x256_bf16")])
 def test_dense_input_gradient(B, n, fi, fo, relu, name):
     assert dense(B, n, fi, fo, relu, "bwd_data") == {name}
