@@ -125,7 +125,10 @@ bool stream_sage_tf_fwd(int64_t n, const uint16_t *H, int64_t ldh, int F_in, con
 {
     const AsyncRows16 a{H, ldh, H, ldh, F_in, F_in, F_in, n};
     const int pitch = int(round_up(size_t(F_in), 8));
-    if (n < kTransformRows || (F_in % kAsyncK16 != 0 && n < kStreamRows)) return false;
+    if (n < (F_in < 256 || Fp <= 24 ? 2 * kManyRows : kTransformRows) || (F_in % kAsyncK16 != 0 && n < kStreamRows)) return false;
+    // (two halves of 32 are a whole tile of 64 there and two thirds of one here: 128 -> 32 22 -> 28 at 181,000 rows, 40 -> 43 at 400,000, 106 -> 100 at
+    // 1,048,576; 100 -> 32 114 -> 132)
+    if (Fp == 32 && (n < kStreamRows / 2 || F_in % kAsyncK16 != 0)) return false;
     if (!a.ok() || !spare || size_t(2) * Fp * pitch * 2 > spare_bytes) return false;
     const AsyncRows16 b = narrow_rows(NarrowSidesT{W_self, W_neigh, F_out, Fp, F_in}, 2 * Fp, F_in, pitch, spare, s);
     launch_rows16<false>("gemm_tf_fwd", a, nullptr, b, HalvesEpilogue<uint16_t>{Ys, Yn, ldy, Fp, F_out}, n, 2 * Fp, s);

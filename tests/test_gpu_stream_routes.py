@@ -73,3 +73,11 @@ def test_input_gradient(B, n, fi, fo, relu, name):
                                                (524287, 384, 66, True, "gemm_dense_bwd_data_bf16"), (524288, 384, 66, True, "gemm_dense_bwd_data_256x256_bf16")])
 def test_dense_input_gradient(B, n, fi, fo, relu, name):
     assert dense(B, n, fi, fo, relu, "bwd_data") == {name}
+
+
+@pytest.mark.parametrize("n,fi,fo,name", [(98303, 256, 47, "gemm_tf_fwd_bf16"), (98304, 256, 47, "gemm_tf_fwd_256x96_bf16"),
+                                          (131071, 128, 47, "gemm_tf_fwd_bf16"), (131072, 128, 47, "gemm_tf_fwd_256x96_bf16"),
+                                          (131071, 256, 20, "gemm_tf_fwd_bf16"), (131072, 256, 20, "gemm_tf_fwd_256x96_bf16"),
+                                          (524287, 128, 32, "gemm_tf_fwd_bf16"), (524288, 128, 32, "gemm_tf_fwd_256x96_bf16")])
+def test_transform_first_forward(B, n, fi, fo, name):
+    assert forward(B, n, fi, fo) == {name}
