@@ -140,7 +140,11 @@ bool stream_sage_tf_bwd_data(int64_t n, const uint16_t *dHnext, int64_t ld_next,
                              hipStream_t s)
 {
     const AsyncRows16 a{dHnext, ld_next, dYn, ldy, Fp, F_out, 2 * Fp, n};
-    if (n < kTransformRows || (Fp < 32 && n < kStreamRows)) return false;
+    // (slabs pair by pair where a half ends in one, two of them where its width is 8 mod 16, and tiles that are half empty.  Both launches, 131,072 /
+    // 262,144 / 400,000 rows: 128 <- 40 21 -> 28 / 35 -> 41 / 52 -> 60, 153 -> 136 at 1,048,576; 128 <- 32 19 -> 21 / 30 -> 29 / 43 -> 41; 256 <- 40 36 -> 36 / 70
+    // -> 61, 43 -> 46 at 160,000; 160 <- 56 45 -> 39 / 84 -> 65)
+    const bool half = F_in > 96 && F_in <= 128, two = Fp % 16 != 0;
+    if (n < (Fp < 32 || (half && two) ? kStreamRows : half || two ? 4 * kManyRows : 2 * kManyRows)) return false;
     if (!a.ok() || !spare || size_t(F_in) * 2 * Fp * 2 > spare_bytes) return false;
     const AsyncRows16 b = narrow_rows(NarrowSides{W_self, W_neigh, F_out, Fp}, F_in, 2 * Fp, 2 * Fp, spare, s);
     launch_rows16<false>("gemm_tf_bwd_data", a, nullptr, b, RowsEpilogue<uint16_t>{dH, ldh}, n, F_in, s);

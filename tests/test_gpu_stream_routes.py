@@ -81,3 +81,11 @@ def test_dense_input_gradient(B, n, fi, fo, relu, name):
                                           (524287, 128, 32, "gemm_tf_fwd_bf16"), (524288, 128, 32, "gemm_tf_fwd_256x96_bf16")])
 def test_transform_first_forward(B, n, fi, fo, name):
     assert forward(B, n, fi, fo) == {name}
+
+
+@pytest.mark.parametrize("n,fi,fo,name", [(131071, 256, 47, "gemm_tf_bwd_data_bf16"), (131072, 256, 47, "gemm_tf_bwd_data_256x256_bf16"),
+                                          (262143, 128, 47, "gemm_tf_bwd_data_bf16"), (262144, 128, 47, "gemm_tf_bwd_data_256x128_bf16"),
+                                          (262143, 256, 40, "gemm_tf_bwd_data_bf16"), (262144, 256, 40, "gemm_tf_bwd_data_256x256_bf16"),
+                                          (1048575, 128, 40, "gemm_tf_bwd_data_bf16"), (1048576, 128, 40, "gemm_tf_bwd_data_256x128_bf16")])
+def test_transform_first_input_gradient(B, n, fi, fo, name):
+    assert backward(B, n, fi, fo, False, "bwd_data") == {name}
