@@ -179,6 +179,9 @@ bool stream_sage_bwd_weight(int64_t n, const uint16_t *H, int64_t ldh, const uin
 {
     const int Fq = int(round_up(size_t(F_in), 8)), No = int(round_up(size_t(F_out), 8));
     const AsyncCols16 a{H, ldh, M, ldm, F_in, Fq, 2 * Fq, n}, b{dHnext, ld_next, dHnext, ld_next, F_out, No, No, n};
+    // (half of the tile empty and a mask for all of it: 64 -> 96 99 -> 80 at 400,000 nodes, 144 -> 123 at 700,000, but 250 -> 255 at 1,500,000 and 812 -> 879 at
+    // 6,000,000, where the partial results no longer tell; 48 -> 96 243 -> 259 and 806 -> 905)
+    if (relu && F_in <= 64 && F_out <= 128 && n >= kStreamRows) return false;
     if (!a.ok() || !b.ok() || (relu && !aligned(Hnext, 4))) return false;
     if (F_out > 128) {
         if (relu) launch_weight16<256, 2, 3, true>("gemm_bwd_weight", a, b, Hnext, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
@@ -212,6 +215,8 @@ bool stream_dense_bwd_weight(int64_t n, const uint16_t *X, int64_t ldx, const ui
     const int Fq = int(round_up(size_t(F_in), 8)), No = int(round_up(size_t(F_out), 8));
     const AsyncCols16 a{X, ldx, X, ldx, F_in, Fq, Fq, n}, b{dY, ld, dY, ld, F_out, No, No, n};
     const int64_t tiles = ceil_div(Fq, 256) * ceil_div(F_out, F_out > 128 ? 256 : 128);
+    // (half of a narrow tile empty: 256 -> 64 34 -> 36 at 80,000 nodes, 39 -> 38 at 98,304; with ReLU 40 -> 43 and 59 -> 53 at 181,000)
+    if (F_out <= 64 && Fq <= 256 && n < (relu ? 2 * kManyRows : kTransformRows)) return false;
     if (n < kManyRows || tiles * w.n_splits < 112 || (F_in <= 128 && F_out <= 128 && n < kStreamRows) ||
         (F_out <= 64 && ceil_div(Fq, 256) * 256 * 2 > 3 * Fq && n < kStreamRows) || !a.ok() || !b.ok() || (relu && !aligned(Y, 4))) return false;
     whole_rounds(n, tiles, w);
@@ -230,7 +235,8 @@ bool stream_sage_tf_bwd_weight(int64_t n, const uint16_t *H, int64_t ldh, const 
 {
     const int Fq = int(round_up(size_t(F_in), 8));
     const AsyncCols16 a{H, ldh, H, ldh, F_in, Fq, Fq, n}, b{dHnext, ld_next, dYn, ldy, F_out, Fp, 2 * Fp, n};
-    if (n < (F_in <= 128 ? kStreamRows : kManyRows) || !a.ok() || !b.ok()) return false;
+    // (a quarter of the tile: 128 -> 32 117 -> 130, 100 -> 20 117 -> 124 at 1,048,576 nodes, 128 -> 20 358 -> 341 at 2,000,000)
+    if (n < (F_in > 128 ? kManyRows : Fp <= 32 ? 2 * kStreamRows : kStreamRows) || !a.ok() || !b.ok()) return false;
     whole_rounds(n, ceil_div(Fq, 256) * ceil_div(2 * Fp, 2 * Fp > 128 ? 256 : 128), w);
     if (2 * Fp > 128) launch_weight16<256, 2, 4, false>("gemm_tf_bwd_weight", a, b, nullptr, 2 * Fp, w.k_per_split, w.n_splits, partial, colsum, s);
     else launch_weight16<128, 1, 6, false>("gemm_tf_bwd_weight", a, b, nullptr, 2 * Fp, w.k_per_split, w.n_splits, partial, colsum, s);

@@ -89,3 +89,19 @@ def test_transform_first_forward(B, n, fi, fo, name):
                                           (1048575, 128, 40, "gemm_tf_bwd_data_bf16"), (1048576, 128, 40, "gemm_tf_bwd_data_256x128_bf16")])
 def test_transform_first_input_gradient(B, n, fi, fo, name):
     assert backward(B, n, fi, fo, False, "bwd_data") == {name}
+
+
+@pytest.mark.parametrize("n,fi,fo,relu,name", [(1048575, 64, 96, True, "gemm_bwd_weight_256x128_bf16"), (1048576, 64, 96, True, "gemm_bwd_weight_128x128_bf16"),
+                                               (1048576, 64, 96, False, "gemm_bwd_weight_256x128_bf16"), (1048576, 72, 96, True, "gemm_bwd_weight_256x128_bf16"),
+                                               (1048576, 64, 136, True, "gemm_bwd_weight_256x256_bf16"),
+                                               (1048576, 128, 47, False, "gemm_tf_bwd_weight_256x128_bf16"), (1048576, 128, 20, False, "gemm_tf_bwd_weight_bf16"),
+                                               (2097152, 64, 20, False, "gemm_tf_bwd_weight_256x128_bf16")])
+def test_weight_gradient(B, n, fi, fo, relu, name):
+    assert backward(B, n, fi, fo, relu, "bwd_weight") == {name}
+
+
+@pytest.mark.parametrize("n,fi,fo,relu,name", [(98303, 256, 64, False, "gemm_dense_bwd_weight_bf16"), (98304, 256, 64, False, "gemm_dense_bwd_weight_256x128_bf16"),
+                                               (131071, 256, 64, True, "gemm_dense_bwd_weight_bf16"), (131072, 256, 64, True, "gemm_dense_bwd_weight_256x128_bf16"),
+                                               (65536, 512, 64, True, "gemm_dense_bwd_weight_256x128_bf16")])
+def test_dense_weight_gradient(B, n, fi, fo, relu, name):
+    assert dense(B, n, fi, fo, relu, "bwd_weight") == {name}
