@@ -89,11 +89,12 @@ struct AsyncWeights {
         const int c = n - (half(n) ? Np : 0);
         return c < N ? c : 0;
     }
-    // whole slabs from kt on inside one matrix; a piece that runs past the end of a row must find another row there
+    // whole slabs from kt on inside one matrix; a piece that runs past the end of a row, by three elements at most, must find other rows there:
+    // one, two of two elements, three of one (256 -> 1, the last layer of a link decoder, 17 us so and 21 lane by lane throughout)
     __host__ __device__ __forceinline__ int run(int kt) const
     {
-        const int end = (!kSide && kt >= R ? K : R) - (N % 4 == 0 ? 0 : 1);
-        return N % 4 != 0 && N < 3 ? 0 : end > kt ? (end - kt) / kAsyncK : 0;
+        const int end = (!kSide && kt >= R ? K : R) - (N % 4 == 0 ? 0 : (N + 2) / N);
+        return end > kt ? (end - kt) / kAsyncK : 0;
     }
     __host__ __device__ __forceinline__ bool pieces() const { return N % 4 == 0; }
     __host__ __device__ __forceinline__ const float *first(int kt) const

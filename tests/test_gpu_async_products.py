@@ -22,7 +22,8 @@ def inside(a, pitch, before):
 
 # 64 x 32, 64 x 64, 64 x 128, 128 x 64, 128 x 96, 128 x 128, 128 x 160; k of one slab and less, of two, with every kind of rest
 @pytest.mark.parametrize("n,fi,fo", [(70, 1, 20), (65, 16, 32), (129, 17, 33), (200, 31, 64), (24700, 18, 128), (49300, 9, 50), (25700, 15, 90),
-                                     (25700, 33, 96), (49153, 20, 128), (25729, 14, 150), (25700, 19, 160), (300, 48, 161), (131, 40, 3), (1, 64, 2)])
+                                     (25700, 33, 96), (49153, 20, 128), (25729, 14, 150), (25700, 19, 160), (300, 48, 161), (131, 40, 3), (1, 64, 2), (130, 256, 1), (70, 35, 1),
+                                     (70, 34, 2), (70, 33, 2)])
 @pytest.mark.parametrize("pitch,before", [(0, 0), (3, 1)])
 def test_dense(B, n, fi, fo, pitch, before):
     X, W, b = normal(n, n, fi), normal(2, fi, fo), normal(3, fo)
