@@ -511,7 +511,8 @@ int tma_bce_logits(int64_t count, int64_t n_pos, const void *z, int64_t ldz, int
  * all n_src rows (leading dimension ldh; NULL to skip) and builds the block's
  * transpose itself (it needs blk_row and max_entries >= the entry count).
  * Workspace: tma_sage_block_bwd_workspace_bytes(n_dst, n_src, max_entries,
- * F_in, F_out, dtype, dH_out != NULL), 256-byte aligned.
+ * F_in, F_out, dtype, dH_out != NULL), 256-byte aligned; what less of it does
+ * is said at tma_sage_layer_bwd.
  * ---------------------------------------------------------------------- */
 size_t tma_neighbor_sample_workspace_bytes(int64_t n_dst);
 

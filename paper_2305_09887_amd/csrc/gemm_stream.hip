@@ -162,9 +162,12 @@ bool plan_stream_weight(int64_t n, int32_t F_in, int32_t F_out, size_t ws_bytes,
 {
     if (F_in < 8 || F_out < 8 || (F_in <= 64 && F_out <= 64) || n < (F_out <= 64 ? 2 * kManyRows : kManyRows)) return false;
     const int64_t tiles = ceil_div(2 * round_up(size_t(F_in), 8), 256) * ceil_div(F_out, F_out > 128 ? 256 : 128);
-    int64_t want = (n >= kStreamRows ? 512 : 256) / tiles;
+    const size_t per_split = size_t(2) * F_in * F_out * 4 + size_t(F_out) * 4, operands = size_t(n) * (2 * size_t(F_in) + size_t(F_out)) * 2;
+    // (one item fewer for every eighth unit where the partial results would be more than half of the operands: 65,536 nodes, 128 / 224 / 256 items: 128 -> 256
+    // 39 / 39 / 42, 66 -> 130 36 / 36 / 38, 256 -> 256 49 / 44 / 47; with less: 181,000 nodes, 128 / 256 items: 128 -> 256 60 / 58, with ReLU 92 / 76, 256 -> 256 95 /
+    // 79 and 163 / 112)
+    int64_t want = (n >= kStreamRows ? 512 : size_t(256 / tiles) * per_split > operands / 2 ? 224 : 256) / tiles;
     if (want < 1) want = 1;
-    const size_t per_split = size_t(2) * F_in * F_out * 4 + size_t(F_out) * 4;
     if (ws_bytes < 512 + per_split) return false;
     if (size_t(want) > (ws_bytes - 512) / per_split) want = int64_t((ws_bytes - 512) / per_split);
     w.k_per_split = int64_t(round_up(size_t(ceil_div(n, want)), kAsyncK16));

@@ -356,8 +356,9 @@ struct BlockBwdWorkspace {
     size_t total() const { return dm_bytes + deg_bytes + rowptr_bytes + 2 * list_bytes + scan_bytes + weight_bytes; }
 };
 
+// least: what the call needs; else what it makes use of
 static BlockBwdWorkspace plan_block_bwd(int64_t n_dst, int64_t n_src, int64_t max_entries, int32_t F_in, int32_t F_out,
-                                        int32_t dtype, bool need_dH)
+                                        int32_t dtype, bool need_dH, bool least)
 {
     BlockBwdWorkspace w{};
     const size_t rows = size_t(n_dst > 0 ? n_dst : 1), srcs = size_t(n_src > 0 ? n_src : 1);
@@ -369,7 +370,7 @@ static BlockBwdWorkspace plan_block_bwd(int64_t n_dst, int64_t n_src, int64_t ma
         w.list_bytes = round_up(items * 4, 256);
         w.scan_bytes = exclusive_scan_i32_workspace_bytes(n_src);
     }
-    w.weight_bytes = sage_gemm_bwd_weight_workspace_bytes(n_dst, F_in, F_out);
+    w.weight_bytes = sage_gemm_bwd_weight_workspace_bytes(n_dst, F_in, F_out, least || dtype != TMA_BF16);
     return w;
 }
 
@@ -410,7 +411,7 @@ static int transpose_block(const char *fn, int64_t n_dst, int64_t n_src, int64_t
 static BlockBwdWorkspace plan_gcn_block_bwd(int64_t n_dst, int64_t n_src, int64_t max_entries, int32_t F_in, int32_t F_out,
                                             int32_t dtype, bool need_dH)
 {
-    BlockBwdWorkspace w = plan_block_bwd(n_dst, n_src, max_entries, F_in, F_out, dtype, need_dH);
+    BlockBwdWorkspace w = plan_block_bwd(n_dst, n_src, max_entries, F_in, F_out, dtype, need_dH, true);
     w.weight_bytes = dense_gemm_bwd_weight_workspace_bytes(n_dst, F_in, F_out);
     return w;
 }
@@ -618,7 +619,7 @@ extern "C" size_t tma_sage_block_bwd_workspace_bytes(int64_t n_dst, int64_t n_sr
                                                      int32_t F_out, int32_t dtype, int32_t need_dH)
 {
     if (n_dst < 0 || n_src < n_dst || max_entries < 0 || F_in < 1 || F_out < 1) return 0;
-    return tma::plan_block_bwd(n_dst, n_src, max_entries, F_in, F_out, dtype, need_dH != 0).total();
+    return tma::plan_block_bwd(n_dst, n_src, max_entries, F_in, F_out, dtype, need_dH != 0, false).total();
 }
 
 extern "C" int tma_sage_block_bwd(int64_t n_dst, int64_t n_src, int64_t max_entries, const int32_t *blk_rowptr,
@@ -639,9 +640,10 @@ extern "C" int tma_sage_block_bwd(int64_t n_dst, int64_t n_src, int64_t max_entr
     TMA_REQUIRE(dW_self && dW_neigh && dbias, TMA_ERR_INVALID_ARG, "%s: gradient output is NULL", fn);
     TMA_REQUIRE(ws && aligned(ws, 256), TMA_ERR_INVALID_ARG, "%s: workspace NULL or not 256-byte aligned", fn);
     const bool need_dH = dH_out != nullptr;
-    const BlockBwdWorkspace w = plan_block_bwd(n_dst, n_src, max_entries, F_in, F_out, dtype, need_dH);
+    BlockBwdWorkspace w = plan_block_bwd(n_dst, n_src, max_entries, F_in, F_out, dtype, need_dH, true);
     TMA_REQUIRE(ws_bytes >= w.total(), TMA_ERR_WORKSPACE_TOO_SMALL, "%s: workspace %zu < %zu bytes", fn, ws_bytes,
                 w.total());
+    w.weight_bytes += ws_bytes - w.total();
     if (n_dst > 0) {
         TMA_REQUIRE(H && M && dHnext && W_self && W_neigh, TMA_ERR_INVALID_ARG, "%s: NULL argument", fn);
         TMA_REQUIRE(act == TMA_ACT_NONE || Hnext, TMA_ERR_INVALID_ARG, "%s: Hnext is required with ReLU", fn);

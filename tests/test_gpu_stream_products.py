@@ -117,3 +117,24 @@ def test_smaller_workspace(B):
         within(dW[2].reshape(1, -1), torch.ones((1, n)).bfloat16(), g, False, "bias gradient")
     with pytest.raises(B.TmaError):
         B.tma_sage_layer_bwd(rowptr, col, inv, X.cuda(), M.cuda(), None, g.cuda(), *w, B.TMA_ACT_NONE, need_dH=False, ws=ws[:1 << 20])
+
+
+# a block's weight gradient, in the workspace that the query asks for, in less, and in less than it needs
+def test_block_workspace(B):
+    n, fi, fo = 65600, 128, 256
+    X, M, g = bf16(1, n, fi), bf16(2, n, fi), bf16(3, n, fo)
+    empty = torch.zeros(n + 1, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    w = torch.zeros(fi, fo, device="cuda"), torch.zeros(fi, fo, device="cuda")
+    dW = torch.empty(fi, fo, device="cuda"), torch.empty(fi, fo, device="cuda"), torch.empty(fo, device="cuda")
+    asked = B.tma_sage_block_bwd_workspace_bytes(n, n, 0, fi, fo, B.TMA_BF16, False)
+
+    def call(ws):
+        B.tma_sage_block_bwd(n, n, 0, *empty, torch.ones(n, device="cuda"), X.cuda(), M.cuda(), None, g.cuda(), *w, B.TMA_ACT_NONE, *dW, ws=ws)
+
+    for share in (1.0, 0.6):
+        ws = torch.empty(int(asked * share) // 256 * 256, dtype=torch.uint8, device="cuda")
+        call(ws)
+        within(torch.cat(dW[:2]), torch.cat([X, M], 1).T, g, False, "weight gradient")
+        within(dW[2].reshape(1, -1), torch.ones((1, n)).bfloat16(), g, False, "bias gradient")
+    with pytest.raises(B.TmaError):
+        call(ws[:1 << 20])
