@@ -25,6 +25,8 @@ namespace tma {
 typedef __attribute__((address_space(3))) const void lds_void;
 __device__ __forceinline__ uint32_t lds_address(const void *p) { return uint32_t(reinterpret_cast<uintptr_t>((lds_void *)(p))); }
 
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"   // (m0 is named as reserved: it is set, all the same, and the compiler sets it again for its own use)
 // E elements per lane from base + the lane's offset in bytes, to consecutive LDS addresses from `lds` on
 template <int E>
 __device__ __forceinline__ void lds_fetch(uint32_t lds, const float *base, uint32_t offset)
@@ -42,6 +44,7 @@ __device__ __forceinline__ void lds_fetch(uint32_t lds, const float *p)
     else
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(lds), "v"(p) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 // All but this wavefront's kVm youngest memory operations are done, and its LDS reads; then the whole block meets.
 template <int kVm>
 __device__ __forceinline__ void wait_and_meet()
