@@ -97,7 +97,7 @@ struct AsyncWeights {
     // lane, 10.9 / 25.7 so)
     __host__ __device__ __forceinline__ int run(int kt) const
     {
-        const int end = (!kSide && kt >= R ? K : R) - (N % 4 == 0 ? 0 : (N + 2) / N);
+        const int end = (!kSide && kt >= R ? K : R) - (N % 4 == 0 ? 0 : N >= 3 ? 1 : 4 - N);
         return end > kt ? (end - kt) / kAsyncK : 0;
     }
     __host__ __device__ __forceinline__ bool pieces() const { return N % 4 == 0; }
