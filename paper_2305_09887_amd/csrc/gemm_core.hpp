@@ -812,38 +812,11 @@ struct SideGrad {
 };
 
 // ---------------------------------------------------------------------------
-// fp32 operands whose inner extent F is not a multiple of four.  Groups along the concatenation of a backward product are
-// padded to Fq = F rounded up to four, so that no group of four straddles the halves (a forward product's order of sums
-// leaves no room for that: see gemm_f32.hpp); the padding reads as zero in both operands.  Groups are fetched whole from 4-byte-aligned addresses: past the end of a row lies the next one, and in the last row the group is
+// fp32 operands of backward products whose inner extent F is not a multiple of four.  Groups along a concatenation are padded to
+// Fq = F rounded up to four, so that no group of four straddles the halves; the padding reads as zero in both operands.  Groups are
+// fetched whole from 4-byte-aligned addresses: past the end of a row lies the next one, and in the last row the group is
 // fetched `shift` elements earlier (RawU).  See rows_u_ok for the arrays this takes.
 // ---------------------------------------------------------------------------
-struct CatRowsU {  // A[m][k] = H[m][k]   (contiguous along k)
-    static constexpr bool kContigK = true;
-    static constexpr bool kGroups = true;
-    typedef RawU Raw;
-    struct Lane {
-        const float *p;   // row
-        bool ok, last;
-    };
-    const float *H;
-    int64_t ldh;
-    int F;
-    int64_t rows;
-    static __device__ __forceinline__ float4 resolve(const Raw &r) { return r.get(); }
-    __device__ __forceinline__ Lane prepare(int64_t m) const
-    {
-        const int64_t mm = m < rows ? m : 0;
-        return Lane{H + mm * ldh, m < rows, mm == rows - 1};
-    }
-    __device__ __forceinline__ Raw load(const Lane &l, int64_t k64) const
-    {
-        const int k = int(k64);
-        const int c = k < F ? k : 0;
-        return load_unaligned4_at(l.p + c, l.last ? F - c : 4, l.ok && k < F ? F - k : 0);
-    }
-    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const { return load(l, kt + dk); }
-};
-
 struct CatRowsTU {  // A[m][k] = (m < Fq ? H[k][m] : M[k][m-Fq])   (contiguous along m); k = node
     static constexpr bool kContigK = false;
     static constexpr bool kGroups = true;
@@ -873,30 +846,6 @@ struct CatRowsTU {  // A[m][k] = (m < Fq ? H[k][m] : M[k][m-Fq])   (contiguous a
         const int64_t at = node < rows ? node : 0;
         // (a padding lane fetches from column 0)
         return load_unaligned4_at(l.p + at * l.ld, at == rows - 1 ? (l.left > 0 ? l.left : F) : 4, ok ? l.left : 0);
-    }
-    __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const { return load(l, kt + dk); }
-};
-
-struct CatWeightsU {  // B[k][n] = k < F ? W_self[k][n] : W_neigh[k-F][n]   (contiguous along n)
-    static constexpr bool kContigK = false;
-    static constexpr bool kGroups = true;
-    typedef RawU Raw;
-    struct Lane {
-        int n;
-    };
-    const float *Ws;
-    const float *Wn;
-    int F;
-    int N;
-    static __device__ __forceinline__ float4 resolve(const Raw &r) { return r.get(); }
-    __device__ __forceinline__ Lane prepare(int64_t n) const { return Lane{int(n)}; }
-    __device__ __forceinline__ Raw load(const Lane &l, int64_t k64) const
-    {
-        const int k = int(k64);
-        const bool second = k >= F;
-        const int c = k - (second ? F : 0);
-        const bool ok = c < F && l.n < N;
-        return load_unaligned4(second ? Wn : Ws, (c < F ? c : 0) * N + (l.n < N ? l.n : 0), F * N, ok ? N - l.n : 0);
     }
     __device__ __forceinline__ Raw load_plain(const Lane &l, int64_t kt, int dk) const { return load(l, kt + dk); }
 };
@@ -1556,8 +1505,7 @@ static inline bool few_tiles(int64_t M, int64_t N, int n_splits = 1)
     return ceil_div(M, int64_t(128)) * ceil_div(N, int64_t(128)) * n_splits < kFewTiles;
 }
 
-// A product of fp32 storage on the fp32 instruction (gemm_f32.hpp).  BK of the 128 x 128 tile: 16 leaves room for a third
-// block per compute unit, 32 halves the barriers.
+// A product of fp32 storage on the fp32 instruction (gemm_f32.hpp).
 template <int BM, int BN, int BK, int WM, int WN, bool kColSum, class AL, class BL, class Epi>
 static void launch_f32(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K, int64_t k_per_split,
                        int n_splits, float *colsum_partial, hipStream_t s)
@@ -1567,7 +1515,7 @@ static void launch_f32(const char *name, const AL &a, const BL &b, const Epi &e,
     const int64_t tiles = ceil_div(M, BM) * n_tiles;
     const int64_t total = tiles * n_splits;
     constexpr int kLdsBytes = 2 * 4 * ((AL::kContigK ? BM * (BK + kPad) : BK * (BM + kPad)) + (BL::kContigK ? BN * (BK + kPad) : BK * (BN + kPad)));
-    constexpr int kPerCu = (BK <= 16 && !Epi::kRowAux && !kColSum && kLdsBytes <= 53 * 1024 ? 3 : 2) * 4 / (WM * WN);
+    constexpr int kPerCu = 2 * 4 / (WM * WN);
     static_assert(kPerCu * kLdsBytes <= 160 * 1024, "blocks per compute unit");
     int64_t blocks_per_die = ceil_div(total, kXcds);
     if (blocks_per_die > 32 * kPerCu) blocks_per_die = 32 * kPerCu;

@@ -21,7 +21,7 @@ namespace tma {
 
 // C[M,N] = A[M,K] B[K,N], k split into ranges of k_per_split; work items and their order over the dies as in gemm_bf16_kernel.
 template <int BM, int BN, int BK, int WM, int WN, bool kColSum, class AL, class BL, class Epi>
-__global__ __launch_bounds__(WM *WN * 64, (BK <= 16 && !Epi::kRowAux && !kColSum ? 3 : 2)) void gemm_f32_kernel(
+__global__ __launch_bounds__(WM *WN * 64, 2) void gemm_f32_kernel(
     AL a, BL b, Epi epi, int64_t M, int N, int64_t K, int64_t k_per_split, int n_tiles, int64_t tiles_per_split, int64_t total_work,
     float *__restrict__ colsum_partial)
 {

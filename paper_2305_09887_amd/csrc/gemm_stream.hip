@@ -17,16 +17,17 @@ namespace tma {
 //   transformed first, input gradient: 128 -> 47 14 -> 17 at 65,536, 30 -> 26 at 181,000; 256 -> 20 (slabs pair by pair) 85 -> 90 at
 //   400,000, 353 -> 303 at 1,500,000; 256 -> 47 3,850 -> 2,050 (4.3 TB/s) at 12,500,000
 constexpr int64_t kManyRows = 65536, kTransformRows = 98304, kStreamRows = int64_t(1) << 20;
-template <bool kMask, class Epi>
+template <bool kMask, bool kNarrow = true, class Epi>      // kNarrow: results of 96 columns and fewer come here
 static void launch_rows16(const char *what, const AsyncRows16 &a, const uint16_t *mask, const AsyncRows16 &b, const Epi &e, int64_t M, int N, hipStream_t s)
 {
     if constexpr (kMask) {
         launch_async16<256, 256, 4, 2, 3, true>(what, a, mask, b, e, M, N, s);
     } else {
-        if (N <= 96) launch_async16<256, 96, 4, 1, 3, false>(what, a, mask, b, e, M, N, s);
+        if constexpr (kNarrow)
+            if (N <= 96) return launch_async16<256, 96, 4, 1, 3, false>(what, a, mask, b, e, M, N, s);
         // (and where tiles of 256 would reach past more columns.  us, with them / so / gemm_bf16_kernel, 181,000 rows: forward 256 -> 300
         // 168 / 150 / 195, 64 -> 384 80 / 64 / 80; input gradient of 300 from 256 96 / 78 / 118.  The mask is better applied once to 256.)
-        else if (N <= 128 || ceil_div(N, 128) % 2 == 1) launch_async16<256, 128, 4, 1, 3, false>(what, a, mask, b, e, M, N, s);
+        if (N <= 128 || ceil_div(N, 128) % 2 == 1) launch_async16<256, 128, 4, 1, 3, false>(what, a, mask, b, e, M, N, s);
         else launch_async16<256, 256, 4, 2, 4, false>(what, a, mask, b, e, M, N, s);
     }
 }
@@ -113,7 +114,7 @@ bool stream_dense_bwd_data(int64_t n, const uint16_t *dY, const uint16_t *Y, int
     const AsyncRows16 b = narrow_rows(NarrowStack{W, W, F_in, F_out}, F_in, F_out, pitch, spare, s);
     const auto launch = [&](const auto &e) {
         if (relu) launch_rows16<true>("gemm_dense_bwd_data", a, Y, b, e, n, F_in, s);
-        else launch_rows16<false>("gemm_dense_bwd_data", a, nullptr, b, e, n, F_in, s);
+        else launch_rows16<false, false>("gemm_dense_bwd_data", a, nullptr, b, e, n, F_in, s);
     };
     if (row_scale) launch(DenseEpilogue<uint16_t, true>{dX, ldx, nullptr, row_scale, false, F_in});
     else launch(DenseEpilogue<uint16_t, false>{dX, ldx, nullptr, nullptr, false, F_in});

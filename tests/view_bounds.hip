@@ -92,10 +92,7 @@ static void rows_of(const char *type, int64_t n, int F_in, int F_out, int64_t ld
     RUN((CatRowsT<T, false>{H.p, ldh, H.p, ldh, F_in, n, 2 * F_in}), 2 * F_in, n);
     RUN((CatRowsT<T, false>{H.p, ldh, H.p, ldh, F_in, n, F_in}), F_in, n);
     if constexpr (sizeof(T) == 4)
-        if (rows_u_ok(n, ldh, F_in)) {
-            RUN((CatRowsU{H.p, ldh, F_in, n}), n, F_in);
-            RUN((CatRowsTU{H.p, ldh, H.p, ldh, F_in, pad4(F_in), n}), 2 * pad4(F_in), n);
-        }
+        if (rows_u_ok(n, ldh, F_in)) RUN((CatRowsTU{H.p, ldh, H.p, ldh, F_in, pad4(F_in), n}), 2 * pad4(F_in), n);
 }
 
 static void weights_of(int F_in, int F_out, bool at_end)
@@ -117,7 +114,6 @@ static void weights_of(int F_in, int F_out, bool at_end)
     }
     RUN((SideWeights<kElementwise>{W.p, V.p, F_in, F_out, Fp}), 2 * Fp, F_in);
     if (weights_u_ok(F_in, F_out)) {
-        RUN((CatWeightsU{W.p, V.p, F_in, F_out}), F_out, 2 * F_in);
         RUN((CatWeightsTU{W.p, V.p, F_in, F_out}), 2 * F_in, F_out);
         RUN((SideWeights<kUnaligned4>{W.p, V.p, F_in, F_out, Fp}), 2 * Fp, F_in);
         RUN((SideWeightsT<kUnaligned4>{W.p, V.p, F_in, F_out, Fp}), F_in, 2 * Fp);
