@@ -31,13 +31,15 @@ static void launch_rows16(const char *what, const AsyncRows16 &a, const uint16_t
         else launch_async16<256, 256, 4, 2, 4, false>(what, a, mask, b, e, M, N, s);
     }
 }
-// rows of narrowed weights beside what a product reads them for: out[r][c], c < pitch
+// rows of narrowed weights beside what a product reads them for: out[r][c], c < pitch (names of launches: one for each kernel)
 struct NarrowStack {   // [W0 ; W1] of R rows each, N columns, zeros up to the pitch
+    static constexpr const char *kName = "narrow_stack_bf16";
     const float *W0, *W1;
     int R, N;
     __device__ __forceinline__ float at(int r, int c) const { return c < N ? (r < R ? W0 + int64_t(r) * N : W1 + int64_t(r - R) * N)[c] : 0.0f; }
 };
 struct NarrowSides {   // [W0 | W1], N columns each padded with zeros to Np
+    static constexpr const char *kName = "narrow_sides_bf16";
     const float *W0, *W1;
     int N, Np;
     __device__ __forceinline__ float at(int r, int c) const
@@ -47,6 +49,7 @@ struct NarrowSides {   // [W0 | W1], N columns each padded with zeros to Np
     }
 };
 struct NarrowSidesT {  // the transpose of [W0 | W1]: row r is column r, R long, zeros up to the pitch
+    static constexpr const char *kName = "narrow_sides_t_bf16";
     const float *W0, *W1;
     int N, Np, R;
     __device__ __forceinline__ float at(int r, int c) const
@@ -64,7 +67,7 @@ static __global__ __launch_bounds__(256) void narrow_rows_kernel(From from, int 
 template <class From>
 static AsyncRows16 narrow_rows(const From &from, int rows, int K, int pitch, void *out, hipStream_t s)
 {
-    TMA_TIMED("prepare_weights_bf16", s);
+    TMA_TIMED(From::kName, s);
     uint16_t *w = static_cast<uint16_t *>(out);
     hipLaunchKernelGGL(narrow_rows_kernel<From>, dim3(unsigned(ceil_div(int64_t(rows) * pitch, 256))), dim3(256), 0, s, from, rows, pitch, w);
     return AsyncRows16{w, pitch, w, pitch, K, K, K, rows};

@@ -105,3 +105,18 @@ def test_weight_gradient(B, n, fi, fo, relu, name):
                                                (65536, 512, 64, True, "gemm_dense_bwd_weight_256x128_bf16")])
 def test_dense_weight_gradient(B, n, fi, fo, relu, name):
     assert dense(B, n, fi, fo, relu, "bwd_weight") == {name}
+
+
+def test_narrowed_weights(B):
+    """A launch's name stands for one kernel: bench.py refuses to match counters with launches otherwise."""
+    def names(call):
+        B.tma_profile_begin(None)
+        call()
+        return {name for name in B.tma_profile_end() if name.startswith(("narrow", "prepare"))}
+
+    n, agg, tf = 131072, weights(128, 256), weights(256, 47)
+    both = names(lambda: B.tma_sage_prepare_weights_bf16(*agg)) | names(
+        lambda: B.tma_sage_layer_bwd(*graph(n), rows(n, 128), rows(n, 128), rows(n, 256), rows(n, 256), *agg, B.TMA_ACT_NONE))
+    assert both == {"prepare_weights_bf16", "narrow_stack_bf16"}
+    assert names(lambda: B.tma_sage_layer_fwd(*graph(n), rows(n, 256), *tf, torch.zeros(47, device="cuda"), B.TMA_ACT_NONE)) == {"narrow_sides_t_bf16"}
+    assert names(lambda: B.tma_sage_layer_bwd(*graph(n), rows(n, 256), rows(n, 256), rows(n, 47), rows(n, 47), *tf, B.TMA_ACT_NONE)) == {"narrow_sides_bf16"}
