@@ -199,14 +199,19 @@ int tma_mean_aggregate(int64_t n, const int32_t *rowptr, const int32_t *colidx,
  *           H' equals that of Z, so H' is all that backward needs.
  * Fastest with 16-byte aligned pointers and leading dimensions that are
  * multiples of 16 bytes (pad rows for widths such as 47, or 100 in bf16).  fp32
- * rows of any width at any 4-byte-aligned address are read in 16-byte groups too;
- * element by element, with the same result, go: [H | M] in the aggregate-first
- * form where F_in is no multiple of four, gradients with an odd width in rows
+ * rows of any width at any 4-byte-aligned address are read in 16-byte groups
+ * too; element by element, with the same result, go: the group of [H | M] in
+ * which one half ends and the other begins, gradients with an odd width in rows
  * that are no multiples of four apart, and bf16 rows that are no multiples of
- * four or not aligned.  A row width that is no multiple of 16 bytes takes
+ * four or not aligned (from 65,536 rows on most bf16 products read any rows of
+ * even pitch at 4-byte-aligned addresses in 16-byte groups, and the ends of such
+ * a row in pairs).  A row width that is no multiple of 16 bytes takes
  * the vector path of the aggregation when ldh and ldm leave room for the last
  * whole 16-byte piece (100 bf16 elements with ld >= 104): the padding elements
  * of M_out up to that piece are then overwritten (with sums of H's padding).
+ * bf16 layers of many rows are fastest with prepared weights where they aggregate
+ * first (below), and where they transform first with F_out, padded to eight, less
+ * than half of F_in: what the outputs then leave of M_out holds narrowed weights.
  * No workspace.
  * ---------------------------------------------------------------------- */
 /* 1 if a layer of these widths aggregates first (M_out = Abar H), 0 if it transforms first. */
@@ -225,8 +230,9 @@ int tma_sage_layer_fwd(int64_t n, const int32_t *rowptr, const int32_t *colidx,
  * (round to nearest even, the rounding the product applies itself), tma_sage_weights_bf16_bytes(F_in, F_out) bytes,
  * 16-byte aligned, caller-owned; call it again whenever the weights have changed.
  * tma_sage_layer_fwd_prepared takes the arguments of tma_sage_layer_fwd plus that array (dtype must be TMA_BF16)
- * and returns the same bits; a layer that transforms first, or operands without 8-byte aligned groups of four,
- * run as in tma_sage_layer_fwd (W_self / W_neigh must therefore be valid too). */
+ * and returns the same bits.  From 65,536 rows on, rows of even pitch at 4-byte-aligned addresses make use of it, below
+ * that 8-byte aligned groups of four; other operands, and a layer that transforms first, run as in tma_sage_layer_fwd
+ * (W_self / W_neigh must therefore be valid too). */
 size_t tma_sage_weights_bf16_bytes(int32_t F_in, int32_t F_out);
 
 int tma_sage_prepare_weights_bf16(const float *W_self, const float *W_neigh, int32_t F_in, int32_t F_out,

@@ -36,7 +36,12 @@ static int dense_fwd_bf16(int64_t n, const uint16_t *X, int64_t ldx, int32_t F_i
     const bool va = groups_ok(X, ldx, F_in);
     const bool vb = F_out % 4 == 0 && aligned(W, 16);
     const char *name = va ? "gemm_dense_fwd_bf16" : "gemm_dense_fwd_bf16_generic";
-#define TMA_DENSE_FWD(VA_, VB_)                                                                   do {                                                                                              CatRows<uint16_t, VA_> a{X, ldx, X, ldx, F_in, n, F_in};                                           SideWeights<VB_> b{W, W, F_in, F_out, pad8(F_out)};                                           launch_by_width<uint16_t, 32, false, VA_>(name, a, b, e, n, N_out, K, kps, 1, nullptr, s);     } while (0)
+#define TMA_DENSE_FWD(VA_, VB_)                                                                    \
+    do {                                                                                           \
+        CatRows<uint16_t, VA_> a{X, ldx, X, ldx, F_in, n, F_in};                                   \
+        SideWeights<VB_> b{W, W, F_in, F_out, pad8(F_out)};                                        \
+        launch_by_width<uint16_t, 32, false, VA_>(name, a, b, e, n, N_out, K, kps, 1, nullptr, s); \
+    } while (0)
     // (va: F_in is a multiple of four, so W holds at least four elements and may be read in unaligned groups)
     if (va && vb) TMA_DENSE_FWD(true, kAligned4);
     else if (va) TMA_DENSE_FWD(true, kUnaligned4);

@@ -8,7 +8,7 @@
 // applied to the fragments, from a third stream into LDS.
 //
 // 12,500,000 rows, gemm_bf16_kernel -> here: forward products of 128 -> 256 and 256 -> 256 11.2 -> 7.8 ms (4.1 TB/s), input gradient of 2 x 256
-// from 256 with ReLU 11.5 -> 7.5 (3.4), transformed first 2.5 -> 1.8 (4.8) and 3.9 -> 2.1 (4.3); a large copy reaches 5.0 TB/s.
+// from 256 with ReLU 11.5 -> 7.5 (3.4 TB/s), transformed first 2.5 -> 1.8 (4.8) and 3.9 -> 2.1 (4.3); a large copy reaches 5.0 TB/s.
 //
 // Sums: groups of 16 k-values in order, one accumulator, as in gemm_bf16_kernel: the same bits.
 #pragma once
@@ -53,7 +53,6 @@ struct Fetch16 {
     uint32_t off[kLoads];
     static __device__ __forceinline__ int load_of(int v, int wave) { return v * kWaves + wave < kI ? v * kWaves + wave : kI - 1; }
     static __device__ __forceinline__ int piece(int row, int slot) { return slot ^ ((row >> 1) & 3); }
-    // `other`: an array in the place of the first part (the mask), of its pitch
     __device__ __forceinline__ void enter_run(const AsyncRows16 &x, int64_t m0, int kt, int wave, int lane)
     {
         const bool first = kt < x.F;

@@ -8,9 +8,12 @@
 // through a ring of kStages buffers, fetched kStages - 1 ahead with one barrier per slab: the first slabs of a tile arrive
 // while the results of the one before are written.
 //
-// us at 5,000 / 12,000 / 125,237 / 1,000,000 rows, 2 x 128 -> 256, staged through registers -> so:
+// us at 5,000 / 12,000 / 125,237 / 1,000,000 rows, 2 x 128 -> 256, staged through registers -> so, the product alone, called again and again:
 //   26 -> 13 / 38 -> 20 / 171 -> 135 / 1,165 -> 1,030      (127 TFLOP/s; what a further slab adds is 150 TFLOP/s, 95 % of
 //   the unit; zeros instead of random data 991: the rest is the write-out, 4 vector instructions a value, and power)
+// In the headline step, after kernels that leave little of its operands in the caches, 125,237 rows take 174 -> 145 to 154.  Counters of
+// that launch: 2.27 of 2.4 GHz, the matrix units busy in 75 % of its cycles; its 1,958 tiles are two rounds and a half of the 768 blocks
+// that the chip holds, so that three rounds' time is paid (85 %).
 // Small products are bound by what a slab takes one wavefront beside its 8 MFMAs: the scalar work of a fetch is kept to a
 // handful of instructions (runs of slabs, a step apart): 16.8 -> 13.2 at 5,000 rows.
 //
