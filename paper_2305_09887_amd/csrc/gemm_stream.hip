@@ -17,6 +17,8 @@ namespace tma {
 //   transformed first, input gradient: 128 -> 47 14 -> 17 at 65,536, 30 -> 26 at 181,000; 256 -> 20 (slabs pair by pair) 85 -> 90 at
 //   400,000, 353 -> 303 at 1,500,000; 256 -> 47 3,850 -> 2,050 (4.3 TB/s) at 12,500,000
 constexpr int64_t kManyRows = 65536, kTransformRows = 98304, kStreamRows = int64_t(1) << 20;
+// rows that gemm_bf16_kernel reads in groups of four; others element by element, and lines below that were drawn against groups do not hold
+static bool quads(const uint16_t *p, int64_t ld) { return aligned(p, 8) && ld % 4 == 0; }
 template <bool kMask, bool kNarrow = true, class Epi>      // kNarrow: results of 96 columns and fewer come here
 static void launch_rows16(const char *what, const AsyncRows16 &a, const uint16_t *mask, const AsyncRows16 &b, const Epi &e, int64_t M, int N, hipStream_t s)
 {
@@ -79,8 +81,21 @@ bool stream_sage_fwd(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *
     const int K = 2 * F_in;
     const AsyncRows16 a{H, ldh, M, ldm, F_in, F_in, K, n};
     if (n < kManyRows || !a.ok() || F_out <= 64) return false;
-    // (halves that end inside a slab: 100 -> 260 and 640 60 -> 60, 80 -> 86 at 80,000 rows, 155 -> 148, 266 -> 253 at 262,144)
-    if (F_in % kAsyncK16 != 0 && (F_out <= 128 ? n < kStreamRows : F_out > 256 && F_in % 4 == 0 && n < 2 * kManyRows)) return false;
+    if (F_in % kAsyncK16 != 0 && F_out <= 128 && n < kStreamRows) return false;
+    if (F_in % kAsyncK16 != 0 && F_in % 4 == 0 && quads(H, ldh) && quads(M, ldm)) {   // halves that end inside a slab: one or two slabs pair by pair
+        const bool two = F_in % 16 != 0, half = ceil_div(F_out, 128) % 2 == 1;
+        if (F_out > 256) {
+            // 131,072 / 200,000 / 400,000 / 1,048,576 rows: 28 -> 300 (tiles of 128) 51 -> 55 / 72 -> 84 / 140 -> 152 / 396 -> 410, -> 400 60 -> 62 / 85 -> 100 /
+            // 166 -> 186 / 480 -> 472; 44 -> 300 59 -> 62 / 83 -> 94 / 166 -> 175 / 474 -> 466; 56 -> 300 65 -> 65 / 94 -> 100 / 188 -> 186; 100 -> 300 89 -> 84 / 126 -> 126
+            const int64_t rows = !two || F_in >= 96 ? 2 * kManyRows : F_in >= 48 ? 4 * kManyRows : F_in >= 32 ? 8 * kManyRows : half ? INT64_MAX : kStreamRows;
+            if (n < rows) return false;
+        } else if (two) {
+            // The tiles of 256 rows leave a fifth of the units without one in the last round.  -> 256, a whole tile of the other kernel: 66,000 / 86,000 / 140,000 /
+            // 200,000 rows 20 28 -> 33 / 29 -> 34 / 41 -> 45 / 53 -> 57, 100 47 -> 51 / 50 -> 51 / 68 -> 67 / 101 -> 100; -> 200, a cut one, 20 86,000 1.04 times, 140,000 0.95
+            const int64_t tiles = ceil_div(n, 256), rounds = ceil_div(tiles, 256);
+            if (tiles * 5 < rounds * 256 * 4 && (F_out == 256 || (F_in < 32 && rounds <= 2))) return false;
+        }
+    }
     launch_rows16<false>("gemm_fwd", a, nullptr,
                          AsyncRows16{Wt, K, Wt, K, K, K, K, F_out}, FwdEpilogue<uint16_t>{Hnext, ld_next, bias, relu}, n, F_out, s);
     return true;

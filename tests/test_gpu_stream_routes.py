@@ -54,7 +54,13 @@ def dense(B, n, fi, fo, relu, what):
 @pytest.mark.parametrize("n,fi,fo,name", [(65536, 128, 256, "gemm_fwd_256x256_bf16"), (65536, 128, 260, "gemm_fwd_256x128_bf16"),
                                           (65536, 128, 384, "gemm_fwd_256x128_bf16"), (65536, 128, 385, "gemm_fwd_256x256_bf16"),
                                           (131071, 100, 300, "gemm_fwd_128x128_bf16"), (131072, 100, 300, "gemm_fwd_256x128_bf16"),
-                                          (65536, 102, 300, "gemm_fwd_256x128_bf16"), (65536, 100, 256, "gemm_fwd_256x256_bf16")])
+                                          (65536, 102, 300, "gemm_fwd_256x128_bf16"), (65536, 100, 256, "gemm_fwd_256x256_bf16"),
+                                          (65537, 100, 256, "gemm_fwd_128x256_bf16"), (104704, 20, 256, "gemm_fwd_128x256_bf16"),
+                                          (104705, 20, 256, "gemm_fwd_256x256_bf16"), (65537, 100, 200, "gemm_fwd_256x256_bf16"),
+                                          (65537, 20, 200, "gemm_fwd_128x256_bf16"), (140000, 20, 200, "gemm_fwd_256x256_bf16"), (65537, 48, 256, "gemm_fwd_256x256_bf16"),
+                                          (262143, 56, 300, "gemm_fwd_128x128_bf16"), (262144, 56, 300, "gemm_fwd_256x128_bf16"),
+                                          (524287, 44, 400, "gemm_fwd_128x128_bf16"), (524288, 44, 400, "gemm_fwd_256x256_bf16"),
+                                          (1048576, 20, 300, "gemm_fwd_128x128_bf16"), (1048576, 20, 400, "gemm_fwd_256x256_bf16")])
 def test_forward(B, n, fi, fo, name):
     assert forward(B, n, fi, fo) == {name}
 
