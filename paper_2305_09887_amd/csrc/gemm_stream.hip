@@ -237,8 +237,13 @@ bool stream_dense_bwd_weight(int64_t n, const uint16_t *X, int64_t ldx, const ui
     const int Fq = int(round_up(size_t(F_in), 8)), No = int(round_up(size_t(F_out), 8));
     const AsyncCols16 a{X, ldx, X, ldx, F_in, Fq, Fq, n}, b{dY, ld, dY, ld, F_out, No, No, n};
     const int64_t tiles = ceil_div(Fq, 256) * ceil_div(F_out, F_out > 128 ? 256 : 128);
-    // (half of a narrow tile empty: 256 -> 64 34 -> 36 at 80,000 nodes, 39 -> 38 at 98,304; with ReLU 40 -> 43 and 59 -> 53 at 181,000)
-    if (F_out <= 64 && Fq <= 256 && n < (relu ? 2 * kManyRows : kTransformRows)) return false;
+    // (half of a narrow tile empty, or three quarters: 256 -> 64 34 -> 36 at 80,000 nodes, 39 -> 38 at 98,304; with ReLU 40 -> 43 and 59 -> 53 at 181,000.  With the
+    // input gradient, 1,048,576 / 4,000,000 nodes: 64 -> 16 with ReLU 190 -> 235 / 679 -> 818, 64 -> 96 302 -> 327 / 1,040 -> 1,107, 64 -> 128 at 2,000,000 0.99 times;
+    // without 128 -> 64 268 -> 279, 0.96 at 1,500,000)
+    if (quads(X, ldx) && quads(dY, ld) && (!relu || quads(Y, ld))) {
+        if (F_out <= 64 && Fq <= 256 && n < (relu ? 2 * kManyRows : kTransformRows)) return false;
+        if (F_in <= 128 && (relu ? F_out <= 96 : F_out <= 64 && n < kStreamRows * 5 / 4)) return false;
+    }
     if (n < kManyRows || tiles * w.n_splits < 112 || (F_in <= 128 && F_out <= 128 && n < kStreamRows) ||
         (F_out <= 64 && ceil_div(Fq, 256) * 256 * 2 > 3 * Fq && n < kStreamRows) || !a.ok() || !b.ok() || (relu && !aligned(Y, 4))) return false;
     whole_rounds(n, tiles, w);

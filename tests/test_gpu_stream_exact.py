@@ -136,7 +136,7 @@ def test_transform_first_without_room(B):
 @pytest.mark.parametrize("n,fi,fo,relu,what", [
     (STREAM, 150, 150, False, ("bwd_data", "bwd_weight")),
     (STREAM + 1, 150, 150, True, ("bwd_data", "bwd_weight")),
-    (STREAM, 128, 64, True, ("bwd_weight",)),
+    (STREAM, 128, 97, True, ("bwd_weight",)),
     (STREAM // 2 + 1, 384, 66, True, ("bwd_data", "bwd_weight")),
     (2 * MANY, 256, 100, True, ("bwd_data", "bwd_weight")),
     (2 * MANY + 1, 300, 100, False, ("bwd_data", "bwd_weight")),

@@ -108,7 +108,9 @@ def test_weight_gradient(B, n, fi, fo, relu, name):
 
 @pytest.mark.parametrize("n,fi,fo,relu,name", [(98303, 256, 64, False, "gemm_dense_bwd_weight_bf16"), (98304, 256, 64, False, "gemm_dense_bwd_weight_256x128_bf16"),
                                                (131071, 256, 64, True, "gemm_dense_bwd_weight_bf16"), (131072, 256, 64, True, "gemm_dense_bwd_weight_256x128_bf16"),
-                                               (65536, 512, 64, True, "gemm_dense_bwd_weight_256x128_bf16")])
+                                               (65536, 512, 64, True, "gemm_dense_bwd_weight_256x128_bf16"),
+                                               (2000000, 64, 96, True, "gemm_dense_bwd_weight_bf16"), (1048576, 64, 97, True, "gemm_dense_bwd_weight_256x128_bf16"),
+                                               (1310719, 128, 64, False, "gemm_dense_bwd_weight_bf16"), (1310720, 128, 64, False, "gemm_dense_bwd_weight_256x128_bf16")])
 def test_dense_weight_gradient(B, n, fi, fo, relu, name):
     assert dense(B, n, fi, fo, relu, "bwd_weight") == {name}
 
