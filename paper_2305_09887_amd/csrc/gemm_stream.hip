@@ -110,7 +110,7 @@ bool stream_sage_bwd_data(int64_t n, const uint16_t *dHnext, const uint16_t *Hne
     if (n < kManyRows || (N < 256 && n < kStreamRows) || N <= (relu ? 128 : 64)) return false;
     // (a last slab pair by pair, where gemm_bf16_kernel reads groups of four: 128 -> 100 32 -> 38 at 98,304 rows, 41 -> 40 at 131,072, 130 -> 110 at
     // 400,000; with ReLU 69 -> 76 at 181,000 and 155 -> 148)
-    if (F_out % kAsyncK16 != 0 && F_out % 4 == 0 && n < (relu ? 4 : 2) * kManyRows) return false;
+    if (F_out % kAsyncK16 != 0 && F_out % 4 == 0 && quads(dHnext, ld_next) && (!relu || quads(Hnext, ld_next)) && n < (relu ? 4 : 2) * kManyRows) return false;
     if (!a.ok() || (relu && !aligned(Hnext, 4)) || !spare || size_t(N) * pitch * 2 > spare_bytes) return false;
     const AsyncRows16 b = narrow_rows(NarrowStack{W_self, W_neigh, F_in, F_out}, N, F_out, pitch, spare, s);
     const BwdDataEpilogue<uint16_t> e{dH_self_out, ldh, dM_scaled_out, inv_deg, F_in};
@@ -127,7 +127,7 @@ bool stream_dense_bwd_data(int64_t n, const uint16_t *dY, const uint16_t *Y, int
     if (n < kTransformRows || (F_in < 256 && n < kStreamRows) || F_in <= 128 || F_out < 64) return false;
     // (a last slab pair by pair: 256 <- 66 and 100 32 -> 36, 33 -> 39 at 98,304 rows, 41 -> 37, 42 -> 40 at 131,072; with ReLU in tiles of 256 that the last
     // column cuts 384 <- 66 86 -> 104 at 181,000, 192 -> 212 at 400,000, 508 -> 500 at 1,048,576)
-    if (F_out % kAsyncK16 != 0 && n < (relu && F_in > 256 ? kStreamRows / 2 : 2 * kManyRows)) return false;
+    if (F_out % kAsyncK16 != 0 && quads(dY, ld) && (!relu || quads(Y, ld)) && n < (relu && F_in > 256 ? kStreamRows / 2 : 2 * kManyRows)) return false;
     if (!a.ok() || (relu && !aligned(Y, 4)) || !spare || !aligned(spare, 16) || size_t(F_in) * pitch * 2 > spare_bytes) return false;
     const AsyncRows16 b = narrow_rows(NarrowStack{W, W, F_in, F_out}, F_in, F_out, pitch, spare, s);
     const auto launch = [&](const auto &e) {
@@ -144,10 +144,10 @@ bool stream_sage_tf_fwd(int64_t n, const uint16_t *H, int64_t ldh, int F_in, con
 {
     const AsyncRows16 a{H, ldh, H, ldh, F_in, F_in, F_in, n};
     const int pitch = int(round_up(size_t(F_in), 8));
-    if (n < (F_in < 256 || Fp <= 24 ? 2 * kManyRows : kTransformRows) || (F_in % kAsyncK16 != 0 && n < kStreamRows)) return false;
+    if (n < (quads(H, ldh) && (F_in < 256 || Fp <= 24) ? 2 * kManyRows : kTransformRows) || (F_in % kAsyncK16 != 0 && n < kStreamRows)) return false;
     // (two halves of 32 are a whole tile of 64 there and two thirds of one here: 128 -> 32 22 -> 28 at 181,000 rows, 40 -> 43 at 400,000, 106 -> 100 at
     // 1,048,576; 100 -> 32 114 -> 132)
-    if (Fp == 32 && (n < kStreamRows / 2 || F_in % kAsyncK16 != 0)) return false;
+    if (Fp == 32 && quads(H, ldh) && (n < kStreamRows / 2 || F_in % kAsyncK16 != 0)) return false;
     if (!a.ok() || !spare || size_t(2) * Fp * pitch * 2 > spare_bytes) return false;
     const AsyncRows16 b = narrow_rows(NarrowSidesT{W_self, W_neigh, F_out, Fp, F_in}, 2 * Fp, F_in, pitch, spare, s);
     launch_rows16<false>("gemm_tf_fwd", a, nullptr, b, HalvesEpilogue<uint16_t>{Ys, Yn, ldy, Fp, F_out}, n, 2 * Fp, s);
@@ -163,7 +163,8 @@ bool stream_sage_tf_bwd_data(int64_t n, const uint16_t *dHnext, int64_t ld_next,
     // 262,144 / 400,000 rows: 128 <- 40 21 -> 28 / 35 -> 41 / 52 -> 60, 153 -> 136 at 1,048,576; 128 <- 32 19 -> 21 / 30 -> 29 / 43 -> 41; 256 <- 40 36 -> 36 / 70
     // -> 61, 43 -> 46 at 160,000; 160 <- 56 45 -> 39 / 84 -> 65)
     const bool half = F_in > 96 && F_in <= 128, two = Fp % 16 != 0;
-    if (n < (Fp < 32 || (half && two) ? kStreamRows : half || two ? 4 * kManyRows : 2 * kManyRows)) return false;
+    if (n < (!quads(dHnext, ld_next) ? (Fp < 32 ? kStreamRows : kTransformRows)
+                                     : Fp < 32 || (half && two) ? kStreamRows : half || two ? 4 * kManyRows : 2 * kManyRows)) return false;
     if (!a.ok() || !spare || size_t(F_in) * 2 * Fp * 2 > spare_bytes) return false;
     const AsyncRows16 b = narrow_rows(NarrowSides{W_self, W_neigh, F_out, Fp}, F_in, 2 * Fp, 2 * Fp, spare, s);
     launch_rows16<false>("gemm_tf_bwd_data", a, nullptr, b, RowsEpilogue<uint16_t>{dH, ldh}, n, F_in, s);
@@ -203,7 +204,8 @@ bool stream_sage_bwd_weight(int64_t n, const uint16_t *H, int64_t ldh, const uin
     const AsyncCols16 a{H, ldh, M, ldm, F_in, Fq, 2 * Fq, n}, b{dHnext, ld_next, dHnext, ld_next, F_out, No, No, n};
     // (half of the tile empty and a mask for all of it: 64 -> 96 99 -> 80 at 400,000 nodes, 144 -> 123 at 700,000, but 250 -> 255 at 1,500,000 and 812 -> 879 at
     // 6,000,000, where the partial results no longer tell; 48 -> 96 243 -> 259 and 806 -> 905)
-    if (relu && F_in <= 64 && F_out <= 128 && n >= kStreamRows) return false;
+    if (relu && F_in <= 64 && F_in % 4 == 0 && F_out <= 128 && n >= kStreamRows && quads(H, ldh) && quads(M, ldm) && quads(dHnext, ld_next) && quads(Hnext, ld_next))
+        return false;
     if (!a.ok() || !b.ok() || (relu && !aligned(Hnext, 4))) return false;
     if (F_out > 128) {
         if (relu) launch_weight16<256, 2, 3, true>("gemm_bwd_weight", a, b, Hnext, F_out, w.k_per_split, w.n_splits, partial, colsum, s);
@@ -263,7 +265,7 @@ bool stream_sage_tf_bwd_weight(int64_t n, const uint16_t *H, int64_t ldh, const 
     const int Fq = int(round_up(size_t(F_in), 8));
     const AsyncCols16 a{H, ldh, H, ldh, F_in, Fq, Fq, n}, b{dHnext, ld_next, dYn, ldy, F_out, Fp, 2 * Fp, n};
     // (a quarter of the tile: 128 -> 32 117 -> 130, 100 -> 20 117 -> 124 at 1,048,576 nodes, 128 -> 20 358 -> 341 at 2,000,000)
-    if (n < (F_in > 128 ? kManyRows : Fp <= 32 ? 2 * kStreamRows : kStreamRows) || !a.ok() || !b.ok()) return false;
+    if (n < (F_in > 128 ? kManyRows : Fp <= 32 && quads(H, ldh) && quads(dHnext, ld_next) ? 2 * kStreamRows : kStreamRows) || !a.ok() || !b.ok()) return false;
     whole_rounds(n, ceil_div(Fq, 256) * ceil_div(2 * Fp, 2 * Fp > 128 ? 256 : 128), w);
     if (2 * Fp > 128) launch_weight16<256, 2, 4, false>("gemm_tf_bwd_weight", a, b, nullptr, 2 * Fp, w.k_per_split, w.n_splits, partial, colsum, s);
     else launch_weight16<128, 1, 6, false>("gemm_tf_bwd_weight", a, b, nullptr, 2 * Fp, w.k_per_split, w.n_splits, partial, colsum, s);

@@ -39,6 +39,13 @@ def forward(B, n, fi, fo):
     return launches(B, lambda: B.tma_sage_layer_fwd(*graph(n), rows(n, fi), *w, torch.zeros(fo, device="cuda"), B.TMA_ACT_NONE, Wt=Wt))
 
 
+def test_rows_that_are_read_element_by_element_elsewhere(B):
+    x = torch.zeros(65537, 102, dtype=torch.bfloat16, device="cuda")[:, :100]
+    w = weights(100, 256)
+    assert launches(B, lambda: B.tma_sage_layer_fwd(*graph(65537), x, *w, torch.zeros(256, device="cuda"), B.TMA_ACT_NONE,
+                                                    Wt=B.tma_sage_prepare_weights_bf16(*w))) == {"gemm_fwd_256x256_bf16"}
+
+
 def backward(B, n, fi, fo, relu, what):
     act = B.TMA_ACT_RELU if relu else B.TMA_ACT_NONE
     got = launches(B, lambda: B.tma_sage_layer_bwd(*graph(n), rows(n, fi), rows(n, fi), rows(n, fo), rows(n, fo), *weights(fi, fo), act))
