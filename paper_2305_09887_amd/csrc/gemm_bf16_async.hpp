@@ -311,7 +311,7 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_async_kernel(AsyncRo
 }
 
 template <int BM, int BN, int WM, int WN, int kStages, bool kMask, class Epi>
-static void launch_async16(const char *what, const AsyncRows16 &a, const uint16_t *mask, const AsyncRows16 &b, const Epi &e, int64_t M, int N, hipStream_t s)
+static void launch_async16(const char *what, const AsyncRows16 &a, const uint16_t *mask, const AsyncRows16 &b, const Epi &e, int64_t M, int N, bool paired, hipStream_t s)
 {
     constexpr int kPerCu = 8 / (WM * WN);
     static_assert(kPerCu * kStages * ((kMask ? 2 : 1) * BM + BN) * 64 <= 152 * 1024, "LDS of the blocks of a unit");
@@ -323,7 +323,7 @@ static void launch_async16(const char *what, const AsyncRows16 &a, const uint16_
     snprintf(name, sizeof(name), "%s_%dx%d_bf16", what, BM, BN);
     TMA_TIMED(name, s);
     const dim3 grid(unsigned(blocks_per_die * kXcds)), block(WM * WN * 64);
-    if (N % BN == 0)
+    if (N % BN == 0 || !paired)      // (where pairs are no words the other only costs: 273 from 128, 123,903 rows, with the weight gradient 162 / 179)
         hipLaunchKernelGGL((gemm_bf16_async_kernel<BM, BN, WM, WN, kStages, kMask, false, Epi>), grid, block, 0, s, a, mask, b, e, M, N, n_tiles, total);
     else
         hipLaunchKernelGGL((gemm_bf16_async_kernel<BM, BN, WM, WN, kStages, kMask, true, Epi>), grid, block, 0, s, a, mask, b, e, M, N, n_tiles, total);

@@ -19,18 +19,20 @@ namespace tma {
 constexpr int64_t kManyRows = 65536, kTransformRows = 98304, kStreamRows = int64_t(1) << 20;
 // rows that gemm_bf16_kernel reads in groups of four; others element by element, and lines below that were drawn against groups do not hold
 static bool quads(const uint16_t *p, int64_t ld) { return aligned(p, 8) && ld % 4 == 0; }
-template <bool kMask, bool kNarrow = true, class Epi>      // kNarrow: results of 96 columns and fewer come here
-static void launch_rows16(const char *what, const AsyncRows16 &a, const uint16_t *mask, const AsyncRows16 &b, const Epi &e, int64_t M, int N, hipStream_t s)
+// kNarrow: results of 96 columns and fewer come here; paired: columns 2c and 2c + 1 are one word (as Epi::pairs_ok says on the device)
+template <bool kMask, bool kNarrow = true, class Epi>
+static void launch_rows16(const char *what, const AsyncRows16 &a, const uint16_t *mask, const AsyncRows16 &b, const Epi &e, int64_t M, int N, bool paired, hipStream_t s)
 {
     if constexpr (kMask) {
-        launch_async16<256, 256, 4, 2, 3, true>(what, a, mask, b, e, M, N, s);
+        launch_async16<256, 256, 4, 2, 3, true>(what, a, mask, b, e, M, N, paired, s);
     } else {
         if constexpr (kNarrow)
-            if (N <= 96) return launch_async16<256, 96, 4, 1, 3, false>(what, a, mask, b, e, M, N, s);
+            if (N <= 96) return launch_async16<256, 96, 4, 1, 3, false>(what, a, mask, b, e, M, N, paired, s);
         // (and where tiles of 256 would reach past more columns.  us, with them / so / gemm_bf16_kernel, 181,000 rows: forward 256 -> 300
-        // 168 / 150 / 195, 64 -> 384 80 / 64 / 80; input gradient of 300 from 256 96 / 78 / 118.  The mask is better applied once to 256.)
-        if (N <= 128 || ceil_div(N, 128) % 2 == 1) launch_async16<256, 128, 4, 1, 3, false>(what, a, mask, b, e, M, N, s);
-        else launch_async16<256, 256, 4, 2, 4, false>(what, a, mask, b, e, M, N, s);
+        // 168 / 150 / 195, 64 -> 384 80 / 64 / 80; input gradient of 300 from 256 96 / 78 / 118.  The mask is better applied once to 256, and
+        // columns that go out one by one are bound by that: 110 -> 273, 528,911 rows 349 / 383)
+        if (N <= 128 || (paired && ceil_div(N, 128) % 2 == 1)) launch_async16<256, 128, 4, 1, 3, false>(what, a, mask, b, e, M, N, paired, s);
+        else launch_async16<256, 256, 4, 2, 4, false>(what, a, mask, b, e, M, N, paired, s);
     }
 }
 // rows of narrowed weights beside what a product reads them for: out[r][c], c < pitch (names of launches: one for each kernel)
@@ -97,7 +99,7 @@ bool stream_sage_fwd(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *
         }
     }
     launch_rows16<false>("gemm_fwd", a, nullptr,
-                         AsyncRows16{Wt, K, Wt, K, K, K, K, F_out}, FwdEpilogue<uint16_t>{Hnext, ld_next, bias, relu}, n, F_out, s);
+                         AsyncRows16{Wt, K, Wt, K, K, K, K, F_out}, FwdEpilogue<uint16_t>{Hnext, ld_next, bias, relu}, n, F_out, F_out % 2 == 0 && ld_next % 2 == 0, s);
     return true;
 }
 
@@ -114,8 +116,9 @@ bool stream_sage_bwd_data(int64_t n, const uint16_t *dHnext, const uint16_t *Hne
     if (!a.ok() || (relu && !aligned(Hnext, 4)) || !spare || size_t(N) * pitch * 2 > spare_bytes) return false;
     const AsyncRows16 b = narrow_rows(NarrowStack{W_self, W_neigh, F_in, F_out}, N, F_out, pitch, spare, s);
     const BwdDataEpilogue<uint16_t> e{dH_self_out, ldh, dM_scaled_out, inv_deg, F_in};
-    if (relu) launch_rows16<true>("gemm_bwd_data", a, Hnext, b, e, n, N, s);
-    else launch_rows16<false>("gemm_bwd_data", a, nullptr, b, e, n, N, s);
+    const bool paired = F_in % 2 == 0 && ldh % 2 == 0;
+    if (relu) launch_rows16<true>("gemm_bwd_data", a, Hnext, b, e, n, N, paired, s);
+    else launch_rows16<false>("gemm_bwd_data", a, nullptr, b, e, n, N, paired, s);
     return true;
 }
 
@@ -131,8 +134,8 @@ bool stream_dense_bwd_data(int64_t n, const uint16_t *dY, const uint16_t *Y, int
     if (!a.ok() || (relu && !aligned(Y, 4)) || !spare || !aligned(spare, 16) || size_t(F_in) * pitch * 2 > spare_bytes) return false;
     const AsyncRows16 b = narrow_rows(NarrowStack{W, W, F_in, F_out}, F_in, F_out, pitch, spare, s);
     const auto launch = [&](const auto &e) {
-        if (relu) launch_rows16<true>("gemm_dense_bwd_data", a, Y, b, e, n, F_in, s);
-        else launch_rows16<false, false>("gemm_dense_bwd_data", a, nullptr, b, e, n, F_in, s);
+        if (relu) launch_rows16<true>("gemm_dense_bwd_data", a, Y, b, e, n, F_in, F_in % 2 == 0 && ldx % 2 == 0, s);
+        else launch_rows16<false, false>("gemm_dense_bwd_data", a, nullptr, b, e, n, F_in, F_in % 2 == 0 && ldx % 2 == 0, s);
     };
     if (row_scale) launch(DenseEpilogue<uint16_t, true>{dX, ldx, nullptr, row_scale, false, F_in});
     else launch(DenseEpilogue<uint16_t, false>{dX, ldx, nullptr, nullptr, false, F_in});
@@ -150,7 +153,7 @@ bool stream_sage_tf_fwd(int64_t n, const uint16_t *H, int64_t ldh, int F_in, con
     if (Fp == 32 && quads(H, ldh) && (n < kStreamRows / 2 || F_in % kAsyncK16 != 0)) return false;
     if (!a.ok() || !spare || size_t(2) * Fp * pitch * 2 > spare_bytes) return false;
     const AsyncRows16 b = narrow_rows(NarrowSidesT{W_self, W_neigh, F_out, Fp, F_in}, 2 * Fp, F_in, pitch, spare, s);
-    launch_rows16<false>("gemm_tf_fwd", a, nullptr, b, HalvesEpilogue<uint16_t>{Ys, Yn, ldy, Fp, F_out}, n, 2 * Fp, s);
+    launch_rows16<false>("gemm_tf_fwd", a, nullptr, b, HalvesEpilogue<uint16_t>{Ys, Yn, ldy, Fp, F_out}, n, 2 * Fp, true, s);
     return true;
 }
 
@@ -167,7 +170,7 @@ bool stream_sage_tf_bwd_data(int64_t n, const uint16_t *dHnext, int64_t ld_next,
                                      : Fp < 32 || (half && two) ? kStreamRows : half || two ? 4 * kManyRows : 2 * kManyRows)) return false;
     if (!a.ok() || !spare || size_t(F_in) * 2 * Fp * 2 > spare_bytes) return false;
     const AsyncRows16 b = narrow_rows(NarrowSides{W_self, W_neigh, F_out, Fp}, F_in, 2 * Fp, 2 * Fp, spare, s);
-    launch_rows16<false>("gemm_tf_bwd_data", a, nullptr, b, RowsEpilogue<uint16_t>{dH, ldh}, n, F_in, s);
+    launch_rows16<false>("gemm_tf_bwd_data", a, nullptr, b, RowsEpilogue<uint16_t>{dH, ldh}, n, F_in, F_in % 2 == 0 && ldh % 2 == 0, s);
     return true;
 }
 

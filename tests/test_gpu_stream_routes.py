@@ -75,7 +75,8 @@ def test_forward(B, n, fi, fo, name):
 @pytest.mark.parametrize("n,fi,fo,relu,name", [(65536, 150, 128, False, "gemm_bwd_data_256x128_bf16"), (65536, 150, 128, True, "gemm_bwd_data_256x256_bf16"),
                                                (131071, 128, 100, False, "gemm_bwd_data_128x256_bf16"), (131072, 128, 100, False, "gemm_bwd_data_256x256_bf16"),
                                                (262143, 128, 100, True, "gemm_bwd_data_128x256_bf16"), (262144, 128, 100, True, "gemm_bwd_data_256x256_bf16"),
-                                               (65536, 128, 102, True, "gemm_bwd_data_256x256_bf16")])
+                                               (65536, 128, 102, True, "gemm_bwd_data_256x256_bf16"),
+                                               (65536, 155, 128, False, "gemm_bwd_data_256x256_bf16")])
 def test_input_gradient(B, n, fi, fo, relu, name):
     assert backward(B, n, fi, fo, relu, "bwd_data") == {name}
 
