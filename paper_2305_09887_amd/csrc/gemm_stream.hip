@@ -17,7 +17,14 @@ namespace tma {
 //   transformed first, input gradient: 128 -> 47 14 -> 17 at 65,536, 30 -> 26 at 181,000; 256 -> 20 (slabs pair by pair) 85 -> 90 at
 //   400,000, 353 -> 303 at 1,500,000; 256 -> 47 3,850 -> 2,050 (4.3 TB/s) at 12,500,000
 constexpr int64_t kManyRows = 65536, kTransformRows = 98304, kStreamRows = int64_t(1) << 20;
-// rows that gemm_bf16_kernel reads in groups of four; others element by element, and lines below that were drawn against groups do not hold
+// tiles of 256 rows leave a fifth of the units, or more, without one in the last round
+static bool unfilled(int64_t n)
+{
+    const int64_t tiles = ceil_div(n, 256);
+    return tiles * 5 < ceil_div(tiles, 256) * 256 * 4;
+}
+// rows that gemm_bf16_kernel reads in groups of four; others element by element (2 x 102 -> 300 at
+// 65,600 rows 117 us, 62 here), and lines below that were drawn against groups do not hold
 static bool quads(const uint16_t *p, int64_t ld) { return aligned(p, 8) && ld % 4 == 0; }
 // kNarrow: results of 96 columns and fewer come here; paired: columns 2c and 2c + 1 are one word (as Epi::pairs_ok says on the device)
 template <bool kMask, bool kNarrow = true, class Epi>
@@ -84,7 +91,7 @@ bool stream_sage_fwd(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *
     const AsyncRows16 a{H, ldh, M, ldm, F_in, F_in, K, n};
     if (n < kManyRows || !a.ok() || F_out <= 64) return false;
     if (F_in % kAsyncK16 != 0 && F_out <= 128 && n < kStreamRows) return false;
-    if (F_in % kAsyncK16 != 0 && F_in % 4 == 0 && quads(H, ldh) && quads(M, ldm)) {   // halves that end inside a slab: one or two slabs pair by pair
+    if (F_in % kAsyncK16 != 0 && F_in % 4 == 0 && F_in < 128 && quads(H, ldh) && quads(M, ldm)) {   // halves that end inside a slab: one or two slabs pair by pair
         const bool two = F_in % 16 != 0, half = ceil_div(F_out, 128) % 2 == 1;
         if (F_out > 256) {
             // 131,072 / 200,000 / 400,000 / 1,048,576 rows: 28 -> 300 (tiles of 128) 51 -> 55 / 72 -> 84 / 140 -> 152 / 396 -> 410, -> 400 60 -> 62 / 85 -> 100 /
@@ -92,10 +99,9 @@ bool stream_sage_fwd(int64_t n, const uint16_t *H, int64_t ldh, const uint16_t *
             const int64_t rows = !two || F_in >= 96 ? 2 * kManyRows : F_in >= 48 ? 4 * kManyRows : F_in >= 32 ? 8 * kManyRows : half ? INT64_MAX : kStreamRows;
             if (n < rows) return false;
         } else if (two) {
-            // The tiles of 256 rows leave a fifth of the units without one in the last round.  -> 256, a whole tile of the other kernel: 66,000 / 86,000 / 140,000 /
+            // -> 256, a whole tile of the other kernel: 66,000 / 86,000 / 140,000 /
             // 200,000 rows 20 28 -> 33 / 29 -> 34 / 41 -> 45 / 53 -> 57, 100 47 -> 51 / 50 -> 51 / 68 -> 67 / 101 -> 100; -> 200, a cut one, 20 86,000 1.04 times, 140,000 0.95
-            const int64_t tiles = ceil_div(n, 256), rounds = ceil_div(tiles, 256);
-            if (tiles * 5 < rounds * 256 * 4 && (F_out == 256 || (F_in < 32 && rounds <= 2))) return false;
+            if (unfilled(n) && (F_out == 256 || (F_in < 32 && n <= 2 * kManyRows))) return false;
         }
     }
     launch_rows16<false>("gemm_fwd", a, nullptr,
@@ -110,9 +116,10 @@ bool stream_sage_bwd_data(int64_t n, const uint16_t *dHnext, const uint16_t *Hne
     const int N = 2 * F_in, pitch = int(round_up(size_t(F_out), 8));
     const AsyncRows16 a{dHnext, ld_next, dHnext, ld_next, F_out, F_out, F_out, n};
     if (n < kManyRows || (N < 256 && n < kStreamRows) || N <= (relu ? 128 : 64)) return false;
-    // (a last slab pair by pair, where gemm_bf16_kernel reads groups of four: 128 -> 100 32 -> 38 at 98,304 rows, 41 -> 40 at 131,072, 130 -> 110 at
-    // 400,000; with ReLU 69 -> 76 at 181,000 and 155 -> 148)
-    if (F_out % kAsyncK16 != 0 && F_out % 4 == 0 && quads(dHnext, ld_next) && (!relu || quads(Hnext, ld_next)) && n < (relu ? 4 : 2) * kManyRows) return false;
+    // (a last slab pair by pair, one of four or fewer, where gemm_bf16_kernel reads groups of four: 128 -> 100 32 -> 38 at 98,304 rows, 41 -> 40 at 131,072, 130 ->
+    // 110 at 400,000; with ReLU 69 -> 76 at 181,000 and 155 -> 148.  With the weight gradient and the gather, 122,000 rows: 256 -> 76 0.74 -> 0.67 of the time before
+    // both, 128 -> 232 0.78, with ReLU 256 -> 232 0.79 -> 0.70)
+    if (F_out % kAsyncK16 != 0 && F_out % 4 == 0 && F_out < 128 && (relu || N <= 256) && quads(dHnext, ld_next) && (!relu || quads(Hnext, ld_next)) && n < (relu ? 4 : 2) * kManyRows) return false;
     if (!a.ok() || (relu && !aligned(Hnext, 4)) || !spare || size_t(N) * pitch * 2 > spare_bytes) return false;
     const AsyncRows16 b = narrow_rows(NarrowStack{W_self, W_neigh, F_in, F_out}, N, F_out, pitch, spare, s);
     const BwdDataEpilogue<uint16_t> e{dH_self_out, ldh, dM_scaled_out, inv_deg, F_in};
@@ -128,9 +135,11 @@ bool stream_dense_bwd_data(int64_t n, const uint16_t *dY, const uint16_t *Y, int
     const int pitch = int(round_up(size_t(F_out), 8));
     const AsyncRows16 a{dY, ld, dY, ld, F_out, F_out, F_out, n};
     if (n < kTransformRows || (F_in < 256 && n < kStreamRows) || F_in <= 128 || F_out < 64) return false;
-    // (a last slab pair by pair: 256 <- 66 and 100 32 -> 36, 33 -> 39 at 98,304 rows, 41 -> 37, 42 -> 40 at 131,072; with ReLU in tiles of 256 that the last
-    // column cuts 384 <- 66 86 -> 104 at 181,000, 192 -> 212 at 400,000, 508 -> 500 at 1,048,576)
-    if (F_out % kAsyncK16 != 0 && quads(dY, ld) && (!relu || quads(Y, ld)) && n < (relu && F_in > 256 ? kStreamRows / 2 : 2 * kManyRows)) return false;
+    // (a last slab pair by pair: 256 <- 66 and 100 32 -> 36, 33 -> 39 at 98,304 rows, 41 -> 37, 42 -> 40 at 131,072; with the weight gradient 100 with ReLU 98 -> 90 at
+    // 122,000; with ReLU in tiles of 256 that the last
+    // column cuts 384 <- 66 86 -> 104 at 181,000, 192 -> 212 at 400,000, 508 -> 500 at 1,048,576.  Five slabs and more: with the weight gradient 256 <- 250 0.76 -> 0.56
+    // of the time before both at 122,000)
+    if (F_out % kAsyncK16 != 0 && F_out < 128 && quads(dY, ld) && (!relu || quads(Y, ld)) && (relu && F_in > 256 ? n < kStreamRows / 2 : unfilled(n) && n < 2 * kManyRows)) return false;
     if (!a.ok() || (relu && !aligned(Y, 4)) || !spare || !aligned(spare, 16) || size_t(F_in) * pitch * 2 > spare_bytes) return false;
     const AsyncRows16 b = narrow_rows(NarrowStack{W, W, F_in, F_out}, F_in, F_out, pitch, spare, s);
     const auto launch = [&](const auto &e) {
@@ -164,9 +173,9 @@ bool stream_sage_tf_bwd_data(int64_t n, const uint16_t *dHnext, int64_t ld_next,
     const AsyncRows16 a{dHnext, ld_next, dYn, ldy, Fp, F_out, 2 * Fp, n};
     // (slabs pair by pair where a half ends in one, two of them where its width is 8 mod 16, and tiles that are half empty.  Both launches, 131,072 /
     // 262,144 / 400,000 rows: 128 <- 40 21 -> 28 / 35 -> 41 / 52 -> 60, 153 -> 136 at 1,048,576; 128 <- 32 19 -> 21 / 30 -> 29 / 43 -> 41; 256 <- 40 36 -> 36 / 70
-    // -> 61, 43 -> 46 at 160,000; 160 <- 56 45 -> 39 / 84 -> 65)
-    const bool half = F_in > 96 && F_in <= 128, two = Fp % 16 != 0;
-    if (n < (!quads(dHnext, ld_next) ? (Fp < 32 ? kStreamRows : kTransformRows)
+    // -> 61, 43 -> 46 at 160,000; 160 <- 56 45 -> 39 / 84 -> 65; with the weight gradient 256 <- 76 118 -> 107 at 122,000)
+    const bool half = F_in > 96 && F_in <= 128, two = Fp % 16 != 0 && Fp < 96;
+    if (n < (!quads(dHnext, ld_next) || (Fp >= 64 && !two) ? (Fp < 32 ? kStreamRows : kTransformRows)
                                      : Fp < 32 || (half && two) ? kStreamRows : half || two ? 4 * kManyRows : 2 * kManyRows)) return false;
     if (!a.ok() || !spare || size_t(F_in) * 2 * Fp * 2 > spare_bytes) return false;
     const AsyncRows16 b = narrow_rows(NarrowSides{W_self, W_neigh, F_out, Fp}, F_in, 2 * Fp, 2 * Fp, spare, s);

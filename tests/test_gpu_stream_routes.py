@@ -65,6 +65,7 @@ def dense(B, n, fi, fo, relu, what):
                                           (65537, 100, 256, "gemm_fwd_128x256_bf16"), (104704, 20, 256, "gemm_fwd_128x256_bf16"),
                                           (104705, 20, 256, "gemm_fwd_256x256_bf16"), (65537, 100, 200, "gemm_fwd_256x256_bf16"),
                                           (65537, 20, 200, "gemm_fwd_128x256_bf16"), (140000, 20, 200, "gemm_fwd_256x256_bf16"), (65537, 48, 256, "gemm_fwd_256x256_bf16"),
+                                          (65536, 200, 300, "gemm_fwd_256x128_bf16"), (65536, 128, 301, "gemm_fwd_256x256_bf16"),
                                           (262143, 56, 300, "gemm_fwd_128x128_bf16"), (262144, 56, 300, "gemm_fwd_256x128_bf16"),
                                           (524287, 44, 400, "gemm_fwd_128x128_bf16"), (524288, 44, 400, "gemm_fwd_256x256_bf16"),
                                           (1048576, 20, 300, "gemm_fwd_128x128_bf16"), (1048576, 20, 400, "gemm_fwd_256x256_bf16")])
@@ -75,16 +76,17 @@ def test_forward(B, n, fi, fo, name):
 @pytest.mark.parametrize("n,fi,fo,relu,name", [(65536, 150, 128, False, "gemm_bwd_data_256x128_bf16"), (65536, 150, 128, True, "gemm_bwd_data_256x256_bf16"),
                                                (131071, 128, 100, False, "gemm_bwd_data_128x256_bf16"), (131072, 128, 100, False, "gemm_bwd_data_256x256_bf16"),
                                                (262143, 128, 100, True, "gemm_bwd_data_128x256_bf16"), (262144, 128, 100, True, "gemm_bwd_data_256x256_bf16"),
-                                               (65536, 128, 102, True, "gemm_bwd_data_256x256_bf16"),
-                                               (65536, 155, 128, False, "gemm_bwd_data_256x256_bf16")])
+                                               (65536, 128, 102, True, "gemm_bwd_data_256x256_bf16"), (65536, 128, 132, True, "gemm_bwd_data_256x256_bf16"),
+                                               (65536, 130, 100, False, "gemm_bwd_data_256x128_bf16"), (65536, 155, 128, False, "gemm_bwd_data_256x256_bf16"),
+                                               (65536, 300, 160, False, "gemm_bwd_data_256x128_bf16")])
 def test_input_gradient(B, n, fi, fo, relu, name):
     assert backward(B, n, fi, fo, relu, "bwd_data") == {name}
 
 
 @pytest.mark.parametrize("n,fi,fo,relu,name", [(98304, 384, 256, False, "gemm_dense_bwd_data_256x128_bf16"),
                                                (98304, 384, 256, True, "gemm_dense_bwd_data_256x256_bf16"),
-                                               (131071, 256, 100, False, "gemm_dense_bwd_data_bf16"), (131072, 256, 100, True, "gemm_dense_bwd_data_256x256_bf16"),
-                                               (524287, 384, 66, True, "gemm_dense_bwd_data_bf16"), (524288, 384, 66, True, "gemm_dense_bwd_data_256x256_bf16")])
+                                               (104704, 256, 100, False, "gemm_dense_bwd_data_bf16"), (104705, 256, 100, True, "gemm_dense_bwd_data_256x256_bf16"),
+                                               (98304, 256, 132, True, "gemm_dense_bwd_data_256x256_bf16"), (524287, 384, 66, True, "gemm_dense_bwd_data_bf16"), (524288, 384, 66, True, "gemm_dense_bwd_data_256x256_bf16")])
 def test_dense_input_gradient(B, n, fi, fo, relu, name):
     assert dense(B, n, fi, fo, relu, "bwd_data") == {name}
 
