@@ -7,8 +7,8 @@
 // while results are written), and no registers, conversions or LDS writes between memory and the matrix units.  A ReLU mask is
 // applied to the fragments, from a third stream into LDS.
 //
-// 12,500,000 rows, gemm_bf16_kernel -> here: forward products of 128 -> 256 and 256 -> 256 11.2 -> 7.8 ms (4.1 TB/s), input gradient of 2 x 256
-// from 256 with ReLU 11.5 -> 7.5 (3.4 TB/s), transformed first 2.5 -> 1.8 (4.8) and 3.9 -> 2.1 (4.3); a large copy reaches 5.0 TB/s.
+// 12,500,000 rows, gemm_bf16_kernel -> here: forward products of 128 -> 256 and 256 -> 256 11.2 -> 6.9 ms (4.7 TB/s), input gradient of 2 x 256
+// from 256 with ReLU 11.5 -> 7.0 (3.6 TB/s), transformed first 2.5 -> 1.7 (5.1) and 3.9 -> 1.7 (5.2); a large copy reaches 5.0 TB/s.
 //
 // Sums: groups of 16 k-values in order, one accumulator, as in gemm_bf16_kernel: the same bits.
 #pragma once
@@ -46,13 +46,15 @@ struct AsyncRows16 {
 
 // One operand's slabs of ROWS rows on their way into LDS, [ROWS][32], the 16-byte pieces of a row exchanged by its row number
 // (fragment reads then spread over the banks): wavefront loads of 16 rows, kLoads of them by each wavefront.
-template <int ROWS, int kWaves>
+template <int ROWS, int kWaves, bool kPaired = false>
 struct Fetch16 {
     static constexpr int kI = ROWS / 16, kLoads = (kI + kWaves - 1) / kWaves;   // (where they do not divide the last is fetched twice)
     const uint16_t *at;     // of the next slab of the run, of row 0 of the tile
     uint32_t off[kLoads];
     static __device__ __forceinline__ int load_of(int v, int wave) { return v * kWaves + wave < kI ? v * kWaves + wave : kI - 1; }
     static __device__ __forceinline__ int piece(int row, int slot) { return slot ^ ((row >> 1) & 3); }
+    // the operand's row that lies in row r: kPaired, of every whole 64 the even ones and then the odd ones (see the write-out)
+    static __device__ __forceinline__ int source(int r) { return kPaired && r < ROWS / 64 * 64 ? (r & ~63) | (r & 31) << 1 | (r >> 5 & 1) : r; }
     __device__ __forceinline__ void enter_run(const AsyncRows16 &x, int64_t m0, int kt, int wave, int lane)
     {
         const bool first = kt < x.F;
@@ -60,7 +62,7 @@ struct Fetch16 {
         const int64_t left = x.rows - 1 - m0;
 #pragma unroll
         for (int v = 0; v < kLoads; ++v) {
-            const int r = load_of(v, wave) * 16 + lane / 4, row = r < left ? r : int(left);
+            const int r = load_of(v, wave) * 16 + lane / 4, from = source(r), row = from < left ? from : int(left);
             off[v] = (uint32_t(row) * uint32_t(first ? x.ld0 : x.ld1) + uint32_t(piece(r, lane & 3) * 8)) * 2u;
         }
     }
@@ -76,7 +78,7 @@ struct Fetch16 {
         for (int v = 0; v < 4 * kLoads; ++v) {
             const int q = v * kWaves + wave < 4 * kI ? v * kWaves + wave : 4 * kI - 1;      // 4 rows each
             const int r = q * 4 + lane / 16, slot = (lane >> 2) & 3;
-            lds_fetch<1>(to + uint32_t(q) * 256u, reinterpret_cast<const float *>(x.at(m0 + r, kt + piece(r, slot) * 8 + (lane & 3) * 2, kZeros)));
+            lds_fetch<1>(to + uint32_t(q) * 256u, reinterpret_cast<const float *>(x.at(m0 + source(r), kt + piece(r, slot) * 8 + (lane & 3) * 2, kZeros)));
         }
     }
 };
@@ -105,7 +107,7 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_async_kernel(AsyncRo
     constexpr int kWaves = WM * WN;
     constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
     typedef Fetch16<BM, kWaves> FA;
-    typedef Fetch16<BN, kWaves> FB;
+    typedef Fetch16<BN, kWaves, true> FB;
     constexpr int kA = BM * kAsyncK16, kB = BN * kAsyncK16;    // elements of a slab
     constexpr int kLoads = (kMask ? 2 : 1) * FA::kLoads + FB::kLoads;
     constexpr int kAhead = kStages - 1;
@@ -113,8 +115,8 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_async_kernel(AsyncRo
     constexpr int kYoung = (kAhead - 1) * kLoads;              // fetches that may be in flight behind a slab's own
     constexpr int kYoungStores = kYoung + kStores < 63 ? kYoung + kStores : 63;
     constexpr int kColChunks = Epi::kColAux ? (BN + 63) / 64 : 0, kRowChunks = Epi::kRowAux ? (BM + 63) / 64 : 0;
-    constexpr int kAuxSlots = kStages;      // the cursor is kAhead slabs, so at most as many tiles, ahead
-    static_assert(BM % (WM * 32) == 0 && BN % (WN * 32) == 0 && kYoung <= 63 && kColChunks <= kWaves && kRowChunks <= kWaves, "tile shape");
+    constexpr int kAuxSlots = kStages + 1;  // the cursor is kStages slabs, so at most as many tiles, ahead
+    static_assert(BM % (WM * 32) == 0 && BN % (WN * 32) == 0 && (WN == 1 || BN % (WN * 64) == 0) && kYoung <= 63 && kColChunks <= kWaves && kRowChunks <= kWaves, "tile shape");
 
     __shared__ __attribute__((aligned(1024))) uint16_t As[kStages][kA];
     __shared__ __attribute__((aligned(1024))) uint16_t Ms[kMask ? kStages : 1][kMask ? kA : 8];
@@ -269,10 +271,15 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_async_kernel(AsyncRo
             stage = stage == kStages - 1 ? 0 : stage + 1;
         }
 
-        // MFMA 32x32 result layout: register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4, column l%32.
+        // MFMA 32x32 result layout: register r of lane l holds row 8*(r/4) + 4*(l/32) + r%4, column l%32 of the fragments.  Of two fragments side by side
+        // the first holds the even columns and the second the odd ones: a lane has both values of a pair, and a wavefront's store goes to two
+        // whole lines of 128 bytes.  (With 32 neighbouring columns in a fragment pairs were traded between lanes through LDS, and a store went to
+        // 64 bytes of four rows each: at 12,500,000 rows, so -> now, forward 128 -> 256 and 256 -> 256 3.02 -> 2.63 and 4.63 -> 4.26 ms, 256 -> 2 x 48
+        // 1.82 -> 1.73, input gradient of 2 x 256 with ReLU 7.56 -> 7.04, of 256 from 2 x 48 2.08 -> 1.69.)
+        auto column = [&](int j) { return wn0 + (j + 1 < TN || j % 2 == 1 ? j / 2 * 64 + 2 * l31 + j % 2 : j * 32 + l31); };
         float caux[TN];
 #pragma unroll
-        for (int j = 0; j < TN; ++j) caux[j] = Epi::kColAux ? col_aux[aux][wn0 + j * 32 + l31] : 0.0f;
+        for (int j = 0; j < TN; ++j) caux[j] = Epi::kColAux ? col_aux[aux][column(j)] : 0.0f;
         const bool whole = m0 + BM <= M && n0 + BN <= N;
         const bool pairs = (kCut ? m0 + BM <= M && N % 2 == 0 : whole) && pairs_ok_of(epi);
 #pragma unroll
@@ -280,26 +287,37 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_async_kernel(AsyncRo
             float raux[16];
 #pragma unroll
             for (int r = 0; r < 16; ++r) raux[r] = Epi::kRowAux ? row_aux[aux][wm0 + i * 32 + 8 * (r / 4) + 4 * hi + (r % 4)] : 0.0f;
+            const int64_t row0 = m0 + wm0 + i * 32 + 4 * hi;
+            auto value = [&](int j, int r) {
+                const int col = n0 + column(j);
+                return epi.value(epi.padding(col) ? 0.0f : acc[i][j][r], caux[j], raux[r], col);
+            };
+            if (pairs) {
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int col = n0 + wn0 + j * 32 + l31;
-                const bool padding = epi.padding(col);
-                const int64_t row0 = m0 + wm0 + i * 32 + 4 * hi;
-                if (pairs) {        // neighbouring lanes trade every other value (see gemm_bf16_kernel)
-                    const int odd = l31 & 1;
+                for (int j = 0; j < TN; j += 2) {
+                    const int col = n0 + column(j);
+                    if (kCut && col >= N) continue;
+                    if (j + 1 < TN) {
 #pragma unroll
-                    for (int r = 0; r < 16; r += 2) {
-                        const float v0 = epi.value(padding ? 0.0f : acc[i][j][r], caux[j], raux[r], col);
-                        const float v1 = epi.value(padding ? 0.0f : acc[i][j][r + 1], caux[j], raux[r + 1], col);
-                        const float got = __shfl_xor(odd ? v0 : v1, 1, kWave);
-                        if (!kCut || col < N) store_pair(epi, row0 + 8 * (r / 4) + r % 4 + odd, col - odd, odd ? pack_bf16(got, v1) : pack_bf16(v0, got));
+                        for (int r = 0; r < 16; ++r) store_pair(epi, row0 + 8 * (r / 4) + r % 4, col, pack_bf16(value(j, r), value(j + 1 < TN ? j + 1 : j, r)));
+                    } else {        // neighbouring lanes trade every other value (see gemm_bf16_kernel)
+                        const int odd = l31 & 1;
+                        const uint32_t select = traded_bytes(l31);
+#pragma unroll
+                        for (int r = 0; r < 16; r += 2)
+                            store_pair(epi, row0 + 8 * (r / 4) + r % 4 + odd, col - odd, traded_pair(value(j, r), value(j, r + 1), select));
                     }
-                } else if (col < N) {
+                }
+            } else {
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        const int64_t row = row0 + 8 * (r / 4) + r % 4;
-                        const float val = epi.value(padding ? 0.0f : acc[i][j][r], caux[j], raux[r], col);
-                        if (row < M) epi.store(row, col, val, 0);
+                for (int j = 0; j < TN; ++j) {
+                    const int col = n0 + column(j);
+                    if (col < N) {
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) {
+                            const int64_t row = row0 + 8 * (r / 4) + r % 4;
+                            if (row < M) epi.store(row, col, value(j, r), 0);
+                        }
                     }
                 }
             }

@@ -1052,6 +1052,16 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
+// A lane's values of two rows R and R + 1 of its column -> neighbouring columns of one row: an even lane gets (column, column + 1) of row R,
+// an odd one (column - 1, column) of row R + 1.  `select`: traded_bytes(lane).
+__device__ __forceinline__ uint32_t traded_bytes(int lane) { return lane & 1 ? 0x03020706u : 0x05040100u; }
+__device__ __forceinline__ uint32_t traded_pair(float v0, float v1, uint32_t select)
+{
+    const uint32_t own = pack_bf16(v0, v1);
+    const uint32_t other = __builtin_amdgcn_mov_dpp(own, 0xB1, 0xF, 0xF, true);   // quad_perm [1, 0, 3, 2]: the neighbouring lane's
+    return __builtin_amdgcn_perm(other, own, select);
+}
+
 constexpr int kGroupK = 16;
 __device__ __forceinline__ void put_bf16(uint16_t *dst, const float4 &v)
 {
@@ -1399,18 +1409,15 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_kernel(AL a, BL b, E
                     const int col = done.n0 + wn0 + j * 32 + l31;
                     if constexpr (kInside && StoresPairs<Epi>::value) {
                         if (pairs) {
-                            // registers r and r + 1 are rows R and R + 1 of this lane's column: an odd lane gives its
-                            // row-R value to the even lane on its left and gets that lane's row-R+1 value, so the
-                            // even lane holds (col, col + 1) of row R and the odd one (col - 1, col) of row R + 1
+                            // registers r and r + 1 are rows R and R + 1 of this lane's column
                             const int odd = l31 & 1;
+                            const uint32_t select = traded_bytes(l31);
 #pragma unroll
                             for (int r = 0; r < 16; r += 2) {
                                 const int64_t row = done.m0 + wm0 + i * 32 + 8 * (r / 4) + 4 * hi + (r % 4);
                                 const float v0 = epi.value(acc[i][j][r], caux[j], raux[r], col);
                                 const float v1 = epi.value(acc[i][j][r + 1], caux[j], raux[r + 1], col);
-                                const float got = __shfl_xor(odd ? v0 : v1, 1, kWave);
-                                const uint32_t word = odd ? pack_bf16(got, v1) : pack_bf16(v0, got);
-                                store_pair(epi, row + odd, col - odd, word);
+                                store_pair(epi, row + odd, col - odd, traded_pair(v0, v1, select));
                             }
                             continue;
                         }

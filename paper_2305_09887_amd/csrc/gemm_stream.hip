@@ -7,15 +7,15 @@ namespace tma {
 
 // Which products come here.  From a tile of 256 rows per compute unit on, and from twice that for a product of few operations a row;
 // where a tile is padded, or slabs are fetched pair by pair, only where bytes alone count.  us, gemm_bf16_kernel -> here:
-//   forward, 65,536 / 125,237 rows: 128 -> 256 38 -> 32 / 66 -> 59, 256 -> 256 57 -> 49 / 97 -> 85; both at 12,500,000: 11,200 -> 7,780 (4.1 TB/s)
+//   forward, 65,536 / 125,237 rows: 128 -> 256 38 -> 32 / 66 -> 59, 256 -> 256 57 -> 49 / 97 -> 85; both at 12,500,000: 11,200 -> 6,890 (4.7 TB/s)
 //   64 -> 128 21 -> 21, 45 -> 39 at 181,000; 100 -> 120 72 -> 78 at 181,000, 555 -> 552 at 1,500,000; 96 -> 64 46 -> 48, 344 -> 347
-//   input gradient with ReLU (with the gather after it): 256 -> 256 85 -> 70 / 163 -> 134, alone at 12,500,000 11,520 -> 7,750; 128 -> 128
+//   input gradient with ReLU (with the gather after it): 256 -> 256 85 -> 70 / 163 -> 134, alone at 12,500,000 11,520 -> 7,040; 128 -> 128
 //   without ReLU 37 -> 33 at 65,536; 96 -> 64 88 -> 83 at 181,000, 178 -> 184 at 400,000, 642 -> 580 at 1,500,000; 64 -> 128 (half the tile) 60 -> 89
 //   dense input gradient, 98,304 / 181,000 / 1,500,000 rows: 256 <- 256 46 -> 36 / 86 -> 56 / 680 -> 395, with ReLU 70 -> 47 / 127 -> 69 / 958 -> 511;
 //   256 <- 64 39 -> 27 / 72 -> 43 / 565 -> 326; 256 <- 47 (slabs pair by pair) 26 -> 25 / 45 -> 45 / 373 -> 414
-//   transformed first, forward 256 -> 47: 28 -> 27 / 48 -> 42 / 2,460 -> 1,820 (4.8 TB/s); 128 -> 47 23 -> 23 at 65,536, 49 -> 43 at 181,000
+//   transformed first, forward 256 -> 47: 28 -> 27 / 48 -> 42 / 2,460 -> 1,730 (5.1 TB/s); 128 -> 47 23 -> 23 at 65,536, 49 -> 43 at 181,000
 //   transformed first, input gradient: 128 -> 47 14 -> 17 at 65,536, 30 -> 26 at 181,000; 256 -> 20 (slabs pair by pair) 85 -> 90 at
-//   400,000, 353 -> 303 at 1,500,000; 256 -> 47 3,850 -> 2,050 (4.3 TB/s) at 12,500,000
+//   400,000, 353 -> 303 at 1,500,000; 256 -> 47 3,850 -> 1,690 (5.2 TB/s) at 12,500,000
 constexpr int64_t kManyRows = 65536, kTransformRows = 98304, kStreamRows = int64_t(1) << 20;
 // tiles of 256 rows leave a fifth of the units, or more, without one in the last round
 static bool unfilled(int64_t n)
