@@ -44,15 +44,17 @@ struct AsyncRows16 {
     }
 };
 
-// One operand's slabs of ROWS rows on their way into LDS, [ROWS][32], the 16-byte pieces of a row exchanged by its row number
-// (fragment reads then spread over the banks): wavefront loads of 16 rows, kLoads of them by each wavefront.
+// One operand's slabs of ROWS rows on their way into LDS, [ROWS][32], the 16-byte pieces of a row exchanged by a quarter of its row number:
+// wavefront loads of 16 rows, kLoads of them by each wavefront.  LDS has 64 banks, 256 bytes, which four rows take, and 16 lanes of a
+// fragment read are served at once: of their 16 rows those that share banks are four apart.  (Exchanged by half of the row number two of them met:
+// such reads alone 235 and 120 bytes a clock and unit; 2 x 256 -> 256 at 2,000,000 rows 789 and 751 us, the other products up to 2 % apart.)
 template <int ROWS, int kWaves, bool kPaired = false>
 struct Fetch16 {
     static constexpr int kI = ROWS / 16, kLoads = (kI + kWaves - 1) / kWaves;   // (where they do not divide the last is fetched twice)
     const uint16_t *at;     // of the next slab of the run, of row 0 of the tile
     uint32_t off[kLoads];
     static __device__ __forceinline__ int load_of(int v, int wave) { return v * kWaves + wave < kI ? v * kWaves + wave : kI - 1; }
-    static __device__ __forceinline__ int piece(int row, int slot) { return slot ^ ((row >> 1) & 3); }
+    static __device__ __forceinline__ int piece(int row, int slot) { return slot ^ ((row >> 2) & 3); }
     // the operand's row that lies in row r: kPaired, of every whole 64 the even ones and then the odd ones (see the write-out)
     static __device__ __forceinline__ int source(int r) { return kPaired && r < ROWS / 64 * 64 ? (r & ~63) | (r & 31) << 1 | (r >> 5 & 1) : r; }
     __device__ __forceinline__ void enter_run(const AsyncRows16 &x, int64_t m0, int kt, int wave, int lane)
@@ -211,7 +213,7 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_async_kernel(AsyncRo
     const int odd_at = a.Fv % 2 ? a.Fv : -1;     // the column of padding that came with a pair
     int stage = 0, aux = 0;
     int storing = 0;     // slabs that are waited for while the stores of a whole tile may be in flight behind their fetches
-    const int swap = (l31 >> 1) & 3;
+    const int swap = (l31 >> 2) & 3;
     const int piece[2] = {(hi ^ swap) * 8, ((2 + hi) ^ swap) * 8};
     const int a_frag = (wm0 + l31) * kAsyncK16, b_frag = (wn0 + l31) * kAsyncK16;
     for (;; work += blocks_per_die) {
