@@ -1512,8 +1512,8 @@ static inline bool few_tiles(int64_t M, int64_t N, int n_splits = 1)
     return ceil_div(M, int64_t(128)) * ceil_div(N, int64_t(128)) * n_splits < kFewTiles;
 }
 
-// A product of fp32 storage on the fp32 instruction (gemm_f32.hpp).
-template <int BM, int BN, int BK, int WM, int WN, bool kColSum, class AL, class BL, class Epi>
+// A product of fp32 storage on the fp32 instruction (gemm_f32.hpp), up to kPerCu blocks to a compute unit.
+template <int BM, int BN, int BK, int WM, int WN, int kPerCu, bool kColSum, class AL, class BL, class Epi>
 static void launch_f32(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K, int64_t k_per_split,
                        int n_splits, float *colsum_partial, hipStream_t s)
 {
@@ -1522,7 +1522,6 @@ static void launch_f32(const char *name, const AL &a, const BL &b, const Epi &e,
     const int64_t tiles = ceil_div(M, BM) * n_tiles;
     const int64_t total = tiles * n_splits;
     constexpr int kLdsBytes = 2 * 4 * ((AL::kContigK ? BM * (BK + kPad) : BK * (BM + kPad)) + (BL::kContigK ? BN * (BK + kPad) : BK * (BN + kPad)));
-    constexpr int kPerCu = 2 * 4 / (WM * WN);
     static_assert(kPerCu * kLdsBytes <= 160 * 1024, "blocks per compute unit");
     int64_t blocks_per_die = ceil_div(total, kXcds);
     if (blocks_per_die > 32 * kPerCu) blocks_per_die = 32 * kPerCu;
@@ -1582,18 +1581,30 @@ static void launch_split_128(const char *name, const AL &a, const BL &b, const E
 }
 
 // A backward product of few rows (see few_rows).  us, from bf16 parts -> so, weight gradient of 128 -> 128 and input gradient of
-// 2 x 128 -> 256: 5,000 rows 14 -> 14 and 16 -> 18, 60,000 rows 34 -> 47 and 60 -> 86.  Tiles, 128 x 64 -> 64 x 64 with up to one
-// of these per compute unit, 5,000 rows: input gradient of 64 -> 64 9.4 -> 7.1, weight gradients of 64 -> 128 18.8 -> 10.9.
+// 2 x 128 -> 256: 5,000 rows 14 -> 14 and 16 -> 18, 60,000 rows 34 -> 47 and 60 -> 86.
+//
+// Its loads, LDS passes and instructions take turns inside a block, so what counts is how many blocks a unit has to
+// choose from, and how evenly the units are loaded.  Tiles of 64 x 64, five blocks to a unit (k in slabs of 16; of 32, half
+// the barriers, where each unit has one tile at most): by what the fullest unit has to do they go before wider tiles, which
+// read less, unless they cost it a tenth more; a unit with a single tile of 128 rows idles through every barrier.
+// us, by width as before (128 x 64 below 384 tiles, 128 x 96, 128 x 128, two blocks to a unit) -> 64 x 64:
+//   weight gradients with ReLU, 5,000 rows 2 x 100 -> 150 14.5 -> 12.9; 40,004 rows 2 x 90 -> 150 62 -> 43, 2 x 160 -> 150 79 -> 56;
+//   input gradients, 14,600 rows 150 from 150 20.5 -> 16.8; 40,004 rows 150 from 100 41 -> 27, 64 from 48 10.4 -> 8.0;
+//   where 128 x 128 stays: 40,004 rows 512 from 256 104 (64 x 64: 118), weight gradient 2 x 128 -> 256 56 (60)
 template <bool kColSum, class AL, class BL, class Epi>
 static void launch_few_rows(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K, int64_t kps,
                             int n_splits, float *colsum, hipStream_t s)
 {
-    if (ceil_div(M, int64_t(64)) * ceil_div(N, 64) * n_splits <= 256)
-        launch_f32<64, 64, 32, 2, 2, kColSum>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
-    else if (N <= 64 || few_tiles(M, N, n_splits))
-        launch_f32<128, 64, 32, 4, 1, kColSum>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
-    else if (N <= 96) launch_f32<128, 96, 32, 4, 1, kColSum>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
-    else launch_f32<128, 128, kColSum ? 16 : 32, 2, 2, kColSum>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    const auto items = [&](int rows, int width) { return ceil_div(M, int64_t(rows)) * ceil_div(N, width) * n_splits; };
+    const auto fullest = [&](int rows, int width) { return ceil_div(items(rows, width), int64_t(256)) * rows * width; };
+    const int64_t narrow = fullest(64, 64) * 11;
+    if (items(64, 64) <= 256)
+        launch_f32<64, 64, 32, 2, 2, 2, kColSum>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    else if (N > 64 && N <= 96 && items(128, 96) > 256 && fullest(128, 96) * 10 < narrow)
+        launch_f32<128, 96, 32, 4, 1, 2, kColSum>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    else if (N > 96 && items(128, 128) > 256 && fullest(128, 128) * 10 < narrow)
+        launch_f32<128, 128, 16, 2, 2, 2, kColSum>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    else launch_f32<64, 64, 16, 2, 2, 5, kColSum>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
 }
 
 // Every backward product of fp32 storage.  kWide: the operands are fetched in groups of four.
