@@ -1530,35 +1530,42 @@ static void launch_f32(const char *name, const AL &a, const BL &b, const Epi &e,
                        dim3(WM * WN * 64), 0, s, a, b, e, M, N, K, k_per_split, n_tiles, tiles, total, colsum_partial);
 }
 
-// A forward product of fp32 storage (gemm_f32_async.hpp).  The tile: as wide as pads least, a padded column priced at what
-// the tile takes for one (us per column of 400,000 x 256: 64 wide 1.86, 96 1.66, 128 1.67, 160 1.61), of 128 rows
-// where that leaves enough tiles for the compute units.  us, 64 x 64 / 64 x 128 / as chosen by width:
-//   5,000 rows, 256 -> 256 and 128: 13.2 / 14.0 / 22.0 and 9.5 / 13.5 / 21.7;  12,000: 19.6 / 22.0 / 24.1 and 13.2 / 14.3 / 22.8
-//   30,000: 44.9 / 40.4 / 38.8 (470 tiles) and 22.5 / 21.5 / 23.6 (235);  30,000, 256 -> 96: 22.4 / - / 19.5 (235), 180 -> 150: 31.1 / - / 28.6
-//   125,237: 157 / 143 / 135 and 81 / 74 / 72;  180 -> 150: 104 / 128 / 84;  64 -> 32: 15.2 / - / 12.6 (64 x 32)
+// A forward product of fp32 storage (gemm_f32_async.hpp).  The tile: the one that gives the fullest of 256 compute units least to do, a value
+// of it, padding included, priced at what that tile takes for one where units have many, and at up to two fifths more where
+// they have one at most, whose waits nothing then covers.  (The shorter k, the more of the time is writing, whose rate
+// is the chip's and not a unit's: below 96 the mean over the units counts in proportion.)  Prices from 400,000 x 256 (us per
+// column: 64 wide 1.86, 96 1.66, 128 1.67, 160 1.61).  1,560 products of 1,700 to 400,000 rows, 41 to 300 columns and
+// k of 32 to 512 take 0.979 of what they take by padding and a count of tiles alone, 99 in 100 at most 1.05 of it, the best
+// tile for each 0.971.  us, by padding -> so:
+//   40,004 rows, k 256, 150 columns 51.0 (128 x 160, 313 tiles) -> 39.8 (128 x 64);  k 180, 200 columns 48.0 (128 x 128, 626) -> 40.5 (64 x 128)
+//   70,000 rows, k 256, 100 columns 53.4 (128 x 128, 547 tiles) -> 45.2 (64 x 64);  125,237 rows, k 256, 256 columns: 128 x 128 as before
+// 64 x 64 of 5,000 rows, 256 -> 256 and 128: 13.2 and 9.5, 64 x 128 14.0 and 13.5, 128 wide 22.0 and 21.7.
 template <class BL, class Epi>
 static void launch_fwd_f32(const char *name, const AsyncRows &a, const BL &b, const Epi &e, int64_t M, int N, hipStream_t s)
 {
     if (M <= 0 || N <= 0 || a.K <= 0) return;
-    const auto padded = [&](int width) { return int64_t(ceil_div(N, width)) * width; };
-    const auto tiles = [&](int rows, int width) { return ceil_div(M, int64_t(rows)) * ceil_div(N, width); };
-    const int widths[] = {128, 96, 160, 64}, prices[] = {167, 166, 161, 186};
-    int w = 0;
-    for (int i = 1; i < 4; ++i)
-        if (padded(widths[i]) * prices[i] < padded(widths[w]) * prices[w]) w = i;
-    // Tiles of 128 rows of which some units have two and others one: those of 64 rows share them out more evenly, where the fullest unit then has
-    // less to do.  us at 12,500 rows, 256 -> 274 28.2 (staged) / 31.0 / 24.4; 53 -> 300 at 20,000 19.1 / 20.9 / 18.2
-    const auto fullest = [&](int rows, int width, int price) { return ceil_div(tiles(rows, width), 256) * rows * width * price; };
-    const bool uneven = (widths[w] == 160 || widths[w] == 96) && tiles(128, widths[w]) > 256 && tiles(128, widths[w]) <= 512 &&
-                        fullest(64, 64, prices[3]) * 10 < fullest(128, widths[w], prices[w]) * 9;
-    if (N <= 32) launch_async<64, 32, 2, 1, 3, 4>(name, a, b, e, M, N, s);
-    else if (uneven) launch_async<64, 64, 2, 2, 3, 4>(name, a, b, e, M, N, s);
-    else if (widths[w] == 160 && tiles(128, 160) >= 200) launch_async<128, 160, 4, 1, 3, 2>(name, a, b, e, M, N, s);
-    else if (widths[w] == 96 && tiles(128, 96) >= 200) launch_async<128, 96, 4, 1, 3, 3>(name, a, b, e, M, N, s);
-    else if (widths[w] == 64 && tiles(128, 64) >= kFewTiles) launch_async<128, 64, 4, 1, 3, 4>(name, a, b, e, M, N, s);
-    else if (widths[w] == 128 && tiles(128, 128) >= kFewTiles) launch_async<128, 128, 2, 2, 3, 3>(name, a, b, e, M, N, s);
-    else if (padded(128) == padded(64) && tiles(64, 128) >= kFewTiles) launch_async<64, 128, 2, 2, 3, 4>(name, a, b, e, M, N, s);
-    else launch_async<64, 64, 2, 2, 3, 4>(name, a, b, e, M, N, s);
+    if (N <= 32) return launch_async<64, 32, 2, 1, 3, 4>(name, a, b, e, M, N, s);   // 64 -> 32, 125,237 rows: 15.2 -> 12.6 us
+    struct Tile { int rows, width, price, alone; };   // per cent
+    constexpr Tile tiles[] = {{64, 64, 110, 110}, {64, 128, 105, 125}, {128, 64, 105, 125}, {128, 96, 100, 130}, {128, 128, 100, 140}, {128, 160, 97, 137}};
+    constexpr int64_t kLongK = 96;
+    const int64_t k = a.K < kLongK ? a.K : kLongK;
+    int best = 0;
+    int64_t least = 0;
+    for (int i = 0; i < 6; ++i) {
+        const Tile &t = tiles[i];
+        const int64_t items = ceil_div(M, int64_t(t.rows)) * ceil_div(N, t.width);
+        const int64_t load = items <= 256 ? 256 * kLongK : ceil_div(items, int64_t(256)) * 256 * k + items * (kLongK - k);
+        const int64_t cost = load * t.rows * t.width * (items <= 256 ? t.alone : t.price);
+        if (i == 0 || cost < least) best = i, least = cost;
+    }
+    switch (best) {
+    case 0: return launch_async<64, 64, 2, 2, 3, 5>(name, a, b, e, M, N, s);
+    case 1: return launch_async<64, 128, 2, 2, 3, 4>(name, a, b, e, M, N, s);
+    case 2: return launch_async<128, 64, 4, 1, 3, 4>(name, a, b, e, M, N, s);
+    case 3: return launch_async<128, 96, 4, 1, 3, 3>(name, a, b, e, M, N, s);
+    case 4: return launch_async<128, 128, 2, 2, 3, 3>(name, a, b, e, M, N, s);
+    default: return launch_async<128, 160, 4, 1, 3, 2>(name, a, b, e, M, N, s);
+    }
 }
 
 // fp32 products with more than 96 columns.  The 256-wide tile of eight wavefronts reads the operand it is wide across
