@@ -24,10 +24,9 @@ struct EntryGate {
 
 // Row gather-reduce over a CSR:  out_v = scale_v * sum_{u in row v} in_u  (+ out_v when accumulate).
 // scale_v = inv_deg[v] when inv_deg != nullptr, else 1.  fp32 accumulation in neighbour order.
-// in_rows: rows of `in` when it is not an n-row matrix (the ids of colidx index it); 0 = n rows.
 int launch_spmm(int64_t n, const int32_t *rowptr, const int32_t *colidx, const float *inv_deg, const void *in,
                 int64_t ld_in, int32_t F, int32_t dtype, void *out, int64_t ld_out, bool accumulate,
-                hipStream_t stream, int64_t in_rows = 0, EntryGate gate = {});
+                hipStream_t stream, EntryGate gate = {});
 
 // Same gather with the layer epilogue fused: out_v = act(scale_v * sum + [out_v] + self_v + bias), or, with
 // scale_all, out_v = act(scale_v * (sum + [out_v] + self_v) + bias) (the GCN form, self inside the normalisation).
@@ -35,8 +34,7 @@ int launch_spmm(int64_t n, const int32_t *rowptr, const int32_t *colidx, const f
 int launch_spmm_combine(int64_t n, const int32_t *rowptr, const int32_t *colidx, const float *inv_deg, const void *in,
                         int64_t ld_in, int32_t F, int32_t dtype, void *out, int64_t ld_out, bool accumulate,
                         const void *self, int64_t ld_self, const float *bias, int32_t F_valid, bool relu,
-                        bool scale_all, const float *edge_scale, hipStream_t stream, int64_t in_rows = 0,
-                        EntryGate gate = {});
+                        bool scale_all, const float *edge_scale, hipStream_t stream, EntryGate gate = {});
 
 // dst_v = inv_deg[v] * g_v (.) [h_v > 0]  (mask only with relu); columns F..F_pad-1 of dst are zeroed.
 // rowptr is read with a gate only.

@@ -526,7 +526,7 @@ extern "C" int tma_pair_product_bwd(int64_t n, int64_t B, int32_t F, const void 
     }
     // dR_v = sum of the node's terms, in ascending term order; nodes outside the batch receive zeros
     const int F_rows = ld_dr >= Fc ? Fc : F;
-    return launch_spmm(n, rowptr, sorted, nullptr, terms, Fc, F_rows, dtype, dR_out, ld_dr, false, s, B > 0 ? 4 * B : 1);
+    return launch_spmm(n, rowptr, sorted, nullptr, terms, Fc, F_rows, dtype, dR_out, ld_dr, false, s);
 }
 
 extern "C" int tma_prelu_fwd(int64_t n, int32_t F, const void *Z, int64_t ldz, const float *slope, int32_t dtype,

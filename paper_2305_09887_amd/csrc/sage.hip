@@ -189,7 +189,7 @@ extern "C" int tma_sage_layer_bwd(int64_t n, const int32_t *rowptr_T, const int3
         if (weigh || weigh_sparse) {
             const EntryGate gate{sparse, weigh ? EntryGate::kAlways : EntryGate::kUpTo};
             if (int rc = launch_spmm_combine(n, rowptr_T, colidx_T, nullptr, dHnext, ld_next, Fp, dtype, dYn, Fp, false, nullptr, 0,
-                                             nullptr, F_out, false, false, inv_deg, s, 0, gate))
+                                             nullptr, F_out, false, false, inv_deg, s, gate))
                 return rc;
         }
         if (!weigh) {
@@ -197,7 +197,7 @@ extern "C" int tma_sage_layer_bwd(int64_t n, const int32_t *rowptr_T, const int3
             if (int rc = launch_scale_mask_rows(n, F_out, Fp, dHnext, Hnext, ld_next, inv_deg, act == TMA_ACT_RELU, dtype,
                                                 dZs, Fp, s, rowptr_T, gate))
                 return rc;
-            if (int rc = launch_spmm(n, rowptr_T, colidx_T, nullptr, dZs, Fp, Fp, dtype, dYn, Fp, false, s, 0, gate)) return rc;
+            if (int rc = launch_spmm(n, rowptr_T, colidx_T, nullptr, dZs, Fp, Fp, dtype, dYn, Fp, false, s, gate)) return rc;
         }
         if (int rc = launch_sage_tf_gemm_bwd_weight(n, H, ldh, dHnext, Hnext, ld_next, dYn, Fp, F_in, F_out, act, dtype,
                                                     dW_self, dW_neigh, dbias, wws, w.weight_bytes, s))

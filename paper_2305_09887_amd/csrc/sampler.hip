@@ -610,7 +610,7 @@ extern "C" int tma_sage_block_fwd(int64_t n_dst, int64_t n_src, const int32_t *b
                 "%s: NULL argument", fn);
     TMA_REQUIRE(ldh >= F_in && ld_next >= F_out && H != M_out, TMA_ERR_BAD_SHAPE, "%s: leading dimensions / aliasing", fn);
     hipStream_t s = as_stream(stream);
-    if (int rc = launch_spmm(n_dst, blk_rowptr, blk_col, inv_deg, H, ldh, F_in, dtype, M_out, F_in, false, s, n_src))
+    if (int rc = launch_spmm(n_dst, blk_rowptr, blk_col, inv_deg, H, ldh, F_in, dtype, M_out, F_in, false, s))
         return rc;
     return launch_sage_gemm_fwd(n_dst, H, ldh, M_out, F_in, F_in, W_self, W_neigh, bias, F_out, act, dtype, Hnext_out, ld_next, s);
 }
@@ -673,12 +673,10 @@ extern "C" int tma_sage_block_bwd(int64_t n_dst, int64_t n_src, int64_t max_entr
                                  scan_ws, s))
         return rc;
     // dH += A^T (D^-1 dM): on top of the product for the dst rows, plain for the rows that are sources only
-    const int64_t n_rows_dm = n_dst > 0 ? n_dst : 1;
-    if (int rc = launch_spmm(n_dst, rowptr_T, sorted, nullptr, dMs, F_in, F_in, dtype, dH_out, ldh, true, s, n_rows_dm))
+    if (int rc = launch_spmm(n_dst, rowptr_T, sorted, nullptr, dMs, F_in, F_in, dtype, dH_out, ldh, true, s))
         return rc;
     char *tail = static_cast<char *>(dH_out) + size_t(n_dst) * size_t(ldh) * elem_size(dtype);
-    return launch_spmm(n_src - n_dst, rowptr_T + n_dst, sorted, nullptr, dMs, F_in, F_in, dtype, tail, ldh, false, s,
-                       n_rows_dm);
+    return launch_spmm(n_src - n_dst, rowptr_T + n_dst, sorted, nullptr, dMs, F_in, F_in, dtype, tail, ldh, false, s);
 }
 
 // ---- GCN layer on a block: m_v = (h_v + sum over the sampled neighbours) / (|S(v)| + 1) ---------------------------
@@ -721,7 +719,7 @@ extern "C" int tma_gcn_block_fwd(int64_t n_dst, int64_t n_src, const int32_t *bl
     hipStream_t s = as_stream(stream);
     // one pass over the sampled rows: neighbours and the own row summed, the sum scaled by 1 / (|S(v)| + 1)
     if (int rc = launch_spmm_combine(n_dst, blk_rowptr, blk_col, c_norm, H, ldh, F_in, dtype, M_out, F_in, false, H, ldh,
-                                     nullptr, F_in, false, true, nullptr, s, n_src))
+                                     nullptr, F_in, false, true, nullptr, s))
         return rc;
     return launch_dense_gemm_fwd(n_dst, M_out, F_in, F_in, W, bias, nullptr, F_out, F_out, act, dtype, Hnext_out, ld_next, s);
 }
@@ -781,10 +779,9 @@ extern "C" int tma_gcn_block_bwd(int64_t n_dst, int64_t n_src, int64_t max_entri
                                  scan_ws, s))
         return rc;
     // dH = (A_S + I)^T P: the dst rows take their own row of P on top of the gathered ones, the others gather only
-    const int64_t n_rows_p = n_dst > 0 ? n_dst : 1;
     if (int rc = launch_spmm_combine(n_dst, rowptr_T, sorted, nullptr, P, F_in, F_in, dtype, dH_out, ldh, false, P, F_in,
-                                     nullptr, F_in, false, false, nullptr, s, n_rows_p))
+                                     nullptr, F_in, false, false, nullptr, s))
         return rc;
     char *tail = static_cast<char *>(dH_out) + size_t(n_dst) * size_t(ldh) * elem_size(dtype);
-    return launch_spmm(n_src - n_dst, rowptr_T + n_dst, sorted, nullptr, P, F_in, F_in, dtype, tail, ldh, false, s, n_rows_p);
+    return launch_spmm(n_src - n_dst, rowptr_T + n_dst, sorted, nullptr, P, F_in, F_in, dtype, tail, ldh, false, s);
 }

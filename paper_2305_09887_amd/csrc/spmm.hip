@@ -19,10 +19,20 @@
 // each taking one contiguous share, with a fixed-order combine through LDS.  The
 // result of a row depends only on its own neighbour list, never on scheduling.
 //
-// Every load in the pipeline is issued unconditionally (an unused slot repeats an
-// address that was just fetched): the wait counters are then exact and a wait for
-// step s never also waits for the loads of step s+1.
+// Every load of the pipeline but a finished row's own (see row_extra) is issued unconditionally (an unused slot
+// repeats an address that was just fetched): the wait counters are then exact and a wait for step s never also
+// waits for the loads of step s+1.
+//
+// Dense graphs whose rows sit in the caches are bound by the vector units: 35 instructions a slot of 256 bf16 columns,
+// 16 of them the sum's, kept these 94 % busy.  So a group has a multiple of four lanes (those past the last chunk repeat
+// it): each fetches one of a step's four ids and multiplies it by the pitch, and the additions that make the four
+// addresses take the other lanes' products as operands; a slot that is not used is skipped by the lane mask; and bounds
+// are read one row ahead.  us, before -> so: 150,000 rows of 50 entries in communities, bf16, 256 columns 248 -> 207, 128
+// 161 -> 130, 64 101 -> 71, 48 103 -> 80, fp32, 128 columns 215 -> 194, 48 105 -> 91; 400,000 rows of 3.3 random ones, bound by memory,
+// 131 -> 125, 72 -> 69, 44 -> 41, 50 -> 50 (48 columns: eight groups to a wavefront instead of ten), 125 -> 123 and 64 -> 63.
 #include "kernels.hpp"
+
+#include <utility>
 
 namespace tma {
 
@@ -92,6 +102,12 @@ __device__ __forceinline__ uint4 load_chunk(const T *p)
     __builtin_memcpy(&v, __builtin_assume_aligned(p, 4), 16);
     return v;
 }
+__device__ __forceinline__ uint4 load_global_chunk(uint64_t address)   // (a number says nothing of where it points)
+{
+    typedef uint32_t Words __attribute__((ext_vector_type(4), aligned(4)));
+    const Words v = *(const __attribute__((address_space(1))) Words *)address;
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
 template <typename T>
 __device__ __forceinline__ void store_chunk(T *p, const float (&v)[Chunk<T>::kElems])
 {
@@ -121,7 +137,6 @@ struct SpmmOut {
     int relu;
     int scale_all;  // the scale multiplies the sum with "+ out_v" / "+ self_v" already added (GCN: s_v (sum + self_v))
     const float *edge_scale;  // neighbour u enters the sum as edge_scale[u] * in_u, and self_v as edge_scale[v] * self_v
-    int64_t in_rows;          // rows of the gathered matrix (>= 1): filler loads stay below it
     int clear_padding;        // elements from F on come out as zeros whatever the gathered rows hold there
     EntryGate gate;
 };
@@ -187,72 +202,110 @@ constexpr int kMinDefer = 24;            // rows up to this length are never def
 constexpr int kMinDeferOverlap = 256;    // the same for fp32 rows with an overlapping last piece (see launch_typed)
 constexpr int kDeferFactor = 4;          // ... nor rows up to this multiple of the mean degree
 constexpr int kMaxRowsPerBlock = 1024;   // rows of one workgroup (row bounds and deferred-row list sit in LDS)
-constexpr int kPartialBytes = 16384;     // LDS for the partial sums of deferred rows
+// LDS for the partial sums of deferred rows.  It leaves room for five workgroups to a compute unit: of seven (16 KB) fewer rows
+// find in the caches what another fetched (bf16, 256 columns: 150,000 rows of 50 entries in communities 212 -> 206 us, 1,000,000 of 20
+// random ones 1,456 -> 1,450; 64 columns 432 -> 423), and more hubs pass at a time (125,000 rows of a power law, 8 columns 51 -> 42).
+constexpr int kPartialBytes = 24576;
 
-// One step of a group's stream: add the rows ids[lo .. hi) (hi - lo <= kStreamU) to the running sum of
+// (A choice between two arrays: without the name of their memory a load from it would wait for all others and be waited for.)
+typedef const __attribute__((address_space(1))) int32_t *GlobalIds;
+
+// One step of a group's stream: add the rows ids[lo .. lo + count) (at most kStreamU) to the running sum of
 // segment `seg`; `last` closes the segment.  seg < 0: nothing left (the loads of such a step are dummies).
 struct Step {
-    int32_t lo, hi, seg;
+    int32_t lo, count, seg;
     bool last;
 };
 
-template <int U>
-__device__ __forceinline__ void issue_ids(const int32_t *__restrict__ ids, int32_t last_entry, const Step &s,
-                                          int32_t (&I)[U])
+// What lane q of every four lanes holds.
+template <int q>
+__device__ __forceinline__ float of_quad(float x)
 {
-    // an unused slot repeats the step's last entry; a step without entries reads any valid entry
-    const int32_t filler = s.hi > s.lo ? s.hi - 1 : (s.lo < last_entry ? s.lo : last_entry);
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), q * 0x55, 0xF, 0xF, true));
+}
+// base + what lane q of every four lanes holds, for q = 0 .. 3: two instructions each, which take the other lane's words as
+// operands.  (Such an instruction may not follow within two states on one that writes the word, five on one that writes the
+// lane mask: the wait at the front.)
+__device__ __forceinline__ void add_of_quad(uint64_t mine, uint64_t base, uint64_t (&sum)[4])
+{
+    uint32_t lo[4], hi[4];
+#define TMA_ADD_OF_QUAD(lo, hi, q)                                                                        \
+    "v_add_co_u32_dpp %" lo ", vcc, %8, %10 quad_perm:[" q "," q "," q "," q "] row_mask:0xf bank_mask:0xf\n\t" \
+    "v_addc_co_u32_dpp %" hi ", vcc, %9, %11, vcc quad_perm:[" q "," q "," q "," q "] row_mask:0xf bank_mask:0xf\n\t"
+    asm("s_nop 4\n\t" TMA_ADD_OF_QUAD("0", "4", "0") TMA_ADD_OF_QUAD("1", "5", "1") TMA_ADD_OF_QUAD("2", "6", "2") TMA_ADD_OF_QUAD("3", "7", "3")
+        : "=&v"(lo[0]), "=&v"(lo[1]), "=&v"(lo[2]), "=&v"(lo[3]), "=&v"(hi[0]), "=&v"(hi[1]), "=&v"(hi[2]), "=&v"(hi[3])
+        : "v"(uint32_t(mine)), "v"(uint32_t(mine >> 32)), "v"(uint32_t(base)), "v"(uint32_t(base >> 32))
+        : "vcc");
+#undef TMA_ADD_OF_QUAD
 #pragma unroll
-    for (int q = 0; q < U; ++q) I[q] = ids[uint32_t(s.lo + q < s.hi ? s.lo + q : filler)];
+    for (int q = 0; q < 4; ++q) sum[q] = uint64_t(hi[q]) << 32 | lo[q];
+}
+template <typename Fn, int... q>
+__device__ __forceinline__ void unrolled(Fn &&fn, std::integer_sequence<int, q...>)
+{
+    (fn(std::integral_constant<int, q>{}), ...);
+}
+template <typename Fn>
+__device__ __forceinline__ void for_each_slot(Fn &&fn)
+{
+    unrolled(fn, std::make_integer_sequence<int, kStreamU>{});
+}
+
+// The id that this lane fetches for its four.  An unused slot repeats the step's last entry, a step without entries the
+// entry before it: rows that this group fetched a moment ago.
+__device__ __forceinline__ int32_t step_id(GlobalIds ids, const Step &s)
+{
+    const int32_t k = int32_t(threadIdx.x) & 3;
+    const int32_t at = s.lo + (k < s.count - 1 ? k : s.count - 1);
+    return ids[uint32_t(at > 0 ? at : 0)];
 }
 
 // The rows of a matrix as a lane reads them: its chunk of row 0, and the rows' pitch in bytes.  Ids are not negative and a
-// pitch fits 32 bits (launch_typed), so that an address is one 32 x 32 + 64 bit multiplication: with 64-bit factors the
-// addresses were a third of the instructions (four of a quarter of the rate each, and sign extensions).
+// pitch fits 32 bits (launch_typed), so that a row is one 32 x 32 bit multiplication away, of a quarter of the rate.
 struct LaneRows {
     const char *first;
     uint32_t pitch;
-    __device__ __forceinline__ const char *at(int32_t id) const { return first + uint64_t(uint32_t(id)) * pitch; }
 };
 
-// kEdge: every neighbour row comes with a weight edge_scale[id], fetched next to the row
-template <typename T, int U, bool kEdge>
-__device__ __forceinline__ void issue_gathers(const LaneRows &in, const float *__restrict__ edge_scale, const Step &s, const int32_t (&I)[U],
-                                              int32_t &recent, uint4 (&V)[U], float (&Wt)[U])
-{
+// The rows of a step and, with kEdge, the weight of the row whose id this lane fetched.
+template <typename T, bool kEdge>
+struct StepRows {
+    uint4 chunk[kStreamU];
+    float weight;
+    __device__ __forceinline__ void issue(const LaneRows &in, const float *__restrict__ edge_scale, int32_t id)
+    {
+        uint64_t at[kStreamU];
+        add_of_quad(uint64_t(uint32_t(id)) * in.pitch, reinterpret_cast<uint64_t>(in.first), at);
 #pragma unroll
-    for (int q = 0; q < U; ++q) {
-        recent = s.lo + q < s.hi ? I[q] : recent;   // unused slot: a row this group fetched a moment ago
-        V[q] = load_chunk(reinterpret_cast<const T *>(in.at(recent)));
-        if constexpr (kEdge) Wt[q] = edge_scale[uint32_t(recent)];
+        for (int q = 0; q < kStreamU; ++q) chunk[q] = load_global_chunk(at[q]);
+        if constexpr (kEdge) weight = edge_scale[uint32_t(id)];
     }
-}
+};
 
 // How a weighted neighbour row enters the sum: its product with the weight rounded on its own, or inside the addition.
 // A forward sum is compared with zero further on, where a unit within a rounding of it is worth 1e-4 of a small batch's
 // gradient and more: which of the two, and the order of the additions, is part of the result (see launch_typed).
 enum class Weighting { kNone, kRounded, kFused };
 
-template <typename T, int U, Weighting kW, bool kFull>
-__device__ __forceinline__ void consume(const Step &s, const uint4 (&V)[U], const float (&Wt)[U],
-                                        float (&acc)[Chunk<T>::kElems])
+template <typename T, Weighting kW>
+__device__ __forceinline__ void consume(const Step &s, const StepRows<T, kW != Weighting::kNone> &rows, float (&acc)[Chunk<T>::kElems])
 {
 #pragma clang fp contract(off)
     constexpr int E = Chunk<T>::kElems;
+    for_each_slot([&](auto q) {
+        float w = 1.0f;
+        if constexpr (kW != Weighting::kNone) w = of_quad<q>(rows.weight);
+        if (q < s.count) {
+            float v[E];
+            Chunk<T>::widen(rows.chunk[q], v);
 #pragma unroll
-    for (int q = 0; q < U; ++q) {
-        // an unused slot's chunk is cleared as it came (four words, whatever the type), so that the sums need no selects;
-        // kFull: there is none in any group of the wavefront
-        const bool used = kFull || s.lo + q < s.hi;
-        float v[E];
-        Chunk<T>::widen(make_uint4(used ? V[q].x : 0u, used ? V[q].y : 0u, used ? V[q].z : 0u, used ? V[q].w : 0u), v);
-#pragma unroll
-        for (int i = 0; i < E; ++i) {
-            if constexpr (kW == Weighting::kFused) acc[i] = fmaf(used ? Wt[q] : 0.0f, v[i], acc[i]);
-            else if constexpr (kW == Weighting::kRounded) acc[i] += (used ? Wt[q] : 0.0f) * v[i];
-            else acc[i] += v[i];
+            for (int i = 0; i < E; ++i) {
+                if constexpr (kW == Weighting::kFused) acc[i] = fmaf(w, v[i], acc[i]);
+                else if constexpr (kW == Weighting::kRounded) acc[i] += w * v[i];
+                else acc[i] += v[i];
+            }
         }
-    }
+    });
 }
 
 // What a row's output needs besides the sum, fetched together with the row's last gathers.
@@ -264,39 +317,30 @@ struct RowExtra {
 // Runs the steps that `gen` hands out through the ids -> gathers -> additions pipeline.  `extra(seg, X)`
 // issues the loads a closing step needs (or nothing); `emit(seg, acc, X)` takes a finished segment.
 template <typename T, Weighting kW, typename Gen, typename Extra, typename Emit>
-__device__ __forceinline__ void stream_segments(const LaneRows &in, const int32_t *__restrict__ ids,
-                                                const float *__restrict__ edge_scale, int32_t last_entry, int32_t recent, bool few_groups,
-                                                Gen &&gen, Extra &&extra, Emit &&emit)
+__device__ __forceinline__ void stream_segments(const LaneRows &in, GlobalIds ids,
+                                                const float *__restrict__ edge_scale, Gen &&gen, Extra &&extra, Emit &&emit)
 {
     constexpr int E = Chunk<T>::kElems;
-    constexpr int U = kStreamU;
-    constexpr bool kEdge = kW != Weighting::kNone;
-    // Steps without an unused slot, where most of them are (wide bf16 rows of dense graphs: two groups or four to a wavefront);
-    // the second copy of the additions costs the others (fp32 rows of 48 with the own row: 34 -> 39 us).
-    constexpr bool kTestFull = sizeof(T) == 2;
-    int32_t I0[U], I1[U];
-    uint4 V0[U], V1[U];
-    float W0[U], W1[U];
+    using Rows = StepRows<T, kW != Weighting::kNone>;
+    Rows V0, V1;
     RowExtra X0, X1;
     float acc[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) acc[i] = 0.0f;
 
     Step a = gen();
-    issue_ids<U>(ids, last_entry, a, I0);
+    int32_t I0 = step_id(ids, a);
     Step b = gen();
-    issue_ids<U>(ids, last_entry, b, I1);
-    issue_gathers<T, U, kEdge>(in, edge_scale, a, I0, recent, V0, W0);
-    extra(a.seg, X0);
+    int32_t I1 = step_id(ids, b);
+    V0.issue(in, edge_scale, I0);
+    extra(a, X0);
     // entering a half: step a has its gathers in flight (V0/X0 in the first half), step b its ids (I1)
-    auto half = [&](int32_t (&Ia)[U], int32_t (&Ib)[U], uint4 (&Va)[U], uint4 (&Vb)[U], float (&Wa)[U],
-                    float (&Wb)[U], RowExtra &Xa, RowExtra &Xb) __attribute__((always_inline)) {
+    auto half = [&](int32_t &Ia, int32_t &Ib, Rows &Va, Rows &Vb, RowExtra &Xa, RowExtra &Xb) __attribute__((always_inline)) {
         const Step c = gen();
-        issue_ids<U>(ids, last_entry, c, Ia);
-        issue_gathers<T, U, kEdge>(in, edge_scale, b, Ib, recent, Vb, Wb);
-        extra(b.seg, Xb);
-        if (kTestFull && few_groups && __all(a.hi - a.lo == U)) consume<T, U, kW, true>(a, Va, Wa, acc);
-        else consume<T, U, kW, false>(a, Va, Wa, acc);
+        Ia = step_id(ids, c);
+        Vb.issue(in, edge_scale, Ib);
+        extra(b, Xb);
+        consume<T, kW>(a, Va, acc);
         if (a.last) {
             emit(a.seg, acc, Xa);
 #pragma unroll
@@ -306,19 +350,21 @@ __device__ __forceinline__ void stream_segments(const LaneRows &in, const int32_
         b = c;
     };
     while (a.seg >= 0) {
-        half(I0, I1, V0, V1, W0, W1, X0, X1);
+        half(I0, I1, V0, V1, X0, X1);
         if (a.seg < 0) break;
-        half(I1, I0, V1, V0, W1, W0, X1, X0);
+        half(I1, I0, V1, V0, X1, X0);
     }
 }
 
+static __device__ const int32_t kNoEntry = 0;   // what stands for the ids of a graph without entries: steps without a row read it
+
 // kExtra: 0 = nothing, 1 = "+ self_v", 2 = "+ out_v" (accumulate).  kScale: multiply by inv_deg[v].
 // kW: weighted neighbours (and self row), see SpmmOut::edge_scale.
-template <typename T, int kExtra, bool kScale, Weighting kW = Weighting::kNone>
+template <typename T, int kExtra, bool kScale, Weighting kW>
 __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, const int32_t *__restrict__ rowptr,
                                                                    const int32_t *__restrict__ colidx,
                                                                    const T *__restrict__ in, int64_t ld_in,
-                                                                   SpmmOut<T> o, int G, int rows_per_group,
+                                                                   SpmmOut<T> o, int n_chunks, int G, int rows_per_group,
                                                                    int min_defer, int last_col)
 {
     constexpr int E = Chunk<T>::kElems;
@@ -326,10 +372,9 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, co
     constexpr bool kEdge = kW != Weighting::kNone;
     constexpr int kHubsPerPass = kPartialBytes / (kSpmmThreads * E * int(sizeof(float)));
     if (shut(o.gate, rowptr, n)) return;
-    __shared__ int32_t bounds[kMaxRowsPerBlock + 1];   // rowptr of the workgroup's rows
-    __shared__ int32_t deferred[kMaxRowsPerBlock];
+    __shared__ int32_t bounds[kMaxRowsPerBlock + 2];   // rowptr of the workgroup's rows
+    __shared__ uint16_t deferred[kMaxRowsPerBlock];
     __shared__ int32_t n_deferred;
-    __shared__ int32_t total_entries;
     __shared__ float partial[kPartialBytes / sizeof(float)];
 
     const int lane = threadIdx.x % kWave;
@@ -349,48 +394,52 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, co
     const int64_t base = (int64_t(blockIdx.x % kDies) * per_die + blockIdx.x / kDies) * rows_per_block;
     if (base >= n) return;
     const int block_rows = int((n - base) < rows_per_block ? (n - base) : rows_per_block);   // >= 1
-    for (int i = threadIdx.x; i <= block_rows; i += kSpmmThreads) bounds[i] = rowptr[base + i];
-    if (threadIdx.x == 0) {
-        n_deferred = 0;
-        total_entries = rowptr[n];
-    }
+    // Entries are counted from the first one, so that the entry before one, where there is none, is at worst the first.
+    const int32_t first_entry = rowptr[0], nnz = rowptr[n];
+    for (int i = threadIdx.x; i <= block_rows; i += kSpmmThreads) bounds[i] = rowptr[base + i] - first_entry;
+    if (threadIdx.x == 0) n_deferred = 0;
+    if (o.bias)   // where the deferred rows' sums come later
+        for (int i = threadIdx.x; i < G * E; i += kSpmmThreads) partial[i] = i < o.F ? o.bias[i] : 0.0f;
     __syncthreads();
-    const int32_t nnz = total_entries;
-    const int32_t *ids = nnz > 0 ? colidx : rowptr;   // readable at index 0 even without entries
-    const int32_t last_entry = nnz > 0 ? nnz - 1 : 0;
+    const GlobalIds ids = nnz > first_entry ? GlobalIds(colidx + first_entry) : GlobalIds(&kNoEntry);
     const int64_t by_mean = int64_t(kDeferFactor) * (int64_t(nnz) / n);
     const int32_t defer_above = by_mean > min_defer ? int32_t(by_mean < INT32_MAX ? by_mean : INT32_MAX) : min_defer;
 
-    // ---- the group's own rows, block-local indices [r, r_end)
+    // ---- the group's own rows, block-local indices [r, r_end): entries [e, end) of row r are still to come
     int r = live ? grp * rows_per_group : block_rows;
     const int r_end = (r + rows_per_group) < block_rows ? (r + rows_per_group) : block_rows;
     const int r_first = r < block_rows ? r : 0;
-    int32_t e = r < r_end ? bounds[r] : 0;
-    bool fresh = true;
+    int32_t e = bounds[r_first], end = bounds[r_first + 1], next_end = bounds[r_first + 2];   // (the last may not be one: unused then)
+    auto skip_long_rows = [&]() {
+        while (r < r_end && end - e > defer_above) {
+            if (sub == 0) deferred[atomicAdd(&n_deferred, 1)] = uint16_t(r);
+            ++r;
+            e = end;
+            end = next_end;
+            next_end = bounds[r < r_end ? r + 2 : 0];
+        }
+    };
+    skip_long_rows();
     auto next_row_step = [&]() {
-        Step s{0, 0, -1, false};
-        while (r < r_end) {
-            const int32_t end = bounds[r + 1];
-            if (fresh && end - e > defer_above) {
-                if (sub == 0) deferred[atomicAdd(&n_deferred, 1)] = r;
-                ++r;
-                e = end;
-                continue;
-            }
-            s.seg = r;
-            s.lo = e;
-            s.hi = (end - e > U) ? e + U : end;
-            s.last = s.hi == end;
-            e = s.hi;
-            fresh = s.last;
-            if (s.last) ++r;
-            break;
+        Step s;
+        const bool open = r < r_end;
+        s.seg = open ? r : -1;
+        s.lo = e;
+        s.count = !open ? 0 : (end - e < U ? end - e : U);
+        e += s.count;
+        s.last = open && e == end;
+        if (s.last) {
+            ++r;
+            end = next_end;
+            next_end = bounds[r < r_end ? r + 2 : 0];
+            skip_long_rows();
         }
         return s;
     };
-    auto row_extra = [&](int32_t seg, RowExtra &X) {
-        const int64_t v = base + (seg >= 0 ? seg : r_first);
+    auto row_extra = [&](const Step &s, RowExtra &X) {
+        const uint32_t v = uint32_t(base) + uint32_t(s.seg >= 0 ? s.seg : r_first);
         if constexpr (kScale) X.scale = o.inv_deg[v];
+        if (kExtra == 0 || !__any(s.last)) return;   // (for all groups of a wavefront or none)
         if constexpr (kExtra == 1) X.raw = load_chunk(o.self + v * o.ld_self + col);
         if constexpr (kExtra == 2) X.raw = load_chunk(o.out + v * o.ld_out + col);
     };
@@ -399,7 +448,11 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, co
         const int f0 = col;
         float res[E];
 #pragma unroll
-        for (int i = 0; i < E; ++i) res[i] = (kScale && !o.scale_all) ? acc[i] * X.scale : acc[i];
+        for (int i = 0; i < E; ++i) res[i] = acc[i];
+        if (kScale && !o.scale_all) {
+#pragma unroll
+            for (int i = 0; i < E; ++i) res[i] *= X.scale;
+        }
         if constexpr (kExtra != 0) {
             float x[E];
             Chunk<T>::widen(X.raw, x);
@@ -412,7 +465,7 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, co
         }
         if (o.bias) {
 #pragma unroll
-            for (int i = 0; i < E; ++i) res[i] += (f0 + i < o.F) ? o.bias[f0 + i] : 0.0f;
+            for (int i = 0; i < E; ++i) res[i] += partial[f0 + i];
         }
         if (o.relu) {
 #pragma unroll
@@ -422,66 +475,72 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, co
 #pragma unroll
             for (int i = 0; i < E; ++i) res[i] = (o.clear_padding && f0 + i >= o.F) ? 0.0f : res[i];
         }
-        store_chunk(o.out + v * o.ld_out + f0, res);
+        if (sub < n_chunks) store_chunk(o.out + v * o.ld_out + f0, res);
     };
-    // a row that exists in the gathered matrix, for the loads of slots that carry nothing yet
-    const int32_t filler_row = int32_t((base + r_first) < o.in_rows ? (base + r_first) : o.in_rows - 1);
     const LaneRows rows{reinterpret_cast<const char *>(in + col), uint32_t(ld_in) * uint32_t(sizeof(T))};
-    stream_segments<T, kW>(rows, ids, o.edge_scale, last_entry, filler_row, gpw <= 4, next_row_step, row_extra, finish);
+    stream_segments<T, kW>(rows, ids, o.edge_scale, next_row_step, row_extra, finish);
     __syncthreads();
 
-    // ---- deferred rows, kHubsPerPass at a time: group g sums the g-th share of each, then a fixed-order combine
+    // ---- deferred rows, some at a time: the groups sum the shares of each, then one group each combines them in order.  A row's
+    // shares, and so the order of its sum, are the groups of n_chunks lanes that a workgroup has room for, whatever its groups are.
     const int n_hubs = n_deferred;
-    const int width = G * E;                         // floats of one partial row
-    for (int h0 = 0; h0 < n_hubs; h0 += kHubsPerPass) {
-        const int h_end = (h0 + kHubsPerPass) < n_hubs ? (h0 + kHubsPerPass) : n_hubs;
+    const int n_shares = (kSpmmThreads / kWave) * (kWave / n_chunks);   // >= NG
+    const int width = n_chunks * E;                  // floats of one partial row
+    const int per_pass = kHubsPerPass < NG ? kHubsPerPass : NG;
+    for (int h0 = 0; h0 < n_hubs; h0 += per_pass) {
+        const int h_end = (h0 + per_pass) < n_hubs ? (h0 + per_pass) : n_hubs;
         if (live) {
-            int h = h0;
+            int h = h0, part = grp;
             int32_t pos = 0, stop = 0;
             bool open = false;
             auto next_share_step = [&]() {
-                Step s{0, 0, -1, false};
+                Step s{pos, 0, -1, false};
                 if (h >= h_end) return s;
                 if (!open) {
                     const int row = deferred[h];
                     const int32_t beg = bounds[row], end = bounds[row + 1];
-                    const int32_t share = int32_t((int64_t(end - beg) + int64_t(NG) * U - 1) / (int64_t(NG) * U)) * U;
-                    const int64_t lo = int64_t(beg) + int64_t(grp) * share;
+                    const int32_t share = int32_t((int64_t(end - beg) + int64_t(n_shares) * U - 1) / (int64_t(n_shares) * U)) * U;
+                    const int64_t lo = int64_t(beg) + int64_t(part) * share;
                     pos = lo < end ? int32_t(lo) : end;
                     stop = (lo + share) < end ? int32_t(lo + share) : end;
                     open = true;
                 }
-                s.seg = h - h0;
+                s.seg = (h - h0) * n_shares + part;
                 s.lo = pos;
-                s.hi = (stop - pos > U) ? pos + U : stop;
-                s.last = s.hi == stop;
-                pos = s.hi;
+                s.count = (stop - pos > U) ? U : stop - pos;
+                pos += s.count;
+                s.last = pos == stop;
                 if (s.last) {
-                    ++h;
                     open = false;
+                    part += NG;
+                    if (part >= n_shares) {
+                        part = grp;
+                        ++h;
+                    }
                 }
                 return s;
             };
-            auto no_extra = [](int32_t, RowExtra &) {};
+            auto no_extra = [](const Step &, RowExtra &) {};
             auto to_lds = [&](int32_t seg, const float (&acc)[E], const RowExtra &) {
+                if (sub >= n_chunks) return;
 #pragma unroll
-                for (int i = 0; i < E; ++i) partial[(seg * NG + grp) * width + sub * E + i] = acc[i];
+                for (int i = 0; i < E; ++i) partial[seg * width + sub * E + i] = acc[i];
             };
-            stream_segments<T, kW>(rows, ids, o.edge_scale, last_entry, filler_row, gpw <= 4, next_share_step, no_extra, to_lds);
+            stream_segments<T, kW>(rows, ids, o.edge_scale, next_share_step, no_extra, to_lds);
         }
         __syncthreads();
-        if (live && grp < h_end - h0) {
+        if (live && sub < n_chunks && grp < h_end - h0) {
             const int64_t v = base + deferred[h0 + grp];
             float acc[E];
 #pragma unroll
             for (int i = 0; i < E; ++i) acc[i] = 0.0f;
-            for (int g = 0; g < NG; ++g)   // fixed order
+            for (int g = 0; g < n_shares; ++g)   // fixed order
 #pragma unroll
-                for (int i = 0; i < E; ++i) acc[i] += partial[(grp * NG + g) * width + sub * E + i];
+                for (int i = 0; i < E; ++i) acc[i] += partial[(grp * n_shares + g) * width + sub * E + i];
             float one[1][E];
 #pragma unroll
             for (int i = 0; i < E; ++i) one[0][i] = acc[i];
-            finish_row<T, 1, 1>(v, o, sub, G, last_col, one);
+            finish_row<T, 1, 1>(v, o, sub, n_chunks, last_col, one);
         }
         __syncthreads();
     }
@@ -621,8 +680,9 @@ static void launch_wide_rows(int64_t n, const int32_t *rowptr, const int32_t *co
 
 template <typename T, int kExtra, bool kScale, Weighting kW = Weighting::kNone>
 static void launch_stream(int64_t n, const int32_t *rowptr, const int32_t *colidx, const T *in, int64_t ld_in,
-                          const SpmmOut<T> &o, int G, int last_col, int min_defer, hipStream_t s)
+                          const SpmmOut<T> &o, int n_chunks, int last_col, int min_defer, hipStream_t s)
 {
+    const int G = int(round_up(size_t(n_chunks), 4));
     // rows per group: long enough a stream for the pipeline to pay, short enough to leave the chip
     // several workgroups per compute unit
     const int NG = (kSpmmThreads / kWave) * (kWave / G);
@@ -637,11 +697,15 @@ static void launch_stream(int64_t n, const int32_t *rowptr, const int32_t *colid
     char name[48];
     snprintf(name, sizeof(name), "%s%s_%s_g%dx1", o.gate.side ? "gated_" : "",
              kW != Weighting::kNone ? "spmm_weighted" : (kExtra == 1 ? "spmm_combine" : (kScale ? "spmm_mean" : "spmm_sum")),
-             sizeof(T) == 4 ? "f32" : "bf16", G);
+             sizeof(T) == 4 ? "f32" : "bf16", n_chunks);
     TMA_TIMED(name, s);
-    hipLaunchKernelGGL((spmm_stream_kernel<T, kExtra, kScale, kW>),
-                       dim3(unsigned(round_up(size_t(ceil_div(n, rpg * NG)), kDies))), dim3(kSpmmThreads), 0, s, n, rowptr,
-                       colidx, in, ld_in, o, G, int(rpg), min_defer, last_col);
+    const dim3 grid(unsigned(round_up(size_t(ceil_div(n, rpg * NG)), kDies)));
+    // Rows of 512 bytes and more, below four million of them: four workgroups to a unit instead of five, by LDS that nobody uses.
+    // Fewer rows at a time find more of their neighbours in the caches (us, five / four: bf16, 256 columns, 150,000 rows
+    // of 50 entries 246 / 236; fp32, 128 columns, 1,000,000 of 20 1,356 / 1,336); 12,500,000 rows of 3.3 4,230 / 4,327.
+    const unsigned spare = n_chunks >= 32 && n < (int64_t(1) << 22) ? 8192 : 0;
+    hipLaunchKernelGGL((spmm_stream_kernel<T, kExtra, kScale, kW>), grid, dim3(kSpmmThreads), spare, s, n, rowptr,
+                       colidx, in, ld_in, o, n_chunks, G, int(rpg), min_defer, last_col);
 }
 
 template <typename T>
@@ -666,7 +730,7 @@ static int launch_typed(int64_t n, const int32_t *rowptr, const int32_t *colidx,
     const auto words = [](const void *p, int64_t ld) { return aligned(p, 4) && (size_t(ld) * sizeof(T)) % 4 == 0; };
     const bool overlap = !vec_ok && F >= E && (size_t(F) * sizeof(T)) % 4 == 0 && row_bytes / 16 <= 64 && !o.accumulate &&
                          words(in, ld_in) && words(o.out, o.ld_out) && (!o.self || words(o.self, o.ld_self));
-    const int last_col = overlap ? F - E : INT32_MAX;
+    const int last_col = overlap ? F - E : int(row_bytes / sizeof(T)) - E;
     // The order of the additions is kept as it was before such rows came here (element by element, in neighbour order):
     // fp32 rows are cut into shares only where one group would take longer than the rest of the launch (means over 90
     // features of a power-law graph, never / above 256 / above 24 entries: 110 / 68 / 32 us at 40,000 nodes, 611 / 359 /
@@ -714,33 +778,33 @@ template <typename T>
 static int spmm_any(int64_t n, const int32_t *rowptr, const int32_t *colidx, const float *inv_deg, const void *in,
                     int64_t ld_in, int32_t F, void *out, int64_t ld_out, bool accumulate, const void *self,
                     int64_t ld_self, const float *bias, int32_t F_valid, bool relu, bool scale_all,
-                    const float *edge_scale, int64_t in_rows, EntryGate gate, hipStream_t stream)
+                    const float *edge_scale, EntryGate gate, hipStream_t stream)
 {
     SpmmOut<T> o{static_cast<T *>(out), ld_out, inv_deg, accumulate ? 1 : 0, static_cast<const T *>(self), ld_self,
-                 bias, F_valid, relu ? 1 : 0, (scale_all && inv_deg) ? 1 : 0, edge_scale, in_rows > 0 ? in_rows : n, F_valid < F ? 1 : 0, gate};
+                 bias, F_valid, relu ? 1 : 0, (scale_all && inv_deg) ? 1 : 0, edge_scale, F_valid < F ? 1 : 0, gate};
     return launch_typed<T>(n, rowptr, colidx, static_cast<const T *>(in), ld_in, F, o, stream);
 }
 
 int launch_spmm(int64_t n, const int32_t *rowptr, const int32_t *colidx, const float *inv_deg, const void *in,
                 int64_t ld_in, int32_t F, int32_t dtype, void *out, int64_t ld_out, bool accumulate,
-                hipStream_t stream, int64_t in_rows, EntryGate gate)
+                hipStream_t stream, EntryGate gate)
 {
     return launch_spmm_combine(n, rowptr, colidx, inv_deg, in, ld_in, F, dtype, out, ld_out, accumulate, nullptr, 0,
-                               nullptr, F, false, false, nullptr, stream, in_rows, gate);
+                               nullptr, F, false, false, nullptr, stream, gate);
 }
 
 int launch_spmm_combine(int64_t n, const int32_t *rowptr, const int32_t *colidx, const float *inv_deg, const void *in,
                         int64_t ld_in, int32_t F, int32_t dtype, void *out, int64_t ld_out, bool accumulate,
                         const void *self, int64_t ld_self, const float *bias, int32_t F_valid, bool relu,
-                        bool scale_all, const float *edge_scale, hipStream_t stream, int64_t in_rows, EntryGate gate)
+                        bool scale_all, const float *edge_scale, hipStream_t stream, EntryGate gate)
 {
     if (n == 0 || F == 0) return TMA_OK;
     if (dtype == TMA_F32)
         return spmm_any<float>(n, rowptr, colidx, inv_deg, in, ld_in, F, out, ld_out, accumulate, self, ld_self, bias,
-                               F_valid, relu, scale_all, edge_scale, in_rows, gate, stream);
+                               F_valid, relu, scale_all, edge_scale, gate, stream);
     if (dtype == TMA_BF16)
         return spmm_any<uint16_t>(n, rowptr, colidx, inv_deg, in, ld_in, F, out, ld_out, accumulate, self, ld_self,
-                                  bias, F_valid, relu, scale_all, edge_scale, in_rows, gate, stream);
+                                  bias, F_valid, relu, scale_all, edge_scale, gate, stream);
     return fail(TMA_ERR_UNSUPPORTED_DTYPE, "spmm: dtype %d", dtype);
 }
 
