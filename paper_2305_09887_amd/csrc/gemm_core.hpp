@@ -1039,18 +1039,7 @@ struct SplitEpiloguePad {  // the same from [H | M] with halves padded to Fq col
 // 32x32x8 one runs at half its rate): lane l holds row l%32 and the eight k-values 8*(l/32) .. +7.  Activations
 // stored in bf16 pass through LDS unchanged, fp32 weights are rounded to nearest even on their way in.
 // ---------------------------------------------------------------------------
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
-// two fp32 values to a pair of bf16, round to nearest even (one v_cvt_pk_bf16_f32)
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
-{
-    floatx2 v;
-    v[0] = lo;
-    v[1] = hi;
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
-}
 
 // A lane's values of two rows R and R + 1 of its column -> neighbouring columns of one row: an even lane gets (column, column + 1) of row R,
 // an odd one (column - 1, column) of row R + 1.  `select`: traded_bytes(lane).
