@@ -201,7 +201,7 @@ constexpr int kStreamU = 4;              // neighbours per step
 constexpr int kMinDefer = 24;            // rows up to this length are never deferred
 constexpr int kMinDeferOverlap = 256;    // the same for fp32 rows with an overlapping last piece (see launch_typed)
 constexpr int kDeferFactor = 4;          // ... nor rows up to this multiple of the mean degree
-constexpr int kMaxRowsPerBlock = 1024;   // rows of one workgroup (row bounds and deferred-row list sit in LDS)
+constexpr int kMaxRowsPerBlock = 512;    // rows of one workgroup (their bounds, scales and the deferred-row list sit in LDS)
 // LDS for the partial sums of deferred rows.  It leaves room for five workgroups to a compute unit: of seven (16 KB) fewer rows
 // find in the caches what another fetched (bf16, 256 columns: 150,000 rows of 50 entries in communities 212 -> 206 us, 1,000,000 of 20
 // random ones 1,456 -> 1,450; 64 columns 432 -> 423), and more hubs pass at a time (125,000 rows of a power law, 8 columns 51 -> 42).
@@ -287,7 +287,7 @@ struct StepRows {
 // gradient and more: which of the two, and the order of the additions, is part of the result (see launch_typed).
 enum class Weighting { kNone, kRounded, kFused };
 
-template <typename T, Weighting kW>
+template <typename T, Weighting kW, bool kFull>
 __device__ __forceinline__ void consume(const Step &s, const StepRows<T, kW != Weighting::kNone> &rows, float (&acc)[Chunk<T>::kElems])
 {
 #pragma clang fp contract(off)
@@ -295,7 +295,7 @@ __device__ __forceinline__ void consume(const Step &s, const StepRows<T, kW != W
     for_each_slot([&](auto q) {
         float w = 1.0f;
         if constexpr (kW != Weighting::kNone) w = of_quad<q>(rows.weight);
-        if (q < s.count) {
+        if (kFull || q < s.count) {   // kFull: no group of the wavefront has an unused slot
             float v[E];
             Chunk<T>::widen(rows.chunk[q], v);
 #pragma unroll
@@ -310,7 +310,6 @@ __device__ __forceinline__ void consume(const Step &s, const StepRows<T, kW != W
 
 // What a row's output needs besides the sum, fetched together with the row's last gathers.
 struct RowExtra {
-    float scale;
     uint4 raw;
 };
 
@@ -318,7 +317,7 @@ struct RowExtra {
 // issues the loads a closing step needs (or nothing); `emit(seg, acc, X)` takes a finished segment.
 template <typename T, Weighting kW, typename Gen, typename Extra, typename Emit>
 __device__ __forceinline__ void stream_segments(const LaneRows &in, GlobalIds ids,
-                                                const float *__restrict__ edge_scale, Gen &&gen, Extra &&extra, Emit &&emit)
+                                                const float *__restrict__ edge_scale, bool few_groups, Gen &&gen, Extra &&extra, Emit &&emit)
 {
     constexpr int E = Chunk<T>::kElems;
     using Rows = StepRows<T, kW != Weighting::kNone>;
@@ -340,7 +339,10 @@ __device__ __forceinline__ void stream_segments(const LaneRows &in, GlobalIds id
         Ia = step_id(ids, c);
         Vb.issue(in, edge_scale, Ib);
         extra(b, Xb);
-        consume<T, kW>(a, Va, acc);
+        // (steps without an unused slot, where most of them are: wide bf16 rows of dense graphs, two groups or four to a wavefront;
+        // 128 columns, 150,000 rows of 50 entries, 143 -> 138 us.  fp32 rows, of half the additions a slot, gain nothing.)
+        if (sizeof(T) == 2 && few_groups && __all(a.count == kStreamU)) consume<T, kW, true>(a, Va, acc);
+        else consume<T, kW, false>(a, Va, acc);
         if (a.last) {
             emit(a.seg, acc, Xa);
 #pragma unroll
@@ -373,6 +375,7 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, co
     constexpr int kHubsPerPass = kPartialBytes / (kSpmmThreads * E * int(sizeof(float)));
     if (shut(o.gate, rowptr, n)) return;
     __shared__ int32_t bounds[kMaxRowsPerBlock + 2];   // rowptr of the workgroup's rows
+    __shared__ float scales[kScale ? kMaxRowsPerBlock : 1];
     __shared__ uint16_t deferred[kMaxRowsPerBlock];
     __shared__ int32_t n_deferred;
     __shared__ float partial[kPartialBytes / sizeof(float)];
@@ -397,6 +400,8 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, co
     // Entries are counted from the first one, so that the entry before one, where there is none, is at worst the first.
     const int32_t first_entry = rowptr[0], nnz = rowptr[n];
     for (int i = threadIdx.x; i <= block_rows; i += kSpmmThreads) bounds[i] = rowptr[base + i] - first_entry;
+    if (kScale)
+        for (int i = threadIdx.x; i < block_rows; i += kSpmmThreads) scales[i] = o.inv_deg[base + i];
     if (threadIdx.x == 0) n_deferred = 0;
     if (o.bias)   // where the deferred rows' sums come later
         for (int i = threadIdx.x; i < G * E; i += kSpmmThreads) partial[i] = i < o.F ? o.bias[i] : 0.0f;
@@ -437,31 +442,31 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, co
         return s;
     };
     auto row_extra = [&](const Step &s, RowExtra &X) {
-        const uint32_t v = uint32_t(base) + uint32_t(s.seg >= 0 ? s.seg : r_first);
-        if constexpr (kScale) X.scale = o.inv_deg[v];
         if (kExtra == 0 || !__any(s.last)) return;   // (for all groups of a wavefront or none)
+        const int64_t v = base + (s.seg >= 0 ? s.seg : r_first);
         if constexpr (kExtra == 1) X.raw = load_chunk(o.self + v * o.ld_self + col);
         if constexpr (kExtra == 2) X.raw = load_chunk(o.out + v * o.ld_out + col);
     };
     auto finish = [&](int32_t seg, const float (&acc)[E], const RowExtra &X) {
         const int64_t v = base + seg;
         const int f0 = col;
+        const float scale = kScale ? scales[seg] : 1.0f;
         float res[E];
 #pragma unroll
         for (int i = 0; i < E; ++i) res[i] = acc[i];
         if (kScale && !o.scale_all) {
 #pragma unroll
-            for (int i = 0; i < E; ++i) res[i] *= X.scale;
+            for (int i = 0; i < E; ++i) res[i] *= scale;
         }
         if constexpr (kExtra != 0) {
             float x[E];
             Chunk<T>::widen(X.raw, x);
 #pragma unroll
-            for (int i = 0; i < E; ++i) res[i] += (kEdge && kExtra == 1) ? X.scale * x[i] : x[i];
+            for (int i = 0; i < E; ++i) res[i] += (kEdge && kExtra == 1) ? scale * x[i] : x[i];
         }
         if (kScale && o.scale_all) {
 #pragma unroll
-            for (int i = 0; i < E; ++i) res[i] *= X.scale;
+            for (int i = 0; i < E; ++i) res[i] *= scale;
         }
         if (o.bias) {
 #pragma unroll
@@ -478,7 +483,7 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, co
         if (sub < n_chunks) store_chunk(o.out + v * o.ld_out + f0, res);
     };
     const LaneRows rows{reinterpret_cast<const char *>(in + col), uint32_t(ld_in) * uint32_t(sizeof(T))};
-    stream_segments<T, kW>(rows, ids, o.edge_scale, next_row_step, row_extra, finish);
+    stream_segments<T, kW>(rows, ids, o.edge_scale, gpw <= 4, next_row_step, row_extra, finish);
     __syncthreads();
 
     // ---- deferred rows, some at a time: the groups sum the shares of each, then one group each combines them in order.  A row's
@@ -526,7 +531,7 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, co
 #pragma unroll
                 for (int i = 0; i < E; ++i) partial[seg * width + sub * E + i] = acc[i];
             };
-            stream_segments<T, kW>(rows, ids, o.edge_scale, next_share_step, no_extra, to_lds);
+            stream_segments<T, kW>(rows, ids, o.edge_scale, gpw <= 4, next_share_step, no_extra, to_lds);
         }
         __syncthreads();
         if (live && sub < n_chunks && grp < h_end - h0) {
