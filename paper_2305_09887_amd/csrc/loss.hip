@@ -3,6 +3,7 @@
 #include "common.hpp"
 
 #include <cmath>
+#include <type_traits>
 
 namespace tma {
 
@@ -27,12 +28,24 @@ __device__ __forceinline__ float block_sum_256(float v)
 }
 
 // Sixteen lanes per node (coalesced row reads): log-sum-exp, loss term,
-// gradient (softmax - onehot)/n.  kRegs > 0: the row (C <= 16 * kRegs) is read once and kept in
-// registers, one exp per element; kRegs = 0: any C, the row is read three times (it stays in L1).
+// gradient (softmax - onehot)/n.  kRegs > 0: the row (16 * (kRegs - 1) < C <= 16 * kRegs) is read once and kept in
+// registers, one exp per element, the next row on its way; kRegs = 0: any C, the row is read three times (it stays in L1).
 // A block walks over several groups of 16 rows so that the number of partial loss sums stays small.
 constexpr int kCeLanes = 16;
 constexpr int kCeRows = 256 / kCeLanes;
 constexpr int kCeMaxBlocks = 2048;
+
+// v and the values of the lanes 8, then 4, 2 and 1 away, of every sixteen.  (Lanes eight apart hold the same after the first
+// exchange, so that a rotation by four is the exchange with the lane four away, and the sum is that of a butterfly, bit by bit.)
+template <typename Op>
+__device__ __forceinline__ float over_sixteen(float v, Op op)
+{
+    const auto from = [](float x, auto control) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(control)::value, 0xF, 0xF, true)); };
+    v = op(v, from(v, std::integral_constant<int, 0x128>{}));   // row_ror:8
+    v = op(v, from(v, std::integral_constant<int, 0x124>{}));   // row_ror:4
+    v = op(v, from(v, std::integral_constant<int, 0x4E>{}));    // quad_perm [2, 3, 0, 1]
+    return op(v, from(v, std::integral_constant<int, 0xB1>{})); // quad_perm [1, 0, 3, 2]
+}
 
 template <typename T, int kRegs>
 __global__ __launch_bounds__(256) void softmax_ce_kernel(int64_t n, int C, const T *__restrict__ logits, int64_t ld_in,
@@ -41,53 +54,69 @@ __global__ __launch_bounds__(256) void softmax_ce_kernel(int64_t n, int C, const
 {
     const int sub = threadIdx.x % kCeLanes;
     const float inv_n = 1.0f / float(n);
+    const int64_t stride = int64_t(gridDim.x) * kCeRows;
     float term = 0.0f;
-    for (int64_t v0 = int64_t(blockIdx.x) * kCeRows; v0 < n; v0 += int64_t(gridDim.x) * kCeRows) {
-        const int64_t v = v0 + threadIdx.x / kCeLanes;
-        const bool live = v < n;
-        const T *z = logits + (live ? v : 0) * ld_in;
-        if constexpr (kRegs > 0) {
+    if constexpr (kRegs > 0) {
+        // this lane's columns of a row and its label; past the last row the one before again, and from column C on the last
+        T raw[kRegs];
+        int32_t label;
+        int64_t v = int64_t(blockIdx.x) * kCeRows + threadIdx.x / kCeLanes;
+        const int64_t first = v < n ? v : n - 1, step = stride * ld_in;
+        const T *z = logits + first * ld_in + sub;
+        const int32_t *y_at = labels + first;
+        T *dz = dlogits ? dlogits + first * ld_in + sub : nullptr;
+        const bool last = sub + (kRegs - 1) * kCeLanes < C;    // of the lane's columns, the only one that may not be there
+        auto fetch = [&]() {
+#pragma unroll
+            for (int k = 0; k < kRegs; ++k) raw[k] = z[k < kRegs - 1 || last ? k * kCeLanes : C - 1 - sub];
+            label = *y_at;
+        };
+        fetch();
+        for (int64_t v0 = int64_t(blockIdx.x) * kCeRows; v0 < n; v0 += stride, v += stride) {
             float zr[kRegs];
             float mx = -INFINITY;
 #pragma unroll
             for (int k = 0; k < kRegs; ++k) {
-                const int c = sub + k * kCeLanes;
-                zr[k] = (live && c < C) ? ld(z + c) : -INFINITY;
+                zr[k] = k < kRegs - 1 || last ? ld(raw + k) : -INFINITY;
                 mx = fmaxf(mx, zr[k]);
             }
-#pragma unroll
-            for (int d = kCeLanes / 2; d >= 1; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d, kWave));
+            const int y = label;
+            if (v + stride < n) z += step, y_at += stride;
+            fetch();      // in flight while this row is worked on
+            mx = over_sixteen(mx, [](float a, float b) { return fmaxf(a, b); });
             float ex[kRegs];
             float se = 0.0f;
 #pragma unroll
-            for (int k = 0; k < kRegs; ++k) {
-                ex[k] = (live && sub + k * kCeLanes < C) ? expf(zr[k] - mx) : 0.0f;
+            for (int k = 0; k < kRegs; ++k) {   // (a column that is not there: exp(-infinity), or NaN where the row's sum is one)
+                ex[k] = expf(zr[k] - mx);
                 se += ex[k];
             }
-#pragma unroll
-            for (int d = kCeLanes / 2; d >= 1; d >>= 1) se += __shfl_xor(se, d, kWave);
-            if (live) {
-                const int y = labels[v];
+            se = over_sixteen(se, [](float a, float b) { return a + b; });
+            if (v < n) {
                 const float lse = mx + logf(se);
                 const float inv_se = 1.0f / se;
 #pragma unroll
                 for (int k = 0; k < kRegs; ++k) {
                     const int c = sub + k * kCeLanes;
                     if (c == y) term += lse - zr[k];
-                    if (dlogits && c < C) st(dlogits + v * ld_in + c, (ex[k] * inv_se - (c == y ? 1.0f : 0.0f)) * inv_n);
+                    if (dz && (k < kRegs - 1 || last)) st(dz + k * kCeLanes, (ex[k] * inv_se - (c == y ? 1.0f : 0.0f)) * inv_n);
                 }
             }
-        } else {
+            if (dz) dz += step;
+        }
+    } else {
+        for (int64_t v0 = int64_t(blockIdx.x) * kCeRows; v0 < n; v0 += stride) {
+            const int64_t v = v0 + threadIdx.x / kCeLanes;
+            const bool live = v < n;
+            const T *z = logits + (live ? v : 0) * ld_in;
             float mx = -INFINITY;
             if (live)
                 for (int c = sub; c < C; c += kCeLanes) mx = fmaxf(mx, ld(z + c));
-#pragma unroll
-            for (int d = kCeLanes / 2; d >= 1; d >>= 1) mx = fmaxf(mx, __shfl_xor(mx, d, kWave));
+            mx = over_sixteen(mx, [](float a, float b) { return fmaxf(a, b); });
             float se = 0.0f;
             if (live)
                 for (int c = sub; c < C; c += kCeLanes) se += expf(ld(z + c) - mx);
-#pragma unroll
-            for (int d = kCeLanes / 2; d >= 1; d >>= 1) se += __shfl_xor(se, d, kWave);
+            se = over_sixteen(se, [](float a, float b) { return a + b; });
             if (live) {
                 const float lse = mx + logf(se);
                 const int y = labels[v];
@@ -219,11 +248,15 @@ extern "C" int tma_softmax_ce(int64_t n, int32_t C, const void *logits, int64_t 
     hipLaunchKernelGGL((softmax_ce_kernel<T, R>), dim3(unsigned(nb)), dim3(256), 0, s, n, C,                      \
                        static_cast<const T *>(logits), ldz, labels, static_cast<T *>(dlogits_out), block_loss)
         if (dtype == TMA_F32) {
-            if (C <= 2 * kCeLanes) TMA_CE(float, 2);
+            if (C <= kCeLanes) TMA_CE(float, 1);
+            else if (C <= 2 * kCeLanes) TMA_CE(float, 2);
+            else if (C <= 3 * kCeLanes) TMA_CE(float, 3);
             else if (C <= 4 * kCeLanes) TMA_CE(float, 4);
             else TMA_CE(float, 0);
         } else {
-            if (C <= 2 * kCeLanes) TMA_CE(uint16_t, 2);
+            if (C <= kCeLanes) TMA_CE(uint16_t, 1);
+            else if (C <= 2 * kCeLanes) TMA_CE(uint16_t, 2);
+            else if (C <= 3 * kCeLanes) TMA_CE(uint16_t, 3);
             else if (C <= 4 * kCeLanes) TMA_CE(uint16_t, 4);
             else TMA_CE(uint16_t, 0);
         }
