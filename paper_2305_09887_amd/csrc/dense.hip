@@ -141,8 +141,9 @@ static WeightSplit plan_dense_weight_split(int64_t n, int32_t F_in, int32_t F_ou
     WeightSplit w;
     w.k_per_split = int64_t(round_up(size_t(ceil_div(n > 0 ? n : 1, want)), 32));
     w.n_splits = int(ceil_div(n > 0 ? n : 1, w.k_per_split));
-    w.partial_bytes = round_up(size_t(w.n_splits) * size_t(F_in) * size_t(F_out) * 4, 256);
-    w.colsum_bytes = round_up(size_t(w.n_splits) * size_t(F_out) * 4, 256);
+    // (room for `want`: see the layer's split in gemm_weight.hip)
+    w.partial_bytes = round_up(size_t(want) * size_t(F_in) * size_t(F_out) * 4, 256);
+    w.colsum_bytes = round_up(size_t(want) * size_t(F_out) * 4, 256);
     return w;
 }
 

@@ -80,8 +80,9 @@ static WeightSplit plan_weight_split(int64_t n, int32_t F_in, int32_t F_out)
     WeightSplit w;
     w.k_per_split = int64_t(round_up(size_t(ceil_div(n > 0 ? n : 1, want)), 32));
     w.n_splits = int(ceil_div(n > 0 ? n : 1, w.k_per_split));
-    w.partial_bytes = round_up(size_t(w.n_splits) * 2 * size_t(F_in) * size_t(F_out) * 4, 256);
-    w.colsum_bytes = round_up(size_t(w.n_splits) * size_t(F_out) * 4, 256);
+    // room for `want`, of which there are never fewer for more rows: what is reserved for a block's most rows holds for any of its batches
+    w.partial_bytes = round_up(size_t(want) * 2 * size_t(F_in) * size_t(F_out) * 4, 256);
+    w.colsum_bytes = round_up(size_t(want) * size_t(F_out) * 4, 256);
     return w;
 }
 
