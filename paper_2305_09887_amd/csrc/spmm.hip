@@ -813,26 +813,40 @@ int launch_spmm_combine(int64_t n, const int32_t *rowptr, const int32_t *colidx,
     return fail(TMA_ERR_UNSUPPORTED_DTYPE, "spmm: dtype %d", dtype);
 }
 
-// dst_v = inv_deg[v] * g_v (.) [h_v > 0]   (rows of F elements; padding up to F_pad is zeroed)
+// dst_v = inv_deg[v] * g_v (.) [h_v > 0]   (rows of F elements; padding up to F_pad is zeroed).  Whole 16-byte pieces of dst a
+// thread (us, element by element -> so: 150,000 rows of 47 bf16 17.4 -> 11.7, 40,004 of 41 fp32 6.6 -> 5.3); `fetched`: pieces of g and h inside a row are.
 template <typename T>
-__global__ __launch_bounds__(256) void scale_mask_rows_kernel(int64_t n, int F, int F_pad, const T *__restrict__ g,
-                                                              const T *__restrict__ h, int64_t ld,
+__global__ __launch_bounds__(256) void scale_mask_rows_kernel(int64_t n, int F, int pieces, const T *__restrict__ g,
+                                                              const T *__restrict__ h, int64_t ld, bool fetched,
                                                               const float *__restrict__ inv_deg, int relu,
                                                               T *__restrict__ dst, int64_t ld_dst,
                                                               const int32_t *__restrict__ rowptr, EntryGate gate)
 {
     if (shut(gate, rowptr, n)) return;
-    const int64_t total = n * F_pad;
+    constexpr int E = Chunk<T>::kElems;
+    const int64_t total = n * pieces;
     const int64_t stride = int64_t(gridDim.x) * 256;
     for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < total; i += stride) {
-        const int64_t v = i / F_pad;
-        const int f = int(i - v * F_pad);
-        float r = 0.0f;
-        if (f < F) {
-            r = load_elem(g + v * ld + f) * inv_deg[v];
-            if (relu && !(load_elem(h + v * ld + f) > 0.0f)) r = 0.0f;
+        const int64_t v = i / pieces;
+        const int f0 = int(i - v * pieces) * E;
+        const T *gv = g + v * ld + f0, *hv = h + v * ld + f0;
+        float x[E], m[E];
+        if (fetched && f0 + E <= F) {
+            const uint4 gw = load_chunk(gv), hw = relu ? load_chunk(hv) : gw;
+            Chunk<T>::widen(gw, x);
+            Chunk<T>::widen(hw, m);
+        } else {
+#pragma unroll
+            for (int j = 0; j < E; ++j) {
+                const bool there = f0 + j < F;
+                x[j] = there ? load_elem(gv + j) : 0.0f;
+                m[j] = there && relu ? load_elem(hv + j) : 0.0f;
+            }
         }
-        store_elem(dst + v * ld_dst + f, r);
+        const float scale = inv_deg[v];
+#pragma unroll
+        for (int j = 0; j < E; ++j) x[j] = f0 + j < F && !(relu && !(m[j] > 0.0f)) ? x[j] * scale : 0.0f;
+        store_chunk(dst + v * ld_dst + f0, x);
     }
 }
 
@@ -841,16 +855,20 @@ int launch_scale_mask_rows(int64_t n, int32_t F, int32_t F_pad, const void *g, c
                            hipStream_t stream, const int32_t *rowptr, EntryGate gate)
 {
     if (n == 0 || F_pad == 0) return TMA_OK;
-    int64_t blocks = ceil_div(n * F_pad, 256);
+    const size_t bytes = (dtype == TMA_BF16 ? 2 : 4);
+    const int pieces = int(size_t(F_pad) * bytes / 16);
+    // (callers' rows are whole pieces; loads of 16 bytes need 4-byte-aligned rows)
+    const bool fetched = (size_t(ld) * bytes) % 4 == 0 && aligned(g, 4) && (!relu || aligned(h, 4));
+    int64_t blocks = ceil_div(n * pieces, 256);
     if (blocks > 256 * 32) blocks = 256 * 32;
     TMA_TIMED(gate.side ? "gated_scale_mask_rows" : "scale_mask_rows", stream);
     if (dtype == TMA_F32)
-        hipLaunchKernelGGL(scale_mask_rows_kernel<float>, dim3(unsigned(blocks)), dim3(256), 0, stream, n, F, F_pad,
-                           static_cast<const float *>(g), static_cast<const float *>(h), ld, inv_deg, relu ? 1 : 0,
+        hipLaunchKernelGGL(scale_mask_rows_kernel<float>, dim3(unsigned(blocks)), dim3(256), 0, stream, n, F, pieces,
+                           static_cast<const float *>(g), static_cast<const float *>(h), ld, fetched, inv_deg, relu ? 1 : 0,
                            static_cast<float *>(dst), ld_dst, rowptr, gate);
     else
-        hipLaunchKernelGGL(scale_mask_rows_kernel<uint16_t>, dim3(unsigned(blocks)), dim3(256), 0, stream, n, F, F_pad,
-                           static_cast<const uint16_t *>(g), static_cast<const uint16_t *>(h), ld, inv_deg,
+        hipLaunchKernelGGL(scale_mask_rows_kernel<uint16_t>, dim3(unsigned(blocks)), dim3(256), 0, stream, n, F, pieces,
+                           static_cast<const uint16_t *>(g), static_cast<const uint16_t *>(h), ld, fetched, inv_deg,
                            relu ? 1 : 0, static_cast<uint16_t *>(dst), ld_dst, rowptr, gate);
     return check_launch("scale_mask_rows");
 }
