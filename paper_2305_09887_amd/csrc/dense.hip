@@ -130,25 +130,34 @@ int launch_dense_gemm_bwd_data(int64_t n, const void *dY, const void *Y, int64_t
 }
 
 // ---- backward: weights ------------------------------------------------------
-static WeightSplit plan_dense_weight_split(int64_t n, int32_t F_in, int32_t F_out)
+static int64_t wanted_dense_ranges(int64_t n, int32_t F_in, int32_t F_out)
 {
     const int bn = F_out <= 64 ? 64 : (F_out <= 96 ? 96 : 128);
     const int64_t tiles = ceil_div(int64_t(F_in), 128) * ceil_div(F_out, bn);
     int64_t want = ceil_div(512, tiles > 0 ? tiles : 1);
     const int64_t max_useful = ceil_div(n > 0 ? n : 1, 128);
     if (want > max_useful) want = max_useful;
-    if (want < 1) want = 1;
+    return want < 1 ? 1 : want;
+}
+
+static WeightSplit plan_dense_weight_split(int64_t n, int32_t F_in, int32_t F_out)
+{
+    const int64_t want = wanted_dense_ranges(n, F_in, F_out);
     WeightSplit w;
     w.k_per_split = int64_t(round_up(size_t(ceil_div(n > 0 ? n : 1, want)), 32));
     w.n_splits = int(ceil_div(n > 0 ? n : 1, w.k_per_split));
-    // (room for `want`: see the layer's split in gemm_weight.hip)
-    w.partial_bytes = round_up(size_t(want) * size_t(F_in) * size_t(F_out) * 4, 256);
-    w.colsum_bytes = round_up(size_t(want) * size_t(F_out) * 4, 256);
+    w.partial_bytes = round_up(size_t(w.n_splits) * size_t(F_in) * size_t(F_out) * 4, 256);
+    w.colsum_bytes = round_up(size_t(w.n_splits) * size_t(F_out) * 4, 256);
     return w;
 }
 
-size_t dense_gemm_bwd_weight_workspace_bytes(int64_t n, int32_t F_in, int32_t F_out)
+// least: what a call needs; else room that never shrinks with more rows (see the layer's in gemm_weight.hip)
+size_t dense_gemm_bwd_weight_workspace_bytes(int64_t n, int32_t F_in, int32_t F_out, bool least)
 {
+    if (!least) {
+        const size_t want = size_t(wanted_dense_ranges(n, F_in, F_out));
+        return round_up(want * size_t(F_in) * size_t(F_out) * 4, 256) + round_up(want * size_t(F_out) * 4, 256);
+    }
     const WeightSplit w = plan_dense_weight_split(n, F_in, F_out);
     return w.partial_bytes + w.colsum_bytes;
 }

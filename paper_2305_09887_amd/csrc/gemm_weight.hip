@@ -70,28 +70,38 @@ int launch_reduce_splits(const float *partial, const float *colsum_partial, int 
 
 // ---- backward: weights ------------------------------------------------------
 
-static WeightSplit plan_weight_split(int64_t n, int32_t F_in, int32_t F_out)
+static int64_t wanted_ranges(int64_t n, int32_t F_in, int32_t F_out)
 {
     const int64_t tiles = ceil_div(2 * int64_t(F_in), 128) * ceil_div(F_out, F_out <= 64 ? 64 : 128);
     int64_t want = ceil_div(512, tiles > 0 ? tiles : 1);
     const int64_t max_useful = ceil_div(n > 0 ? n : 1, 128);
     if (want > max_useful) want = max_useful;
-    if (want < 1) want = 1;
+    return want < 1 ? 1 : want;
+}
+
+static WeightSplit plan_weight_split(int64_t n, int32_t F_in, int32_t F_out)
+{
+    const int64_t want = wanted_ranges(n, F_in, F_out);
     WeightSplit w;
     w.k_per_split = int64_t(round_up(size_t(ceil_div(n > 0 ? n : 1, want)), 32));
     w.n_splits = int(ceil_div(n > 0 ? n : 1, w.k_per_split));
-    // room for `want`, of which there are never fewer for more rows: what is reserved for a block's most rows holds for any of its batches
-    w.partial_bytes = round_up(size_t(want) * 2 * size_t(F_in) * size_t(F_out) * 4, 256);
-    w.colsum_bytes = round_up(size_t(want) * size_t(F_out) * 4, 256);
+    w.partial_bytes = round_up(size_t(w.n_splits) * 2 * size_t(F_in) * size_t(F_out) * 4, 256);
+    w.colsum_bytes = round_up(size_t(w.n_splits) * size_t(F_out) * 4, 256);
     return w;
 }
 
-size_t sage_gemm_bwd_weight_workspace_bytes(int64_t n, int32_t F_in, int32_t F_out, bool least)
+// least: what a call needs; else what is asked for: room for the ranges before they are rounded to 32 rows, which never shrinks with more rows (what a
+// trainer on blocks reserves for its most rows holds for every batch), and for what the streamed product makes use of
+size_t sage_gemm_bwd_weight_workspace_bytes(int64_t n, int32_t F_in, int32_t F_out, int32_t dtype, bool least)
 {
-    const WeightSplit w = plan_weight_split(n, F_in, F_out);
-    size_t bytes = w.partial_bytes + w.colsum_bytes;
+    if (least) {
+        const WeightSplit w = plan_weight_split(n, F_in, F_out);
+        return w.partial_bytes + w.colsum_bytes;
+    }
+    const size_t want = size_t(wanted_ranges(n, F_in, F_out));
+    size_t bytes = round_up(want * 2 * size_t(F_in) * size_t(F_out) * 4, 256) + round_up(want * size_t(F_out) * 4, 256);
     WeightSplit u;
-    if (!least && plan_stream_weight(n, F_in, F_out, SIZE_MAX, u) && u.partial_bytes + u.colsum_bytes > bytes) bytes = u.partial_bytes + u.colsum_bytes;
+    if (dtype == TMA_BF16 && plan_stream_weight(n, F_in, F_out, SIZE_MAX, u) && u.partial_bytes + u.colsum_bytes > bytes) bytes = u.partial_bytes + u.colsum_bytes;
     return bytes;
 }
 

@@ -61,7 +61,7 @@ int launch_sage_gemm_bwd_data(int64_t n, const void *dHnext, const void *Hnext, 
 
 // [dW_self ; dW_neigh] = [H | M]^T dZ,  dbias = 1^T dZ   (split over nodes, two-stage fixed-order reduction)
 // least: what the call needs; else what it makes use of
-size_t sage_gemm_bwd_weight_workspace_bytes(int64_t n, int32_t F_in, int32_t F_out, bool least = true);
+size_t sage_gemm_bwd_weight_workspace_bytes(int64_t n, int32_t F_in, int32_t F_out, int32_t dtype, bool least);
 int launch_sage_gemm_bwd_weight(int64_t n, const void *H, int64_t ldh, const void *M, int64_t ldm, const void *dHnext,
                                 const void *Hnext, int64_t ld_next, int32_t F_in, int32_t F_out, int32_t act,
                                 int32_t dtype,
@@ -133,7 +133,7 @@ int launch_dense_gemm_fwd(int64_t n, const void *X, int64_t ldx, int32_t F_in, c
 int launch_dense_gemm_bwd_data(int64_t n, const void *dY, const void *Y, int64_t ld, const float *W, int32_t F_in,
                                int32_t F_out, int32_t act, int32_t dtype, const float *row_scale, void *dX,
                                int64_t ldx, hipStream_t s, void *spare = nullptr, size_t spare_bytes = 0);
-size_t dense_gemm_bwd_weight_workspace_bytes(int64_t n, int32_t F_in, int32_t F_out);
+size_t dense_gemm_bwd_weight_workspace_bytes(int64_t n, int32_t F_in, int32_t F_out, bool least = true);
 int launch_dense_gemm_bwd_weight(int64_t n, const void *X, int64_t ldx, const void *dY, const void *Y, int64_t ld,
                                  int32_t F_in, int32_t F_out, int32_t act, int32_t dtype, float *dW, float *dbias,
                                  void *ws, size_t ws_bytes, hipStream_t s);

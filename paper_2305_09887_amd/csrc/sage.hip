@@ -27,7 +27,7 @@ static BwdWorkspace plan_bwd(int64_t n, int32_t F_in, int32_t F_out, int32_t dty
     const size_t rows = size_t(n > 0 ? n : 1);
     if (aggregates_first(F_in, F_out, dtype)) {
         w.dm_bytes = need_dH ? round_up(rows * size_t(F_in) * elem_size(dtype), 256) : 0;
-        w.weight_bytes = sage_gemm_bwd_weight_workspace_bytes(n, F_in, F_out, least || dtype != TMA_BF16);
+        w.weight_bytes = sage_gemm_bwd_weight_workspace_bytes(n, F_in, F_out, dtype, least);
     } else {  // scaled dZ and dYn, [n, Fp] each
         w.dm_bytes = 2 * round_up(rows * size_t(pad_cols(F_out, dtype)) * elem_size(dtype), 256);
         w.weight_bytes = sage_tf_gemm_bwd_weight_workspace_bytes(n, F_in, F_out, dtype);

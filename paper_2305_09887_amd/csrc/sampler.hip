@@ -370,7 +370,7 @@ static BlockBwdWorkspace plan_block_bwd(int64_t n_dst, int64_t n_src, int64_t ma
         w.list_bytes = round_up(items * 4, 256);
         w.scan_bytes = exclusive_scan_i32_workspace_bytes(n_src);
     }
-    w.weight_bytes = sage_gemm_bwd_weight_workspace_bytes(n_dst, F_in, F_out, least || dtype != TMA_BF16);
+    w.weight_bytes = sage_gemm_bwd_weight_workspace_bytes(n_dst, F_in, F_out, dtype, least);
     return w;
 }
 
@@ -409,10 +409,10 @@ static int transpose_block(const char *fn, int64_t n_dst, int64_t n_src, int64_t
 
 // The same workspace layout with the weight-gradient scratch of the one-matrix (GCN) layer.
 static BlockBwdWorkspace plan_gcn_block_bwd(int64_t n_dst, int64_t n_src, int64_t max_entries, int32_t F_in, int32_t F_out,
-                                            int32_t dtype, bool need_dH)
+                                            int32_t dtype, bool need_dH, bool least)
 {
     BlockBwdWorkspace w = plan_block_bwd(n_dst, n_src, max_entries, F_in, F_out, dtype, need_dH, true);
-    w.weight_bytes = dense_gemm_bwd_weight_workspace_bytes(n_dst, F_in, F_out);
+    w.weight_bytes = dense_gemm_bwd_weight_workspace_bytes(n_dst, F_in, F_out, least);
     return w;
 }
 
@@ -728,7 +728,7 @@ extern "C" size_t tma_gcn_block_bwd_workspace_bytes(int64_t n_dst, int64_t n_src
                                                     int32_t F_out, int32_t dtype, int32_t need_dH)
 {
     if (n_dst < 0 || n_src < n_dst || max_entries < 0 || F_in < 1 || F_out < 1) return 0;
-    return tma::plan_gcn_block_bwd(n_dst, n_src, max_entries, F_in, F_out, dtype, need_dH != 0).total();
+    return tma::plan_gcn_block_bwd(n_dst, n_src, max_entries, F_in, F_out, dtype, need_dH != 0, false).total();
 }
 
 extern "C" int tma_gcn_block_bwd(int64_t n_dst, int64_t n_src, int64_t max_entries, const int32_t *blk_rowptr,
@@ -748,7 +748,7 @@ extern "C" int tma_gcn_block_bwd(int64_t n_dst, int64_t n_src, int64_t max_entri
     TMA_REQUIRE(dW && dbias, TMA_ERR_INVALID_ARG, "%s: gradient output is NULL", fn);
     TMA_REQUIRE(ws && aligned(ws, 256), TMA_ERR_INVALID_ARG, "%s: workspace NULL or not 256-byte aligned", fn);
     const bool need_dH = dH_out != nullptr;
-    const BlockBwdWorkspace w = plan_gcn_block_bwd(n_dst, n_src, max_entries, F_in, F_out, dtype, need_dH);
+    const BlockBwdWorkspace w = plan_gcn_block_bwd(n_dst, n_src, max_entries, F_in, F_out, dtype, need_dH, true);
     TMA_REQUIRE(ws_bytes >= w.total(), TMA_ERR_WORKSPACE_TOO_SMALL, "%s: workspace %zu < %zu bytes", fn, ws_bytes,
                 w.total());
     if (n_dst > 0) {
