@@ -18,7 +18,10 @@ template <bool VA, class AL, class BL>
 static void fwd_launch(const AL &a, const BL &b, const FwdEpilogue<uint16_t> &e, int64_t n, int F_out, int64_t K, int64_t kps,
                        hipStream_t s)
 {
-    if (F_out <= 64 || few_tiles(n, F_out))
+    const bool narrow = F_out <= 64 || few_tiles(n, F_out);
+    if (few_rows_narrow(n, n, F_out, 1, 128, narrow ? 64 : VA && F_out > 128 && F_out <= 256 ? 256 : 128, 120))
+        launch_gemm<64, 64, 32, 2, 2, false, uint16_t, 3>(VA ? "gemm_fwd_64x64_bf16" : "gemm_fwd_64x64_bf16_generic", a, b, e, n, F_out, K, kps, 1, nullptr, s);
+    else if (narrow)
         launch_gemm<128, 64, 32, 4, 1, false, uint16_t>(VA ? "gemm_fwd_128x64_bf16" : "gemm_fwd_128x64_bf16_generic", a, b, e, n, F_out, K,
                                                  kps, 1, nullptr, s);
     else if constexpr (VA) {

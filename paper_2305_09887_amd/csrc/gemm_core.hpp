@@ -1453,7 +1453,7 @@ static inline bool weights_u_ok(int64_t F_in, int64_t F_out) { return F_in * F_o
 static inline int pad4(int F) { return (F + 3) / 4 * 4; }
 
 // BK: k-values per slab of the bf16 kernel (gemm_split_kernel, CT = float, has its own).
-template <int BM, int BN, int BK, int WM, int WN, bool kColSum, typename CT = float, class AL, class BL, class Epi>
+template <int BM, int BN, int BK, int WM, int WN, bool kColSum, typename CT = float, int kBlocks = 0, class AL, class BL, class Epi>
 static void launch_gemm(const char *name, const AL &a, const BL &b, const Epi &e, int64_t M, int N, int64_t K,
                         int64_t k_per_split, int n_splits, float *colsum_partial, hipStream_t s)
 {
@@ -1466,7 +1466,7 @@ static void launch_gemm(const char *name, const AL &a, const BL &b, const Epi &e
     constexpr int kLdsBytes = 2 * 2 * ((AL::kContigK ? BM * (BK + kPad) : BK * (BM + kPad)) + (BL::kContigK ? BN * (BK + kPad) : BK * (BN + kPad)));
     constexpr int kByWaves = 2 * 4 / (WM * WN) > 0 ? 2 * 4 / (WM * WN) : 1;
     constexpr int kByLds = 160 * 1024 / kLdsBytes > 0 ? 160 * 1024 / kLdsBytes : 1;
-    constexpr int kPerCu = sizeof(CT) == 4 ? kSplitPerCu * 4 / (WM * WN) : kByWaves < kByLds ? kByWaves : kByLds;
+    constexpr int kPerCu = kBlocks ? kBlocks : sizeof(CT) == 4 ? kSplitPerCu * 4 / (WM * WN) : kByWaves < kByLds ? kByWaves : kByLds;
     int64_t blocks_per_die = ceil_div(total, kXcds);
     if (blocks_per_die > 32 * kPerCu) blocks_per_die = 32 * kPerCu;
     const dim3 grid(unsigned(blocks_per_die * kXcds)), block(WM * WN * 64);
@@ -1499,6 +1499,17 @@ constexpr int64_t kFewTiles = TMA_GEMM_FEW_TILES;
 static inline bool few_tiles(int64_t M, int64_t N, int n_splits = 1)
 {
     return ceil_div(M, int64_t(128)) * ceil_div(N, int64_t(128)) * n_splits < kFewTiles;
+}
+
+// A bf16 product of few rows (see few_rows) in tiles of 64 x 64, three blocks to a compute unit: where the fullest unit then has less to do, by
+// `price` hundredths more a value, than with tiles of `rows` x `width`.  Geometric mean of 72 products each of 1,700 to 60,000 rows, 64 to 256 columns in and
+// 48 to 256 out: forward (price 120) 0.89 of the time, input gradients 0.88 and weight gradients 0.93 (110).  us at 5,000 rows, 2 x 256 -> 64
+// forward 9.5 -> 7.2, input gradient of 128 from 256 9.8 -> 7.1; at 40,004, 2 x 64 -> 48 forward 7.6 -> 6.4, input gradient of 64 from 256 14.5 -> 11.7; as
+// before: 40,004 rows, 2 x 256 -> 256 forward 31 (64 x 64: 34).  Five blocks to a unit or k in slabs of 64 gain nothing on three.
+static inline bool few_rows_narrow(int64_t of_rows, int64_t M, int N, int n_splits, int rows, int width, int price)
+{
+    const auto fullest = [&](int r, int w) { return ceil_div(ceil_div(M, int64_t(r)) * ceil_div(N, w) * n_splits, int64_t(256)) * r * w; };
+    return few_rows(of_rows) && fullest(64, 64) * price < fullest(rows, width) * 100;
 }
 
 // A product of fp32 storage on the fp32 instruction (gemm_f32.hpp), up to kPerCu blocks to a compute unit.
@@ -1623,9 +1634,14 @@ static void launch_by_width(const char *name, const AL &a, const BL &b, const Ep
                             int64_t kps, int n_splits, float *colsum, hipStream_t s)
 {
     if constexpr (sizeof(CT) == 4) launch_split<kColSum, kWide>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
-    else if (N <= 64 || few_tiles(M, N, n_splits)) launch_gemm<128, 64, BK, 4, 1, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
-    else if (N <= 96) launch_gemm<128, 96, BK, 4, 1, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
-    else launch_gemm<128, 128, BK, 2, 2, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    else {
+        const int width = N <= 64 || few_tiles(M, N, n_splits) ? 64 : N <= 96 ? 96 : 128;
+        if (few_rows_narrow(kColSum ? K : M, M, N, n_splits, 128, width, 110))
+            launch_gemm<64, 64, BK, 2, 2, kColSum, CT, 3>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+        else if (width == 64) launch_gemm<128, 64, BK, 4, 1, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+        else if (width == 96) launch_gemm<128, 96, BK, 4, 1, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+        else launch_gemm<128, 128, BK, 2, 2, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+    }
 }
 
 }  // namespace tma
