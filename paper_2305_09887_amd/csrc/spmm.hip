@@ -25,9 +25,8 @@
 //
 // Dense graphs whose rows sit in the caches are bound by the vector units: 35 instructions a slot of 256 bf16 columns,
 // 16 of them the sum's, kept these 94 % busy.  So a group has a multiple of four lanes (those past the last chunk repeat
-// it): each fetches one of a step's four ids and multiplies it by the pitch, and the additions that make the four
-// addresses take the other lanes' products as operands; a slot that is not used is skipped by the lane mask; and bounds
-// are read one row ahead.  us, before -> so: 150,000 rows of 50 entries in communities, bf16, 256 columns 248 -> 207, 128
+// it): each fetches one of a step's four ids and multiplies it by the pitch, and takes the other lanes' products by lane
+// permutes; a slot that is not used is skipped by the lane mask; and bounds are read one row ahead.  us, before -> so: 150,000 rows of 50 entries in communities, bf16, 256 columns 248 -> 207, 128
 // 161 -> 130, 64 101 -> 71, 48 103 -> 80, fp32, 128 columns 215 -> 194, 48 105 -> 91; 400,000 rows of 3.3 random ones, bound by memory,
 // 131 -> 125, 72 -> 69, 44 -> 41, 50 -> 50 (48 columns: eight groups to a wavefront instead of ten), 125 -> 123 and 64 -> 63.
 #include "kernels.hpp"
@@ -217,28 +216,24 @@ struct Step {
     bool last;
 };
 
-// What lane q of every four lanes holds.
+// What lane q of every four lanes holds.  (Additions in assembler that take another lane's word as an operand are one instruction less an
+// address, but their carry has to be waited for, which only the compiler does by itself: with the waits written out they are as fast as this,
+// within 1.5 % at 1 to 64 pieces a row, dense and sparse.)
 template <int q>
-__device__ __forceinline__ float of_quad(float x)
+__device__ __forceinline__ uint32_t of_quad(uint32_t x)
 {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), q * 0x55, 0xF, 0xF, true));
+    return uint32_t(__builtin_amdgcn_update_dpp(0, int32_t(x), q * 0x55, 0xF, 0xF, true));
 }
-// base + what lane q of every four lanes holds, for q = 0 .. 3: two instructions each, which take the other lane's words as
-// operands.  (Such an instruction may not follow within two states on one that writes the word, five on one that writes the
-// lane mask: the wait at the front.)
-__device__ __forceinline__ void add_of_quad(uint64_t mine, uint64_t base, uint64_t (&sum)[4])
+// (words side by side: shifted and joined they would be added one by one)
+template <int q>
+__device__ __forceinline__ uint64_t of_quad(uint64_t x)
 {
-    uint32_t lo[4], hi[4];
-#define TMA_ADD_OF_QUAD(lo, hi, q)                                                                        \
-    "v_add_co_u32_dpp %" lo ", vcc, %8, %10 quad_perm:[" q "," q "," q "," q "] row_mask:0xf bank_mask:0xf\n\t" \
-    "v_addc_co_u32_dpp %" hi ", vcc, %9, %11, vcc quad_perm:[" q "," q "," q "," q "] row_mask:0xf bank_mask:0xf\n\t"
-    asm("s_nop 4\n\t" TMA_ADD_OF_QUAD("0", "4", "0") TMA_ADD_OF_QUAD("1", "5", "1") TMA_ADD_OF_QUAD("2", "6", "2") TMA_ADD_OF_QUAD("3", "7", "3")
-        : "=&v"(lo[0]), "=&v"(lo[1]), "=&v"(lo[2]), "=&v"(lo[3]), "=&v"(hi[0]), "=&v"(hi[1]), "=&v"(hi[2]), "=&v"(hi[3])
-        : "v"(uint32_t(mine)), "v"(uint32_t(mine >> 32)), "v"(uint32_t(base)), "v"(uint32_t(base >> 32))
-        : "vcc");
-#undef TMA_ADD_OF_QUAD
-#pragma unroll
-    for (int q = 0; q < 4; ++q) sum[q] = uint64_t(hi[q]) << 32 | lo[q];
+    typedef uint32_t Words __attribute__((ext_vector_type(2)));
+    const Words mine = __builtin_bit_cast(Words, x);
+    Words there;
+    there.x = of_quad<q>(mine.x);
+    there.y = of_quad<q>(mine.y);
+    return __builtin_bit_cast(uint64_t, there);
 }
 template <typename Fn, int... q>
 __device__ __forceinline__ void unrolled(Fn &&fn, std::integer_sequence<int, q...>)
@@ -274,10 +269,8 @@ struct StepRows {
     float weight;
     __device__ __forceinline__ void issue(const LaneRows &in, const float *__restrict__ edge_scale, int32_t id)
     {
-        uint64_t at[kStreamU];
-        add_of_quad(uint64_t(uint32_t(id)) * in.pitch, reinterpret_cast<uint64_t>(in.first), at);
-#pragma unroll
-        for (int q = 0; q < kStreamU; ++q) chunk[q] = load_global_chunk(at[q]);
+        const uint64_t mine = uint64_t(uint32_t(id)) * in.pitch, first = reinterpret_cast<uint64_t>(in.first);
+        for_each_slot([&](auto q) { chunk[q] = load_global_chunk(first + of_quad<q>(mine)); });
         if constexpr (kEdge) weight = edge_scale[uint32_t(id)];
     }
 };
@@ -294,7 +287,7 @@ __device__ __forceinline__ void consume(const Step &s, const StepRows<T, kW != W
     constexpr int E = Chunk<T>::kElems;
     for_each_slot([&](auto q) {
         float w = 1.0f;
-        if constexpr (kW != Weighting::kNone) w = of_quad<q>(rows.weight);
+        if constexpr (kW != Weighting::kNone) w = __uint_as_float(of_quad<q>(__float_as_uint(rows.weight)));
         if (kFull || q < s.count) {   // kFull: no group of the wavefront has an unused slot
             float v[E];
             Chunk<T>::widen(rows.chunk[q], v);
