@@ -658,7 +658,7 @@ int tma_average(float *const *W_ptrs, int32_t n_trainers, uint64_t active_mask,
  *     dst[i, :] = src[l2g[i], :]     for i in [0, n_loc)
  * Rows are row_bytes long; src_ld_bytes / dst_ld_bytes are the row pitches.
  * Any element type: 16-byte copies when pointers, pitches and row_bytes are
- * multiples of 16, 4-byte copies when multiples of 4, else byte copies.
+ * multiples of 4 and a row has 16 bytes, 4-byte copies of shorter rows, else byte copies.
  * ---------------------------------------------------------------------- */
 int tma_gather_rows(int64_t n_loc, const int32_t *l2g, const void *src, int64_t src_ld_bytes,
                     int64_t row_bytes, void *dst, int64_t dst_ld_bytes, tma_stream_t stream);

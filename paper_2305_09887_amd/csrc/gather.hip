@@ -58,7 +58,9 @@ static int launch_gather(int64_t n_loc, const int32_t *d_n, const int32_t *l2g, 
     // what its threads have in flight per block, less where that leaves the chip without eight blocks per compute unit
     int64_t block_pieces = ceil_div(n_loc * pieces, int64_t(256 * 8));
     block_pieces = block_pieces < 256 ? 256 : block_pieces > 256 * kCopies ? 256 * kCopies : block_pieces;
-    const int64_t rows_per_block = pieces < block_pieces ? block_pieces / pieces : 1;
+    int64_t rows_per_block = pieces < block_pieces ? block_pieces / pieces : 1;
+    constexpr int64_t kMostBlocks = (int64_t(1) << 24) - 1;   // (a launch has fewer than 2^32 threads)
+    if (ceil_div(n_loc, rows_per_block) > kMostBlocks) rows_per_block = ceil_div(n_loc, kMostBlocks);
     TMA_TIMED(sizeof(W) == 16 ? "gather_rows_w16" : (sizeof(W) == 4 ? "gather_rows_w4" : "gather_rows_w1"), s);
     hipLaunchKernelGGL(gather_rows_kernel<W>, dim3(unsigned(ceil_div(n_loc, rows_per_block))), dim3(256), 0, s, n_loc,
                        d_n, l2g, static_cast<const char *>(src), src_ld, int32_t(pieces), int32_t(row_bytes - int64_t(sizeof(W))),

@@ -46,3 +46,12 @@ def test_count_on_the_device(B, count):
     B.tma_gather_rows_dev(ids, torch.tensor([count], dtype=torch.int32, device="cuda"), src, out)
     kept.as_strided((300, 100), (112, 1), 0)[:n].copy_(want)
     assert torch.equal(flat, kept)
+
+
+def test_more_rows_than_a_launch_has_blocks(B):
+    n, width = (1 << 24) + 5, 513     # a row alone fills a block
+    src, _ = placed(1009, width, width, 0, 5)
+    ids = torch.randint(0, 1009, (n,), generator=torch.Generator().manual_seed(6), dtype=torch.int32).cuda()
+    out = B.tma_gather_rows(ids, src)
+    for at in range(0, n, 1 << 20):
+        assert torch.equal(out[at:at + (1 << 20)], src[ids[at:at + (1 << 20)].long()])
