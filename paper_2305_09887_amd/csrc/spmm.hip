@@ -512,7 +512,7 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, co
                     open = false;
                     part += NG;
                     if (part >= n_shares) {
-                        part = grp;
+                        part -= n_shares;
                         ++h;
                     }
                 }
