@@ -400,7 +400,7 @@ __global__ __launch_bounds__(kSpmmThreads) void spmm_stream_kernel(int64_t n, co
         for (int i = threadIdx.x; i < G * E; i += kSpmmThreads) partial[i] = i < o.F ? o.bias[i] : 0.0f;
     __syncthreads();
     const GlobalIds ids = nnz > first_entry ? GlobalIds(colidx + first_entry) : GlobalIds(&kNoEntry);
-    const int64_t by_mean = int64_t(kDeferFactor) * (int64_t(nnz) / n);
+    const int64_t by_mean = int64_t(kDeferFactor) * (int64_t(nnz - first_entry) / n);
     const int32_t defer_above = by_mean > min_defer ? int32_t(by_mean < INT32_MAX ? by_mean : INT32_MAX) : min_defer;
 
     // ---- the group's own rows, block-local indices [r, r_end): entries [e, end) of row r are still to come
