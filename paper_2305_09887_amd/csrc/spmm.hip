@@ -200,7 +200,8 @@ constexpr int kStreamU = 4;              // neighbours per step
 constexpr int kMinDefer = 24;            // rows up to this length are never deferred
 constexpr int kMinDeferOverlap = 256;    // the same for fp32 rows with an overlapping last piece (see launch_typed)
 constexpr int kDeferFactor = 4;          // ... nor rows up to this multiple of the mean degree
-constexpr int kMaxRowsPerBlock = 512;    // rows of one workgroup (their bounds, scales and the deferred-row list sit in LDS)
+constexpr int kMaxRowsPerBlock = 512;    // rows of one workgroup (their bounds, scales and the deferred-row list sit in LDS;
+// groups of four lanes, rows of up to four pieces, so have 8 rows at most: 12,500,000 rows of 3.3 entries, 1 and 4 pieces 937 and 1,128 us, of 1,024 rows 961 and 1,147)
 // LDS for the partial sums of deferred rows.  It leaves room for five workgroups to a compute unit: of seven (16 KB) fewer rows
 // find in the caches what another fetched (bf16, 256 columns: 150,000 rows of 50 entries in communities 212 -> 206 us, 1,000,000 of 20
 // random ones 1,456 -> 1,450; 64 columns 432 -> 423), and more hubs pass at a time (125,000 rows of a power law, 8 columns 51 -> 42).
@@ -688,8 +689,12 @@ static void launch_stream(int64_t n, const int32_t *rowptr, const int32_t *colid
     // costs two extra steps to fill and drain, so on very long row ranges (millions of rows: every block runs many
     // rounds anyway) 16 rows per group amortise it better (12.5 M rows: -7 %), while on a dense cache-resident
     // graph (mean degree 44, 144 k rows) longer groups only lengthen the tail (+15 %).
+    // Rows of 512 bytes and more, below four million of them: 6 rows at most.  What counts there is how many rows a die has at hand at a time, in
+    // whose neighbours, where these are near, its 4 MB of L2 have to hold.  us, 8 rows / 8 with a workgroup less to a unit / 6, 512-byte fp32 rows unless
+    // said: communities of 1,000 rows, 150,000 of 50 entries 226 / 204 / 191, 40,000 of 3.3 11.9 / 14.7 / 12.0, 1,000,000 of 20 785 / 771 / 768; random
+    // ones, 400,000 of 3.3 125 / 131 / 125, 1,000,000 of 20 1,454 / 1,449 / 1,452; power law, 700,000 of 3.3 244 / 264 / 254; 1 KB rows, communities, 150,000 of 50 439 / 399 / 378.
     int64_t rpg = ceil_div(n, int64_t(NG) * 256 * 6);
-    const int64_t rpg_max = n >= (int64_t(1) << 22) ? 16 : 8;
+    const int64_t rpg_max = n >= (int64_t(1) << 22) ? 16 : n_chunks >= 32 ? 6 : 8;
     rpg = rpg < 4 ? 4 : (rpg > rpg_max ? rpg_max : rpg);
     if (rpg * NG > kMaxRowsPerBlock) rpg = kMaxRowsPerBlock / NG;
     char name[48];
@@ -698,11 +703,7 @@ static void launch_stream(int64_t n, const int32_t *rowptr, const int32_t *colid
              sizeof(T) == 4 ? "f32" : "bf16", n_chunks);
     TMA_TIMED(name, s);
     const dim3 grid(unsigned(round_up(size_t(ceil_div(n, rpg * NG)), kDies)));
-    // Rows of 512 bytes and more, below four million of them: four workgroups to a unit instead of five, by LDS that nobody uses.
-    // Fewer rows at a time find more of their neighbours in the caches (us, five / four: bf16, 256 columns, 150,000 rows
-    // of 50 entries 246 / 236; fp32, 128 columns, 1,000,000 of 20 1,356 / 1,336); 12,500,000 rows of 3.3 4,230 / 4,327.
-    const unsigned spare = n_chunks >= 32 && n < (int64_t(1) << 22) ? 8192 : 0;
-    hipLaunchKernelGGL((spmm_stream_kernel<T, kExtra, kScale, kW>), grid, dim3(kSpmmThreads), spare, s, n, rowptr,
+    hipLaunchKernelGGL((spmm_stream_kernel<T, kExtra, kScale, kW>), grid, dim3(kSpmmThreads), 0, s, n, rowptr,
                        colidx, in, ld_in, o, n_chunks, G, int(rpg), min_defer, last_col);
 }
 
