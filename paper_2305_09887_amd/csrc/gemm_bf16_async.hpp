@@ -117,7 +117,7 @@ __global__ __launch_bounds__(WM *WN * 64, 2) void gemm_bf16_async_kernel(AsyncRo
     constexpr int kYoung = (kAhead - 1) * kLoads;              // fetches that may be in flight behind a slab's own
     constexpr int kYoungStores = kYoung + kStores < 63 ? kYoung + kStores : 63;
     constexpr int kColChunks = Epi::kColAux ? (BN + 63) / 64 : 0, kRowChunks = Epi::kRowAux ? (BM + 63) / 64 : 0;
-    constexpr int kAuxSlots = kStages + 1;  // the cursor is kStages slabs, so at most as many tiles, ahead
+    constexpr int kAuxSlots = kStages;      // the cursor is kAhead slabs, so at most as many tiles, ahead
     static_assert(BM % (WM * 32) == 0 && BN % (WN * 32) == 0 && (WN == 1 || BN % (WN * 64) == 0) && kYoung <= 63 && kColChunks <= kWaves && kRowChunks <= kWaves, "tile shape");
 
     __shared__ __attribute__((aligned(1024))) uint16_t As[kStages][kA];
