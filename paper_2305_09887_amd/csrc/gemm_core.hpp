@@ -19,6 +19,7 @@
 #pragma once
 #include "kernels.hpp"
 
+#include <string_view>
 #include <type_traits>
 
 namespace tma {
@@ -1502,10 +1503,14 @@ static inline bool few_tiles(int64_t M, int64_t N, int n_splits = 1)
 }
 
 // A bf16 product of few rows (see few_rows) in tiles of 64 x 64, three blocks to a compute unit: where the fullest unit then has less to do, by
-// `price` hundredths more a value, than with tiles of `rows` x `width`.  Geometric mean of 72 products each of 1,700 to 60,000 rows, 64 to 256 columns in and
-// 48 to 256 out: forward (price 120) 0.89 of the time, input gradients 0.88 and weight gradients 0.93 (110).  us at 5,000 rows, 2 x 256 -> 64
-// forward 9.5 -> 7.2, input gradient of 128 from 256 9.8 -> 7.1; at 40,004, 2 x 64 -> 48 forward 7.6 -> 6.4, input gradient of 64 from 256 14.5 -> 11.7; as
-// before: 40,004 rows, 2 x 256 -> 256 forward 31 (64 x 64: 34).  Five blocks to a unit or k in slabs of 64 gain nothing on three.
+// `price` hundredths more a value, than with tiles of `rows` x `width`.  Forward products of layers that aggregate first (price 120); forward
+// products, input and weight gradients of dense layers, and forward products and weight gradients of layers that transform first (110).
+// Geometric mean of 72 products each of 1,700 to 60,000 rows, 64 to 256 columns in and 48 to 256 out: forward 0.89 of the time, input gradients of
+// dense layers 0.88 and weight gradients of those two 0.93.  us at 5,000 rows, 2 x 256 -> 64 forward 9.5 -> 7.2, dense input gradient of 128 from 256 9.8 -> 7.1; at
+// 40,004, 2 x 64 -> 48 forward 7.6 -> 6.4, dense input gradient of 64 from 256 14.5 -> 11.7; as before: 40,004 rows, 2 x 256 -> 256 forward
+// 31 (64 x 64: 34).  Five blocks to a unit or k in slabs of 64 gain nothing on three.
+// The other backward products, whose tiles are chosen in their own places, were not measured so: input and weight gradients of layers that aggregate
+// first and input gradients of those that transform first have tiles of 128 rows at any number of them.
 static inline bool few_rows_narrow(int64_t of_rows, int64_t M, int N, int n_splits, int rows, int width, int price)
 {
     const auto fullest = [&](int r, int w) { return ceil_div(ceil_div(M, int64_t(r)) * ceil_div(N, w) * n_splits, int64_t(256)) * r * w; };
@@ -1636,9 +1641,12 @@ static void launch_by_width(const char *name, const AL &a, const BL &b, const Ep
     if constexpr (sizeof(CT) == 4) launch_split<kColSum, kWide>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
     else {
         const int width = N <= 64 || few_tiles(M, N, n_splits) ? 64 : N <= 96 ? 96 : 128;
-        if (few_rows_narrow(kColSum ? K : M, M, N, n_splits, 128, width, 110))
-            launch_gemm<64, 64, BK, 2, 2, kColSum, CT, 3>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
-        else if (width == 64) launch_gemm<128, 64, BK, 4, 1, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
+        if (few_rows_narrow(kColSum ? K : M, M, N, n_splits, 128, width, 110)) {
+            const std::string_view whole(name), what = whole.substr(0, whole.find("_bf16"));
+            char tiled[64];
+            snprintf(tiled, sizeof(tiled), "%.*s_64x64%s", int(what.size()), name, name + what.size());
+            launch_gemm<64, 64, BK, 2, 2, kColSum, CT, 3>(tiled, a, b, e, M, N, K, kps, n_splits, colsum, s);
+        } else if (width == 64) launch_gemm<128, 64, BK, 4, 1, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
         else if (width == 96) launch_gemm<128, 96, BK, 4, 1, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
         else launch_gemm<128, 128, BK, 2, 2, kColSum, CT>(name, a, b, e, M, N, K, kps, n_splits, colsum, s);
     }
