@@ -26,9 +26,11 @@
 // Dense graphs whose rows sit in the caches are bound by the vector units: 35 instructions a slot of 256 bf16 columns,
 // 16 of them the sum's, kept these 94 % busy.  So a group has a multiple of four lanes (those past the last chunk repeat
 // it): each fetches one of a step's four ids and multiplies it by the pitch, and takes the other lanes' products by lane
-// permutes; a slot that is not used is skipped by the lane mask; and bounds are read one row ahead.  us, before -> so: 150,000 rows of 50 entries in communities, bf16, 256 columns 248 -> 207, 128
-// 161 -> 130, 64 101 -> 71, 48 103 -> 80, fp32, 128 columns 215 -> 194, 48 105 -> 91; 400,000 rows of 3.3 random ones, bound by memory,
-// 131 -> 125, 72 -> 69, 44 -> 41, 50 -> 50 (48 columns: eight groups to a wavefront instead of ten), 125 -> 123 and 64 -> 63.
+// permutes; a slot that is not used is skipped by the lane mask; and bounds are read one row ahead.  us, before -> so, means: 150,000 rows of 50
+// entries in communities of 1,000, bf16, 256 columns 255 -> 190, 128 159 -> 130, 64 98 -> 69, 48 105 -> 82, fp32, 128 columns 247 -> 179, 48 110 -> 99; 400,000
+// rows of 3.3 random ones, bound by memory, 131 -> 125, 72 -> 66, 44 -> 39, 50 -> 48, 125 -> 125 and 64 -> 64.  Groups fill a wavefront less well so (rows of 9, 10 and 21 pieces:
+// five, five and two of them instead of seven, six and three), which rows in memory do not notice, 125,000 of 3.3 random ones, 9 and 21 fp32 pieces
+// 21 -> 20 and 36.5 -> 34.9, nor dense ones; a power law's long rows do, 125,000 of 3.3, 9, 10 and 21 pieces 26.3 -> 26.1, 24.6 -> 25.5 and 40.5 -> 42.8.
 #include "kernels.hpp"
 
 #include <utility>
@@ -202,9 +204,9 @@ constexpr int kMinDeferOverlap = 256;    // the same for fp32 rows with an overl
 constexpr int kDeferFactor = 4;          // ... nor rows up to this multiple of the mean degree
 constexpr int kMaxRowsPerBlock = 512;    // rows of one workgroup (their bounds, scales and the deferred-row list sit in LDS;
 // groups of four lanes, rows of up to four pieces, so have 8 rows at most: 12,500,000 rows of 3.3 entries, 1 and 4 pieces 937 and 1,128 us, of 1,024 rows 961 and 1,147)
-// LDS for the partial sums of deferred rows.  It leaves room for five workgroups to a compute unit: of seven (16 KB) fewer rows
-// find in the caches what another fetched (bf16, 256 columns: 150,000 rows of 50 entries in communities 212 -> 206 us, 1,000,000 of 20
-// random ones 1,456 -> 1,450; 64 columns 432 -> 423), and more hubs pass at a time (125,000 rows of a power law, 8 columns 51 -> 42).
+// LDS for the partial sums of deferred rows: room for five workgroups to a compute unit instead of the seven of 16 KB, and more hubs pass at a time.  us, 16 KB ->
+// 24, means: power law, 125,000 rows of 3.3 entries, 8 bf16 columns 95 -> 75, fp32, 12 and 36 columns 26.1 -> 22.9 and 28.8 -> 25.8, 1,000,000 of 20, 128 columns
+// 1,289 -> 1,280, of 3.3 345 -> 359; bf16, 256 columns, 150,000 of 50 in communities and 1,000,000 of 20 random ones 205 and 1,454, either way.
 constexpr int kPartialBytes = 24576;
 
 // (A choice between two arrays: without the name of their memory a load from it would wait for all others and be waited for.)
@@ -334,7 +336,7 @@ __device__ __forceinline__ void stream_segments(const LaneRows &in, GlobalIds id
         Vb.issue(in, edge_scale, Ib);
         extra(b, Xb);
         // (steps without an unused slot, where most of them are: wide bf16 rows of dense graphs, two groups or four to a wavefront;
-        // 128 columns, 150,000 rows of 50 entries, 143 -> 138 us.  fp32 rows, of half the additions a slot, gain nothing.)
+        // 128 columns, 150,000 rows of 50 entries, 3 % less.  fp32 rows, of half the additions a slot, gain nothing.)
         if (sizeof(T) == 2 && few_groups && __all(a.count == kStreamU)) consume<T, kW, true>(a, Va, acc);
         else consume<T, kW, false>(a, Va, acc);
         if (a.last) {
@@ -689,12 +691,14 @@ static void launch_stream(int64_t n, const int32_t *rowptr, const int32_t *colid
     // costs two extra steps to fill and drain, so on very long row ranges (millions of rows: every block runs many
     // rounds anyway) 16 rows per group amortise it better (12.5 M rows: -7 %), while on a dense cache-resident
     // graph (mean degree 44, 144 k rows) longer groups only lengthen the tail (+15 %).
-    // Rows of 512 bytes and more, below four million of them: 6 rows at most.  What counts there is how many rows a die has at hand at a time, in
-    // whose neighbours, where these are near, its 4 MB of L2 have to hold.  us, 8 rows / 8 with a workgroup less to a unit / 6, 512-byte fp32 rows unless
-    // said: communities of 1,000 rows, 150,000 of 50 entries 226 / 204 / 191, 40,000 of 3.3 11.9 / 14.7 / 12.0, 1,000,000 of 20 785 / 771 / 768; random
-    // ones, 400,000 of 3.3 125 / 131 / 125, 1,000,000 of 20 1,454 / 1,449 / 1,452; power law, 700,000 of 3.3 244 / 264 / 254; 1 KB rows, communities, 150,000 of 50 439 / 399 / 378.
+    // Rows of 512 bytes and more, below four million of them: 6 rows at most, of fewer than 2^18 5.  What counts there is how many rows a die has at
+    // hand at a time, in whose neighbours, where these are near, its 4 MB of L2 have to hold.  us, means over 512-byte fp32 rows, 8 rows / 8 with a
+    // workgroup less to a unit / 6 / 5 or 4: communities of 1,000 rows, 150,000 of 50 entries 226 / 204 / 191 / 175 (4), 125,000 of 20 86 / - / 77 / 73, 40,000 of 3.3
+    // 11.9 / 14.7 / 12.0 / 11.9 (4), 1,000,000 of 20 785 / 771 / 768 / 755 (4); random ones, 125,000 of 3.3 42.0 / - / 42.5 / 41.4, 400,000 124.8 / 130.5 / 124.8 / 127.6 (4);
+    // power law, 125,000 of 3.3 44.1 / - / 46.2 / 43.8, 700,000 244 / 264 / 254 / 269 (4); 1 KB rows, communities, 150,000 of 50 439 / 399 / 378 / 355 (4),
+    // power law, 60,000 of 3.3 43.0 / - / 46.2 / 44.7.
     int64_t rpg = ceil_div(n, int64_t(NG) * 256 * 6);
-    const int64_t rpg_max = n >= (int64_t(1) << 22) ? 16 : n_chunks >= 32 ? 6 : 8;
+    const int64_t rpg_max = n >= (int64_t(1) << 22) ? 16 : n_chunks < 32 ? 8 : n >= (int64_t(1) << 18) ? 6 : 5;
     rpg = rpg < 4 ? 4 : (rpg > rpg_max ? rpg_max : rpg);
     if (rpg * NG > kMaxRowsPerBlock) rpg = kMaxRowsPerBlock / NG;
     char name[48];
