@@ -17,7 +17,8 @@
 // tail of the launch: rows longer than a threshold (a multiple of the mean
 // degree) are deferred and then summed by all groups of the workgroup together,
 // each taking one contiguous share, with a fixed-order combine through LDS.  The
-// result of a row depends only on its own neighbour list, never on scheduling.
+// result of a row depends only on its own neighbour list and the mean degree, never
+// on scheduling.
 //
 // Every load of the pipeline but a finished row's own (see row_extra) is issued unconditionally (an unused slot
 // repeats an address that was just fetched): the wait counters are then exact and a wait for step s never also
